@@ -49,6 +49,7 @@
 // retry needs.
 #include <type_traits>
 
+#include "lds_sort.h"
 #include "lmk_gs_internal.h"
 #include "tile_test.h"
 
@@ -57,16 +58,6 @@ namespace lmk {
 constexpr u32 kMaskArea = 32;       // rectangles whose kept tiles the projection kernel recorded as a bit mask
 
 // ---------------------------------------------------------------- walking a primitive's tiles
-// t / w and t % w for t < 2^22 (a tile grid has at most 2^22 tiles), 1 <= w <= 4096; inv_w = 1 / w
-__device__ __forceinline__ void div_tiles(u32 t, u32 w, float inv_w, u32 &row, u32 &col)
-{
-    u32 q = (u32)((float)t * inv_w);            // within one of the quotient
-    int r = (int)(t - q * w);
-    if (r < 0) { q -= 1u; r += (int)w; }
-    else if (r >= (int)w) { q += 1u; r -= (int)w; }
-    row = q; col = (u32)r;
-}
-
 // A rectangle of up to kMaskArea tiles, walked by its own lane: f(tile id) for every tile that
 // gets a pair, in row-major order.  Under binning rule 1 (TIGHT) those are the set bits of `mask`.
 template <bool TIGHT, class F>
@@ -188,7 +179,7 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     ScratchHeader *__restrict__ header, u32 *__restrict__ big_idx,
     const u32 *__restrict__ block_sums, u32 pre_blocks,
     const u64 *__restrict__ block_offsets, const u64 *__restrict__ group_totals,
-    u32 *__restrict__ bin_count, uint2 *__restrict__ list, u64 list_capacity)
+    u32 *__restrict__ bin_count, uint2 *__restrict__ list, u64 list_capacity, u64 dense_min)
 {
     constexpr bool LDS = LDS_TILES > 0;
     constexpr u32 kThreads = BinShape<LDS_TILES>::kThreads, kPer = BinShape<LDS_TILES>::kPer;
@@ -200,6 +191,7 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     __shared__ u32 s_wave[kWaves][2];
     __shared__ u32 s_base[2];
     __shared__ u64 s_part[kWaves];
+    if (dense_min != ~0ull && header->dup_count >= dense_min) return;    // no read where the host has ruled it out
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     {   // the projection stage counted the pairs of every 256 primitives: a workgroup none of whose
         // primitives was binned (culled, or a skipped voxel range) leaves without reading one
@@ -393,6 +385,7 @@ __global__ __launch_bounds__(kLargeThreads) void count_large_kernel(
 // per-tile sort leaves them zero for the next call.
 // With SMALL (up to 8192 tiles) every thread reads its eight counters once and everything else works
 // from registers and LDS.
+//   classes[5]  (kDenseClass) 1 = the frame's lists come from dense_emit_kernel, sorted: nothing is emitted or sorted here
 constexpr u32 kSmallThreads = 64, kSmallItems = 8, kSmallCap = kSmallThreads * kSmallItems;   // 512
 constexpr u32 kLowThreads = 256, kLowItems = 8;                                               // 2048
 constexpr u32 kMidThreads = 512, kMidItems = 8, kMid = kMidThreads * kMidItems;               // 4096
@@ -420,7 +413,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     const u32 *__restrict__ tile_count, const u32 *__restrict__ large_count, u32 num_tiles, u64 capacity, ScratchHeader *__restrict__ header,
     u64 *__restrict__ tile_offsets, u32 *__restrict__ tile_cursor, u64 *__restrict__ prim_offsets_if_empty,
     u32 *__restrict__ order, u32 *__restrict__ order_copy, u32 *__restrict__ classes,
-    uint2 *__restrict__ chunk_list, u64 chunk_capacity)
+    uint2 *__restrict__ chunk_list, u64 chunk_capacity, u64 dense_min)
 {
     constexpr u32 kWaves = kScanThreads / kWave;
     // the running positions of the emit kernel are 32 bits wide: absolute where every position
@@ -465,6 +458,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     // classes and the chunk list; both need the list lengths and D
     const bool ranges_part = blockIdx.x == 0;
     if (tid == 0 && ranges_part) {
+        classes[kDenseClass] = dense_min != ~0ull && header->dup_count >= dense_min ? 1u : 0u;   // as the counting kernels decided
         header->dup_count = D;
         header->status = overflow ? LMK_GS_ERR_CAPACITY : LMK_GS_OK;      // of this call; the frame's earlier calls do not count
         // with no primitives nothing else writes the one-entry prefix sum over the primitives
@@ -646,14 +640,17 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void emit_kernel(
     const u64 *__restrict__ tile_offsets, u32 *__restrict__ tile_cursor, const ScratchHeader *__restrict__ header,
     const u32 *__restrict__ big_idx, const u64 *__restrict__ block_offsets, const u64 *__restrict__ group_totals,
     const u32 *__restrict__ bin_count, const uint2 *__restrict__ list, u64 list_capacity,
-    u32 bin_blocks, u32 giant_blocks, u64 capacity, u64 *__restrict__ keys)
+    u32 bin_blocks, u32 giant_blocks, u64 capacity, u64 *__restrict__ keys, const u32 *__restrict__ classes)
 {
     constexpr bool LDS = LDS_TILES > 0;
     constexpr u32 kThreads = BinShape<LDS_TILES>::kThreads, kPer = BinShape<LDS_TILES>::kPer;
     constexpr u32 kWaves = BinShape<LDS_TILES>::kWaves;
     __shared__ u32 s_cur[LDS ? LDS_TILES : 1];
     __shared__ u64 s_part[kWaves];
-    if (header->status != LMK_GS_OK) return;                // more pairs than the buffers hold: nothing is emitted
+    // (here and below the flag is read together with what is needed anyway: one round trip to memory)
+    const u32 elsewhere = classes[kDenseClass];             // the lists are written by dense_emit_kernel
+    const int32_t status = header->status;                  // more pairs than the buffers hold: nothing is emitted
+    if ((elsewhere != 0u) | (status != LMK_GS_OK)) return;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     if (blockIdx.x >= bin_blocks) {
         for_each_listed<kThreads>(header, big_idx, n, blockIdx.x - bin_blocks, gridDim.x - bin_blocks, giant_blocks, tid,
@@ -748,98 +745,6 @@ __global__ __launch_bounds__(kPreBlock) void prim_offsets_kernel(
 }
 
 // ---------------------------------------------------------------- per-tile sort
-// Sorts up to THREADS * ITEMS pairs of one tile by (depth bits, index) with a merge sort:
-// each thread sorts ITEMS composites in registers (a fixed network, no memory traffic), the
-// runs of 2, 4 and 8 neighbouring lanes are merged in registers too (bitonic merges with DPP
-// lane exchanges), and from there the sorted runs are merged pairwise through LDS, run length
-// doubling: a thread finds where its ITEMS outputs start in the two runs (merge-path binary
-// search) and merges them sequentially.  Runs are stored with one padding slot per 16 elements
-// so that the strided accesses of neighbouring threads spread over the LDS banks.  Instances:
-// 64 threads x 2 / 4 / 8 (one wavefront per short list, which is most tiles), 256 x 8,
-// 512 x 8, and 1024 x 16 (most of a compute unit's LDS) for the chunks of the longest lists.
-__device__ __forceinline__ u32 ts_slot(u32 p) { return p + (p >> 4); }
-
-__device__ __forceinline__ void ts_cswap(u64 &a, u64 &b)
-{
-    const u64 lo = a < b ? a : b, hi = a < b ? b : a;
-    a = lo; b = hi;
-}
-
-// ITEMS outputs, starting at output `diag`, of the merge of the sorted runs s[a0, a1) and s[a1, b1)
-template <u32 ITEMS>
-__device__ __forceinline__ void merge_from_lds(const u64 *s, u32 a0, u32 a1, u32 b1, u32 diag, u64 (&e)[ITEMS])
-{
-    const u32 lenA = a1 - a0, lenB = b1 - a1;
-    u32 l0 = diag > lenB ? diag - lenB : 0, h0 = diag < lenA ? diag : lenA;
-    while (l0 < h0) {
-        const u32 mid = (l0 + h0) >> 1;
-        if (s[ts_slot(a0 + mid)] < s[ts_slot(a1 + diag - 1 - mid)]) l0 = mid + 1; else h0 = mid;
-    }
-    u32 i = a0 + l0, j = a1 + (diag - l0);
-    u64 ka = i < a1 ? s[ts_slot(i)] : ~0ull;
-    u64 kb = j < b1 ? s[ts_slot(j)] : ~0ull;
-    // Straight-line steps, selects only: an exhausted run shows the maximum value, which also is
-    // what the padding holds, so "A first unless B is smaller" needs no bounds in the comparison
-    // (a tie is between padding values, where the side does not matter).  The one LDS read per
-    // step is not branched around: when the run has just been used up it reads slot 0 and the
-    // value is dropped.
-#pragma unroll
-    for (u32 k = 0; k < ITEMS; ++k) {
-        const bool takeA = ka <= kb;
-        e[k] = takeA ? ka : kb;
-        const u32 next = (takeA ? i : j) + 1u;
-        const u32 lim = takeA ? a1 : b1;
-        const bool more = next < lim;
-        const u32 at = more ? next : 0u;
-        const u64 v = s[ts_slot(at)];
-        const u64 nv = more ? v : ~0ull;
-        i = takeA ? next : i;
-        j = takeA ? j : next;
-        ka = takeA ? nv : ka;
-        kb = takeA ? kb : nv;
-    }
-}
-
-// The first three merge rounds need no LDS: the runs of 2, 4 and 8 neighbouring lanes are merged
-// with a bitonic merge network whose lane exchanges are DPP moves (mirror within 2 / 4 / 8
-// lanes for the first, "flip" stage, lane xor 1 / 2 for the half-cleaners that follow).
-template <int CTRL>
-__device__ __forceinline__ u64 ts_dpp(u64 v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(u32)v, CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u32)(v >> 32), CTRL, 0xf, 0xf, true);
-    return ((u64)(u32)hi << 32) | (u64)(u32)lo;
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;            // quad_perm [1,0,3,2], [2,3,0,1]
-constexpr int kDppMirror4 = 0x1B, kDppMirror8 = 0x141;     // quad_perm [3,2,1,0], row_half_mirror
-
-// one stage across lanes: element k meets element k (FLIP: ITEMS - 1 - k) of the partner lane;
-// the lower lane of the pair keeps the smaller value
-template <int CTRL, bool FLIP, u32 ITEMS>
-__device__ __forceinline__ void ts_lane_stage(u64 (&e)[ITEMS], bool upper)
-{
-    u64 p[ITEMS];
-#pragma unroll
-    for (u32 k = 0; k < ITEMS; ++k) p[k] = ts_dpp<CTRL>(e[FLIP ? ITEMS - 1 - k : k]);
-#pragma unroll
-    for (u32 k = 0; k < ITEMS; ++k) {
-        const bool mine = (e[k] < p[k]) != upper;           // lower keeps the smaller, upper the larger
-        e[k] = mine ? e[k] : p[k];
-    }
-}
-
-// a bitonic sequence of ITEMS values in registers -> ascending
-template <u32 ITEMS>
-__device__ __forceinline__ void ts_clean(u64 (&e)[ITEMS])
-{
-#pragma unroll
-    for (u32 j = ITEMS >> 1; j > 0; j >>= 1) {
-#pragma unroll
-        for (u32 i = 0; i < ITEMS; ++i)
-            if ((i & j) == 0) ts_cswap(e[i], e[i | j]);
-    }
-}
-
 // On entry keys[beg .. beg + n) holds what the emit kernel wrote: depth bits << 32 | primitive index,
 // the composite the list is ordered by.  On return keys/vals (or keys_out/vals_out) hold the
 // sorted pairs in their final form, key = tile << 32 | depth bits, value = primitive index.
@@ -848,62 +753,8 @@ __device__ __forceinline__ void sort_pairs_in_lds(u64 *keys, u32 *vals, u64 beg,
                                                   u64 *keys_out = nullptr, u32 *vals_out = nullptr)
 {
     if (!keys_out) { keys_out = keys; vals_out = vals; }    // in place unless the caller wants the result elsewhere
-    constexpr u32 CAP = THREADS * ITEMS;
-    constexpr u32 kLaneRun = 8 * ITEMS;                     // sorted run length after the lane merges
     const u32 tid = threadIdx.x;
-    const u32 m = (n + ITEMS - 1) / ITEMS * ITEMS;          // elements in play: n rounded up to whole runs
-    const u32 o0 = tid * ITEMS;
-    const bool active = o0 < m;
-    // each thread's ITEMS consecutive composites; beyond n the maximum value, which sorts to the end
-    u64 e[ITEMS];
-#pragma unroll
-    for (u32 k = 0; k < ITEMS; ++k)
-        e[k] = o0 + k < n ? keys[beg + o0 + k] : ~0ull;
-    // sort the run in registers (bitonic network)
-#pragma unroll
-    for (u32 k = 2; k <= ITEMS; k <<= 1) {
-#pragma unroll
-        for (u32 j = k >> 1; j > 0; j >>= 1) {
-#pragma unroll
-            for (u32 i = 0; i < ITEMS; ++i) {
-                const u32 l = i ^ j;
-                if (l > i) {
-                    if ((i & k) == 0) ts_cswap(e[i], e[l]); else ts_cswap(e[l], e[i]);
-                }
-            }
-        }
-    }
-    // runs of 2, 4, 8 lanes (every lane takes part; lanes beyond m hold the maximum value)
-    ts_lane_stage<kDppXor1, true, ITEMS>(e, (tid & 1u) != 0u);
-    ts_clean<ITEMS>(e);
-    ts_lane_stage<kDppMirror4, true, ITEMS>(e, (tid & 2u) != 0u);
-    ts_lane_stage<kDppXor1, false, ITEMS>(e, (tid & 1u) != 0u);
-    ts_clean<ITEMS>(e);
-    ts_lane_stage<kDppMirror8, true, ITEMS>(e, (tid & 4u) != 0u);
-    ts_lane_stage<kDppXor2, false, ITEMS>(e, (tid & 2u) != 0u);
-    ts_lane_stage<kDppXor1, false, ITEMS>(e, (tid & 1u) != 0u);
-    ts_clean<ITEMS>(e);
-    if (active) {
-#pragma unroll
-        for (u32 k = 0; k < ITEMS; ++k) s[ts_slot(o0 + k)] = e[k];
-    }
-    __syncthreads();
-
-    for (u32 run = kLaneRun; run < m && run < CAP; run <<= 1) {
-        if (active) {
-            // outputs [o0, o0 + ITEMS) of the pair of runs holding them: A = [a0, a1), B = [a1, b1)
-            const u32 a0 = (o0 / (2 * run)) * (2 * run);
-            const u32 a1 = a0 + run < m ? a0 + run : m;
-            const u32 b1 = a0 + 2 * run < m ? a0 + 2 * run : m;
-            merge_from_lds<ITEMS>(s, a0, a1, b1, o0 - a0, e);
-        }
-        __syncthreads();
-        if (active) {
-#pragma unroll
-            for (u32 k = 0; k < ITEMS; ++k) s[ts_slot(o0 + k)] = e[k];
-        }
-        __syncthreads();
-    }
+    sort_in_lds<THREADS, ITEMS>(n, s, [&](u32 i) { return keys[beg + i]; });
     const u64 hi_bits = (u64)tile << 32;
     for (u32 p = tid; p < n; p += THREADS) {
         const u64 c = s[ts_slot(p)];
@@ -1007,7 +858,8 @@ __global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
     u32 num_tiles)
 {
     __shared__ u64 s[kMid + kMid / 16];
-    const u32 chunks = classes[4];
+    const u32 chunks = classes[4], elsewhere = classes[kDenseClass];
+    if (elsewhere) return;
     if (blockIdx.x < chunks) {
         const uint2 c = chunk_list[blockIdx.x];
         if (c.x >= num_tiles) return;
@@ -1044,7 +896,7 @@ __global__ __launch_bounds__(kLowThreads) void tile_sort_low_kernel(
     __shared__ u64 s[CAP + CAP / 16];
     __shared__ u64 s_split[2];
     if (blockIdx.x < merge_blocks) {
-        const u64 segments = (u64)classes[4] * kPerChunk;
+        const u64 segments = classes[kDenseClass] ? 0ull : (u64)classes[4] * kPerChunk;
         for (u64 g = blockIdx.x; g < segments; g += merge_blocks) {
             const uint2 c = chunk_list[g / kPerChunk];
             if (c.x >= num_tiles) continue;
@@ -1057,7 +909,8 @@ __global__ __launch_bounds__(kLowThreads) void tile_sort_low_kernel(
     }
     const u32 k = blockIdx.x - merge_blocks;
     const u32 first = classes[0] + classes[3] + classes[1];
-    if (k >= classes[2] || first + k >= num_tiles) return;
+    const u32 low = classes[kDenseClass] ? 0u : classes[2];
+    if (k >= low || first + k >= num_tiles) return;
     const u32 tile = order[first + k];
     if (tile >= num_tiles) return;
     const u64 beg = tile_offsets[tile];
@@ -1078,7 +931,7 @@ __global__ __launch_bounds__(kSmallThreads) void tile_sort_small_kernel(
     __shared__ u64 s[kSmallCap + kSmallCap / 16];
     __shared__ u64 s_split[2];
     if (blockIdx.x < merge_blocks) {
-        const u64 segments = (u64)classes[4] * kPerChunk;
+        const u64 segments = classes[kDenseClass] ? 0ull : (u64)classes[4] * kPerChunk;
         for (u64 g = blockIdx.x; g < segments; g += merge_blocks) {
             const uint2 c = chunk_list[g / kPerChunk];
             if (c.x >= num_tiles) continue;
@@ -1091,8 +944,8 @@ __global__ __launch_bounds__(kSmallThreads) void tile_sort_small_kernel(
     }
     const u32 k = blockIdx.x - merge_blocks;
     if (k >= num_tiles) return;
-    const u32 tile = order[num_tiles - 1 - k];
-    if (tile >= num_tiles) return;
+    const u32 tile = order[num_tiles - 1 - k], elsewhere = classes[kDenseClass];
+    if ((tile >= num_tiles) | (elsewhere != 0u)) return;
     const u64 beg = tile_offsets[tile];
     const u64 len = tile_offsets[tile + 1] - beg;
     if (len < 1 || len > (u64)kSmallCap) return;
@@ -1128,7 +981,8 @@ __global__ __launch_bounds__(kHugeThreads) void tile_sort_huge_kernel(
         if (threadIdx.x == 0) { header->big_count = 0; header->giant_count = 0; }
         for (u32 t = threadIdx.x; t < 2u * (num_tiles + 1u); t += kHugeThreads) tile_count[t] = 0;
     }
-    if (blockIdx.x >= classes[0] || blockIdx.x >= num_tiles) return;
+    const u32 huge = classes[kDenseClass] ? 0u : classes[0];
+    if (blockIdx.x >= huge || blockIdx.x >= num_tiles) return;
     const u32 tile = order[blockIdx.x];
     if (tile >= num_tiles) return;
     const u64 beg = tile_offsets[tile];
@@ -1251,12 +1105,18 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
     const u32 large_blocks_emit = (large_blocks * kLargeThreads + bin_threads - 1) / bin_threads;
     hipError_t e;
 
+    const bool dense = dense_possible(n, out, pp.tiles_x, pp.tiles_y);
+    const u64 dense_min = dense ? (u64)kDenseRatio * n : ~0ull;
+    if (dense) {
+        e = launch_dense_count(proj, n, pp, out, tile_count, header, dense_min, stream);
+        if (e != hipSuccess) return e;
+    }
     if (L.bin_blocks > 0) {
         auto count = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(L.bin_blocks), dim3(bin_threads), 0, stream,
                                proj.tiles_touched, rect, tile_masks, n, pp.tiles_x, num_tiles, tile_count, header, big_idx,
                                reinterpret_cast<const u32 *>(scratch + L.block_sums), L.pre_blocks,
-                               block_offsets, group_totals, bin_count, list, out.capacity);
+                               block_offsets, group_totals, bin_count, list, out.capacity, dense_min);
         };
         if (lds_tiles == kLdsTilesSmall) { if (tight) count(count_kernel<kLdsTilesSmall, true>); else count(count_kernel<kLdsTilesSmall, false>); }
         else if (lds_tiles == kLdsTilesLarge) { if (tight) count(count_kernel<kLdsTilesLarge, true>); else count(count_kernel<kLdsTilesLarge, false>); }
@@ -1274,12 +1134,12 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
         hipLaunchKernelGGL(tile_scan_kernel<true>, dim3(2), dim3(kScanThreads), 0, stream,
                            tile_count, large_count, num_tiles, out.capacity, header, out.tile_offsets, tile_cursor,
                            n == 0 ? proj.offsets : nullptr, order, out.tile_order, classes, chunk_list,
-                           out.capacity / 2048 + 2);
+                           out.capacity / 2048 + 2, dense_min);
     else
         hipLaunchKernelGGL(tile_scan_kernel<false>, dim3(2), dim3(kScanThreads), 0, stream,
                            tile_count, large_count, num_tiles, out.capacity, header, out.tile_offsets, tile_cursor,
                            n == 0 ? proj.offsets : nullptr, order, out.tile_order, classes, chunk_list,
-                           out.capacity / 2048 + 2);
+                           out.capacity / 2048 + 2, dense_min);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (L.bin_blocks > 0) {
@@ -1287,7 +1147,7 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
             hipLaunchKernelGGL(kernel, dim3(L.bin_blocks + giant_blocks + large_blocks_emit), dim3(bin_threads), 0, stream,
                                proj.tiles_touched, rect, proj.depth, feat, tile_masks, n, pp, num_tiles,
                                out.tile_offsets, tile_cursor, header, big_idx, block_offsets, group_totals,
-                               bin_count, list, out.capacity, L.bin_blocks, giant_blocks, out.capacity, out.keys);
+                               bin_count, list, out.capacity, L.bin_blocks, giant_blocks, out.capacity, out.keys, classes);
         };
         auto emit_for = [&](auto lds_tag) {
             constexpr u32 LT = decltype(lds_tag)::value;
@@ -1299,6 +1159,10 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
         else emit_for(std::integral_constant<u32, 0u>());
         e = hipGetLastError();
         if (e != hipSuccess) return e;
+        if (dense) {
+            e = launch_dense_emit(n, pp, out, header, classes, stream);
+            if (e != hipSuccess) return e;
+        }
         if (proj.offsets) {
             hipLaunchKernelGGL(prim_offsets_kernel, dim3(L.pre_blocks), dim3(kPreBlock), 0, stream,
                                proj.tiles_touched, n, block_offsets, group_totals, proj.offsets);

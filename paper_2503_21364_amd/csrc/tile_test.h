@@ -55,5 +55,15 @@ __device__ __forceinline__ bool tile_kept(const TileTest &t, u32 tx, u32 ty)
     return qmin <= t.tau;
 }
 
+// t / w and t % w for t < 2^22 (a tile grid has at most 2^22 tiles), 1 <= w <= 4096; inv_w = 1 / w
+__device__ __forceinline__ void div_tiles(u32 t, u32 w, float inv_w, u32 &row, u32 &col)
+{
+    u32 q = (u32)((float)t * inv_w);            // within one of the quotient
+    int r = (int)(t - q * w);
+    if (r < 0) { q -= 1u; r += (int)w; }
+    else if (r >= (int)w) { q += 1u; r -= (int)w; }
+    row = q; col = (u32)r;
+}
+
 }  // namespace lmk
 #endif
