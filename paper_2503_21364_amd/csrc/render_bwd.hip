@@ -11,26 +11,32 @@
 // stops the walk and everything behind it get nothing; where a was clamped to 0.99 it depends
 // on neither o nor q.
 //
-// One workgroup per 16x16 tile, one thread per pixel, each wavefront an 8x8 block.  Entries are
-// staged in LDS in batches of 256.  Per batch every wavefront first tests, one entry per lane,
-// which entries can reach alpha >= 1/255 anywhere in its block (the block test of blend_kernel)
-// and keeps their slots in a list; its pixels then only walk that list.  Pass 1 repeats the
-// forward walk with the arithmetic of blend_kernel (same expression for log2(alpha), same
-// comparisons), which gives every pixel its final transmittance and the position of its last
+// One workgroup per 16x16 tile, one thread per pixel, each wavefront an 8x8 block, each group of 16
+// lanes (row) a 4x4 sub-block of it.  Entries are staged in LDS in batches of 255 (slot 255 is a null
+// record that never contributes).  Per batch every wavefront first tests, one entry per lane, which
+// entries can reach alpha >= 1/255 in its block and then in each sub-block (the tests of blend_kernel) and
+// keeps their slots in one list per row; the pixels of a row walk that list, four entries at a time.
+// Pass 1 repeats the forward walk with the arithmetic of blend_kernel (same expression for log2(alpha),
+// same comparisons), which gives every pixel its final transmittance and the position of its last
 // composited entry.  Pass 2 takes the batches, and each list, back to front: T_i is recovered as
-// T_{i+1} / (1 - a_i), S_i is a running sum.  What is summed over the pixels of an entry are not the
-// nine gradient components themselves but nine moments from which they follow linearly, with
-// m = a dL/da (0 where a was clamped): sum m dx, sum m dy, sum m dx^2, sum m dx dy, sum m dy^2,
-// sum m, and sum w dL/dC per channel; the per-entry factors (A, B, C, 1 / opacity) are applied once
-// per (tile, entry) when the sums leave the workgroup.  A pixel without a contribution adds zeros,
-// so the arithmetic has no branches.  The sums go over the 4 lanes of a quad with DPP adds, over
-// the quads and rows of the tile with LDS float atomics, and leave the workgroup as one global
-// float atomic per (entry, component): the order of these additions is not fixed, so results
-// differ from run to run by fp32 rounding.
+// T_{i+1} / (1 - a_i), S_i is a running sum.
 //
-// Bound by vector-instruction issue (the exponent evaluation of the forward pass, twice, the
-// gradient arithmetic and the reductions); HBM traffic is the forward's gather, twice, plus 36
-// bytes of atomics per pair.
+// What is summed over the pixels of an entry are not the nine gradient components themselves but nine
+// moments from which they follow: with m = a dL/da (0 where a was clamped) the sums of m {1, x, y, x^2,
+// x y, y^2} over the pixel positions, and of w dL/dC per channel.  Against the four entries of a step the
+// pixel's factors -- {1, x, y, x^2}, {x y, y^2} and its upstream gradient -- are constants, so these sums
+// are matrix products: (entry x pixel) . (pixel x moment), one 4x4x4 block per row, on the matrix cores in
+// double precision (m and w go in as they are, every product is exact, and the positions can be taken
+// from the tile's reference point; moving the moments to the splat's centre would lose digits in fp32).
+// m and w change from lane = pixel to lane = (entry, pixels) through LDS.  The results are added to
+// per-entry LDS accumulators, moved to the splat's centre and multiplied by the per-entry factors (A, B,
+// C, 1 / opacity) once per (tile, entry), and leave the workgroup as one global float atomic per (entry,
+// component): the order of these additions is not fixed, so results differ from run to run by fp32
+// rounding.
+//
+// Bound by vector-instruction issue (the exponent evaluation of the forward pass, twice, and the
+// gradient arithmetic) and by the LDS pipe; HBM traffic is the forward's gather, twice, plus 36 bytes of
+// atomics per pair.
 #include "lmk_gs_internal.h"
 #include "blend_reach.h"
 
@@ -38,48 +44,25 @@ namespace lmk {
 
 namespace {
 
-constexpr u32 kBwdThreads = 256, kBwdBatch = 256;
+constexpr u32 kBwdThreads = 256, kBwdBatch = 255, kNullSlot = 255;
 constexpr u32 kBwdWaves = kBwdThreads / kWave;
-typedef unsigned char slot_t;               // a slot of the staged batch (kBwdBatch <= 256)
-static_assert(kBwdBatch <= 256 && (kBwdBatch & (kBwdBatch - 1)) == 0, "slots are bytes and masked");
-static_assert(kBwdBatch <= kBwdThreads, "one thread stages one entry");
-constexpr u32 kGradComps = 9;               // u, v, A, B, C, opacity, r, g, b
+typedef unsigned char slot_t;               // a slot of the staged batch
+constexpr u32 kBwdStep = 4;                 // list entries walked together
+constexpr u32 kBwdList = kBwdBatch + 1u + 2u * kBwdStep;    // a list and the null slots behind it
+static_assert(kBwdList % kBwdStep == 0, "lists are read four slots at a time");
+constexpr u32 kTurnStride = kWave + 4;      // floats between the four entries of a step in LDS (bank spread)
+constexpr u32 kGradComps = 9;               // moments: m x, m y, m x^2, m x y, m y^2, m, then w per channel
 
 struct BwdParams {
     u32 width, height, tiles_x, num_tiles;
     float bg0, bg1, bg2;
 };
 
-// sum over the 16 lanes of a row, returned in every lane of the row
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v)
+__device__ __forceinline__ void wave_fence()
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-// Sums over the 16 lanes of a row, transposed on the way: lane k of every quad ends with the
-// row's sums of components k and 4 + k (sA, sB); component 8 ends in every lane (sC).  A step
-// pairs two components: the even side of the exchange keeps the first and hands over the second,
-// the odd side the other way round, so every step halves the registers in play.
-__device__ __forceinline__ void row_sums_transposed(const float (&v)[kGradComps], bool odd, bool upper,
-                                                     float &sA, float &sB, float &sC)
-{
-    float r[4];
-#pragma unroll
-    for (u32 c = 0; c < 4; ++c) {                                  // lane xor 1: components (2c, 2c + 1)
-        const float keep = odd ? v[2 * c + 1] : v[2 * c], send = odd ? v[2 * c] : v[2 * c + 1];
-        r[c] = keep + dpp_f<0xB1>(send);                           // quad_perm [1,0,3,2]
-    }
-    const float r8 = v[8] + dpp_f<0xB1>(v[8]);
-    {                                                              // lane xor 2: (r0, r1) and (r2, r3)
-        const float keepA = upper ? r[1] : r[0], sendA = upper ? r[0] : r[1];
-        const float keepB = upper ? r[3] : r[2], sendB = upper ? r[2] : r[3];
-        sA = keepA + dpp_f<0x4E>(sendA);                           // quad_perm [2,3,0,1]
-        sB = keepB + dpp_f<0x4E>(sendB);
-    }
-    sC = r8 + dpp_f<0x4E>(r8);
-    // ... and over the four quads of the row (rotations by one and two quads keep a lane's place in its quad)
-    sA += dpp_f<0x124>(sA); sB += dpp_f<0x124>(sB); sC += dpp_f<0x124>(sC);      // row_ror:4
-    sA += dpp_f<0x128>(sA); sB += dpp_f<0x128>(sB); sC += dpp_f<0x128>(sC);      // row_ror:8
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // one list entry on its way from the feature records to LDS: fetched a batch ahead, so that the two
@@ -122,7 +105,7 @@ __device__ __forceinline__ u32 block_survivors(const float4 *s_geo, const float4
 // survivor per lane, tested against the four sub-blocks; list order is kept
 __device__ __forceinline__ void subblock_survivors(const float4 *s_geo, const float4 *s_cop, const float4 *s_tst,
                                                    const slot_t *list8, u32 n8, float bx, float by, u32 lane,
-                                                   slot_t (*list4)[kBwdBatch], u32 (&n4)[4], const u32 (&limit)[4])
+                                                   slot_t (*list4)[kBwdList], u32 (&n4)[4], const u32 (&limit)[4])
 {
     n4[0] = n4[1] = n4[2] = n4[3] = 0u;
     for (u32 k0 = 0; k0 < n8; k0 += kWave) {
@@ -147,22 +130,29 @@ __device__ __forceinline__ void subblock_survivors(const float4 *s_geo, const fl
     }
 }
 
-__global__ __launch_bounds__(kBwdThreads) void blend_backward_kernel(
+// the four slots at position k of a row's list; beyond the row's own end null slots
+__device__ __forceinline__ u32 list_word(const slot_t *list, u32 k, u32 n_pad)
+{
+    return *reinterpret_cast<const u32 *>(list + (k < n_pad ? k : n_pad));
+}
+
+__global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     const u64 *__restrict__ tile_offsets, const u32 *__restrict__ tile_order, const u32 *__restrict__ vals,
     const float4 *__restrict__ feat, BwdParams bp, const float *__restrict__ grad_rgb,
     const float *__restrict__ grad_T, float *__restrict__ grad_feat)
 {
     // the staged form of blend_kernel (stage_entry), so that log2(alpha) is evaluated exactly as there
-    __shared__ float4 s_geo[kBwdBatch];          // du, dv, A', -B/A
-    __shared__ float4 s_cop[kBwdBatch];          // -0.5 log2(e) (C - B^2/A), lo, r, g
-    __shared__ float4 s_tst[kBwdBatch];          // B', C', b, -B/C
-    __shared__ u32 s_id[kBwdBatch];              // primitive index
-    // double precision: the LDS adds a double in a fraction of the time it takes for a float (measured on
-    // this chip: 0.3 against 3 cycles per lane), and the sums of a tile lose nothing on the way
-    __shared__ double s_acc[kBwdBatch][kGradComps];
-    __shared__ slot_t s_list[kBwdWaves][kBwdBatch];
-    __shared__ slot_t s_list4[kBwdWaves][4][kBwdBatch];
+    __shared__ float4 s_geo[kBwdBatch + 1];      // du, dv, A', -B/A
+    __shared__ float4 s_cop[kBwdBatch + 1];      // -0.5 log2(e) (C - B^2/A), lo, r, g
+    __shared__ float4 s_tst[kBwdBatch + 1];      // B', C', b, -B/C
+    __shared__ u32 s_id[kBwdBatch + 1];          // primitive index
+    __shared__ double s_acc[kBwdBatch + 1][kGradComps];
+    // per wavefront: the block's survivors while the lists are built, then m (and w) of a step on their
+    // way from lane = pixel to lane = (entry, pixels)
+    __shared__ __attribute__((aligned(16))) float s_turn[kBwdWaves][kBwdStep * kTurnStride];
+    __shared__ __attribute__((aligned(16))) slot_t s_list4[kBwdWaves][4][kBwdList];
     __shared__ u32 s_last[kBwdWaves];
+    static_assert(sizeof(s_turn[0]) >= kBwdBatch, "the survivors' slots fit");
 
     if (blockIdx.x >= bp.num_tiles) return;
     // the tiles with the longest lists first, when the caller has the hint
@@ -182,8 +172,26 @@ __global__ __launch_bounds__(kBwdThreads) void blend_backward_kernel(
     const u64 start = tile_offsets[tile], end = tile_offsets[tile + 1];
     const u64 len64 = end - start;
     const u32 len = len64 < 0xffffff00ull ? (u32)len64 : 0xffffff00u;     // a tile's list is far shorter
-    slot_t *my_list = s_list[wv];
-    const slot_t *my_list4 = s_list4[wv][grp];
+    slot_t *my_list = reinterpret_cast<slot_t *>(s_turn[wv]);
+    slot_t *my_list4 = s_list4[wv][grp];
+
+    if (tid == kNullSlot) {
+        s_geo[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+        s_cop[tid] = make_float4(0.f, -1000.0f, 0.f, 0.f);
+        s_tst[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+        s_id[tid] = 0u;
+    }
+    // lists of the staged batch; returns the longest of the four, n_mine = the length of this row's
+    auto build_lists = [&](u32 cnt, const u32 (&limit)[4], u32 (&n4)[4], u32 &n_mine) -> u32 {
+        const u32 n8 = block_survivors(s_geo, s_cop, s_tst, cnt, bx, by, lane, my_list);
+        wave_fence();
+        subblock_survivors(s_geo, s_cop, s_tst, my_list, n8, bx, by, lane, s_list4[wv], n4, limit);
+        n_mine = grp == 0u ? n4[0] : (grp == 1u ? n4[1] : (grp == 2u ? n4[2] : n4[3]));
+        if (gl < 2u * kBwdStep) my_list4[n_mine + gl] = (slot_t)kNullSlot;
+        wave_fence();
+        const u32 l01 = n4[0] > n4[1] ? n4[0] : n4[1], l23 = n4[2] > n4[3] ? n4[2] : n4[3];
+        return l01 > l23 ? l01 : l23;
+    };
 
     // ---- pass 1: the forward walk
     float T = 1.0f;
@@ -200,25 +208,30 @@ __global__ __launch_bounds__(kBwdThreads) void blend_backward_kernel(
         __syncthreads();
         next = fetch_entry(vals, feat, start + base + kBwdBatch + tid, tid < kBwdBatch && base + kBwdBatch + tid < len);
         if (__builtin_amdgcn_ballot_w64(!done) == 0ull) continue;     // this wavefront is finished
-        const u32 n8 = block_survivors(s_geo, s_cop, s_tst, cnt, bx, by, lane, my_list);
-        u32 n4[4];
+        u32 n4[4], n_mine;
         const u32 no_limit[4] = { kBwdBatch, kBwdBatch, kBwdBatch, kBwdBatch };
-        subblock_survivors(s_geo, s_cop, s_tst, my_list, n8, bx, by, lane, s_list4[wv], n4, no_limit);
-        const u32 n_mine = grp == 0u ? n4[0] : (grp == 1u ? n4[1] : (grp == 2u ? n4[2] : n4[3]));
-        const u32 l01 = n4[0] > n4[1] ? n4[0] : n4[1], l23 = n4[2] > n4[3] ? n4[2] : n4[3];
-        const u32 longest = l01 > l23 ? l01 : l23;
-        for (u32 k = 0; k < longest; ++k) {
-            const bool in_list = k < n_mine;
-            const u32 j = (u32)my_list4[in_list ? k : 0u] & (kBwdBatch - 1u);
-            const float4 g = s_geo[j];
-            const float4 co = s_cop[j];
-            const float dx = g.x - ox, dy = g.y - oy;
-            const float alpha = fminf(0.99f, __builtin_amdgcn_exp2f(log2_alpha(g, co, dx, dy)));
-            const float Tn = fmaf(-T, alpha, T);
-            const bool hit = in_list && !done && !(alpha < 1.0f / 255.0f);
-            const bool stop = hit && Tn < 1e-4f;
-            if (hit && !stop) { T = Tn; last = base + j + 1u; }
-            done = done || stop;
+        const u32 longest = build_lists(cnt, no_limit, n4, n_mine);
+        const u32 n_pad = (n_mine + kBwdStep - 1u) & ~(kBwdStep - 1u);
+        for (u32 k = 0; k < longest; k += kBwdStep) {
+            const u32 word = list_word(my_list4, k, n_pad);
+            float alpha[kBwdStep];
+#pragma unroll
+            for (u32 q = 0; q < kBwdStep; ++q) {
+                const u32 j = (word >> (8u * q)) & 255u;
+                const float4 g = s_geo[j];
+                const float2 co = *reinterpret_cast<const float2 *>(&s_cop[j]);
+                alpha[q] = fminf(0.99f, __builtin_amdgcn_exp2f(log2_alpha(g, make_float4(co.x, co.y, 0.f, 0.f), g.x - ox, g.y - oy)));
+            }
+#pragma unroll
+            for (u32 q = 0; q < kBwdStep; ++q) {
+                const float Tn = fmaf(-T, alpha[q], T);
+                const bool hit = !done && !(alpha[q] < 1.0f / 255.0f);
+                const bool stop = hit && Tn < 1e-4f;
+                const bool upd = hit && !stop;
+                T = upd ? Tn : T;
+                last = upd ? base + 1u + ((word >> (8u * q)) & 255u) : last;
+                done = done || stop;
+            }
             if (__builtin_amdgcn_ballot_w64(!done) == 0ull) break;     // all 64 pixels stopped
         }
     }
@@ -256,6 +269,27 @@ __global__ __launch_bounds__(kBwdThreads) void blend_backward_kernel(
     const float gT_end = gT * T_end;
     float Sr = bp.bg0 * T_end, Sg = bp.bg1 * T_end, Sb = bp.bg2 * T_end;
     T = T_end;
+    // the matrix products.  v_mfma_f64_4x4x4, four blocks: block b = row b of this wavefront; operand A
+    // (entry i, pixel slot k) sits in lane i + 4 b + 16 k, operand B (pixel slot k, moment j) in lane
+    // j + 4 b + 16 k, the result (entry i, moment j) in lane j + 4 b + 16 i.  In instruction s of four the
+    // pixel slot k stands for pixel (x, y) = (s, k) of the sub-block.
+    const u32 ml = lane & 3u, mb = (lane >> 2) & 3u, mk = lane >> 4;
+    float *turn = s_turn[wv];
+    double B1[kBwdStep], B2[kBwdStep], B3[kBwdStep];
+    {
+        turn[lane] = gr; turn[kWave + lane] = gg; turn[2 * kWave + lane] = gb;
+        wave_fence();
+        const float my = by + ((float)((mb >> 1) * 4u + mk) - 3.5f);
+#pragma unroll
+        for (u32 s = 0; s < kBwdStep; ++s) {
+            const float mx = bx + ((float)((mb & 1u) * 4u + s) - 3.5f);
+            B1[s] = ml == 0u ? 1.0 : (double)(ml == 1u ? mx : (ml == 2u ? my : mx * mx));
+            B2[s] = ml == 0u ? (double)(mx * my) : (ml == 1u ? (double)(my * my) : 0.0);
+            B3[s] = ml < 3u ? (double)turn[(ml < 3u ? ml : 0u) * kWave + mb * 16u + mk * 4u + s] : 0.0;
+        }
+        wave_fence();
+    }
+    const slot_t *out_list = s_list4[wv][mb];
     const u32 batches = (max_last + kBwdBatch - 1) / kBwdBatch;
     next = fetch_entry(vals, feat, start + (batches - 1u) * kBwdBatch + tid,
                        tid < kBwdBatch && (batches - 1u) * kBwdBatch + tid < max_last);
@@ -270,79 +304,110 @@ __global__ __launch_bounds__(kBwdThreads) void blend_backward_kernel(
         }
         // the batch in front of this one (all of its slots lie below max_last)
         next = fetch_entry(vals, feat, start + base - kBwdBatch + tid, b > 0u && tid < kBwdBatch);
-        for (u32 k = tid; k < kBwdBatch * kGradComps; k += kBwdThreads) (&s_acc[0][0])[k] = 0.0;
+        for (u32 k = tid; k < (kBwdBatch + 1u) * kGradComps; k += kBwdThreads) (&s_acc[0][0])[k] = 0.0;
         __syncthreads();
         // a wavefront none of whose pixels walked this far has nothing to add (it still takes part
         // in the barriers and the flush below)
-        const u32 n8 = base < wl ? block_survivors(s_geo, s_cop, s_tst, cnt, bx, by, lane, my_list) : 0u;
-        u32 n4[4];
-        u32 limit[4];
+        u32 longest = 0, n4[4] = { 0u, 0u, 0u, 0u }, n_mine = 0;
+        if (base < wl) {
+            u32 limit[4];
 #pragma unroll
-        for (u32 q = 0; q < 4; ++q) limit[q] = sub_last[q] > base ? sub_last[q] - base : 0u;
-        subblock_survivors(s_geo, s_cop, s_tst, my_list, n8, bx, by, lane, s_list4[wv], n4, limit);
-        const u32 n_mine = grp == 0u ? n4[0] : (grp == 1u ? n4[1] : (grp == 2u ? n4[2] : n4[3]));
-        const u32 l01 = n4[0] > n4[1] ? n4[0] : n4[1], l23 = n4[2] > n4[3] ? n4[2] : n4[3];
-        const u32 longest = l01 > l23 ? l01 : l23;
-        for (u32 k = longest; k-- > 0;) {
-            const bool in_list = k < n_mine;
-            const u32 j = (u32)my_list4[in_list ? k : 0u] & (kBwdBatch - 1u);    // the same for the 16 lanes of a row
-            const float4 g = s_geo[j];
-            const float4 co = s_cop[j];
-            const float dx = g.x - ox, dy = g.y - oy;
-            const float raw = __builtin_amdgcn_exp2f(log2_alpha(g, co, dx, dy));
-            const float alpha = fminf(0.99f, raw);
-            const bool hit = in_list && base + j < last && !(alpha < 1.0f / 255.0f);
-            const u64 hits = __builtin_amdgcn_ballot_w64(hit);
-            if (hits == 0ull) continue;                                  // nothing from this wavefront
+            for (u32 q = 0; q < 4; ++q) limit[q] = sub_last[q] > base ? sub_last[q] - base : 0u;
+            longest = build_lists(cnt, limit, n4, n_mine);
+        }
+        const u32 n_pad = (n_mine + kBwdStep - 1u) & ~(kBwdStep - 1u);
+        const u32 n_out = mb == 0u ? n4[0] : (mb == 1u ? n4[1] : (mb == 2u ? n4[2] : n4[3]));
+        const u32 out_pad = (n_out + kBwdStep - 1u) & ~(kBwdStep - 1u);
+        const u32 my_last = last > base ? last - base : 0u;                 // slots below it lie in front of this pixel's end
+        for (u32 k = (longest + kBwdStep - 1u) & ~(kBwdStep - 1u); k > 0;) {
+            k -= kBwdStep;
+            const u32 word = list_word(my_list4, k, n_pad);                 // the same for the 16 lanes of a row
+            float4 co[kBwdStep];
+            float raw[kBwdStep];
+            bool hit[kBwdStep], any = false;
+#pragma unroll
+            for (u32 q = 0; q < kBwdStep; ++q) {
+                const u32 j = (word >> (8u * q)) & 255u;
+                const float4 g = s_geo[j];
+                co[q] = s_cop[j];
+                raw[q] = __builtin_amdgcn_exp2f(log2_alpha(g, co[q], g.x - ox, g.y - oy));
+                hit[q] = j < my_last && !(raw[q] < 1.0f / 255.0f);          // of fminf(0.99, raw): the same
+                any = any || hit[q];
+            }
+            if (__builtin_amdgcn_ballot_w64(any) == 0ull) continue;          // nothing from this wavefront
             // a pixel without a contribution goes through the same arithmetic with a = 0: T and S
-            // stay as they are and all nine moments are zero
-            const float a = hit ? alpha : 0.0f;
-            const float blue = s_tst[j].z;
-            const float inv = __builtin_amdgcn_rcpf(1.0f - a);     // 1 - a >= 0.01; one ulp is enough here
-            // dL/da = (dL/dC . (T c - S) - dL/dT_end T_end) / (1 - a), T = transmittance behind the entry
-            const float num = fmaf(gr, fmaf(T, co.z, -Sr), fmaf(gg, fmaf(T, co.w, -Sg), fmaf(gb, fmaf(T, blue, -Sb), -gT_end)));
-            T *= inv;                                              // transmittance in front of this entry
-            const float w = a * T;
-            Sr = fmaf(co.z, w, Sr); Sg = fmaf(co.w, w, Sg); Sb = fmaf(blue, w, Sb);
-            const float m = (raw > 0.99f ? 0.0f : a) * (num * inv);     // a dL/da; a clamped alpha depends on nothing
-            float v[kGradComps];
-            v[0] = m * dx; v[1] = m * dy;
-            v[2] = v[0] * dx; v[3] = v[0] * dy; v[4] = v[1] * dy;
-            v[5] = m;
-            v[6] = w * gr; v[7] = w * gg; v[8] = w * gb;
-            // over the row in registers, over the rows of the tile in LDS: the first quad of every row
-            // that had a contribution adds, each lane the two components it ended up with
-            float sA, sB, sC;
-            row_sums_transposed(v, (lane & 1u) != 0u, (lane & 2u) != 0u, sA, sB, sC);
-            const bool row_hit = ((hits >> (lane & 48u)) & 0xffffull) != 0ull;
-            if (row_hit && (lane & 12u) == 0u) {
-                double *rec = s_acc[j];
-                atomicAdd(rec + (lane & 3u), (double)sA);
-                atomicAdd(rec + 4u + (lane & 3u), (double)sB);
-                if ((lane & 3u) == 0u) atomicAdd(rec + 8u, (double)sC);
+            // stay as they are and all its moments are zero
+            float m[kBwdStep], w[kBwdStep];
+#pragma unroll
+            for (u32 q = kBwdStep; q-- > 0;) {
+                const float a = hit[q] ? fminf(0.99f, raw[q]) : 0.0f;
+                const float blue = s_tst[(word >> (8u * q)) & 255u].z;
+                const float inv = __builtin_amdgcn_rcpf(1.0f - a);     // 1 - a >= 0.01; one ulp is enough here
+                // dL/da = (dL/dC . (T c - S) - dL/dT_end T_end) / (1 - a), T = transmittance behind the entry
+                const float num = fmaf(gr, fmaf(T, co[q].z, -Sr), fmaf(gg, fmaf(T, co[q].w, -Sg), fmaf(gb, fmaf(T, blue, -Sb), -gT_end)));
+                T *= inv;                                              // transmittance in front of this entry
+                w[q] = a * T;
+                Sr = fmaf(co[q].z, w[q], Sr); Sg = fmaf(co[q].w, w[q], Sg); Sb = fmaf(blue, w[q], Sb);
+                m[q] = (raw[q] > 0.99f ? 0.0f : a) * (num * inv);      // a dL/da; a clamped alpha depends on nothing
+            }
+            // lane = pixel -> lane = (entry, row, four pixels); LDS accesses of a wavefront complete in order
+#pragma unroll
+            for (u32 q = 0; q < kBwdStep; ++q) turn[q * kTurnStride + lane] = m[q];
+            wave_fence();
+            const float4 am = *reinterpret_cast<const float4 *>(turn + ml * kTurnStride + mb * 16u + mk * 4u);
+            wave_fence();
+#pragma unroll
+            for (u32 q = 0; q < kBwdStep; ++q) turn[q * kTurnStride + lane] = w[q];
+            wave_fence();
+            const float4 aw = *reinterpret_cast<const float4 *>(turn + ml * kTurnStride + mb * 16u + mk * 4u);
+            wave_fence();
+            const double Am[kBwdStep] = { (double)am.x, (double)am.y, (double)am.z, (double)am.w };
+            const double Aw[kBwdStep] = { (double)aw.x, (double)aw.y, (double)aw.z, (double)aw.w };
+            double d1 = 0.0, d2 = 0.0, d3 = 0.0;
+#pragma unroll
+            for (u32 s = 0; s < kBwdStep; ++s) {
+                d1 = __builtin_amdgcn_mfma_f64_4x4x4f64(Am[s], B1[s], d1, 0, 0, 0);
+                d2 = __builtin_amdgcn_mfma_f64_4x4x4f64(Am[s], B2[s], d2, 0, 0, 0);
+                d3 = __builtin_amdgcn_mfma_f64_4x4x4f64(Aw[s], B3[s], d3, 0, 0, 0);
+            }
+            // lane j + 4 b + 16 i: moment j of entry i of row b
+            const u32 slot = out_list[(k < out_pad ? k : out_pad) + mk];
+            if (slot != kNullSlot) {
+                double *rec = s_acc[slot];
+                atomicAdd(rec + (ml == 0u ? 5u : ml - 1u), d1);
+                if (ml < 2u) atomicAdd(rec + 3u + ml, d2);
+                if (ml < 3u) atomicAdd(rec + 6u + ml, d3);
             }
         }
         __syncthreads();
-        // from the moments of an entry to its gradient: q = A dx^2 + 2 B dx dy + C dy^2, da/dq = -a / 2,
-        // da/do = a / o; the staged A' = -0.5 log2(e) A, B' = -log2(e) B, C' = -0.5 log2(e) C give
-        // d/du = ln 2 (2 A' sum m dx + B' sum m dy), d/dv = ln 2 (B' sum m dx + 2 C' sum m dy).
+        // from the moments of an entry to its gradient.  About the splat's centre (u, v), seen from the
+        // reference point: sum m dx = u M - M_x with dx = u - x, and so on; q = A dx^2 + 2 B dx dy + C dy^2,
+        // da/dq = -a / 2, da/do = a / o; the staged A' = -0.5 log2(e) A, B' = -log2(e) B, C' = -0.5 log2(e) C
+        // give d/du = ln 2 (2 A' sum m dx + B' sum m dy), d/dv = ln 2 (B' sum m dx + 2 C' sum m dy).
         // Consecutive lanes take the consecutive components of an entry, so that the atomics of one
         // instruction fall into few cache lines (nine lanes per 36-byte record)
         for (u32 idx = tid; idx < cnt * kGradComps; idx += kBwdThreads) {
             const u32 e = idx / kGradComps, c = idx - e * kGradComps;
             const float kLn2 = 0.6931471805599453f;
-            float v = (float)s_acc[e][c];
-            if (c < 2u) {
-                const float mx = (float)s_acc[e][0], my = (float)s_acc[e][1];
-                const float Aq = s_geo[e].z, Bq = s_tst[e].x, Cq = s_tst[e].y;
-                v = c == 0u ? kLn2 * fmaf(2.0f * Aq, mx, Bq * my) : kLn2 * fmaf(Bq, mx, 2.0f * Cq * my);
-            } else if (c == 2u || c == 4u) {
-                v *= -0.5f;
-            } else if (c == 3u) {
-                v = -v;
+            const double *rec = s_acc[e];
+            double own = rec[c];
+            if (c < 5u) {
+                const float4 g = s_geo[e];
+                const double u = (double)g.x, v = (double)g.y, M = rec[5], mx = u * M - rec[0], my = v * M - rec[1];
+                if (c < 2u) {
+                    const double Aq = (double)g.z, Bq = (double)s_tst[e].x, Cq = (double)s_tst[e].y;
+                    own = (double)kLn2 * (c == 0u ? 2.0 * Aq * mx + Bq * my : Bq * mx + 2.0 * Cq * my);
+                } else {
+                    // sum m p q' with p, q' in {dx, dy}: p (sum m q') - q'_centre M_p + M_pq
+                    const double p = c == 4u ? v : u, q = c == 2u ? u : v, mq = c == 2u ? mx : my;
+                    const double Mp = c == 4u ? rec[1] : rec[0];
+                    own = p * mq - q * Mp + own;
+                    own *= c == 3u ? -1.0 : -0.5;
+                }
             } else if (c == 5u) {
-                v *= __builtin_amdgcn_exp2f(-s_cop[e].y);       // 1 / opacity
+                own *= (double)__builtin_amdgcn_exp2f(-s_cop[e].y);       // 1 / opacity
             }
+            const float v = (float)own;
             if (v != 0.0f) atomicAdd(grad_feat + (size_t)s_id[e] * LMK_GS_FEAT_STRIDE + c, v);
         }
     }
