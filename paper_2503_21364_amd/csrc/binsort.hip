@@ -31,14 +31,15 @@
 //            advances the tile's running position pair by pair, again with lane-consecutive
 //            atomics, eight steps in flight.  What is written is the composite the list is
 //            ordered by, depth bits << 32 | index.
-//   tile sort  every tile's slice is sorted by that composite with a merge sort in LDS and
-//            rewritten in its final form (key = tile << 32 | depth bits, value = index): one
-//            wavefront for lists of up to 512 pairs, 256 threads up to 2048, 512 threads up to
-//            4096.  A list of up to 16384 pairs is cut into 4096-pair chunks, sorted by
-//            workgroups of the 512-thread launch and merged in two rounds between the two pair
-//            buffers by workgroups of the 256-thread and the one-wavefront launch.  Lists beyond
-//            that get a workgroup of 1024 threads each: 16384-pair chunks in LDS, then pairwise
-//            merges through LDS-staged windows.
+//   tile sort  every tile's slice is sorted by that composite and rewritten in its final form (key = tile <<
+//            32 | depth bits, value = index): 512 threads for lists of up to 4096 pairs, 256 up to 2048, one
+//            wavefront up to 512 (the two smaller classes in one launch).  The pairs go to buckets of
+//            equal depth steps in LDS, one or two in each, and are ranked inside them; where a bucket gets
+//            more than 64 (equal depths, dense clusters) the list goes through a merge sort instead.  A
+//            list of up to 16384 pairs is cut into 4096-pair chunks, sorted by workgroups of the 512-thread
+//            launch and merged in two rounds between the two pair buffers, by workgroups of the 256-thread
+//            launch and by a launch of wavefronts.  Lists beyond that get a workgroup of 1024 threads each:
+//            16384-pair chunks merge-sorted in LDS, then pairwise merges through LDS-staged windows.
 //
 // Integer work, bound by HBM traffic, global atomic throughput and, in the per-tile sorts, by
 // LDS bandwidth and vector issue.  Atomics on one address are served one after the other (about
@@ -753,7 +754,7 @@ __device__ __forceinline__ void sort_pairs_in_lds(u64 *keys, u32 *vals, u64 beg,
                                                   u64 *keys_out = nullptr, u32 *vals_out = nullptr)
 {
     if (!keys_out) { keys_out = keys; vals_out = vals; }    // in place unless the caller wants the result elsewhere
-    const u32 tid = threadIdx.x;
+    const u32 tid = team_thread<THREADS>();
     sort_in_lds<THREADS, ITEMS>(n, s, [&](u32 i) { return keys[beg + i]; });
     const u64 hi_bits = (u64)tile << 32;
     for (u32 p = tid; p < n; p += THREADS) {
@@ -761,7 +762,135 @@ __device__ __forceinline__ void sort_pairs_in_lds(u64 *keys, u32 *vals, u64 beg,
         keys_out[beg + p] = hi_bits | (c >> 32);
         vals_out[beg + p] = (u32)c;
     }
-    __syncthreads();                                        // s may be refilled by the caller
+    team_sync<THREADS>();                                        // s may be refilled by the caller
+}
+
+// The same result for up to THREADS * ITEMS pairs with one counting step instead of the merge rounds: the
+// composites go to buckets by depth, equal steps between the list's smallest and largest, as many buckets
+// as pairs fit; a bucket holds one or two of them, and the place of a pair in its
+// bucket is the number of smaller ones there.  Some 60 vector instructions and a dozen LDS accesses a pair
+// where the merge sort takes 300 and 25.  1080p, 3 M primitives, 4.9 M pairs: lists of 2049 to 4096 pairs and
+// chunks 42 -> 24 us, of 513 to 2048 35 -> 22 us.  Equal steps of the depth's bits instead of the depth
+// (steps of equal ratio) crowd what is far into few buckets: inside a scene half of the long lists then
+// fell back.  A list with more than kMaxBucket pairs in one bucket (equal
+// depths, a dense cluster in front of a far background) is left to the merge sort: returns false, nothing
+// written.  Called by the whole team (a workgroup, or one wavefront); cnt holds THREADS * ITEMS / 2 words, two 16-bit counters each.
+constexpr u32 kMaxBucket = 64;
+
+template <u32 THREADS, u32 ITEMS>
+__device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg, u32 n, u32 tile, u64 *s, u32 *cnt)
+{
+    constexpr u32 CAP = THREADS * ITEMS, kWords = ITEMS / 2, kWaves = THREADS / kWave;
+    static_assert(CAP < 65536u && ITEMS % 2u == 0u, "positions are 16 bits wide, two to a word");
+    const u32 tid = team_thread<THREADS>(), lane = tid & (kWave - 1), wv = tid / kWave;
+    u64 e[ITEMS];
+    u32 lo = ~0u, hi = 0u;
+#pragma unroll
+    for (u32 k = 0; k < ITEMS; ++k) {
+        const u32 p = k * THREADS + tid;
+        e[k] = p < n ? keys[beg + p] : 0ull;
+    }
+#pragma unroll
+    for (u32 k = 0; k < ITEMS; ++k) {
+        const u32 d = (u32)(e[k] >> 32);
+        if (k * THREADS + tid < n) { lo = d < lo ? d : lo; hi = d > hi ? d : hi; }
+    }
+#pragma unroll
+    for (u32 k = 0; k < kWords; ++k) cnt[k * THREADS + tid] = 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const u32 a = __shfl_xor(lo, o, 64), b = __shfl_xor(hi, o, 64);
+        lo = a < lo ? a : lo; hi = b > hi ? b : hi;
+    }
+    u32 *part = reinterpret_cast<u32 *>(s);                 // free until the scatter
+    if (kWaves > 1u) {
+        if (lane == 0) { part[2 * wv] = lo; part[2 * wv + 1] = hi; }
+        team_sync<THREADS>();
+#pragma unroll
+        for (u32 k = 0; k < kWaves; ++k) {
+            const u32 a = part[2 * k], b = part[2 * k + 1];
+            lo = a < lo ? a : lo; hi = b > hi ? b : hi;
+        }
+    }
+    // equal steps of the depth itself (positive, so its bits order alike): a pixel column holds more of what
+    // is far.  A difference, a product with a positive constant and a conversion are all monotone, which is
+    // all that is needed; an infinite depth is left to the merge sort.
+    const float z0 = __uint_as_float(lo), z1 = __uint_as_float(hi);
+    const float scale = z1 > z0 ? (float)CAP / (z1 - z0) : 0.0f;
+    const bool plain = z1 < 3.0e38f && scale < 3.0e38f;     // the same for the whole team
+    auto bucket = [&](u64 c) -> u32 {
+        const u32 b = (u32)((__uint_as_float((u32)(c >> 32)) - z0) * scale);
+        return b < CAP - 1u ? b : CAP - 1u;
+    };
+    team_sync<THREADS>();                                        // counters clear, `part` read
+#pragma unroll
+    for (u32 k = 0; k < ITEMS; ++k) {
+        if (k * THREADS + tid < n) {
+            const u32 b = bucket(e[k]);
+            atomicAdd(&cnt[b >> 1], 1u << ((b & 1u) * 16u));
+        }
+    }
+    team_sync<THREADS>();
+    // exclusive scan: ITEMS consecutive buckets per thread
+    u32 w[kWords], sum = 0;
+    bool over = !plain;
+#pragma unroll
+    for (u32 k = 0; k < kWords; ++k) {
+        w[k] = cnt[tid * kWords + k];
+        over = over || (w[k] & 0xffffu) > kMaxBucket || (w[k] >> 16) > kMaxBucket;
+        sum += (w[k] & 0xffffu) + (w[k] >> 16);
+    }
+    u32 incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const u32 t = __shfl_up(incl, o, 64);
+        if ((int)lane >= o) incl += t;
+    }
+    if (kWaves > 1u && lane == kWave - 1) part[wv] = incl;
+    if (team_any<THREADS>(over)) return false;                // the same for the whole team
+    u32 run = incl - sum;
+    if (kWaves > 1u) {
+#pragma unroll
+        for (u32 k = 0; k < kWaves; ++k) run += k < wv ? part[k] : 0u;
+    }
+#pragma unroll
+    for (u32 k = 0; k < kWords; ++k) {
+        const u32 c0 = w[k] & 0xffffu, c1 = w[k] >> 16;
+        cnt[tid * kWords + k] = run | ((run + c0) << 16);
+        run += c0 + c1;
+    }
+    team_sync<THREADS>();
+#pragma unroll
+    for (u32 k = 0; k < ITEMS; ++k) {
+        if (k * THREADS + tid < n) {
+            const u32 b = bucket(e[k]), sh = (b & 1u) * 16u;
+            s[(atomicAdd(&cnt[b >> 1], 1u << sh) >> sh) & 0xffffu] = e[k];
+        }
+    }
+    team_sync<THREADS>();
+    // a bucket's counter now stands at its end, the one before at its start
+    const u64 hi_bits = (u64)tile << 32;
+#pragma unroll 2
+    for (u32 p = tid; p < n; p += THREADS) {
+        const u64 c = s[p];
+        const u32 b = bucket(c);
+        const u32 end = (cnt[b >> 1] >> ((b & 1u) * 16u)) & 0xffffu;
+        const u32 start = b ? (cnt[(b - 1u) >> 1] >> (((b - 1u) & 1u) * 16u)) & 0xffffu : 0u;
+        u32 at = start;
+        for (u32 j = start; j < end; ++j) at += s[j] < c ? 1u : 0u;
+        keys[beg + at] = hi_bits | (c >> 32);
+        vals[beg + at] = (u32)c;
+    }
+    return true;
+}
+
+// a list (or chunk) of 1 .. THREADS * ITEMS pairs, in place
+template <u32 THREADS, u32 ITEMS>
+__device__ __forceinline__ void sort_list(u64 *keys, u32 *vals, u64 beg, u32 n, u32 tile, u64 *s, u32 *cnt)
+{
+    if (bucket_sort_pairs<THREADS, ITEMS>(keys, vals, beg, n, tile, s, cnt)) return;
+    team_sync<THREADS>();                                        // `s` is free again
+    sort_pairs_in_lds<THREADS, ITEMS>(keys, vals, beg, n, tile, s);
 }
 
 // ---------------------------------------------------------------- merges between the pair buffers
@@ -858,6 +987,7 @@ __global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
     u32 num_tiles)
 {
     __shared__ u64 s[kMid + kMid / 16];
+    __shared__ __attribute__((aligned(16))) u32 s_cnt[kMid / 2];
     const u32 chunks = classes[4], elsewhere = classes[kDenseClass];
     if (elsewhere) return;
     if (blockIdx.x < chunks) {
@@ -868,7 +998,7 @@ __global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
         const u64 c0 = (u64)c.y * kMid;
         if (c0 >= len) return;                              // cannot happen with a consistent table
         const u32 n = (u32)(len - c0 < (u64)kMid ? len - c0 : (u64)kMid);
-        sort_pairs_in_lds<kMidThreads, kMidItems>(keys, vals, beg + c0, n, c.x, s);     // n >= 1
+        sort_list<kMidThreads, kMidItems>(keys, vals, beg + c0, n, c.x, s, s_cnt);     // n >= 1
         return;
     }
     const u32 k = blockIdx.x - chunks;
@@ -879,22 +1009,28 @@ __global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
     const u64 beg = tile_offsets[tile];
     const u64 len = tile_offsets[tile + 1] - beg;
     if (len < 2 || len > (u64)kMid) return;                 // cannot happen with a consistent table
-    sort_pairs_in_lds<kMidThreads, kMidItems>(keys, vals, beg, (u32)len, tile, s);
+    sort_list<kMidThreads, kMidItems>(keys, vals, beg, (u32)len, tile, s, s_cnt);
 }
 
-// Lists of kSmallCap + 1 .. kLow pairs, one workgroup each, and before them the first merge round
-// of the long lists (runs of kMid pairs, pair buffers -> alternate buffers), kLow outputs per
-// workgroup: a fixed number of workgroups walks the segments.
+// Lists of up to kLow pairs: one workgroup each above kSmallCap pairs, one wavefront each below.  Before
+// them the first merge round of the long lists (runs of kMid pairs, pair buffers -> alternate buffers), kLow
+// outputs per workgroup: a fixed number of workgroups walks the segments.  All of this is latency rather
+// than work, so it shares a launch (the short lists in one of their own: 10 000 primitives at 256 x 256
+// 6.4 + 7.0 us, together 7.7 us).
 constexpr u32 kMergeBlocks1 = 1024, kMergeBlocks2 = 2048;
+constexpr u32 kShortPerBlock = kLowThreads / kSmallThreads;
 __global__ __launch_bounds__(kLowThreads) void tile_sort_low_kernel(
     u64 *__restrict__ keys, u32 *__restrict__ vals, u64 *__restrict__ keys_alt, u32 *__restrict__ vals_alt,
     const u64 *__restrict__ tile_offsets, const u32 *__restrict__ order, const u32 *__restrict__ classes,
-    const uint2 *__restrict__ chunk_list, u32 num_tiles, u32 merge_blocks)
+    const uint2 *__restrict__ chunk_list, u32 num_tiles, u32 merge_blocks, u32 low_blocks)
 {
     constexpr u32 CAP = kLowThreads * kLowItems;
     constexpr u32 kPerChunk = kMid / CAP;                   // output segments per chunk
+    constexpr u32 kShortWords = kSmallCap + kSmallCap / 16; // LDS of a wavefront's own list
     __shared__ u64 s[CAP + CAP / 16];
+    __shared__ __attribute__((aligned(16))) u32 s_cnt[CAP / 2];
     __shared__ u64 s_split[2];
+    static_assert(kShortPerBlock * kShortWords <= CAP + CAP / 16 && kShortPerBlock * kSmallCap <= CAP, "a share each");
     if (blockIdx.x < merge_blocks) {
         const u64 segments = classes[kDenseClass] ? 0ull : (u64)classes[4] * kPerChunk;
         for (u64 g = blockIdx.x; g < segments; g += merge_blocks) {
@@ -907,59 +1043,62 @@ __global__ __launch_bounds__(kLowThreads) void tile_sort_low_kernel(
         }
         return;
     }
-    const u32 k = blockIdx.x - merge_blocks;
-    const u32 first = classes[0] + classes[3] + classes[1];
-    const u32 low = classes[kDenseClass] ? 0u : classes[2];
-    if (k >= low || first + k >= num_tiles) return;
-    const u32 tile = order[first + k];
-    if (tile >= num_tiles) return;
-    const u64 beg = tile_offsets[tile];
-    const u64 len = tile_offsets[tile + 1] - beg;
-    if (len < 2 || len > (u64)CAP) return;                  // cannot happen with a consistent table
-    sort_pairs_in_lds<kLowThreads, kLowItems>(keys, vals, beg, (u32)len, tile, s);
-}
-
-// Short lists (1 .. 512 pairs): one wavefront each, walking `order` from its short end.  Before
-// them the second and last merge round of the long lists (runs of 2 * kMid pairs, alternate
-// buffers -> pair buffers; a list of one such run is copied), kSmallCap outputs per segment.
-__global__ __launch_bounds__(kSmallThreads) void tile_sort_small_kernel(
-    u64 *__restrict__ keys, u32 *__restrict__ vals, const u64 *__restrict__ keys_alt, const u32 *__restrict__ vals_alt,
-    const u64 *__restrict__ tile_offsets, const u32 *__restrict__ order, const u32 *__restrict__ classes,
-    const uint2 *__restrict__ chunk_list, u32 num_tiles, u32 merge_blocks)
-{
-    constexpr u32 kPerChunk = kMid / kSmallCap;
-    __shared__ u64 s[kSmallCap + kSmallCap / 16];
-    __shared__ u64 s_split[2];
-    if (blockIdx.x < merge_blocks) {
-        const u64 segments = classes[kDenseClass] ? 0ull : (u64)classes[4] * kPerChunk;
-        for (u64 g = blockIdx.x; g < segments; g += merge_blocks) {
-            const uint2 c = chunk_list[g / kPerChunk];
-            if (c.x >= num_tiles) continue;
-            const u64 beg = tile_offsets[c.x];
-            const u64 len = tile_offsets[c.x + 1] - beg;
-            merge_segment<kSmallThreads, kSmallItems>(keys_alt + beg, vals_alt + beg, keys + beg, vals + beg, len,
-                                                      2 * (u64)kMid, (u64)c.y * kPerChunk + g % kPerChunk, c.x, s, s_split);
-        }
+    const u32 block = blockIdx.x - merge_blocks;
+    const u32 first = classes[0] + classes[3] + classes[1], low = classes[2], elsewhere = classes[kDenseClass];
+    if (elsewhere) return;
+    if (block < low_blocks) {
+        if (block >= low || first + block >= num_tiles) return;
+        const u32 tile = order[first + block];
+        if (tile >= num_tiles) return;
+        const u64 beg = tile_offsets[tile];
+        const u64 len = tile_offsets[tile + 1] - beg;
+        if (len < 2 || len > (u64)CAP) return;              // cannot happen with a consistent table
+        sort_list<kLowThreads, kLowItems>(keys, vals, beg, (u32)len, tile, s, s_cnt);
         return;
     }
-    const u32 k = blockIdx.x - merge_blocks;
+    // the short lists, 1 .. kSmallCap pairs; from here on every wavefront goes its own way
+    const u32 wv = threadIdx.x / kWave;
+    const u32 k = first + low + (block - low_blocks) * kShortPerBlock + wv;
     if (k >= num_tiles) return;
-    const u32 tile = order[num_tiles - 1 - k], elsewhere = classes[kDenseClass];
-    if ((tile >= num_tiles) | (elsewhere != 0u)) return;
+    const u32 tile = order[k];
+    if (tile >= num_tiles) return;
     const u64 beg = tile_offsets[tile];
     const u64 len = tile_offsets[tile + 1] - beg;
     if (len < 1 || len > (u64)kSmallCap) return;
     if (len == 1) {                                         // nothing to sort: only the pair's form changes
-        if (threadIdx.x == 0) {
+        if ((threadIdx.x & (kWave - 1u)) == 0u) {
             const u64 c = keys[beg];
             keys[beg] = ((u64)tile << 32) | (c >> 32); vals[beg] = (u32)c;
         }
         return;
     }
-    // fewer elements per lane for shorter lists: all 64 lanes work in every merge round
-    if (len <= 2u * kSmallThreads) sort_pairs_in_lds<kSmallThreads, 2u>(keys, vals, beg, (u32)len, tile, s);
-    else if (len <= 4u * kSmallThreads) sort_pairs_in_lds<kSmallThreads, 4u>(keys, vals, beg, (u32)len, tile, s);
-    else sort_pairs_in_lds<kSmallThreads, kSmallItems>(keys, vals, beg, (u32)len, tile, s);
+    u64 *my_s = s + wv * kShortWords;
+    u32 *my_cnt = s_cnt + wv * (kSmallCap / 2);
+    // fewer elements per lane for shorter lists
+    if (len <= 2u * kSmallThreads) sort_list<kSmallThreads, 2u>(keys, vals, beg, (u32)len, tile, my_s, my_cnt);
+    else if (len <= 4u * kSmallThreads) sort_list<kSmallThreads, 4u>(keys, vals, beg, (u32)len, tile, my_s, my_cnt);
+    else sort_list<kSmallThreads, kSmallItems>(keys, vals, beg, (u32)len, tile, my_s, my_cnt);
+}
+
+// The second and last merge round of the long lists (runs of 2 * kMid pairs, alternate buffers -> pair
+// buffers; a list of one such run is copied), kSmallCap outputs per segment.
+__global__ __launch_bounds__(kSmallThreads) void tile_merge_kernel(
+    u64 *__restrict__ keys, u32 *__restrict__ vals, const u64 *__restrict__ keys_alt, const u32 *__restrict__ vals_alt,
+    const u64 *__restrict__ tile_offsets, const u32 *__restrict__ classes,
+    const uint2 *__restrict__ chunk_list, u32 num_tiles)
+{
+    constexpr u32 kPerChunk = kMid / kSmallCap;
+    __shared__ u64 s[kSmallCap + kSmallCap / 16];
+    __shared__ u64 s_split[2];
+    const u64 segments = classes[kDenseClass] ? 0ull : (u64)classes[4] * kPerChunk;
+    for (u64 g = blockIdx.x; g < segments; g += gridDim.x) {
+        const uint2 c = chunk_list[g / kPerChunk];
+        if (c.x >= num_tiles) continue;
+        const u64 beg = tile_offsets[c.x];
+        const u64 len = tile_offsets[c.x + 1] - beg;
+        merge_segment<kSmallThreads, kSmallItems>(keys_alt + beg, vals_alt + beg, keys + beg, vals + beg, len,
+                                                  2 * (u64)kMid, (u64)c.y * kPerChunk + g % kPerChunk, c.x, s, s_split);
+    }
 }
 
 // ---------------------------------------------------------------- lists beyond kHuge pairs
@@ -1184,12 +1323,15 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
                        tile_count);
     hipLaunchKernelGGL(tile_sort_mid_kernel, dim3(max_mid), dim3(kMidThreads), 0, stream,
                        out.keys, out.vals, out.tile_offsets, order, classes, chunk_list, num_tiles);
-    hipLaunchKernelGGL(tile_sort_low_kernel, dim3(merge1 + max_low), dim3(kLowThreads), 0, stream,
+    const u32 short_blocks = (num_tiles + kShortPerBlock - 1) / kShortPerBlock;
+    hipLaunchKernelGGL(tile_sort_low_kernel, dim3(merge1 + max_low + short_blocks), dim3(kLowThreads), 0, stream,
                        out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, order, classes,
-                       chunk_list, num_tiles, merge1);
-    hipLaunchKernelGGL(tile_sort_small_kernel, dim3(merge2 + num_tiles), dim3(kSmallThreads), 0, stream,
-                       out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, order, classes,
-                       chunk_list, num_tiles, merge2);
+                       chunk_list, num_tiles, merge1, max_low);
+    // no list of the frame can be long if the buffers do not hold that many pairs
+    if (out.capacity > kMid)
+        hipLaunchKernelGGL(tile_merge_kernel, dim3(merge2), dim3(kSmallThreads), 0, stream,
+                           out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, classes,
+                           chunk_list, num_tiles);
     return hipGetLastError();
 }
 

@@ -98,13 +98,34 @@ __device__ __forceinline__ void ts_clean(u64 (&e)[ITEMS])
     }
 }
 
-// n >= 1 composites load(0 .. n) to s[ts_slot(0 .. n)], ascending.  Called by the whole workgroup; ends with a barrier.
+// What THREADS threads that work on one list wait on: a workgroup's barrier, or, for one wavefront -- which
+// may be one of several in its workgroup, each with a list of its own -- only the order of its LDS accesses.
+template <u32 THREADS>
+__device__ __forceinline__ void team_sync()
+{
+    if (THREADS > kWave) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+template <u32 THREADS>
+__device__ __forceinline__ bool team_any(bool v)
+{
+    return THREADS > kWave ? __syncthreads_or(v) != 0 : __builtin_amdgcn_ballot_w64(v) != 0ull;
+}
+template <u32 THREADS>
+__device__ __forceinline__ u32 team_thread() { return THREADS > kWave ? threadIdx.x : threadIdx.x & (kWave - 1u); }
+
+// n >= 1 composites load(0 .. n) to s[ts_slot(0 .. n)], ascending.  Called by the whole team; ends with its barrier.
 template <u32 THREADS, u32 ITEMS, class Load>
 __device__ __forceinline__ void sort_in_lds(u32 n, u64 *s, Load &&load)
 {
     constexpr u32 CAP = THREADS * ITEMS;
     constexpr u32 kLaneRun = 8 * ITEMS;                     // sorted run length after the lane merges
-    const u32 tid = threadIdx.x;
+    const u32 tid = team_thread<THREADS>();
     const u32 m = (n + ITEMS - 1) / ITEMS * ITEMS;          // elements in play: n rounded up to whole runs
     const u32 o0 = tid * ITEMS;
     const bool active = o0 < m;
@@ -141,7 +162,7 @@ __device__ __forceinline__ void sort_in_lds(u32 n, u64 *s, Load &&load)
 #pragma unroll
         for (u32 k = 0; k < ITEMS; ++k) s[ts_slot(o0 + k)] = e[k];
     }
-    __syncthreads();
+    team_sync<THREADS>();
 
     for (u32 run = kLaneRun; run < m && run < CAP; run <<= 1) {
         if (active) {
@@ -151,12 +172,12 @@ __device__ __forceinline__ void sort_in_lds(u32 n, u64 *s, Load &&load)
             const u32 b1 = a0 + 2 * run < m ? a0 + 2 * run : m;
             merge_from_lds<ITEMS>(s, a0, a1, b1, o0 - a0, e);
         }
-        __syncthreads();
+        team_sync<THREADS>();
         if (active) {
 #pragma unroll
             for (u32 k = 0; k < ITEMS; ++k) s[ts_slot(o0 + k)] = e[k];
         }
-        __syncthreads();
+        team_sync<THREADS>();
     }
 }
 
