@@ -172,6 +172,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     const u64 start = tile_offsets[tile], end = tile_offsets[tile + 1];
     const u64 len64 = end - start;
     const u32 len = len64 < 0xffffff00ull ? (u32)len64 : 0xffffff00u;     // a tile's list is far shorter
+    if (len == 0u) return;                                          // the same for the whole workgroup
     slot_t *my_list = reinterpret_cast<slot_t *>(s_turn[wv]);
     slot_t *my_list4 = s_list4[wv][grp];
 
@@ -304,7 +305,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
         }
         // the batch in front of this one (all of its slots lie below max_last)
         next = fetch_entry(vals, feat, start + base - kBwdBatch + tid, b > 0u && tid < kBwdBatch);
-        for (u32 k = tid; k < (kBwdBatch + 1u) * kGradComps; k += kBwdThreads) (&s_acc[0][0])[k] = 0.0;
+        for (u32 k = tid; k < cnt * kGradComps; k += kBwdThreads) (&s_acc[0][0])[k] = 0.0;
         __syncthreads();
         // a wavefront none of whose pixels walked this far has nothing to add (it still takes part
         // in the barriers and the flush below)
