@@ -42,7 +42,6 @@ struct ScratchLayout {
     size_t block_sums;    // u32 [pre_blocks]      tile counts per preprocess workgroup (256 primitives)
     size_t block_offsets; // u64 [pre_blocks + 1]  their exclusive prefix sum within groups of kScanGroup
     size_t group_totals;  // u64 [groups]          total of each group
-    size_t voxel_flags;   // u8  [n]           voxel filter: 1 = the voxel may reach the image (at most n voxels)
     size_t tile_masks;    // u32 [n]           binning rule 1: kept tiles of rectangles of up to 32 tiles
     size_t bin_count;     // u32 [bin_blocks]  entries in each counting workgroup's list of (tile, start of its run)
     size_t tile_cursor;   // u32 [tiles + 1] running position of the listed primitives' pairs inside every tile's slice
@@ -68,7 +67,6 @@ inline ScratchLayout scratch_layout(u32 n, u64 capacity, u32 tiles)
     L.block_sums = o;    o += align256(sizeof(u32) * (size_t)(L.pre_blocks + 1));
     L.block_offsets = o; o += align256(sizeof(u64) * ((size_t)L.pre_blocks + 1));
     L.group_totals = o;  o += align256(sizeof(u64) * ((size_t)L.pre_blocks / kScanGroup + 2));
-    L.voxel_flags = o;   o += align256((size_t)n + 1);
     L.tile_masks = o;    o += align256(sizeof(u32) * ((size_t)n + 1));
     L.bin_count = o;     o += align256(sizeof(u32) * ((size_t)L.bin_blocks + 1));
     L.tile_cursor = o;   o += align256(sizeof(u32) * ((size_t)tiles + 1));
