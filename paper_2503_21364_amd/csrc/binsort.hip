@@ -819,8 +819,7 @@ __device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg,
     const float scale = z1 > z0 ? (float)CAP / (z1 - z0) : 0.0f;
     const bool plain = z1 < 3.0e38f && scale < 3.0e38f;     // the same for the whole team
     auto bucket = [&](u64 c) -> u32 {
-        const u32 b = (u32)((__uint_as_float((u32)(c >> 32)) - z0) * scale);
-        return b < CAP - 1u ? b : CAP - 1u;
+        return (u32)fminf((__uint_as_float((u32)(c >> 32)) - z0) * scale, (float)(CAP - 1u));     // NaN: the last one
     };
     team_sync<THREADS>();                                        // counters clear, `part` read
 #pragma unroll
