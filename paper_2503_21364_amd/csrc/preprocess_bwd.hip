@@ -311,6 +311,10 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
 #pragma unroll
         for (u32 k = 0; k < VEC; ++k) mine[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    if (VEC == 1u) {                                        // consecutive as they are
+        if (i < n) reinterpret_cast<f32x4 *>(g_sh)[i] = *mine;
+        return;
+    }
     wave_fence();
     f32x4 *dst = reinterpret_cast<f32x4 *>(g_sh) + (size_t)first * VEC;
 #pragma unroll
