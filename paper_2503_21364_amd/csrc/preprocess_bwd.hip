@@ -134,6 +134,9 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
             const u32 v = k * kWave + lane;
             buf[k] = v < recs * VEC ? __builtin_nontemporal_load(src + v) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
+    } else if (live) {
+#pragma unroll
+        for (u32 k = 0; k < VEC; ++k) buf[k] = own[k];
     }
     float mx = 0.f, my = 0.f, mz = 0.f, gcol[3] = { 0.f, 0.f, 0.f }, gm[3] = { 0.f, 0.f, 0.f };
     if (!live) {
@@ -264,7 +267,7 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
             stage[v / VEC * (VEC + 1) + v % VEC] = buf[k];
         }
     }
-    wave_fence();
+    if (VEC > 1u) wave_fence();
     if (live) {
         // colour
         const float vx = mx - pp.cam.cam_pos[0], vy = my - pp.cam.cam_pos[1], vz = mz - pp.cam.cam_pos[2];
@@ -277,7 +280,7 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
         {
 #pragma unroll
             for (u32 k = 0; k < VEC; ++k) {
-                const f32x4 t = staged ? mine[k] : own[k];
+                const f32x4 t = staged ? mine[k] : buf[k];
                 coef[4 * k] = t.x; coef[4 * k + 1] = t.y; coef[4 * k + 2] = t.z; coef[4 * k + 3] = t.w;
             }
         }
