@@ -32,11 +32,14 @@
 // per-entry LDS accumulators, moved to the splat's centre and multiplied by the per-entry factors (A, B,
 // C, 1 / opacity) once per (tile, entry), and leave the workgroup as one global float atomic per (entry,
 // component): the order of these additions is not fixed, so results differ from run to run by fp32
-// rounding.
+// rounding.  A non-finite upstream gradient reaches the entries composited in its row, a non-finite colour
+// the pixels that composite it; an infinite one may come out as NaN (the moments are differences).
 //
 // Bound by vector-instruction issue (the exponent evaluation of the forward pass, twice, and the
 // gradient arithmetic) and by the LDS pipe; HBM traffic is the forward's gather, twice, plus 36 bytes of
 // atomics per pair.
+#include <type_traits>
+
 #include "lmk_gs_internal.h"
 #include "blend_reach.h"
 
@@ -152,6 +155,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     __shared__ __attribute__((aligned(16))) float s_turn[kBwdWaves][kBwdStep * kTurnStride];
     __shared__ __attribute__((aligned(16))) slot_t s_list4[kBwdWaves][4][kBwdList];
     __shared__ u32 s_last[kBwdWaves];
+    __shared__ u32 s_odd;                        // a colour of the list is not finite
     static_assert(sizeof(s_turn[0]) >= kBwdBatch, "the survivors' slots fit");
 
     if (blockIdx.x >= bp.num_tiles) return;
@@ -254,6 +258,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     }
     __syncthreads();                    // pass 1 is over in every wavefront: LDS is free
     if (lane == 0) s_last[wv] = wl;
+    if (tid == 0) s_odd = 0u;
     __syncthreads();
     u32 max_last = 0;
 #pragma unroll
@@ -268,6 +273,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     const float gb = inside ? grad_rgb[2 * plane + pix] : 0.0f;
     const float gT = (inside && grad_T) ? grad_T[pix] : 0.0f;
     const float gT_end = gT * T_end;
+    const bool odd_grad = __builtin_amdgcn_ballot_w64(!(fabsf(gr) + fabsf(gg) + fabsf(gb) + fabsf(gT_end) < 3.0e38f)) != 0ull;
     float Sr = bp.bg0 * T_end, Sg = bp.bg1 * T_end, Sb = bp.bg2 * T_end;
     T = T_end;
     // the matrix products.  v_mfma_f64_4x4x4, four blocks: block b = row b of this wavefront; operand A
@@ -302,6 +308,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
             const StagedEntry se = stage_entry(next.a, next.b, next.blue, X0, Y0);
             s_geo[tid] = se.geo; s_cop[tid] = se.cop; s_tst[tid] = se.tst;
             s_id[tid] = next.id;
+            if (!(fabsf(se.cop.z) + fabsf(se.cop.w) + fabsf(se.tst.z) < 3.0e38f)) s_odd = 1u;
         }
         // the batch in front of this one (all of its slots lie below max_last)
         next = fetch_entry(vals, feat, start + base - kBwdBatch + tid, b > 0u && tid < kBwdBatch);
@@ -320,66 +327,86 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
         const u32 n_out = mb == 0u ? n4[0] : (mb == 1u ? n4[1] : (mb == 2u ? n4[2] : n4[3]));
         const u32 out_pad = (n_out + kBwdStep - 1u) & ~(kBwdStep - 1u);
         const u32 my_last = last > base ? last - base : 0u;                 // slots below it lie in front of this pixel's end
-        for (u32 k = (longest + kBwdStep - 1u) & ~(kBwdStep - 1u); k > 0;) {
-            k -= kBwdStep;
-            const u32 word = list_word(my_list4, k, n_pad);                 // the same for the 16 lanes of a row
-            float4 co[kBwdStep];
-            float raw[kBwdStep];
-            bool hit[kBwdStep], any = false;
+        // Zero times a value that is not finite is NaN.  Where such a value is around (ODD), an entry that a pixel
+        // does not composite leaves the pixel's S alone, and one that no pixel of a row composites adds nothing for
+        // the row; elsewhere both would add zeros and are not asked for.
+        auto walk = [&](auto odd_tag) {
+            constexpr bool ODD = decltype(odd_tag)::value;
+            for (u32 k = (longest + kBwdStep - 1u) & ~(kBwdStep - 1u); k > 0;) {
+                k -= kBwdStep;
+                const u32 word = list_word(my_list4, k, n_pad);                 // the same for the 16 lanes of a row
+                float4 co[kBwdStep];
+                float raw[kBwdStep];
+                bool hit[kBwdStep], any = false;
 #pragma unroll
-            for (u32 q = 0; q < kBwdStep; ++q) {
-                const u32 j = (word >> (8u * q)) & 255u;
-                const float4 g = s_geo[j];
-                co[q] = s_cop[j];
-                raw[q] = __builtin_amdgcn_exp2f(log2_alpha(g, co[q], g.x - ox, g.y - oy));
-                hit[q] = j < my_last && !(raw[q] < 1.0f / 255.0f);          // of fminf(0.99, raw): the same
-                any = any || hit[q];
+                for (u32 q = 0; q < kBwdStep; ++q) {
+                    const u32 j = (word >> (8u * q)) & 255u;
+                    const float4 g = s_geo[j];
+                    co[q] = s_cop[j];
+                    raw[q] = __builtin_amdgcn_exp2f(log2_alpha(g, co[q], g.x - ox, g.y - oy));
+                    hit[q] = j < my_last && !(raw[q] < 1.0f / 255.0f);          // of fminf(0.99, raw): the same
+                    any = any || hit[q];
+                }
+                if (__builtin_amdgcn_ballot_w64(any) == 0ull) continue;          // nothing from this wavefront
+                if (ODD) {
+#pragma unroll
+                    for (u32 q = 0; q < kBwdStep; ++q)
+                        if (!hit[q]) co[q].z = co[q].w = 0.0f;
+                }
+                // a pixel without a contribution goes through the same arithmetic with a = 0: T and S
+                // stay as they are and all its moments are zero
+                float m[kBwdStep], w[kBwdStep];
+#pragma unroll
+                for (u32 q = kBwdStep; q-- > 0;) {
+                    const float a = hit[q] ? fminf(0.99f, raw[q]) : 0.0f;
+                    const float blue = ODD && !hit[q] ? 0.0f : s_tst[(word >> (8u * q)) & 255u].z;
+                    const float inv = __builtin_amdgcn_rcpf(1.0f - a);     // 1 - a >= 0.01; one ulp is enough here
+                    // dL/da = (dL/dC . (T c - S) - dL/dT_end T_end) / (1 - a), T = transmittance behind the entry
+                    const float num = fmaf(gr, fmaf(T, co[q].z, -Sr), fmaf(gg, fmaf(T, co[q].w, -Sg), fmaf(gb, fmaf(T, blue, -Sb), -gT_end)));
+                    T *= inv;                                              // transmittance in front of this entry
+                    w[q] = a * T;
+                    Sr = fmaf(co[q].z, w[q], Sr); Sg = fmaf(co[q].w, w[q], Sg); Sb = fmaf(blue, w[q], Sb);
+                    m[q] = (raw[q] > 0.99f ? 0.0f : a) * (num * inv);      // a dL/da; a clamped alpha depends on nothing
+                }
+                // lane = pixel -> lane = (entry, row, four pixels); LDS accesses of a wavefront complete in order
+#pragma unroll
+                for (u32 q = 0; q < kBwdStep; ++q) turn[q * kTurnStride + lane] = m[q];
+                wave_fence();
+                const float4 am = *reinterpret_cast<const float4 *>(turn + ml * kTurnStride + mb * 16u + mk * 4u);
+                wave_fence();
+#pragma unroll
+                for (u32 q = 0; q < kBwdStep; ++q) turn[q * kTurnStride + lane] = w[q];
+                wave_fence();
+                const float4 aw = *reinterpret_cast<const float4 *>(turn + ml * kTurnStride + mb * 16u + mk * 4u);
+                wave_fence();
+                const double Am[kBwdStep] = { (double)am.x, (double)am.y, (double)am.z, (double)am.w };
+                const double Aw[kBwdStep] = { (double)aw.x, (double)aw.y, (double)aw.z, (double)aw.w };
+                double d1 = 0.0, d2 = 0.0, d3 = 0.0;
+#pragma unroll
+                for (u32 s = 0; s < kBwdStep; ++s) {
+                    d1 = __builtin_amdgcn_mfma_f64_4x4x4f64(Am[s], B1[s], d1, 0, 0, 0);
+                    d2 = __builtin_amdgcn_mfma_f64_4x4x4f64(Am[s], B2[s], d2, 0, 0, 0);
+                    d3 = __builtin_amdgcn_mfma_f64_4x4x4f64(Aw[s], B3[s], d3, 0, 0, 0);
+                }
+                // lane j + 4 b + 16 i: moment j of entry i of row b
+                u32 slot = out_list[(k < out_pad ? k : out_pad) + mk];
+                if (ODD) {
+                    u64 hits[kBwdStep];
+#pragma unroll
+                    for (u32 q = 0; q < kBwdStep; ++q) hits[q] = __builtin_amdgcn_ballot_w64(hit[q]);
+                    const u64 h = mk == 0u ? hits[0] : (mk == 1u ? hits[1] : (mk == 2u ? hits[2] : hits[3]));
+                    if (((h >> (16u * mb)) & 0xffffull) == 0ull) slot = kNullSlot;
+                }
+                if (slot != kNullSlot) {
+                    double *rec = s_acc[slot];
+                    atomicAdd(rec + (ml == 0u ? 5u : ml - 1u), d1);
+                    if (ml < 2u) atomicAdd(rec + 3u + ml, d2);
+                    if (ml < 3u) atomicAdd(rec + 6u + ml, d3);
+                }
             }
-            if (__builtin_amdgcn_ballot_w64(any) == 0ull) continue;          // nothing from this wavefront
-            // a pixel without a contribution goes through the same arithmetic with a = 0: T and S
-            // stay as they are and all its moments are zero
-            float m[kBwdStep], w[kBwdStep];
-#pragma unroll
-            for (u32 q = kBwdStep; q-- > 0;) {
-                const float a = hit[q] ? fminf(0.99f, raw[q]) : 0.0f;
-                const float blue = s_tst[(word >> (8u * q)) & 255u].z;
-                const float inv = __builtin_amdgcn_rcpf(1.0f - a);     // 1 - a >= 0.01; one ulp is enough here
-                // dL/da = (dL/dC . (T c - S) - dL/dT_end T_end) / (1 - a), T = transmittance behind the entry
-                const float num = fmaf(gr, fmaf(T, co[q].z, -Sr), fmaf(gg, fmaf(T, co[q].w, -Sg), fmaf(gb, fmaf(T, blue, -Sb), -gT_end)));
-                T *= inv;                                              // transmittance in front of this entry
-                w[q] = a * T;
-                Sr = fmaf(co[q].z, w[q], Sr); Sg = fmaf(co[q].w, w[q], Sg); Sb = fmaf(blue, w[q], Sb);
-                m[q] = (raw[q] > 0.99f ? 0.0f : a) * (num * inv);      // a dL/da; a clamped alpha depends on nothing
-            }
-            // lane = pixel -> lane = (entry, row, four pixels); LDS accesses of a wavefront complete in order
-#pragma unroll
-            for (u32 q = 0; q < kBwdStep; ++q) turn[q * kTurnStride + lane] = m[q];
-            wave_fence();
-            const float4 am = *reinterpret_cast<const float4 *>(turn + ml * kTurnStride + mb * 16u + mk * 4u);
-            wave_fence();
-#pragma unroll
-            for (u32 q = 0; q < kBwdStep; ++q) turn[q * kTurnStride + lane] = w[q];
-            wave_fence();
-            const float4 aw = *reinterpret_cast<const float4 *>(turn + ml * kTurnStride + mb * 16u + mk * 4u);
-            wave_fence();
-            const double Am[kBwdStep] = { (double)am.x, (double)am.y, (double)am.z, (double)am.w };
-            const double Aw[kBwdStep] = { (double)aw.x, (double)aw.y, (double)aw.z, (double)aw.w };
-            double d1 = 0.0, d2 = 0.0, d3 = 0.0;
-#pragma unroll
-            for (u32 s = 0; s < kBwdStep; ++s) {
-                d1 = __builtin_amdgcn_mfma_f64_4x4x4f64(Am[s], B1[s], d1, 0, 0, 0);
-                d2 = __builtin_amdgcn_mfma_f64_4x4x4f64(Am[s], B2[s], d2, 0, 0, 0);
-                d3 = __builtin_amdgcn_mfma_f64_4x4x4f64(Aw[s], B3[s], d3, 0, 0, 0);
-            }
-            // lane j + 4 b + 16 i: moment j of entry i of row b
-            const u32 slot = out_list[(k < out_pad ? k : out_pad) + mk];
-            if (slot != kNullSlot) {
-                double *rec = s_acc[slot];
-                atomicAdd(rec + (ml == 0u ? 5u : ml - 1u), d1);
-                if (ml < 2u) atomicAdd(rec + 3u + ml, d2);
-                if (ml < 3u) atomicAdd(rec + 6u + ml, d3);
-            }
-        }
+        };
+        if (odd_grad || s_odd != 0u) walk(std::true_type());                // wave-uniform
+        else walk(std::false_type());
         __syncthreads();
         // from the moments of an entry to its gradient.  About the splat's centre (u, v), seen from the
         // reference point: sum m dx = u M - M_x with dx = u - x, and so on; q = A dx^2 + 2 B dx dy + C dy^2,
