@@ -192,10 +192,10 @@ int32_t lmk_gs_preprocess_culled(const lmk_gs_gaussians *g, const lmk_gs_voxel_i
  * How: that order has no ties, so the order in which a tile's pairs arrive in the
  * tile's slice is free -- the pairs are counted per tile, the counts are scanned into
  * the ranges, every pair is written straight into its tile's slice, and each slice
- * is sorted on its own.  A frame of 32 or more pairs per primitive (in buffers of at least 2^18
- * pairs, keys_alt 16-byte aligned) takes another way to the same arrays: the primitives are
- * put in order once and every tile's list is written front to back.  proj->offsets, when present, receives the exclusive prefix
- * sum of tiles_touched.  keys_alt/vals_alt are working space.
+ * is sorted on its own.  A frame of many pairs per primitive -- 22 and one for every 480
+ * tiles, at least 32 -- takes another way to the same arrays, if keys_alt is 16-byte aligned and the
+ * buffers hold at least 2^18 pairs: the primitives are put in order once and every tile's list is written
+ * front to back.  proj->offsets, when present, receives the exclusive prefix sum of tiles_touched.  keys_alt/vals_alt are working space.
  * If the pair count D exceeds `capacity`, nothing is emitted: the status word
  * becomes LMK_GS_ERR_CAPACITY, every tile range is empty (lmk_gs_render then gives
  * the background), keys/vals are left as they were, and D (lmk_gs_read_status) tells

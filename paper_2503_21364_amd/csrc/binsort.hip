@@ -1243,8 +1243,8 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
     const u32 large_blocks_emit = (large_blocks * kLargeThreads + bin_threads - 1) / bin_threads;
     hipError_t e;
 
-    const bool dense = dense_possible(n, out, pp.tiles_x, pp.tiles_y);
-    const u64 dense_min = dense ? (u64)kDenseRatio * n : ~0ull;
+    const u64 dense_min = dense_min_pairs(n, out, pp.tiles_x, pp.tiles_y);
+    const bool dense = dense_min != ~0ull;
     if (dense) {
         e = launch_dense_count(proj, n, pp, out, tile_count, header, dense_min, stream);
         if (e != hipSuccess) return e;

@@ -511,12 +511,15 @@ __global__ __launch_bounds__(kDenseThreads) void dense_emit_kernel(
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
-bool dense_possible(u32 n, const lmk_gs_binned &out, u32 tiles_x, u32 tiles_y)
+u64 dense_min_pairs(u32 n, const lmk_gs_binned &out, u32 tiles_x, u32 tiles_y)
 {
-    if (n == 0 || out.capacity < kDenseMinCapacity || out.capacity < (u64)kDenseRatio * n) return false;
-    if (reinterpret_cast<uintptr_t>(out.keys_alt) & 15u) return false;      // the workspace holds 16-byte vectors
+    constexpr u64 kNever = ~0ull;
+    if (n == 0 || out.capacity < kDenseMinCapacity) return kNever;
+    if (reinterpret_cast<uintptr_t>(out.keys_alt) & 15u) return kNever;     // the workspace holds 16-byte vectors
     const DenseLayout L = dense_layout(n, tiles_x, tiles_y);
-    return L.bins <= kMaxBinUnits / kDenseWaves && L.total <= out.capacity * sizeof(u64);
+    const u32 ratio = kDenseRatio + L.bins / kDenseBins;
+    const u64 least = (u64)(ratio > kDenseRatioMin ? ratio : kDenseRatioMin) * n;
+    return L.bins <= kMaxBinUnits / kDenseWaves && least <= out.capacity && L.total <= out.capacity * sizeof(u64) ? least : kNever;
 }
 
 hipError_t launch_dense_count(const lmk_gs_projected &proj, u32 n, const ProjParams &pp, const lmk_gs_binned &out,

@@ -1,0 +1,68 @@
+"""Which way stage 2 takes, and that both ways give the oracle's lists, bit for bit.
+
+Frames of many pairs per primitive are put together from the depth-ordered primitives, all others from
+counted and sorted pairs; the line is 22 pairs per primitive and one more for every 30 bins of 4 x 4 tiles, at
+least 32, in buffers of at least 2^18 pairs.  The word that the device leaves in the scratch buffer (the sixth of the
+eight in front of the chunk list, which is the last part) tells which way a frame went."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from paper_2503_21364_amd import binding as B, scenes
+import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def went_dense(fr) -> bool:
+    chunks = (8 * (fr.capacity // 2048 + 2) + 255) // 256 * 256
+    word = fr.scratch[fr.scratch_bytes - chunks - 256:].view(torch.int32)[5].item()
+    assert word in (0, 1)
+    return word == 1
+
+
+def per_primitive(w, h):
+    bins = ((w + 15) // 16 + 3) // 4 * (((h + 15) // 16 + 3) // 4)
+    return max(32, 22 + bins // 30)
+
+
+def _boxes(n, w, h, tiles, last, seed):
+    """n axis-aligned splats in front of a camera that looks along z; tiles = (columns, rows) that the support rectangle of
+    each covers, last = those of the last one."""
+    rng = np.random.default_rng(seed)
+    cam = dict(scenes.make_camera(np.eye(3, 4), (0, 0, 0), w, h, 60.0), binning=0)
+    f = float(cam["fx"])
+    mean, scale = [], []
+    for i in range(n):
+        cols, rows = tiles if i + 1 < n else last
+        z = rng.uniform(2.0, 9.0)
+        centre = []
+        for count, size in ((cols, w), (rows, h)):          # an odd count is centred on a tile, an even one on a border
+            lo, hi = (count + 1) // 2 + 1, (size // 16) - (count + 1) // 2 - 1
+            centre.append(16.0 * rng.integers(lo, hi + 1) + (8.0 if count % 2 else 0.0))
+        half = [8.0 * c - 4.0 for c in (cols, rows)]        # a quarter of a tile short of the next one
+        var = [(x * x) / 11.09 - float(cam["lowpass"]) for x in half]
+        mean.append([(centre[0] - float(cam["cx"])) * z / f, (centre[1] - float(cam["cy"])) * z / float(cam["fy"]), z])
+        scale.append([np.sqrt(var[0]) * z / f, np.sqrt(var[1]) * z / f, 1e-4])
+    return scenes.hand_placed_scene(mean, scale, opacity=list(rng.uniform(0.1, 0.9, n))), cam
+
+
+@pytest.mark.parametrize("w,h,tiles,below", [
+    (640, 360, (8, 4), (31, 1)),            # 60 bins: 32 pairs per primitive
+    (1920, 1080, (13, 3), (38, 1)),         # 510: 39
+    (3840, 2160, (10, 9), (89, 1)),         # 2040: 90
+])
+def test_the_line_in_pairs_per_primitive(w, h, tiles, below):
+    n = 300
+    assert tiles[0] * tiles[1] == per_primitive(w, h) == below[0] * below[1] + 1
+    for last in (tiles, below):
+        # J has a third column away from the axis: the off-axis part of a flat splat changes nothing but rounding
+        sc, cam = _boxes(n, w, h, tiles, last, seed=w)
+        pre = ref.preprocess(sc, cam)
+        binned = ref.bin_sort(pre, cam)
+        want = n * tiles[0] * tiles[1] - (tiles[0] * tiles[1] - last[0] * last[1])
+        assert binned.D == want
+        fr = P.gpu_frame(B.Scene(sc), cam, 1 << 18)
+        P.compare_binned(fr, binned)
+        assert went_dense(fr) == (last is tiles)
