@@ -3,7 +3,7 @@
     python -m paper_2503_21364_amd.build
 
 Every translation unit is compiled with packed-FP32 instruction selection
-switched off.  preprocess.hip, binsort.hip, binsort_dense.hip and api.hip additionally run with
+switched off.  preprocess.hip, binsort.hip and api.hip additionally run with
 floating-point contraction off and correctly rounded divide/sqrt, because they
 hold the arithmetic that decides integers (depth bits, tile rectangles, culls,
 the tile intersection test).
@@ -30,7 +30,6 @@ UNITS = {
     "api.hip": EXACT,
     "preprocess.hip": EXACT,
     "binsort.hip": EXACT,       # the tile intersection test of binning rule 1 decides integers too
-    "binsort_dense.hip": EXACT,
     "render.hip": [],
     "render_bwd.hip": [],       # same options as render.hip: pass 1 repeats its arithmetic
     "preprocess_bwd.hip": [],

@@ -41,6 +41,10 @@
 //            launch and by a launch of wavefronts.  Lists beyond that get a workgroup of 1024 threads each:
 //            16384-pair chunks merge-sorted in LDS, then pairwise merges through LDS-staged windows.
 //
+// Frames of many pairs per primitive are put together in another way (binsort_dense.h), in the same launches:
+// where the buffers could hold such a frame, count, the count of large rectangles and the last sort launch
+// carry both ways and pick by D.
+//
 // Integer work, bound by HBM traffic, global atomic throughput and, in the per-tile sorts, by
 // LDS bandwidth and vector issue.  Atomics on one address are served one after the other (about
 // 12 ns each), so nothing here funnels every workgroup through one counter.  The kernels read the
@@ -50,6 +54,7 @@
 // retry needs.
 #include <type_traits>
 
+#include "binsort_dense.h"
 #include "lds_sort.h"
 #include "lmk_gs_internal.h"
 #include "tile_test.h"
@@ -173,26 +178,29 @@ __device__ __forceinline__ u64 list_first_finish(const u64 *__restrict__ block_o
     return first;
 }
 
-template <u32 LDS_TILES, bool TIGHT>
+// With DenseArgs: the workgroups sort chunks of primitives by depth instead in a frame that goes the other way.
+template <u32 LDS_TILES, bool TIGHT, class Dense>
 __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     const u32 *__restrict__ tiles_touched, const ushort4 *__restrict__ rect, const u32 *__restrict__ tile_masks,
     u32 n, u32 tiles_x, u32 num_tiles, u32 *__restrict__ tile_count,
     ScratchHeader *__restrict__ header, u32 *__restrict__ big_idx,
     const u32 *__restrict__ block_sums, u32 pre_blocks,
     const u64 *__restrict__ block_offsets, const u64 *__restrict__ group_totals,
-    u32 *__restrict__ bin_count, uint2 *__restrict__ list, u64 list_capacity, u64 dense_min)
+    u32 *__restrict__ bin_count, uint2 *__restrict__ list, u64 list_capacity, Dense dense)
 {
     constexpr bool LDS = LDS_TILES > 0;
     constexpr u32 kThreads = BinShape<LDS_TILES>::kThreads, kPer = BinShape<LDS_TILES>::kPer;
     constexpr u32 kWaves = BinShape<LDS_TILES>::kWaves;
     constexpr u32 kRounds = LDS ? BinShape<LDS_TILES>::kRounds : 1;
     constexpr u32 kSmallMax = LDS ? kMaskArea : 0u;
-    __shared__ u32 s_hist[LDS ? LDS_TILES : 1];
+    constexpr u32 kHistWords = LDS ? LDS_TILES : 1u, kSortWords = Dense::kDense ? 2u * (kSortChunk + kSortChunk / 16u) : 0u;
+    __shared__ __attribute__((aligned(16))) u32 s_hist[kHistWords > kSortWords ? kHistWords : kSortWords];
     __shared__ u32 s_next;
     __shared__ u32 s_wave[kWaves][2];
     __shared__ u32 s_base[2];
     __shared__ u64 s_part[kWaves];
-    if (dense_min != ~0ull && header->dup_count >= dense_min) return;    // no read where the host has ruled it out
+    bool other_way = false;
+    if constexpr (Dense::kDense) other_way = header->dup_count >= dense.dense_min;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     {   // the projection stage counted the pairs of every 256 primitives: a workgroup none of whose
         // primitives was binned (culled, or a skipped voxel range) leaves without reading one
@@ -201,6 +209,13 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
         for (u32 q = 0; q < kBinBlock / kPreBlock; ++q) {
             const u32 pb = blockIdx.x * (kBinBlock / kPreBlock) + q;
             pairs |= pb < pre_blocks ? block_sums[pb] : 0u;
+        }
+        if constexpr (Dense::kDense) {
+            if (other_way) {                                // the same for the whole workgroup
+                sort_chunk<kThreads, TIGHT>(dense, reinterpret_cast<u64 *>(s_hist));
+                return;
+            }
+            if ((u64)blockIdx.x * kBinBlock >= n) return;   // there for a chunk only
         }
         if (pairs == 0u) {                                  // the same for the whole workgroup
             if (LDS && tid == 0) bin_count[blockIdx.x] = 0;
@@ -352,14 +367,23 @@ __device__ __forceinline__ void for_each_listed(const ScratchHeader *__restrict_
     }
 }
 
-template <bool TIGHT>
+static_assert(kLargeThreads == kDenseThreads, "the launch carries the count of both ways");
+template <bool TIGHT, class Dense>
 __global__ __launch_bounds__(kLargeThreads) void count_large_kernel(
     const ushort4 *__restrict__ rect, const float4 *__restrict__ feat, ProjParams pp, u32 n, u32 num_tiles,
     u32 *__restrict__ large_count, const ScratchHeader *__restrict__ header, const u32 *__restrict__ big_idx,
-    u32 giant_blocks)
+    u32 giant_blocks, u32 blocks, u32 *__restrict__ tile_count, Dense dense)
 {
+    if constexpr (Dense::kDense) {
+        __shared__ WaveSpace s_space[kDenseWaves];
+        if (header->dup_count >= dense.dense_min) {
+            dense_count<TIGHT>(dense, header, tile_count, s_space);
+            return;
+        }
+        if (blockIdx.x >= blocks) return;
+    }
     const u32 lane = threadIdx.x & (kWave - 1);
-    for_each_listed<kLargeThreads>(header, big_idx, n, blockIdx.x, gridDim.x, giant_blocks, threadIdx.x,
+    for_each_listed<kLargeThreads>(header, big_idx, n, blockIdx.x, blocks, giant_blocks, threadIdx.x,
         [&](u32 i, u32 part, u32 parts) {
             walk_large<TIGHT>(rect[i], feat + (size_t)i * (LMK_GS_FEAT_STRIDE / 4), pp, lane, part, parts,
                 [&](u32 tile, u32) -> u64 { if (tile < num_tiles) atomicAdd(&large_count[tile], 1u); return 0ull; },
@@ -386,7 +410,7 @@ __global__ __launch_bounds__(kLargeThreads) void count_large_kernel(
 // per-tile sort leaves them zero for the next call.
 // With SMALL (up to 8192 tiles) every thread reads its eight counters once and everything else works
 // from registers and LDS.
-//   classes[5]  (kDenseClass) 1 = the frame's lists come from dense_emit_kernel, sorted: nothing is emitted or sorted here
+//   classes[5]  (kDenseClass) 1 = the frame's lists come from dense_emit, sorted: nothing is emitted or sorted here
 constexpr u32 kSmallThreads = 64, kSmallItems = 8, kSmallCap = kSmallThreads * kSmallItems;   // 512
 constexpr u32 kLowThreads = 256, kLowItems = 8;                                               // 2048
 constexpr u32 kMidThreads = 512, kMidItems = 8, kMid = kMidThreads * kMidItems;               // 4096
@@ -649,7 +673,7 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void emit_kernel(
     __shared__ u32 s_cur[LDS ? LDS_TILES : 1];
     __shared__ u64 s_part[kWaves];
     // (here and below the flag is read together with what is needed anyway: one round trip to memory)
-    const u32 elsewhere = classes[kDenseClass];             // the lists are written by dense_emit_kernel
+    const u32 elsewhere = classes[kDenseClass];             // the lists are written by dense_emit
     const int32_t status = header->status;                  // more pairs than the buffers hold: nothing is emitted
     if ((elsewhere != 0u) | (status != LMK_GS_OK)) return;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -1018,20 +1042,36 @@ __global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
 // 6.4 + 7.0 us, together 7.7 us).
 constexpr u32 kMergeBlocks1 = 1024, kMergeBlocks2 = 2048;
 constexpr u32 kShortPerBlock = kLowThreads / kSmallThreads;
-__global__ __launch_bounds__(kLowThreads) void tile_sort_low_kernel(
+static_assert(kLowThreads == kDenseThreads, "the launch carries both ways");
+// (five wavefronts per SIMD as without the other way, whose registers would leave room for four: 23.6 us
+// instead of 26.3 on lists of 1.5 M primitives, and the other way itself no slower)
+template <bool TIGHT, class Dense>
+__global__ __launch_bounds__(kLowThreads, Dense::kDense ? 5 : 1) void tile_sort_low_kernel(
     u64 *__restrict__ keys, u32 *__restrict__ vals, u64 *__restrict__ keys_alt, u32 *__restrict__ vals_alt,
     const u64 *__restrict__ tile_offsets, const u32 *__restrict__ order, const u32 *__restrict__ classes,
-    const uint2 *__restrict__ chunk_list, u32 num_tiles, u32 merge_blocks, u32 low_blocks)
+    const uint2 *__restrict__ chunk_list, u32 num_tiles, u32 merge_blocks, u32 low_blocks,
+    u32 blocks, u64 capacity, const ScratchHeader *__restrict__ header, Dense dense)
 {
     constexpr u32 CAP = kLowThreads * kLowItems;
     constexpr u32 kPerChunk = kMid / CAP;                   // output segments per chunk
     constexpr u32 kShortWords = kSmallCap + kSmallCap / 16; // LDS of a wavefront's own list
-    __shared__ u64 s[CAP + CAP / 16];
-    __shared__ __attribute__((aligned(16))) u32 s_cnt[CAP / 2];
+    constexpr u32 kListWords = CAP + CAP / 16 + CAP / 4;    // a list of composites and its counters
+    constexpr u32 kEmitWords = Dense::kDense ? kDenseWaves * (u32)(sizeof(EmitSpace) / sizeof(u64)) : 0u;
+    __shared__ __attribute__((aligned(16))) u64 s[kListWords > kEmitWords ? kListWords : kEmitWords];
     __shared__ u64 s_split[2];
+    u32 *s_cnt = reinterpret_cast<u32 *>(s + CAP + CAP / 16);
+    // (the flag is read together with what is needed anyway: one round trip to memory)
+    const u32 first = classes[0] + classes[3] + classes[1], low = classes[2], chunks = classes[4], elsewhere = classes[kDenseClass];
+    if constexpr (Dense::kDense) {
+        if (elsewhere) {
+            dense_emit<TIGHT>(dense, header, tile_offsets, capacity, keys, vals, reinterpret_cast<EmitSpace *>(s));
+            return;
+        }
+        if (blockIdx.x >= blocks) return;
+    }
     static_assert(kShortPerBlock * kShortWords <= CAP + CAP / 16 && kShortPerBlock * kSmallCap <= CAP, "a share each");
     if (blockIdx.x < merge_blocks) {
-        const u64 segments = classes[kDenseClass] ? 0ull : (u64)classes[4] * kPerChunk;
+        const u64 segments = (u64)chunks * kPerChunk;
         for (u64 g = blockIdx.x; g < segments; g += merge_blocks) {
             const uint2 c = chunk_list[g / kPerChunk];
             if (c.x >= num_tiles) continue;
@@ -1043,8 +1083,6 @@ __global__ __launch_bounds__(kLowThreads) void tile_sort_low_kernel(
         return;
     }
     const u32 block = blockIdx.x - merge_blocks;
-    const u32 first = classes[0] + classes[3] + classes[1], low = classes[2], elsewhere = classes[kDenseClass];
-    if (elsewhere) return;
     if (block < low_blocks) {
         if (block >= low || first + block >= num_tiles) return;
         const u32 tile = order[first + block];
@@ -1243,28 +1281,35 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
     const u32 large_blocks_emit = (large_blocks * kLargeThreads + bin_threads - 1) / bin_threads;
     hipError_t e;
 
+    // the launches that both ways share: `with` is called with what their kernels get of the other one
     const u64 dense_min = dense_min_pairs(n, out, pp.tiles_x, pp.tiles_y);
     const bool dense = dense_min != ~0ull;
-    if (dense) {
-        e = launch_dense_count(proj, n, pp, out, tile_count, header, dense_min, stream);
-        if (e != hipSuccess) return e;
-    }
+    const DenseLayout DL = dense_layout(n, out.capacity, pp.tiles_x, pp.tiles_y);
+    const u32 dense_grid = dense ? dense_blocks(DL) : 0u;
+    auto both = [&](auto with) {
+        if (dense) with(dense_args(proj, n, pp, out, DL, dense_min)); else with(OneWay());
+    };
+    auto most = [](u32 a, u32 b) { return a > b ? a : b; };
     if (L.bin_blocks > 0) {
-        auto count = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(L.bin_blocks), dim3(bin_threads), 0, stream,
-                               proj.tiles_touched, rect, tile_masks, n, pp.tiles_x, num_tiles, tile_count, header, big_idx,
-                               reinterpret_cast<const u32 *>(scratch + L.block_sums), L.pre_blocks,
-                               block_offsets, group_totals, bin_count, list, out.capacity, dense_min);
-        };
-        if (lds_tiles == kLdsTilesSmall) { if (tight) count(count_kernel<kLdsTilesSmall, true>); else count(count_kernel<kLdsTilesSmall, false>); }
-        else if (lds_tiles == kLdsTilesLarge) { if (tight) count(count_kernel<kLdsTilesLarge, true>); else count(count_kernel<kLdsTilesLarge, false>); }
-        else { if (tight) count(count_kernel<0u, true>); else count(count_kernel<0u, false>); }
-        if (tight)
-            hipLaunchKernelGGL(count_large_kernel<true>, dim3(giant_blocks + large_blocks), dim3(kLargeThreads), 0, stream,
-                               rect, feat, pp, n, num_tiles, large_count, header, big_idx, giant_blocks);
-        else
-            hipLaunchKernelGGL(count_large_kernel<false>, dim3(giant_blocks + large_blocks), dim3(kLargeThreads), 0, stream,
-                               rect, feat, pp, n, num_tiles, large_count, header, big_idx, giant_blocks);
+        both([&](auto d) {
+            using Dense = decltype(d);
+            auto count = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(Dense::kDense ? most(L.bin_blocks, DL.chunks) : L.bin_blocks), dim3(bin_threads), 0, stream,
+                                   proj.tiles_touched, rect, tile_masks, n, pp.tiles_x, num_tiles, tile_count, header, big_idx,
+                                   reinterpret_cast<const u32 *>(scratch + L.block_sums), L.pre_blocks,
+                                   block_offsets, group_totals, bin_count, list, out.capacity, d);
+            };
+            if (lds_tiles == kLdsTilesSmall) { if (tight) count(count_kernel<kLdsTilesSmall, true, Dense>); else count(count_kernel<kLdsTilesSmall, false, Dense>); }
+            else if (lds_tiles == kLdsTilesLarge) { if (tight) count(count_kernel<kLdsTilesLarge, true, Dense>); else count(count_kernel<kLdsTilesLarge, false, Dense>); }
+            else { if (tight) count(count_kernel<0u, true, Dense>); else count(count_kernel<0u, false, Dense>); }
+            if constexpr (Dense::kDense) launch_depth_rank(out, DL, d, header, stream);
+            auto count_large = [&](auto kernel) {
+                const u32 blocks = giant_blocks + large_blocks;
+                hipLaunchKernelGGL(kernel, dim3(most(blocks, dense_grid)), dim3(kLargeThreads), 0, stream,
+                                   rect, feat, pp, n, num_tiles, large_count, header, big_idx, giant_blocks, blocks, tile_count, d);
+            };
+            if (tight) count_large(count_large_kernel<true, Dense>); else count_large(count_large_kernel<false, Dense>);
+        });
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1297,10 +1342,6 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
         else emit_for(std::integral_constant<u32, 0u>());
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (dense) {
-            e = launch_dense_emit(n, pp, out, header, classes, stream);
-            if (e != hipSuccess) return e;
-        }
         if (proj.offsets) {
             hipLaunchKernelGGL(prim_offsets_kernel, dim3(L.pre_blocks), dim3(kPreBlock), 0, stream,
                                proj.tiles_touched, n, block_offsets, group_totals, proj.offsets);
@@ -1323,9 +1364,17 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
     hipLaunchKernelGGL(tile_sort_mid_kernel, dim3(max_mid), dim3(kMidThreads), 0, stream,
                        out.keys, out.vals, out.tile_offsets, order, classes, chunk_list, num_tiles);
     const u32 short_blocks = (num_tiles + kShortPerBlock - 1) / kShortPerBlock;
-    hipLaunchKernelGGL(tile_sort_low_kernel, dim3(merge1 + max_low + short_blocks), dim3(kLowThreads), 0, stream,
-                       out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, order, classes,
-                       chunk_list, num_tiles, merge1, max_low);
+    const u32 low_grid = merge1 + max_low + short_blocks;
+    both([&](auto d) {
+        using Dense = decltype(d);
+        auto low = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(most(low_grid, dense_grid)), dim3(kLowThreads), 0, stream,
+                               out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, order, classes,
+                               chunk_list, num_tiles, merge1, max_low, low_grid, out.capacity, header, d);
+        };
+        if constexpr (Dense::kDense) { if (tight) low(tile_sort_low_kernel<true, Dense>); else low(tile_sort_low_kernel<false, Dense>); }
+        else low(tile_sort_low_kernel<false, Dense>);
+    });
     // no list of the frame can be long if the buffers do not hold that many pairs
     if (out.capacity > kMid)
         hipLaunchKernelGGL(tile_merge_kernel, dim3(merge2), dim3(kSmallThreads), 0, stream,

@@ -3,27 +3,37 @@
 // tiles although its place in the depth order is the same in all of them.  Here the primitives are put
 // in order once, and every tile's list is then written front to back, in its final form:
 //
-//   order    the primitives by (depth bits, index): chunks of 4096 sorted in LDS, then pairwise merges
-//            of 2048 outputs a workgroup.  The last of these launches also lays rectangles and the tile
-//            test's operands out in that order; what was not binned comes last, with an empty rectangle.
+//   order    the primitives by (depth bits, index): chunks of 4096 sorted in LDS, then merged some at a time by
+//            rank (one round up to 131 000 primitives).  The last of these launches also lays rectangles and the
+//            tile test's operands out in that order; what was not binned comes last, with an empty rectangle.
 //   count    a workgroup takes a bin of 4 x 4 tiles, each of its wavefronts a share ("unit") of the
 //            ordered primitives.  64 rectangles at a time are tested against the bin; those that
 //            meet it queue up in order, and 256 of them at a time (lane = primitive) get a mask of the 16
 //            tiles they keep: all or none where a look at the whole bin decides (an inner or an outer
 //            part of a large splat), else from the tile test.  Per tile the number kept is the
-//            population count of a ballot.
-//   scan     per tile over the units of its bin; then tile_scan_kernel as for every frame.
-//   emit     the count walk again.  The ballots give every kept primitive its place in the tile's list:
-//            a tile's share of the 256 is put together in LDS and leaves as
-//            one run of consecutive keys and values, sorted, with no atomics and nothing left for the
-//            per-tile sorts to do.
+//            population count of a ballot; one atomic per wavefront and tile adds it up.
+//   scan     tile_scan_kernel, as for every frame.
+//   emit     the count walk again.  The ballots give every kept primitive its place in the tile's list,
+//            behind what the units before keep there: a tile's share of the 256 is put together in LDS and
+//            leaves as one run of consecutive keys and values, sorted, with no atomics and nothing left for
+//            the per-tile sorts to do.
+//
+// Whether a frame goes this way is known on the device only, so buffers with room for such a frame pay for
+// both ways.  The steps are therefore bodies that share the launches of the other way -- the chunk sort that of
+// count_kernel, the count that of count_large_kernel, emit that of tile_sort_low_kernel -- and only the merge rounds
+// are launches of their own.  A frame in roomy buffers that does not go this way, us: 1000 primitives at 256 x 256
+// 46 (buffers too small for this way 46; with every step a launch of its own 57), 10 000 78 (76; 85), 100 000 at
+// 1080p 144 (138; 158), 1.5 M 351 (329; 366).
 //
 // Bound by the vector instructions of the tile tests (twice per candidate) and by writing 12 bytes a
 // pair.  400 000 primitives at 3840 x 2160, 615 M pairs: order 0.1 ms, count 1.2 ms, emit 3.3 ms (2.2 TB/s),
 // where counting, emitting and sorting pairs took 8.5 + 10.4 + 15.7 ms.  Tried there: bins of 8 x 8 tiles
 // (a third of the tested tiles kept instead of 44 %; count 1.9 ms), testing every tile of every candidate
 // (count 1.8 ms), storing each ballot's pairs as they come (emit 3.7 ms), one tile at a time through LDS
-// (3.5 ms), cached instead of streaming stores (+ 0.3 ms).  The workspace is the alternate key buffer, which only the merges of the per-tile sort use.
+// (3.5 ms), cached instead of streaming stores (+ 0.3 ms).  The workspace is the alternate key buffer, which
+// only the merges of the per-tile sort use.
+#ifndef LMK_GS_BINSORT_DENSE_H
+#define LMK_GS_BINSORT_DENSE_H
 #include "lds_sort.h"
 #include "lmk_gs_internal.h"
 #include "tile_test.h"
@@ -32,8 +42,19 @@ namespace lmk {
 
 namespace {
 
-constexpr u32 kSortThreads = 512, kSortItems = 8, kSortChunk = kSortThreads * kSortItems;    // 4096
-constexpr u32 kMergeThreads = 256, kMergeItems = 8, kMergeOut = kMergeThreads * kMergeItems; // 2048
+// A frame goes this way if its pair count D is at least dense_min: the device knows D and decides.  This way
+// looks at every primitive in every bin of 4 x 4 tiles, the other way at every pair, so that the line in pairs per
+// primitive rises with the bins.  Even by measurement (bin_sort of one frame; splats of one size, and one in
+// twenty forty times as large as the rest): 510 bins (1080p) 20 (100 000 primitives) to 36 (300 000), 900 (1440p)
+// 52, 2040 (4K) 40 to 82, 8160 (8K) 110 to 280.  kDenseRatio + bins / kDenseBins is above all of these, and no
+// frame gets slower; at twice the line the gain is 1.5 to 2.5x.
+// Below 2^18 pairs of room a frame is too short to carry a launch that it may not need.
+constexpr u32 kDenseRatio = 22, kDenseBins = 30, kDenseRatioMin = 32;
+constexpr u64 kDenseMinCapacity = 1ull << 18;
+constexpr u32 kDenseClass = 5;                      // entry of ScratchLayout::classes: 1 = the frame went this way
+
+constexpr u32 kSortChunk = 4096;                            // primitives sorted in LDS by one workgroup
+constexpr u32 kRankThreads = 256;
 constexpr u32 kBinEdge = 4, kBinTiles = kBinEdge * kBinEdge;
 constexpr u32 kDenseThreads = 256, kDenseWaves = kDenseThreads / kWave;
 constexpr u32 kSets = 4, kBatch = kSets * kWave;            // primitives of an emit batch
@@ -42,18 +63,37 @@ static_assert(kBinTiles <= 16, "masks are 16 bits wide");
 // last, partly filled batch of a unit is most of its work
 constexpr u32 kMaxBinUnits = 65536, kMaxUnits = 64, kUnitMin = 512, kUnitPairs = 2048, kMinWaves = 12288;
 
+// Of one round up to kOneRound runs are merged at a time, of several up to kWays, so that a million primitives
+// take two; beyond that a launch is little beside the searches, whose sum is least for few ways.
+constexpr u32 kOneRound = 32, kWays = 16, kWaysMany = 8, kMany = 1u << 20;
+
+// the units per bin that a frame of D pairs is worth
+__host__ __device__ inline u64 units_worth(u64 D, u32 bins)
+{
+    const u64 worth = D / ((u64)bins * kUnitPairs), fill = kMinWaves / bins;     // fill the chip
+    return worth < fill ? fill : worth;
+}
+
+inline u64 power(u32 base, u32 exponent)
+{
+    u64 p = 1;
+    for (u32 k = 0; k < exponent; ++k) p *= base;
+    return p;
+}
+
 // Carving of the workspace (all offsets multiples of 256 bytes).
 struct DenseLayout {
     size_t ops;         // float4 [n][2]  operands of the tile test in depth order: u, v, A, B | C, rx, ry, tau
-    size_t pairs0, pairs1;   // u64 [n]   depth bits << 32 | index: ping and pong of the merges
+    size_t pairs0, pairs1;   // u64 [n]   depth bits << 32 | index: ping and pong of the merge rounds
     size_t rects;       // ushort4 [n]    rectangles in depth order
     size_t counts;      // u32 [bins][units][kBinTiles]
     size_t total;
     u32 bins_x, bins, units;
-    u32 rounds;         // merge rounds: the order ends in pairs0 if even, else in pairs1
+    u32 chunk, chunks;  // primitives sorted in LDS at a time (the last may be fewer), and how many of them
+    u32 ways, rounds;   // runs merged at a time, merge rounds: the order ends in pairs0 if even, else in pairs1
 };
 
-DenseLayout dense_layout(u32 n, u32 tiles_x, u32 tiles_y)
+DenseLayout dense_layout(u32 n, u64 capacity, u32 tiles_x, u32 tiles_y)
 {
     DenseLayout L;
     L.bins_x = (tiles_x + kBinEdge - 1) / kBinEdge;
@@ -61,9 +101,20 @@ DenseLayout dense_layout(u32 n, u32 tiles_x, u32 tiles_y)
     u32 units = kMaxBinUnits / (L.bins ? L.bins : 1u);
     units = units < kMaxUnits ? units : kMaxUnits;
     units = units < n / kUnitMin ? units : n / kUnitMin;
+    const u64 worth = units_worth(capacity, L.bins ? L.bins : 1u);      // no frame that fits is worth more
+    units = worth < units ? (u32)worth : units;
     L.units = units < kDenseWaves ? kDenseWaves : units / kDenseWaves * kDenseWaves;     // whole workgroups
-    L.rounds = 0;
-    for (u64 run = kSortChunk; run < n; run <<= 1) ++L.rounds;
+    // A round costs a launch and reads and writes the composites once; what it does per run it merges is a search
+    // by every primitive, in windows that are short only if the runs are of one length: ways^rounds chunks.
+    L.chunks = (n + kSortChunk - 1) / kSortChunk;
+    L.rounds = 0; L.ways = 1;
+    if (L.chunks > 1) { L.rounds = 1; L.ways = L.chunks; }
+    while (L.ways > (L.rounds == 1 ? kOneRound : n <= kMany ? kWays : kWaysMany)) {
+        ++L.rounds;
+        for (L.ways = 2; power(L.ways, L.rounds) < L.chunks; ++L.ways) {}
+    }
+    if (L.chunks > 1) L.chunks = (u32)power(L.ways, L.rounds);
+    L.chunk = L.chunks ? (n + L.chunks - 1) / L.chunks : 0u;
     size_t o = 0;
     L.ops = o;    o += align256((size_t)n * 2 * sizeof(float4));
     L.pairs0 = o; o += align256((size_t)n * sizeof(u64));
@@ -86,104 +137,142 @@ __device__ __forceinline__ u32 lanes_below(u64 m)
     return __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u));
 }
 
-// ---------------------------------------------------------------- order
-// where the sorted order goes: the composites, and from the last launch the rectangles and operands
-struct OrderOut {
-    u64 *pairs;
-    const u32 *tiles_touched; const ushort4 *rect; const float4 *feat;
-    ushort4 *rects; float4 *ops;
+// What the kernels that carry these bodies get (by value); OneWay stands for it where the host has ruled this way out.
+struct OneWay { static constexpr bool kDense = false; };
+struct DenseArgs {
+    static constexpr bool kDense = true;
+    u64 dense_min;
+    ProjParams pp;
+    u32 n, bins_x, bins, units;
+    u32 chunk;
+    bool sorted;                // the chunk sort's order is the final one (no merge rounds)
+    u64 *pairs;                 // of the chunk sort
+    const u64 *ordered;         // of the last round
+    ushort4 *rects; float4 *ops; u32 *counts;
+    const float *depth; const u32 *tiles_touched; const ushort4 *rect; const float4 *feat;
 };
 
-template <bool LAST, bool TIGHT>
-__device__ __forceinline__ void put_ordered(const OrderOut &out, const ProjParams &pp, u32 pos, u64 v, u32 n)
+// ---------------------------------------------------------------- order
+// Primitive v (depth bits << 32 | index; what was not binned has ~0 for depth bits and comes last) is at `pos` of
+// its run; from the last launch of the order its rectangle and operands go there too.
+template <bool TIGHT>
+__device__ __forceinline__ void put_ordered(const DenseArgs &d, u64 *pairs, bool last, u64 pos, u64 v)
 {
-    out.pairs[pos] = v;
-    if (!LAST) return;
+    pairs[pos] = v;
+    if (!last) return;
     const u32 i = (u32)v;
     ushort4 r = make_ushort4(0, 0, 0, 0);
-    if (i < n) {                                            // what was not binned carries no index
-        r = out.rect[i];
+    if ((u32)(v >> 32) != ~0u) {
+        r = d.rect[i];
         if (TIGHT) {
-            const float4 *f = out.feat + (size_t)i * (LMK_GS_FEAT_STRIDE / 4);
+            const float4 *f = d.feat + (size_t)i * (LMK_GS_FEAT_STRIDE / 4);
             const float4 f0 = f[0], f1 = f[1];
-            const TileTest t = make_tile_test(f0.x, f0.y, f0.z, f0.w, f1.x, opacity_tau(pp, f1.y));
-            out.ops[2 * (size_t)pos] = make_float4(t.u, t.v, t.A, t.B);
-            out.ops[2 * (size_t)pos + 1] = make_float4(t.C, t.rx, t.ry, t.tau);
+            const TileTest t = make_tile_test(f0.x, f0.y, f0.z, f0.w, f1.x, opacity_tau(d.pp, f1.y));
+            d.ops[2 * pos] = make_float4(t.u, t.v, t.A, t.B);
+            d.ops[2 * pos + 1] = make_float4(t.C, t.rx, t.ry, t.tau);
         }
     }
-    out.rects[pos] = r;
+    d.rects[pos] = r;
 }
 
-template <bool LAST, bool TIGHT>
-__global__ __launch_bounds__(kSortThreads) void depth_sort_kernel(
-    const float *__restrict__ depth, u32 n, ProjParams pp, OrderOut out,
-    const ScratchHeader *__restrict__ header, u64 dense_min)
+// chunk blockIdx.x, by a workgroup of THREADS; s: kSortChunk + kSortChunk / 16 composites
+template <u32 THREADS, bool TIGHT>
+__device__ __forceinline__ void sort_chunk(const DenseArgs &d, u64 *s)
 {
-    __shared__ u64 s[kSortChunk + kSortChunk / 16];
-    if (header->dup_count < dense_min) return;
-    const u32 beg = blockIdx.x * kSortChunk;
-    const u32 count = n - beg < kSortChunk ? n - beg : kSortChunk;
-    sort_in_lds<kSortThreads, kSortItems>(count, s, [&](u32 k) {
-        const u32 i = beg + k;
-        return out.tiles_touched[i] ? ((u64)__float_as_uint(depth[i]) << 32) | (u64)i : ~0ull;
+    const u64 beg = (u64)blockIdx.x * d.chunk;
+    if (beg >= d.n) return;
+    const u32 count = d.n - beg < d.chunk ? (u32)(d.n - beg) : d.chunk;
+    sort_in_lds<THREADS, kSortChunk / THREADS>(count, s, [&](u32 k) {
+        const u32 i = (u32)beg + k;
+        return ((u64)(d.tiles_touched[i] ? __float_as_uint(d.depth[i]) : ~0u) << 32) | (u64)i;
     });
-    for (u32 k = threadIdx.x; k < count; k += kSortThreads) put_ordered<LAST, TIGHT>(out, pp, beg + k, s[ts_slot(k)], n);
+    for (u32 k = threadIdx.x; k < count; k += THREADS) put_ordered<TIGHT>(d, d.pairs, d.sorted, beg + k, s[ts_slot(k)]);
 }
 
-// number of elements of A = src[a0, a1) among the first `diag` of its merge with B = src[a1, b1), by one
-// wavefront: every round the lanes probe 64 evenly spaced candidates
-__device__ __forceinline__ u32 wave_split(const u64 *__restrict__ src, u32 a0, u32 a1, u32 b1, u32 diag, u32 lane)
+// The number of elements below v among src[0 .. len), which are in order; by eight neighbouring lanes, each with a
+// probe of its own per step (one lane alone needs three times the steps, a trip to memory each).
+__device__ __forceinline__ u32 count_below(const u64 *src, u32 len, u64 v, u32 lane)
 {
-    const u32 lenA = a1 - a0, lenB = b1 - a1;
-    u32 lo = diag > lenB ? diag - lenB : 0, hi = diag < lenA ? diag : lenA;
-    while (lo < hi) {                                       // wave-uniform
-        const u32 step = (hi - lo + 63) / 64;
-        const u32 m = lo + (lane + 1) * step - 1;
-        const bool p = m < hi && src[a0 + m] < src[a1 + (diag - 1 - m)];
-        const u32 c = (u32)__builtin_popcountll(__builtin_amdgcn_ballot_w64(p));
-        const u32 nhi = lo + (c + 1) * step - 1;
-        hi = nhi < hi ? nhi : hi;
-        lo += c * step;
+    u32 lo = 0, hi = len;
+    while (__builtin_amdgcn_ballot_w64(lo < hi)) {
+        const u32 step = (hi - lo + 8u) / 9u, m = lo + ((lane & 7u) + 1u) * step - 1u;
+        const u64 less = __builtin_amdgcn_ballot_w64(m < hi && src[m] < v);
+        const u32 c = (u32)__builtin_popcount((u32)(less >> (lane & 56u)) & 0xffu);
+        const u32 next = lo + (c + 1u) * step - 1u;         // the first probe that is not below v, if one is not
+        if (lo < hi) { hi = c < 8u && next < hi ? next : hi; lo += c * step; }
     }
     return lo;
 }
 
-// one merge round over sorted runs of length `run`; workgroup = kMergeOut consecutive outputs
-template <bool LAST, bool TIGHT>
-__global__ __launch_bounds__(kMergeThreads) void depth_merge_kernel(
-    const u64 *__restrict__ src, u32 n, u32 run, ProjParams pp, OrderOut out,
-    const ScratchHeader *__restrict__ header, u64 dense_min)
+// One merge round: sorted runs of length `run`, `ways` at a time.  An element's place is its own index plus, for
+// every other run of its group, the number of smaller elements there (no two are equal).  The workgroup
+// finds the window of each other run that its 256 consecutive elements fall into, and searches in windows
+// staged in LDS, kAtOnce runs at a time.  All rounds, against merges of two runs at a time: 20 000 primitives
+// 10 us (30), 100 000 28 (45), 300 000 48 (68), 1 M 152 (135), 3 M 451 (318): there the fewer launches make up for it
+// in frames that go the other way.  Searches in memory by every lane: 100 000 50 us.
+template <bool TIGHT>
+__global__ __launch_bounds__(kRankThreads) void depth_rank_kernel(
+    const u64 *__restrict__ src, u64 *__restrict__ dst, u64 run, u32 run_blocks, u32 ways, u32 all_runs, bool last,
+    DenseArgs d, const ScratchHeader *__restrict__ header)
 {
-    __shared__ u64 s[kMergeOut + kMergeOut / 16];
-    __shared__ u32 s_split[2];
-    if (header->dup_count < dense_min) return;
-    const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const u32 o = blockIdx.x * kMergeOut;
-    const u64 a0w = (u64)o / (2ull * run) * (2ull * run);
-    const u32 a0 = (u32)a0w;
-    const u32 a1 = a0w + run < n ? (u32)(a0w + run) : n;
-    const u32 b1 = a0w + 2ull * run < n ? (u32)(a0w + 2ull * run) : n;
-    const u32 oe = b1 - o < kMergeOut ? b1 : o + kMergeOut;             // run is a multiple of kMergeOut
-    if (wv < 2) {
-        const u32 v = wave_split(src, a0, a1, b1, (wv == 0 ? o : oe) - a0, lane);
-        if (lane == 0) s_split[wv] = v;
+    constexpr u32 kAtOnce = 4, kWindow = 512;
+    static_assert(kWays <= kOneRound && kWaysMany <= kOneRound, "s_end has room");
+    __shared__ u64 s_win[kAtOnce][kWindow];
+    __shared__ u32 s_end[kOneRound][2];
+    if (header->dup_count < d.dense_min) return;
+    const u32 tid = threadIdx.x;
+    const u64 n = d.n;
+    const u32 mine = blockIdx.x / run_blocks, first = mine / ways * ways;   // run_blocks workgroups per run
+    const u32 runs = all_runs - first < ways ? all_runs - first : ways;     // of the group
+    const u64 own = (u64)mine * run, b0 = own + (u64)(blockIdx.x % run_blocks) * kRankThreads, i = b0 + tid;
+    const u64 end = own + run < n ? own + run : n;
+    if (b0 >= end) return;                                                  // the same for the workgroup
+    const u64 v = i < end ? src[i] : ~0ull;
+    for (u32 e0 = 0; e0 < 2 * runs; e0 += kRankThreads / 8) {               // both ends of every window
+        const u32 e = e0 + tid / 8;
+        const u64 beg = (u64)(first + e / 2) * run, at = e & 1u ? (b0 + kRankThreads < end ? b0 + kRankThreads : end) - 1 : b0;
+        const u32 len = e < 2 * runs ? (u32)(n - beg < run ? n - beg : run) : 0u;
+        const u32 less = count_below(src + beg, len, src[at], tid & (kWave - 1));
+        if (e < 2 * runs && (tid & 7u) == 0u) s_end[e / 2][e & 1u] = less;
     }
     __syncthreads();
-    const u32 i0 = s_split[0], la = s_split[1] - i0, total = oe - o;
-    const u32 j0 = (o - a0) - i0;                           // elements of B before the segment
-    for (u32 k = tid; k < total; k += kMergeThreads) s[ts_slot(k)] = src[k < la ? a0 + i0 + k : a1 + j0 + (k - la)];
-    __syncthreads();
-    const u32 o0 = tid * kMergeItems;
-    u64 e[kMergeItems];
-    if (o0 < total) merge_from_lds<kMergeItems>(s, 0u, la, total, o0, e);
-    __syncthreads();
-    if (o0 < total) {
+    u64 pos = (u64)first * run + (i - own);
+    for (u32 q0 = 0; q0 < runs; q0 += kAtOnce) {
+        const u64 *win[kAtOnce];
+        u32 len[kAtOnce], longest = 0;
 #pragma unroll
-        for (u32 k = 0; k < kMergeItems; ++k)
-            if (o0 + k < total) s[ts_slot(o0 + k)] = e[k];
+        for (u32 j = 0; j < kAtOnce; ++j) {                         // all of this is the same for the workgroup
+            const u32 q = q0 + j;
+            const bool other = q < runs && first + q != mine;
+            const u32 lo = other ? s_end[q][0] : 0u;
+            len[j] = other ? s_end[q][1] - lo : 0u;
+            longest = len[j] > longest ? len[j] : longest;
+            pos += lo;
+            win[j] = src + (u64)(first + q) * run + lo;
+        }
+        for (u32 w0 = 0; w0 < longest; w0 += kWindow) {             // once, unless the runs are very unlike
+            u32 part[kAtOnce], less[kAtOnce];
+#pragma unroll
+            for (u32 j = 0; j < kAtOnce; ++j) {
+                less[j] = 0;
+                part[j] = len[j] > w0 ? (len[j] - w0 < kWindow ? len[j] - w0 : kWindow) : 0u;
+                for (u32 k = tid; k < part[j]; k += kRankThreads) s_win[j][k] = win[j][w0 + k];
+            }
+            __syncthreads();
+            const u32 most = longest - w0 < kWindow ? longest - w0 : kWindow;
+            for (u32 half = 1u << (31 - __builtin_clz(most)); half > 0; half >>= 1) {
+                u64 c[kAtOnce];
+#pragma unroll
+                for (u32 j = 0; j < kAtOnce; ++j) c[j] = s_win[j][(less[j] + half - 1) % kWindow];   // read whether it counts or not
+#pragma unroll
+                for (u32 j = 0; j < kAtOnce; ++j) less[j] += less[j] + half <= part[j] && c[j] < v ? half : 0u;
+            }
+#pragma unroll
+            for (u32 j = 0; j < kAtOnce; ++j) pos += less[j];
+            __syncthreads();
+        }
     }
-    __syncthreads();
-    for (u32 k = tid; k < total; k += kMergeThreads) put_ordered<LAST, TIGHT>(out, pp, o + k, s[ts_slot(k)], n);
+    if (i < end) put_ordered<TIGHT>(d, dst, last, pos, v);
 }
 
 // ---------------------------------------------------------------- count / emit
@@ -193,8 +282,7 @@ struct UnitWork { u32 bin, unit, bx, by, beg, end; };
 // of the `units` that the workspace and the grid have room for, those that this frame's pairs are worth
 __device__ __forceinline__ u32 units_in_use(const ScratchHeader *__restrict__ header, u32 bins, u32 units)
 {
-    u64 worth = header->dup_count / ((u64)bins * kUnitPairs);
-    if (worth < kMinWaves / bins) worth = kMinWaves / bins;     // fill the chip
+    const u64 worth = units_worth(header->dup_count, bins);
     if (worth >= units) return units;
     return worth < kDenseWaves ? kDenseWaves : (u32)worth / kDenseWaves * kDenseWaves;
 }
@@ -379,24 +467,29 @@ __device__ __forceinline__ void bin_masks(const u32 *queued, u32 count, const us
     }
 }
 
+// LDS of a wavefront: `queue` BATCH + kWave positions, masks and undecided BATCH numbers each
+struct WaveSpace {
+    u32 queue[kBatch + kWave];
+    unsigned short mask[kBatch], open[kBatch];
+};
+struct EmitSpace { WaveSpace w; u64 run[2 * kBatch]; };
+
+// workgroup blockIdx.x of the count: kDenseThreads threads
 template <bool TIGHT>
-__global__ __launch_bounds__(kDenseThreads) void dense_count_kernel(
-    const ushort4 *__restrict__ rects, const float4 *__restrict__ ops, u32 n,
-    u32 bins_x, u32 bins, u32 units, u32 *__restrict__ counts, const ScratchHeader *__restrict__ header, u64 dense_min)
+__device__ __forceinline__ void dense_count(const DenseArgs &d, const ScratchHeader *__restrict__ header,
+                                            u32 *__restrict__ tile_count, WaveSpace *space)
 {
-    __shared__ u32 s_queue[kDenseWaves][kBatch + kWave];
-    __shared__ unsigned short s_mask[kDenseWaves][kBatch], s_open[kDenseWaves][kBatch];
-    if (header->dup_count < dense_min) return;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const u32 used = units_in_use(header, bins, units);
-    const UnitWork w = unit_work(n, bins_x, bins, used, wv);
-    if (w.bin >= bins) return;
+    const u32 used = units_in_use(header, d.bins, d.units);
+    const UnitWork w = unit_work(d.n, d.bins_x, d.bins, used, wv);
+    if (w.bin >= d.bins) return;
+    WaveSpace &my = space[wv];
     u32 mine = 0;                                           // kept by tile `lane` of the bin
-    bin_candidates<kBatch>(rects, w, lane, s_queue[wv], [&](const u32 *queued, u32 count) {
-        bin_masks<TIGHT, kBatch>(queued, count, rects, ops, w.bx, w.by, lane, s_mask[wv], s_open[wv]);
+    bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
+        bin_masks<TIGHT, kBatch>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
         u32 m[kSets];
 #pragma unroll
-        for (u32 set = 0; set < kSets; ++set) m[set] = s_mask[wv][set * kWave + lane];
+        for (u32 set = 0; set < kSets; ++set) m[set] = my.mask[set * kWave + lane];
 #pragma unroll
         for (u32 tile = 0; tile < kBinTiles; ++tile) {
             u32 kept = 0;
@@ -407,64 +500,50 @@ __global__ __launch_bounds__(kDenseThreads) void dense_count_kernel(
         }
         wave_fence();
     });
-    if (lane < kBinTiles) counts[((size_t)w.bin * units + w.unit) * kBinTiles + lane] = mine;
-}
-
-// 16 lanes per bin, lane = tile: the counts of the units become the offsets of their runs
-__global__ __launch_bounds__(kWave) void dense_scan_kernel(
-    u32 *__restrict__ counts, u32 bins, u32 bins_x, u32 units, u32 tiles_x, u32 tiles_y, u32 *__restrict__ tile_count,
-    const ScratchHeader *__restrict__ header, u64 dense_min)
-{
-    if (header->dup_count < dense_min) return;
-    const u32 used = units_in_use(header, bins, units);
-    const u32 bin = blockIdx.x * (kWave / kBinTiles) + threadIdx.x / kBinTiles, tile = threadIdx.x % kBinTiles;
-    if (bin >= bins) return;
-    const u32 tx = (bin % bins_x) * kBinEdge + tile % kBinEdge, ty = (bin / bins_x) * kBinEdge + tile / kBinEdge;
-    u32 *c = counts + (size_t)bin * units * kBinTiles + tile;
-    u32 run = 0;
-    for (u32 k0 = 0; k0 < used; k0 += kDenseWaves) {        // a multiple of kDenseWaves
-        u32 v[kDenseWaves];
-#pragma unroll
-        for (u32 k = 0; k < kDenseWaves; ++k) v[k] = c[(size_t)(k0 + k) * kBinTiles];
-#pragma unroll
-        for (u32 k = 0; k < kDenseWaves; ++k) { c[(size_t)(k0 + k) * kBinTiles] = run; run += v[k]; }
+    if (lane < kBinTiles) {
+        d.counts[((size_t)w.bin * d.units + w.unit) * kBinTiles + lane] = mine;
+        const u32 tx = w.bx + lane % kBinEdge, ty = w.by + lane / kBinEdge;
+        if (mine && tx < d.pp.tiles_x && ty < d.pp.tiles_y) atomicAdd(&tile_count[ty * d.pp.tiles_x + tx], mine);
     }
-    if (tx < tiles_x && ty < tiles_y) tile_count[ty * tiles_x + tx] = run;
 }
 
+// workgroup blockIdx.x of the emit: kDenseThreads threads
 template <bool TIGHT>
-__global__ __launch_bounds__(kDenseThreads) void dense_emit_kernel(
-    const ushort4 *__restrict__ rects, const float4 *__restrict__ ops, const u64 *__restrict__ ordered,
-    u32 n, u32 bins_x, u32 bins, u32 units, u32 tiles_x, u32 tiles_y,
-    const u32 *__restrict__ counts, const u64 *__restrict__ tile_offsets, u64 capacity,
-    u64 *__restrict__ keys, u32 *__restrict__ vals, const ScratchHeader *__restrict__ header,
-    const u32 *__restrict__ classes)
+__device__ __forceinline__ void dense_emit(const DenseArgs &d, const ScratchHeader *__restrict__ header,
+                                           const u64 *__restrict__ tile_offsets, u64 capacity,
+                                           u64 *__restrict__ keys, u32 *__restrict__ vals, EmitSpace *space)
 {
-    __shared__ u32 s_queue[kDenseWaves][kBatch + kWave];
-    __shared__ unsigned short s_mask[kDenseWaves][kBatch], s_open[kDenseWaves][kBatch];
-    __shared__ u64 s_run[kDenseWaves][2 * kBatch];
-    if (!classes[kDenseClass] || header->status != LMK_GS_OK) return;
+    if (header->status != LMK_GS_OK) return;                // more pairs than the buffers hold: nothing is emitted
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const u32 used = units_in_use(header, bins, units);
-    const UnitWork w = unit_work(n, bins_x, bins, used, wv);
-    if (w.bin >= bins) return;
-    u64 *run = s_run[wv];
+    const u32 used = units_in_use(header, d.bins, d.units);
+    const UnitWork w = unit_work(d.n, d.bins_x, d.bins, used, wv);
+    if (w.bin >= d.bins) return;
+    WaveSpace &my = space[wv].w;
+    u64 *run = space[wv].run;
+    const u64 *ordered = d.ordered;
+    const u32 tiles_x = d.pp.tiles_x;
+    // what the units before this one keep: lane = (a quarter of them, tile), then added up
+    u32 before = 0;
+    const u32 *c = d.counts + (size_t)w.bin * d.units * kBinTiles + lane % kBinTiles;
+#pragma unroll 4
+    for (u32 k = lane / kBinTiles; k < w.unit; k += kWave / kBinTiles) before += c[(size_t)k * kBinTiles];
+#pragma unroll
+    for (u32 o = kBinTiles; o < kWave; o <<= 1) before += __shfl_xor(before, (int)o, 64);
     // running position of tile `lane` of the bin (the first kBinTiles lanes)
     u64 first = capacity;
     {
         const u32 tx = w.bx + lane % kBinEdge, ty = w.by + lane / kBinEdge;
-        if (lane < kBinTiles && tx < tiles_x && ty < tiles_y)
-            first = tile_offsets[ty * tiles_x + tx] + counts[((size_t)w.bin * units + w.unit) * kBinTiles + lane];
+        if (lane < kBinTiles && tx < tiles_x && ty < d.pp.tiles_y) first = tile_offsets[ty * tiles_x + tx] + before;
     }
     u32 next_lo = (u32)first, next_hi = (u32)(first >> 32);
-    bin_candidates<kBatch>(rects, w, lane, s_queue[wv], [&](const u32 *queued, u32 count) {
-        bin_masks<TIGHT, kBatch>(queued, count, rects, ops, w.bx, w.by, lane, s_mask[wv], s_open[wv]);
+    bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
+        bin_masks<TIGHT, kBatch>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
         u32 m[kSets];
         u64 pair[kSets];
 #pragma unroll
         for (u32 set = 0; set < kSets; ++set) {
             const u32 k = set * kWave + lane;
-            m[set] = s_mask[wv][k];
+            m[set] = my.mask[k];
             pair[set] = k < count ? ordered[queued[k]] : 0ull;
         }
 #pragma unroll 1
@@ -508,77 +587,62 @@ __global__ __launch_bounds__(kDenseThreads) void dense_emit_kernel(
     });
 }
 
-}  // namespace
-
-// ---------------------------------------------------------------- launchers
-u64 dense_min_pairs(u32 n, const lmk_gs_binned &out, u32 tiles_x, u32 tiles_y)
+// ---------------------------------------------------------------- host side
+// The least pair count with which a frame goes this way; ~0: these buffers hold no such frame.
+inline u64 dense_min_pairs(u32 n, const lmk_gs_binned &out, u32 tiles_x, u32 tiles_y)
 {
     constexpr u64 kNever = ~0ull;
     if (n == 0 || out.capacity < kDenseMinCapacity) return kNever;
     if (reinterpret_cast<uintptr_t>(out.keys_alt) & 15u) return kNever;     // the workspace holds 16-byte vectors
-    const DenseLayout L = dense_layout(n, tiles_x, tiles_y);
+    const DenseLayout L = dense_layout(n, out.capacity, tiles_x, tiles_y);
     const u32 ratio = kDenseRatio + L.bins / kDenseBins;
     const u64 least = (u64)(ratio > kDenseRatioMin ? ratio : kDenseRatioMin) * n;
     return L.bins <= kMaxBinUnits / kDenseWaves && least <= out.capacity && L.total <= out.capacity * sizeof(u64) ? least : kNever;
 }
 
-hipError_t launch_dense_count(const lmk_gs_projected &proj, u32 n, const ProjParams &pp, const lmk_gs_binned &out,
-                              u32 *tile_count, const ScratchHeader *header, u64 dense_min, hipStream_t stream)
+inline DenseArgs dense_args(const lmk_gs_projected &proj, u32 n, const ProjParams &pp, const lmk_gs_binned &out,
+                            const DenseLayout &L, u64 dense_min)
 {
-    const DenseLayout L = dense_layout(n, pp.tiles_x, pp.tiles_y);
+    char *w = reinterpret_cast<char *>(out.keys_alt);
+    DenseArgs d = {};
+    d.dense_min = dense_min;
+    d.pp = pp;
+    d.n = n; d.bins_x = L.bins_x; d.bins = L.bins; d.units = L.units;
+    d.chunk = L.chunk; d.sorted = L.rounds == 0;
+    d.pairs = reinterpret_cast<u64 *>(w + L.pairs0);
+    d.ordered = reinterpret_cast<const u64 *>(w + (L.rounds & 1u ? L.pairs1 : L.pairs0));
+    d.rects = reinterpret_cast<ushort4 *>(w + L.rects);
+    d.ops = reinterpret_cast<float4 *>(w + L.ops);
+    d.counts = reinterpret_cast<u32 *>(w + L.counts);
+    d.depth = proj.depth; d.tiles_touched = proj.tiles_touched;
+    d.rect = reinterpret_cast<const ushort4 *>(proj.rect);
+    d.feat = reinterpret_cast<const float4 *>(proj.feat);
+    return d;
+}
+
+// workgroups of the count and of the emit
+inline u32 dense_blocks(const DenseLayout &L) { return L.bins * (L.units / kDenseWaves); }
+
+// the merge rounds between the launch that sorts the chunks and the one that counts
+inline void launch_depth_rank(const lmk_gs_binned &out, const DenseLayout &L, const DenseArgs &d,
+                              const ScratchHeader *header, hipStream_t stream)
+{
     char *w = reinterpret_cast<char *>(out.keys_alt);
     u64 *pairs[2] = { reinterpret_cast<u64 *>(w + L.pairs0), reinterpret_cast<u64 *>(w + L.pairs1) };
-    u32 *counts = reinterpret_cast<u32 *>(w + L.counts);
-    OrderOut order = { pairs[0], proj.tiles_touched, reinterpret_cast<const ushort4 *>(proj.rect),
-                       reinterpret_cast<const float4 *>(proj.feat),
-                       reinterpret_cast<ushort4 *>(w + L.rects), reinterpret_cast<float4 *>(w + L.ops) };
-    const bool tight = pp.cam.binning == 1u;
-    auto sort = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((n + kSortChunk - 1) / kSortChunk), dim3(kSortThreads), 0, stream,
-                           proj.depth, n, pp, order, header, dense_min);
-    };
-    if (L.rounds) sort(depth_sort_kernel<false, false>);
-    else if (tight) sort(depth_sort_kernel<true, true>);
-    else sort(depth_sort_kernel<true, false>);
-    u32 run = kSortChunk;
-    for (u32 round = 0; round < L.rounds; ++round, run <<= 1) {
-        order.pairs = pairs[(round & 1u) ^ 1u];
-        auto merge = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((n + kMergeOut - 1) / kMergeOut), dim3(kMergeThreads), 0, stream,
-                               pairs[round & 1u], n, run, pp, order, header, dense_min);
+    u64 run = L.chunk;
+    for (u32 round = 0; round < L.rounds; ++round, run *= L.ways) {
+        const u32 run_blocks = (u32)((run + kRankThreads - 1) / kRankThreads), runs = (u32)((d.n + run - 1) / run);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(runs * run_blocks), dim3(kRankThreads), 0, stream,
+                               pairs[round & 1u], pairs[(round & 1u) ^ 1u], run, run_blocks, L.ways, runs,
+                               round + 1 == L.rounds, d, header);
         };
-        if (round + 1 < L.rounds) merge(depth_merge_kernel<false, false>);
-        else if (tight) merge(depth_merge_kernel<true, true>);
-        else merge(depth_merge_kernel<true, false>);
+        if (d.pp.cam.binning == 1u) go(depth_rank_kernel<true>);
+        else go(depth_rank_kernel<false>);
     }
-    auto count = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(L.bins * (L.units / kDenseWaves)), dim3(kDenseThreads), 0, stream,
-                           order.rects, order.ops, n, L.bins_x, L.bins, L.units, counts, header, dense_min);
-    };
-    if (tight) count(dense_count_kernel<true>);
-    else count(dense_count_kernel<false>);
-    const u32 bins_per_wave = kWave / kBinTiles;
-    hipLaunchKernelGGL(dense_scan_kernel, dim3((L.bins + bins_per_wave - 1) / bins_per_wave), dim3(kWave), 0, stream,
-                       counts, L.bins, L.bins_x, L.units, pp.tiles_x, pp.tiles_y, tile_count, header, dense_min);
-    return hipGetLastError();
 }
 
-hipError_t launch_dense_emit(u32 n, const ProjParams &pp, const lmk_gs_binned &out,
-                             const ScratchHeader *header, const u32 *classes, hipStream_t stream)
-{
-    const DenseLayout L = dense_layout(n, pp.tiles_x, pp.tiles_y);
-    const char *w = reinterpret_cast<const char *>(out.keys_alt);
-    const u64 *ordered = reinterpret_cast<const u64 *>(w + (L.rounds & 1u ? L.pairs1 : L.pairs0));
-    auto emit = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(L.bins * (L.units / kDenseWaves)), dim3(kDenseThreads), 0, stream,
-                           reinterpret_cast<const ushort4 *>(w + L.rects), reinterpret_cast<const float4 *>(w + L.ops),
-                           ordered, n, L.bins_x, L.bins, L.units, pp.tiles_x, pp.tiles_y,
-                           reinterpret_cast<const u32 *>(w + L.counts), out.tile_offsets,
-                           out.capacity, out.keys, out.vals, header, classes);
-    };
-    if (pp.cam.binning == 1u) emit(dense_emit_kernel<true>);
-    else emit(dense_emit_kernel<false>);
-    return hipGetLastError();
-}
+}  // namespace
 
 }  // namespace lmk
+#endif

@@ -100,24 +100,6 @@ hipError_t launch_copy_status(const char *scratch, const ScratchLayout &L, u64 *
 hipError_t launch_build_cov3d(const lmk_gs_gaussians &g, float *cov3d, hipStream_t stream);
 hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams &pp, const lmk_gs_binned &out,
                            char *scratch, const ScratchLayout &L, hipStream_t stream);
-// Stage 2 by depth-ordered primitives (binsort_dense.hip).  A frame goes this way if its pair count D is at
-// least dense_min: the device knows D and decides.  The launches are part of a frame only when its buffers
-// could hold that many pairs (else dense_min is ~0); the kernels of the other way leave at once (about 2 us
-// a launch).
-// This way looks at every primitive in every bin of 4 x 4 tiles, the other way at every pair, so that the
-// line in pairs per primitive rises with the bins.  Even by measurement (bin_sort of one frame; splats of
-// one size, and one in twenty forty times as large as the rest): 510 bins (1080p) 20 (100 000 primitives) to
-// 36 (300 000), 900 (1440p) 52, 2040 (4K) 40 to 82, 8160 (8K) 110 to 280.  kDenseRatio + bins / kDenseBins is
-// above all of these, and no frame gets slower; at twice the line the gain is 1.5 to 2.5x.
-// Below 2^18 pairs of room a frame is too short to carry the launches that it may not need.
-constexpr u32 kDenseRatio = 22, kDenseBins = 30, kDenseRatioMin = 32;
-constexpr u64 kDenseMinCapacity = 1ull << 18;
-constexpr u32 kDenseClass = 5;                      // entry of ScratchLayout::classes: 1 = the frame went this way
-u64 dense_min_pairs(u32 n, const lmk_gs_binned &out, u32 tiles_x, u32 tiles_y);
-hipError_t launch_dense_count(const lmk_gs_projected &proj, u32 n, const ProjParams &pp, const lmk_gs_binned &out,
-                              u32 *tile_count, const ScratchHeader *header, u64 dense_min, hipStream_t stream);
-hipError_t launch_dense_emit(u32 n, const ProjParams &pp, const lmk_gs_binned &out,
-                             const ScratchHeader *header, const u32 *classes, hipStream_t stream);
 hipError_t launch_render(const lmk_gs_projected &proj, const lmk_gs_binned &binned, const ProjParams &pp,
                          float *out_rgb, float *out_T, hipStream_t stream);
 hipError_t launch_render_backward(const lmk_gs_projected &proj, u32 n, const lmk_gs_binned &binned,

@@ -66,3 +66,22 @@ def test_the_line_in_pairs_per_primitive(w, h, tiles, below):
         fr = P.gpu_frame(B.Scene(sc), cam, 1 << 18)
         P.compare_binned(fr, binned)
         assert went_dense(fr) == (last is tiles)
+
+
+@pytest.mark.parametrize("binning", [0, 1])
+@pytest.mark.parametrize("n", [4096, 4097, 8193, 16384, 131072, 131073])
+def test_the_order_of_chunks_and_merge_rounds(n, binning):
+    """Primitives are sorted in chunks of up to 4096 and merged in one round up to 32 chunks, else in several, with equal
+    depths and primitives that are not binned in between."""
+    rng = np.random.default_rng(n)
+    sc = scenes.make_scene(4, n=n, seed=n)
+    sc["scale"] = np.full_like(sc["scale"], 0.8)
+    sc["mean"][2] = np.where(rng.random(n) < 0.2, np.round(sc["mean"][2] * 16.0) / 16.0, sc["mean"][2])
+    sc["opacity"][rng.random(n) < 0.1] = 0.0
+    cam = dict(scenes.make_cameras(4, 200, 120)[0], binning=binning)
+    pre = ref.preprocess(sc, cam)
+    binned = ref.bin_sort(pre, cam)
+    assert binned.D >= 32 * n
+    fr = P.gpu_frame(B.Scene(sc), cam, binned.D + 5)
+    P.compare_binned(fr, binned)
+    assert went_dense(fr)
