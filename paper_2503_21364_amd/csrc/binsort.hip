@@ -34,8 +34,8 @@
 //   tile sort  every tile's slice is sorted by that composite and rewritten in its final form (key = tile <<
 //            32 | depth bits, value = index): 512 threads for lists of up to 4096 pairs, 256 up to 2048, one
 //            wavefront up to 512 (the two smaller classes in one launch).  The pairs go to buckets of
-//            equal depth steps in LDS, one or two in each, and are ranked inside them; where a bucket gets
-//            more than 64 (equal depths, dense clusters) the list goes through a merge sort instead.  A
+//            equal depth steps in LDS, one or two in each, and are ranked inside them; where the buckets get
+//            too full (equal depths, dense clusters) the list goes through a merge sort instead.  A
 //            list of up to 16384 pairs is cut into 4096-pair chunks, sorted by workgroups of the 512-thread
 //            launch and merged in two rounds between the two pair buffers, by workgroups of the 256-thread
 //            launch and by a launch of wavefronts.  Lists beyond that get a workgroup of 1024 threads each:
@@ -796,15 +796,31 @@ __device__ __forceinline__ void sort_pairs_in_lds(u64 *keys, u32 *vals, u64 beg,
 // where the merge sort takes 300 and 25.  1080p, 3 M primitives, 4.9 M pairs: lists of 2049 to 4096 pairs and
 // chunks 42 -> 24 us, of 513 to 2048 35 -> 22 us.  Equal steps of the depth's bits instead of the depth
 // (steps of equal ratio) crowd what is far into few buckets: inside a scene half of the long lists then
-// fell back.  A list with more than kMaxBucket pairs in one bucket (equal
-// depths, a dense cluster in front of a far background) is left to the merge sort: returns false, nothing
-// written.  Called by the whole team (a workgroup, or one wavefront); cnt holds THREADS * ITEMS / 2 words, two 16-bit counters each.
-constexpr u32 kMaxBucket = 64;
+// fell back.
+//
+// What the buckets cost beyond that is the ranking, by the size of a pair's bucket on average over the pairs:
+// lists of clusters of one size are even with the merge sort, less the try, at 7 (64 threads), 18 (256) and 22
+// (512), and one large bucket holds up its wavefront.  Beyond these limits (a surface in front of a far background,
+// equal depths) the list is left to the merge sort: returns false, nothing written.  Lists that are far beyond
+// show it in a quarter of their pairs, or in their depths being one, and leave before the rest is counted.
+// Stage 2 of 1024 lists of 3500 pairs: evenly spread 133 us (merge sort alone 154), a thin surface before a far
+// background 158 (170 without the early leave); of 1500 pairs 76 (86), 88 (96); of 450 pairs 47 (49), 50 (54).
+// Called by the whole team (a workgroup, or one wavefront); cnt holds THREADS * ITEMS / 2 words, two 16-bit counters each.
+template <u32 THREADS> struct BucketLimits {
+    static constexpr u32 kMean = THREADS == 64u ? 7u : (THREADS == 256u ? 18u : 22u);
+    static constexpr u32 kMax = THREADS == 64u ? 24u : 64u;
+    static constexpr u32 kProbeMax = THREADS == 64u ? 12u : 24u;     // in a quarter of the list
+};
 
 template <u32 THREADS, u32 ITEMS>
 __device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg, u32 n, u32 tile, u64 *s, u32 *cnt)
 {
     constexpr u32 CAP = THREADS * ITEMS, kWords = ITEMS / 2, kWaves = THREADS / kWave;
+    constexpr u32 kProbe = ITEMS < 4u ? 1u : ITEMS / 4u;
+    // a thread's share of the sum of squares is clamped, so that it and the count fit one word
+    constexpr u32 kCountBits = 13, kShareMax = 1000;
+    using Limits = BucketLimits<THREADS>;
+    static_assert(CAP < (1u << kCountBits) && THREADS * kShareMax < (1u << (32 - kCountBits)), "one word");
     static_assert(CAP < 65536u && ITEMS % 2u == 0u, "positions are 16 bits wide, two to a word");
     const u32 tid = team_thread<THREADS>(), lane = tid & (kWave - 1), wv = tid / kWave;
     u64 e[ITEMS];
@@ -826,8 +842,9 @@ __device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg,
         const u32 a = __shfl_xor(lo, o, 64), b = __shfl_xor(hi, o, 64);
         lo = a < lo ? a : lo; hi = b > hi ? b : hi;
     }
-    u32 *part = reinterpret_cast<u32 *>(s);                 // free until the scatter
+    u32 *part = reinterpret_cast<u32 *>(s), *flag = part + 2u * kWaves;     // free until the scatter
     if (kWaves > 1u) {
+        if (tid < 2u) flag[tid] = 0u;
         if (lane == 0) { part[2 * wv] = lo; part[2 * wv + 1] = hi; }
         team_sync<THREADS>();
 #pragma unroll
@@ -841,28 +858,39 @@ __device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg,
     // all that is needed; an infinite depth is left to the merge sort.
     const float z0 = __uint_as_float(lo), z1 = __uint_as_float(hi);
     const float scale = z1 > z0 ? (float)CAP / (z1 - z0) : 0.0f;
-    const bool plain = z1 < 3.0e38f && scale < 3.0e38f;     // the same for the whole team
+    if (!(z1 < 3.0e38f) || scale == 0.0f || !(scale < 3.0e38f)) return false;         // the same for the whole team
     auto bucket = [&](u64 c) -> u32 {
         return (u32)fminf((__uint_as_float((u32)(c >> 32)) - z0) * scale, (float)(CAP - 1u));     // NaN: the last one
     };
     team_sync<THREADS>();                                        // counters clear, `part` read
+    bool over = false;
 #pragma unroll
-    for (u32 k = 0; k < ITEMS; ++k) {
+    for (u32 k = 0; k < kProbe; ++k) {
+        if (k * THREADS + tid < n) {
+            const u32 b = bucket(e[k]), sh = (b & 1u) * 16u;
+            over = over || ((atomicAdd(&cnt[b >> 1], 1u << sh) >> sh) & 0xffffu) >= Limits::kProbeMax;
+        }
+    }
+    if (team_any<THREADS>(over, flag)) return false;            // the same for the whole team
+#pragma unroll
+    for (u32 k = kProbe; k < ITEMS; ++k) {
         if (k * THREADS + tid < n) {
             const u32 b = bucket(e[k]);
             atomicAdd(&cnt[b >> 1], 1u << ((b & 1u) * 16u));
         }
     }
     team_sync<THREADS>();
-    // exclusive scan: ITEMS consecutive buckets per thread
-    u32 w[kWords], sum = 0;
-    bool over = !plain;
+    // exclusive scan: ITEMS consecutive buckets per thread; above the count the sum of the squares
+    u32 w[kWords], sum = 0, squares = 0;
 #pragma unroll
     for (u32 k = 0; k < kWords; ++k) {
         w[k] = cnt[tid * kWords + k];
-        over = over || (w[k] & 0xffffu) > kMaxBucket || (w[k] >> 16) > kMaxBucket;
-        sum += (w[k] & 0xffffu) + (w[k] >> 16);
+        const u32 c0 = w[k] & 0xffffu, c1 = w[k] >> 16;
+        over = over || c0 > Limits::kMax || c1 > Limits::kMax;
+        sum += c0 + c1;
+        squares += c0 * c0 + c1 * c1;
     }
+    sum |= (squares < kShareMax ? squares : kShareMax) << kCountBits;
     u32 incl = sum;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -870,12 +898,17 @@ __device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg,
         if ((int)lane >= o) incl += t;
     }
     if (kWaves > 1u && lane == kWave - 1) part[wv] = incl;
-    if (team_any<THREADS>(over)) return false;                // the same for the whole team
-    u32 run = incl - sum;
+    if (team_any<THREADS>(over, flag + 1)) return false;
+    u32 run = incl - sum, total = kWaves > 1u ? 0u : (u32)__builtin_amdgcn_readlane((int)incl, (int)kWave - 1);
     if (kWaves > 1u) {
 #pragma unroll
-        for (u32 k = 0; k < kWaves; ++k) run += k < wv ? part[k] : 0u;
+        for (u32 k = 0; k < kWaves; ++k) {
+            run += k < wv ? part[k] : 0u;
+            total += part[k];
+        }
     }
+    if ((total >> kCountBits) > Limits::kMean * n) return false;        // the same for the whole team
+    run &= (1u << kCountBits) - 1u;
 #pragma unroll
     for (u32 k = 0; k < kWords; ++k) {
         const u32 c0 = w[k] & 0xffffu, c1 = w[k] >> 16;
@@ -907,11 +940,17 @@ __device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg,
     return true;
 }
 
-// a list (or chunk) of 1 .. THREADS * ITEMS pairs, in place
+// a list (or chunk) of 1 .. THREADS * ITEMS pairs, in place; s: list_words(THREADS * ITEMS) words.  The counters lie behind
+// the composites, where the merge sort has the end of its padded ones: 40 KB for 4096 pairs, so that four
+// workgroups fit a compute unit (43 KB, three: 1.5 M primitives in roomy buffers, 30 000 such workgroups of which most leave at
+// once, 350 us a frame instead of 344); 20 KB for 2048, eight (21 KB, seven: a launch of 1024 such lists 30 us instead of 23).
+constexpr u32 list_words(u32 pairs) { return pairs + pairs / 4u; }
 template <u32 THREADS, u32 ITEMS>
-__device__ __forceinline__ void sort_list(u64 *keys, u32 *vals, u64 beg, u32 n, u32 tile, u64 *s, u32 *cnt)
+__device__ __forceinline__ void sort_list(u64 *keys, u32 *vals, u64 beg, u32 n, u32 tile, u64 *s)
 {
-    if (bucket_sort_pairs<THREADS, ITEMS>(keys, vals, beg, n, tile, s, cnt)) return;
+    constexpr u32 CAP = THREADS * ITEMS;
+    static_assert(CAP + CAP / 16u <= list_words(CAP), "the merge sort fits as well");
+    if (bucket_sort_pairs<THREADS, ITEMS>(keys, vals, beg, n, tile, s, reinterpret_cast<u32 *>(s + CAP))) return;
     team_sync<THREADS>();                                        // `s` is free again
     sort_pairs_in_lds<THREADS, ITEMS>(keys, vals, beg, n, tile, s);
 }
@@ -1009,8 +1048,7 @@ __global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
     const u32 *__restrict__ order, const u32 *__restrict__ classes, const uint2 *__restrict__ chunk_list,
     u32 num_tiles)
 {
-    __shared__ u64 s[kMid + kMid / 16];
-    __shared__ __attribute__((aligned(16))) u32 s_cnt[kMid / 2];
+    __shared__ u64 s[list_words(kMid)];
     const u32 chunks = classes[4], elsewhere = classes[kDenseClass];
     if (elsewhere) return;
     if (blockIdx.x < chunks) {
@@ -1021,7 +1059,7 @@ __global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
         const u64 c0 = (u64)c.y * kMid;
         if (c0 >= len) return;                              // cannot happen with a consistent table
         const u32 n = (u32)(len - c0 < (u64)kMid ? len - c0 : (u64)kMid);
-        sort_list<kMidThreads, kMidItems>(keys, vals, beg + c0, n, c.x, s, s_cnt);     // n >= 1
+        sort_list<kMidThreads, kMidItems>(keys, vals, beg + c0, n, c.x, s);     // n >= 1
         return;
     }
     const u32 k = blockIdx.x - chunks;
@@ -1032,7 +1070,7 @@ __global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
     const u64 beg = tile_offsets[tile];
     const u64 len = tile_offsets[tile + 1] - beg;
     if (len < 2 || len > (u64)kMid) return;                 // cannot happen with a consistent table
-    sort_list<kMidThreads, kMidItems>(keys, vals, beg, (u32)len, tile, s, s_cnt);
+    sort_list<kMidThreads, kMidItems>(keys, vals, beg, (u32)len, tile, s);
 }
 
 // Lists of up to kLow pairs: one workgroup each above kSmallCap pairs, one wavefront each below.  Before
@@ -1054,12 +1092,12 @@ __global__ __launch_bounds__(kLowThreads, Dense::kDense ? 5 : 1) void tile_sort_
 {
     constexpr u32 CAP = kLowThreads * kLowItems;
     constexpr u32 kPerChunk = kMid / CAP;                   // output segments per chunk
-    constexpr u32 kShortWords = kSmallCap + kSmallCap / 16; // LDS of a wavefront's own list
-    constexpr u32 kListWords = CAP + CAP / 16 + CAP / 4;    // a list of composites and its counters
+    constexpr u32 kShortWords = list_words(kSmallCap);      // LDS of a wavefront's own list
+    constexpr u32 kListWords = list_words(CAP);
     constexpr u32 kEmitWords = Dense::kDense ? kDenseWaves * (u32)(sizeof(EmitSpace) / sizeof(u64)) : 0u;
     __shared__ __attribute__((aligned(16))) u64 s[kListWords > kEmitWords ? kListWords : kEmitWords];
-    __shared__ u64 s_split[2];
-    u32 *s_cnt = reinterpret_cast<u32 *>(s + CAP + CAP / 16);
+    u64 *s_split = s + CAP + CAP / 16;                      // two words behind what the merge stages
+    static_assert(CAP + CAP / 16 + 2 <= kListWords, "they fit");
     // (the flag is read together with what is needed anyway: one round trip to memory)
     const u32 first = classes[0] + classes[3] + classes[1], low = classes[2], chunks = classes[4], elsewhere = classes[kDenseClass];
     if constexpr (Dense::kDense) {
@@ -1069,7 +1107,7 @@ __global__ __launch_bounds__(kLowThreads, Dense::kDense ? 5 : 1) void tile_sort_
         }
         if (blockIdx.x >= blocks) return;
     }
-    static_assert(kShortPerBlock * kShortWords <= CAP + CAP / 16 && kShortPerBlock * kSmallCap <= CAP, "a share each");
+    static_assert(kShortPerBlock * kShortWords <= kListWords, "a share each");
     if (blockIdx.x < merge_blocks) {
         const u64 segments = (u64)chunks * kPerChunk;
         for (u64 g = blockIdx.x; g < segments; g += merge_blocks) {
@@ -1090,7 +1128,7 @@ __global__ __launch_bounds__(kLowThreads, Dense::kDense ? 5 : 1) void tile_sort_
         const u64 beg = tile_offsets[tile];
         const u64 len = tile_offsets[tile + 1] - beg;
         if (len < 2 || len > (u64)CAP) return;              // cannot happen with a consistent table
-        sort_list<kLowThreads, kLowItems>(keys, vals, beg, (u32)len, tile, s, s_cnt);
+        sort_list<kLowThreads, kLowItems>(keys, vals, beg, (u32)len, tile, s);
         return;
     }
     // the short lists, 1 .. kSmallCap pairs; from here on every wavefront goes its own way
@@ -1110,11 +1148,10 @@ __global__ __launch_bounds__(kLowThreads, Dense::kDense ? 5 : 1) void tile_sort_
         return;
     }
     u64 *my_s = s + wv * kShortWords;
-    u32 *my_cnt = s_cnt + wv * (kSmallCap / 2);
     // fewer elements per lane for shorter lists
-    if (len <= 2u * kSmallThreads) sort_list<kSmallThreads, 2u>(keys, vals, beg, (u32)len, tile, my_s, my_cnt);
-    else if (len <= 4u * kSmallThreads) sort_list<kSmallThreads, 4u>(keys, vals, beg, (u32)len, tile, my_s, my_cnt);
-    else sort_list<kSmallThreads, kSmallItems>(keys, vals, beg, (u32)len, tile, my_s, my_cnt);
+    if (len <= 2u * kSmallThreads) sort_list<kSmallThreads, 2u>(keys, vals, beg, (u32)len, tile, my_s);
+    else if (len <= 4u * kSmallThreads) sort_list<kSmallThreads, 4u>(keys, vals, beg, (u32)len, tile, my_s);
+    else sort_list<kSmallThreads, kSmallItems>(keys, vals, beg, (u32)len, tile, my_s);
 }
 
 // The second and last merge round of the long lists (runs of 2 * kMid pairs, alternate buffers -> pair

@@ -111,10 +111,15 @@ __device__ __forceinline__ void team_sync()
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 }
+// Does any thread say so?  With team_sync; `flag` is a word of LDS, zero since before an earlier team_sync and the team's
+// own for this call (__syncthreads_or has LDS of its own).
 template <u32 THREADS>
-__device__ __forceinline__ bool team_any(bool v)
+__device__ __forceinline__ bool team_any(bool v, u32 *flag)
 {
-    return THREADS > kWave ? __syncthreads_or(v) != 0 : __builtin_amdgcn_ballot_w64(v) != 0ull;
+    if (THREADS <= kWave) return __builtin_amdgcn_ballot_w64(v) != 0ull;
+    if (v) *flag = 1u;
+    __syncthreads();
+    return *flag != 0u;
 }
 template <u32 THREADS>
 __device__ __forceinline__ u32 team_thread() { return THREADS > kWave ? threadIdx.x : threadIdx.x & (kWave - 1u); }

@@ -35,6 +35,21 @@ def test_one_tile(n, kind):
     P.compare_binned(fr, ofr.binned)
 
 
+@pytest.mark.parametrize("n", [60, 200, 450, 1500, 2100, 3500, 4096])
+@pytest.mark.parametrize("size", [6, 8, 17, 20, 24, 40, 70])
+def test_clusters_around_the_limits(n, size):
+    """Clusters of one size, whose buckets are around the fullest that are still ranked: on one side the list
+    leaves for the merge sort after a quarter or all of it is counted, on the other it does not."""
+    rng = np.random.default_rng(n + size)
+    mean = np.zeros((n, 3))
+    mean[:, 2] = rng.permutation(2.0 + 0.01 * (np.arange(n) // size) + 1e-6 * rng.integers(0, 2, n))
+    sc = scenes.hand_placed_scene(mean, (0.01, 0.01, 0.01), opacity=list(rng.uniform(0.05, 0.9, n)))
+    cam = scenes.make_camera(np.eye(3, 4), (0, 0, 0), 16, 16, 60.0)
+    ofr = ref.render_frame(sc, cam)
+    assert ofr.binned.D == n
+    P.compare_binned(P.gpu_frame(B.Scene(sc), cam, n + 5), ofr.binned)
+
+
 def test_many_lists_of_all_classes():
     """A frame whose tiles hold from none to several thousand pairs, primitives in random order."""
     sc = scenes.make_scene(0, n=60000, seed=8)
