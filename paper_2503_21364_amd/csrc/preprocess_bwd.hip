@@ -17,7 +17,7 @@
 // Culls and clamps are constants of the derivative: a primitive that was not binned
 // (tiles_touched == 0) gets zeros, a colour channel clamped at 0 passes nothing on.
 //
-// Bound by HBM traffic: 36 B of gradient + 56 B of geometry + 192 B of SH in, 44 B + 192 B out
+// Bound by HBM traffic: 36 B of gradient + 40 B of geometry + 192 B of SH in, 44 B + 192 B out
 // per binned primitive (at degree 3).
 #include <cmath>
 
@@ -94,7 +94,7 @@ __device__ __forceinline__ void sh_basis_and_grad(float x, float y, float z, con
     }
 }
 
-template <u32 DEG>
+template <u32 DEG, bool STAGE>
 __global__ __launch_bounds__(256) void preprocess_backward_kernel(
     const float *__restrict__ mean, const float *__restrict__ scale, const float *__restrict__ rot,
     const float *__restrict__ sh, u32 n, ProjParams pp, ShK shk,
@@ -106,26 +106,40 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
     constexpr u32 STRIDE = LMK_GS_SH_STRIDE(DEG);
     constexpr u32 VEC = STRIDE / 4;
     // The SH records and their gradients are most of the bytes.  A lane that reads its own record touches
-    // a cache line of its own per instruction; the wavefront instead moves the whole block of its 64 records
-    // in consecutive 16-byte vectors, streamed past the caches, through LDS (one padding vector per record
-    // against bank conflicts): 3 M primitives of degree 3 370 -> 272 us (5.6 TB/s; with cached accesses
+    // a cache line of its own per instruction; with STAGE the wavefront instead moves the whole block of its 64
+    // records in consecutive 16-byte vectors, streamed past the caches, through LDS (one padding vector per record
+    // against bank conflicts): 3 M primitives of degree 3 353 -> 269 us (5.6 TB/s; with cached accesses
     // 315 us, with streaming stores from the lanes 1120 us).  Where few of the 64 were binned, those read
     // their own records and the rest of the block is not read: a record is one and a half cache lines, so
     // beyond some 40 of them all lines of the block are touched anyway (the line preprocess_kernel draws).
     // The block is requested ahead of the geometry and goes to LDS behind it (250 000 primitives of degree 2
-    // 17.6 -> 16.5 us).
+    // 17.6 -> 16.5 us).  Which calls stage: see launch_preprocess_backward.
     constexpr u32 kDirectMax = 40;
-    __shared__ f32x4 s_rec[256 / kWave][kWave * (VEC + 1)];
+    __shared__ f32x4 s_rec[STAGE ? 256 / kWave : 1][STAGE ? kWave * (VEC + 1) : 1];
     const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t N = n;
+    auto culled = [&] {
+        g_mean[i] = 0.f; g_mean[N + i] = 0.f; g_mean[2 * N + i] = 0.f;
+        g_scale[i] = 0.f; g_scale[N + i] = 0.f; g_scale[2 * N + i] = 0.f;
+        g_rot[i] = 0.f; g_rot[N + i] = 0.f; g_rot[2 * N + i] = 0.f; g_rot[3 * N + i] = 0.f;
+        g_opacity[i] = 0.f;
+    };
+    if (!STAGE) {
+        if (i >= n) return;
+        if (tiles_touched[i] == 0u) {
+            culled();
+#pragma unroll
+            for (u32 k = 0; k < VEC; ++k) reinterpret_cast<f32x4 *>(g_sh)[(size_t)i * VEC + k] = f32x4{0.f, 0.f, 0.f, 0.f};
+            return;
+        }
+    }
     const u32 lane = threadIdx.x & (kWave - 1), first = i - lane;
     if (first >= n) return;                                 // the whole wavefront
     const u32 recs = n - first < kWave ? n - first : kWave;
     const f32x4 *own = reinterpret_cast<const f32x4 *>(sh) + (size_t)i * VEC;
-    f32x4 *stage = s_rec[threadIdx.x / kWave], *mine = stage + lane * (VEC + 1);
-    const size_t N = n;
-    const bool live = i < n && tiles_touched[i] != 0u;
-    // (a record of degree 0 is one vector: the lanes' own are consecutive)
-    const bool staged = VEC > 1u && (u32)__builtin_popcountll(__builtin_amdgcn_ballot_w64(live)) > kDirectMax;     // wave-uniform
+    f32x4 *stage = s_rec[STAGE ? threadIdx.x / kWave : 0u], *mine = stage + (STAGE ? lane * (VEC + 1) : 0u);
+    const bool live = !STAGE || (i < n && tiles_touched[i] != 0u);
+    const bool staged = STAGE && (u32)__builtin_popcountll(__builtin_amdgcn_ballot_w64(live)) > kDirectMax;     // wave-uniform
     f32x4 buf[VEC];
     if (staged) {           // in flight during the geometry below
         const f32x4 *src = reinterpret_cast<const f32x4 *>(sh) + (size_t)first * VEC;
@@ -134,18 +148,13 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
             const u32 v = k * kWave + lane;
             buf[k] = v < recs * VEC ? __builtin_nontemporal_load(src + v) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
-    } else if (live) {
+    } else if (STAGE && live) {
 #pragma unroll
         for (u32 k = 0; k < VEC; ++k) buf[k] = own[k];
     }
     float mx = 0.f, my = 0.f, mz = 0.f, gcol[3] = { 0.f, 0.f, 0.f }, gm[3] = { 0.f, 0.f, 0.f };
     if (!live) {
-        if (i < n) {
-            g_mean[i] = 0.f; g_mean[N + i] = 0.f; g_mean[2 * N + i] = 0.f;
-            g_scale[i] = 0.f; g_scale[N + i] = 0.f; g_scale[2 * N + i] = 0.f;
-            g_rot[i] = 0.f; g_rot[N + i] = 0.f; g_rot[2 * N + i] = 0.f; g_rot[3 * N + i] = 0.f;
-            g_opacity[i] = 0.f;
-        }
+        if (i < n) culled();
     } else {
         const float *gf = grad_feat + (size_t)i * LMK_GS_FEAT_STRIDE;
         const float gu = gf[0], gv = gf[1], gA = gf[2], gB = gf[3], gC = gf[4];
@@ -267,7 +276,7 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
             stage[v / VEC * (VEC + 1) + v % VEC] = buf[k];
         }
     }
-    if (VEC > 1u) wave_fence();
+    if (STAGE) wave_fence();
     if (live) {
         // colour
         const float vx = mx - pp.cam.cam_pos[0], vy = my - pp.cam.cam_pos[1], vz = mz - pp.cam.cam_pos[2];
@@ -280,7 +289,7 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
         {
 #pragma unroll
             for (u32 k = 0; k < VEC; ++k) {
-                const f32x4 t = staged ? mine[k] : buf[k];
+                const f32x4 t = staged ? mine[k] : (STAGE ? buf[k] : own[k]);
                 coef[4 * k] = t.x; coef[4 * k + 1] = t.y; coef[4 * k + 2] = t.z; coef[4 * k + 3] = t.w;
             }
         }
@@ -303,7 +312,7 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
         {
 #pragma unroll
             for (u32 k = 0; k < VEC; ++k)
-                mine[k] = f32x4{gout[4 * k], gout[4 * k + 1], gout[4 * k + 2], gout[4 * k + 3]};
+                (STAGE ? mine : reinterpret_cast<f32x4 *>(g_sh) + (size_t)i * VEC)[k] = f32x4{gout[4 * k], gout[4 * k + 1], gout[4 * k + 2], gout[4 * k + 3]};
         }
         const float dd = gdx * dxn + gdy * dyn + gdz * dzn;
         gm[0] += (gdx - dxn * dd) / len;
@@ -314,10 +323,7 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
 #pragma unroll
         for (u32 k = 0; k < VEC; ++k) mine[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    if (VEC == 1u) {                                        // consecutive as they are
-        if (i < n) reinterpret_cast<f32x4 *>(g_sh)[i] = *mine;
-        return;
-    }
+    if (!STAGE) return;
     wave_fence();
     f32x4 *dst = reinterpret_cast<f32x4 *>(g_sh) + (size_t)first * VEC;
 #pragma unroll
@@ -336,16 +342,26 @@ hipError_t launch_preprocess_backward(const lmk_gs_gaussians &g, const ProjParam
     static const ShK shk = make_shk();
     if (g.n == 0) return hipSuccess;
     const u32 blocks = (g.n + 255u) / 256u;
+    // Staged or every lane its own record.  Own records stay in the caches between passes where all arrays together
+    // fit the 256 MB behind the L2, and short ones cost the lanes little: there streaming loses.  Measured, us
+    // (own / staged), all binned | a quarter binned:
+    //   degree 0, a vector each:  500 000 14.1 / 15.0 | 14.3 / 18.3, 1 M 26.4 / 26.9 | 26.5 / 33.7, 3 M 93 / 94 | 98 / 114
+    //   degree 1 (232 bytes a primitive in and out):  250 000 10.4 / 10.8, 500 000 18.7 / 21.9, 1 M 36.3 / 38.9, 1.4 M 57.7 / 51.0
+    //   degree 2 (360):  180 000 13.7 / 12.4 | 13.2 / 9.4, 250 000 17.3 / 16.6, 350 000 22.8 / 25.8 | 22.3 / 18.5,
+    //                    500 000 29.9 / 35.4 | 28.5 / 24.6, 700 000 41.9 / 44.6, 1 M 80 / 60
+    //   degree 3 (520):  100 000 13.9 / 10.6, 350 000 35.7 / 34.1, 1 M 108 / 82
+    const bool own = g.sh_degree == 0 || (g.sh_degree == 1 && g.n < (1u << 20)) ||
+                     (g.sh_degree == 2 && g.n >= 300000u && g.n < 700000u);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, stream,
                            g.mean, g.scale, g.rot, g.sh, g.n, pp, shk, proj.tiles_touched, grad_feat,
                            out.mean, out.scale, out.rot, out.opacity, out.sh);
     };
     switch (g.sh_degree) {
-        case 0: launch(preprocess_backward_kernel<0>); break;
-        case 1: launch(preprocess_backward_kernel<1>); break;
-        case 2: launch(preprocess_backward_kernel<2>); break;
-        default: launch(preprocess_backward_kernel<3>); break;
+        case 0: launch(preprocess_backward_kernel<0, false>); break;
+        case 1: if (own) launch(preprocess_backward_kernel<1, false>); else launch(preprocess_backward_kernel<1, true>); break;
+        case 2: if (own) launch(preprocess_backward_kernel<2, false>); else launch(preprocess_backward_kernel<2, true>); break;
+        default: launch(preprocess_backward_kernel<3, true>); break;
     }
     return hipGetLastError();
 }

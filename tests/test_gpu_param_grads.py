@@ -22,3 +22,15 @@ def test_counts_and_shares(n, culled, deg):
     cam = scenes.make_cameras(0, 128, 96)[0]
     st = _compare_projection(sc, cam, 7 + n)
     assert st["visible"] >= n - culled - n // 4
+
+
+@pytest.mark.parametrize("deg,n", [(1, 1 << 20), (2, 299_999), (2, 300_000), (2, 699_999), (2, 700_000)])
+def test_both_ways_of_moving_records(deg, n):
+    """From 2^20 primitives of degree 1 on, and outside 300 000 to 700 000 of degree 2, records are staged; in between the
+    lanes move their own."""
+    sc = scenes.make_scene(0, n=n, seed=n % 97)
+    sc["sh_degree"] = deg
+    gone = np.random.default_rng(n).random(n) < np.linspace(0.0, 1.0, n)       # from all binned to none
+    sc["mean"][2, gone] += np.float32(60.0)
+    st = _compare_projection(sc, scenes.make_cameras(0, 320, 200)[0], 3)
+    assert st["visible"] > n // 3
