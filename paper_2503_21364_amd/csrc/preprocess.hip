@@ -53,52 +53,98 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // fx x + (cx + r0) z < -fx R, linear in the position, so the box corners decide.  Evaluated in
 // fp32 without contraction like every step that decides an integer; the slack terms make
 // rounding keep a voxel rather than drop it.
-__device__ __forceinline__ bool voxel_visible(const ProjParams &pp, const float4 b0, const float4 b1)
+struct VoxelTest { float sx, sy, cl, cr, ct, cb, cm; };      // what depends on the camera only
+
+static VoxelTest make_voxel_test(const ProjParams &pp)
 {
-    const float *V = pp.cam.view;
-    const float lo[3] = { b0.x, b0.y, b0.z }, hi[3] = { b0.w, b1.x, b1.y };
-    const float smax = b1.z;
     const float XW = (float)(pp.tiles_x * LMK_GS_TILE), YH = (float)(pp.tiles_y * LMK_GS_TILE);
     const float st = sqrtf(11.09f);
-    const float Rx = (st * sqrtf(1.0f + pp.lim_x * pp.lim_x)) * smax;
-    const float Ry = (st * sqrtf(1.0f + pp.lim_y * pp.lim_y)) * smax;
     const float r0 = sqrtf(11.09f * pp.cam.lowpass);
-    const float cl = pp.cam.cx + r0, cr = (pp.cam.cx - r0) - XW;
-    const float ct = pp.cam.cy + r0, cb = (pp.cam.cy - r0) - YH;
-    const float cm = (XW + YH) + (fabsf(pp.cam.cx) + fabsf(pp.cam.cy));
-    float zmax = 0.f, maxL = 0.f, minR = 0.f, maxT = 0.f, minB = 0.f, mag = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const float wx = (k & 1) ? hi[0] : lo[0], wy = (k & 2) ? hi[1] : lo[1], wz = (k & 4) ? hi[2] : lo[2];
-        const float x = V[0] * wx + V[1] * wy + V[2] * wz + V[3];
-        const float y = V[4] * wx + V[5] * wy + V[6] * wz + V[7];
-        const float z = V[8] * wx + V[9] * wy + V[10] * wz + V[11];
-        const float L = pp.cam.fx * x + cl * z, R = pp.cam.fx * x + cr * z;
-        const float T = pp.cam.fy * y + ct * z, B = pp.cam.fy * y + cb * z;
-        const float m = (pp.cam.fx * fabsf(x) + pp.cam.fy * fabsf(y)) + cm * fabsf(z);
-        if (k == 0) { zmax = z; maxL = L; minR = R; maxT = T; minB = B; mag = m; }
-        else {
-            zmax = z > zmax ? z : zmax; maxL = L > maxL ? L : maxL; minR = R < minR ? R : minR;
-            maxT = T > maxT ? T : maxT; minB = B < minB ? B : minB; mag = m > mag ? m : mag;
-        }
-    }
-    const float slack = 1e-5f * mag;
-    const float bx = (pp.cam.fx * Rx) * 1.004f, by = (pp.cam.fy * Ry) * 1.004f;
-    if (zmax + 1e-5f * fabsf(zmax) < pp.cam.near_z) return false;
-    if (maxL + slack < -bx) return false;
-    if (minR - slack > bx) return false;
-    if (maxT + slack < -by) return false;
-    if (minB - slack > by) return false;
+    VoxelTest t;
+    t.sx = st * sqrtf(1.0f + pp.lim_x * pp.lim_x);
+    t.sy = st * sqrtf(1.0f + pp.lim_y * pp.lim_y);
+    t.cl = pp.cam.cx + r0; t.cr = (pp.cam.cx - r0) - XW;
+    t.ct = pp.cam.cy + r0; t.cb = (pp.cam.cy - r0) - YH;
+    t.cm = (XW + YH) + (fabsf(pp.cam.cx) + fabsf(pp.cam.cy));
+    return t;
+}
+
+// extremes over the corners
+struct VoxelSpan { float zmax, maxL, minR, maxT, minB, mag; };
+
+__device__ __forceinline__ VoxelSpan voxel_corner(const ProjParams &pp, const VoxelTest &t, const float4 b0, const float4 b1, u32 k)
+{
+    const float *V = pp.cam.view;
+    const float wx = (k & 1u) ? b0.w : b0.x, wy = (k & 2u) ? b1.x : b0.y, wz = (k & 4u) ? b1.y : b0.z;
+    const float x = V[0] * wx + V[1] * wy + V[2] * wz + V[3];
+    const float y = V[4] * wx + V[5] * wy + V[6] * wz + V[7];
+    const float z = V[8] * wx + V[9] * wy + V[10] * wz + V[11];
+    VoxelSpan s;
+    s.zmax = z;
+    s.maxL = pp.cam.fx * x + t.cl * z; s.minR = pp.cam.fx * x + t.cr * z;
+    s.maxT = pp.cam.fy * y + t.ct * z; s.minB = pp.cam.fy * y + t.cb * z;
+    s.mag = (pp.cam.fx * fabsf(x) + pp.cam.fy * fabsf(y)) + t.cm * fabsf(z);
+    return s;
+}
+
+__device__ __forceinline__ bool voxel_passes(const ProjParams &pp, const VoxelTest &t, const VoxelSpan &s, float smax)
+{
+    const float slack = 1e-5f * s.mag;
+    const float bx = (pp.cam.fx * (t.sx * smax)) * 1.004f, by = (pp.cam.fy * (t.sy * smax)) * 1.004f;
+    if (s.zmax + 1e-5f * fabsf(s.zmax) < pp.cam.near_z) return false;
+    if (s.maxL + slack < -bx) return false;
+    if (s.minR - slack > bx) return false;
+    if (s.maxT + slack < -by) return false;
+    if (s.minB - slack > by) return false;
     return true;
 }
 
+__device__ __forceinline__ bool voxel_visible(const ProjParams &pp, const VoxelTest &t, const float4 b0, const float4 b1)
+{
+    VoxelSpan s = voxel_corner(pp, t, b0, b1, 0u);
+#pragma unroll
+    for (u32 k = 1; k < 8; ++k) {
+        const VoxelSpan c = voxel_corner(pp, t, b0, b1, k);
+        s.zmax = c.zmax > s.zmax ? c.zmax : s.zmax; s.maxL = c.maxL > s.maxL ? c.maxL : s.maxL;
+        s.minR = c.minR < s.minR ? c.minR : s.minR; s.maxT = c.maxT > s.maxT ? c.maxT : s.maxT;
+        s.minB = c.minB < s.minB ? c.minB : s.minB; s.mag = c.mag > s.mag ? c.mag : s.mag;
+    }
+    return voxel_passes(pp, t, s, b1.z);
+}
+
+// The same by eight neighbouring lanes, a corner each (all eight are active): true in all of them.  A corner beyond
+// the range of fp32 keeps the voxel.
+template <int CTRL>
+__device__ __forceinline__ float voxel_dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ void voxel_join(VoxelSpan &s)
+{
+    s.zmax = fmaxf(s.zmax, voxel_dpp<CTRL>(s.zmax)); s.mag = fmaxf(s.mag, voxel_dpp<CTRL>(s.mag));
+    s.maxL = fmaxf(s.maxL, voxel_dpp<CTRL>(s.maxL)); s.maxT = fmaxf(s.maxT, voxel_dpp<CTRL>(s.maxT));
+    s.minR = fminf(s.minR, voxel_dpp<CTRL>(s.minR)); s.minB = fminf(s.minB, voxel_dpp<CTRL>(s.minB));
+}
+__device__ __forceinline__ bool voxel_visible8(const ProjParams &pp, const VoxelTest &t, const float4 b0, const float4 b1)
+{
+    VoxelSpan s = voxel_corner(pp, t, b0, b1, threadIdx.x & 7u);
+    if (!(s.mag < 3.0e38f)) s.mag = __int_as_float(0x7f800000);
+    voxel_join<0xB1>(s);        // quad_perm [1,0,3,2]
+    voxel_join<0x4E>(s);        // quad_perm [2,3,0,1]
+    voxel_join<0x141>(s);       // row_half_mirror
+    return s.mag > 3.0e38f || voxel_passes(pp, t, s, b1.z);
+}
+
+constexpr u32 kFewVoxels = 64;          // two rounds of a workgroup, and half the work of one lane a voxel
+
 // One thread per voxel.
 __global__ __launch_bounds__(256) void voxel_flags_kernel(
-    const float4 *__restrict__ box, u32 num_voxels, ProjParams pp, unsigned char *__restrict__ voxel_flags)
+    const float4 *__restrict__ box, u32 num_voxels, ProjParams pp, VoxelTest test, unsigned char *__restrict__ voxel_flags)
 {
     const u32 v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= num_voxels) return;
-    voxel_flags[v] = voxel_visible(pp, box[2 * (size_t)v], box[2 * (size_t)v + 1]) ? 1 : 0;
+    voxel_flags[v] = voxel_visible(pp, test, box[2 * (size_t)v], box[2 * (size_t)v + 1]) ? 1 : 0;
 }
 
 // Sigma = (R S)(R S)^T from an unnormalised quaternion (w, x, y, z) and the scales (Sec. 2.2 Eq. 8)
@@ -193,7 +239,7 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
     float *__restrict__ depth, u32 *__restrict__ tiles_touched, ushort4 *__restrict__ rect,
     float4 *__restrict__ feat, u32 *__restrict__ tile_masks,
     const unsigned char *__restrict__ voxel_flags, const float4 *__restrict__ voxel_box,
-    const uint2 *__restrict__ block_range, u32 num_voxels,
+    const uint2 *__restrict__ block_range, u32 num_voxels, VoxelTest test,
     unsigned char *__restrict__ block_visible, ScratchHeader *__restrict__ header,
     u32 *__restrict__ tile_count, u32 num_tiles, u32 *__restrict__ block_sums)
 {
@@ -202,15 +248,26 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
     reset_frame_state(header, tile_count, num_tiles, i, gridDim.x * kPreBlock);
     if (block_range) {
         // voxel filter: does any voxel holding one of this workgroup's primitives pass?  The caller's flags
-        // of this frame, or the test itself: a group of 256 has primitives of a voxel or two, and testing them
-        // here costs less than a launch that tests every voxel once (1283 x 717, 1.2 M primitives: 5 us)
+        // of this frame, or the test itself: by eight lanes a voxel where the group has primitives of a voxel or
+        // two, as usual, by one where it has many (2 M primitives in 7200 voxels: a launch of its own for all voxels
+        // before this one 53.8 us, one lane a voxel here 57.6, eight 54.5; in 1.2 M voxels 61.1, 58.8, 76.4)
         const uint2 r = block_range[blockIdx.x];
         // a corrupt range can only cost time, never an out-of-bounds read
         const u32 last = r.y < num_voxels ? r.y : num_voxels - 1;
+        const u64 voxels = r.x <= last ? (u64)(last - r.x) + 1ull : 0ull;
         int mine = 0;
-        for (u32 v = r.x + threadIdx.x; v <= last; v += kPreBlock) {
-            if (voxel_flags) mine |= voxel_flags[v];
-            else mine |= voxel_visible(pp, voxel_box[2 * (size_t)v], voxel_box[2 * (size_t)v + 1]) ? 1 : 0;
+        if (voxel_flags) {
+            for (u64 k = threadIdx.x; k < voxels; k += kPreBlock) mine |= voxel_flags[r.x + k];
+        } else if (voxels <= kFewVoxels) {
+            for (u64 k = threadIdx.x / 8u; k < voxels; k += kPreBlock / 8u) {
+                const size_t v = 2 * (size_t)(r.x + k);
+                mine |= voxel_visible8(pp, test, voxel_box[v], voxel_box[v + 1]) ? 1 : 0;
+            }
+        } else {
+            for (u64 k = threadIdx.x; k < voxels; k += kPreBlock) {
+                const size_t v = 2 * (size_t)(r.x + k);
+                mine |= voxel_visible(pp, test, voxel_box[v], voxel_box[v + 1]) ? 1 : 0;
+            }
         }
         const int any = __syncthreads_or(mine);
         if (block_visible && threadIdx.x == 0) block_visible[blockIdx.x] = any ? 1 : 0;
@@ -536,13 +593,14 @@ hipError_t launch_preprocess(const lmk_gs_gaussians &g, const lmk_gs_voxel_index
         boxes = reinterpret_cast<const float4 *>(index->box);
         vflags = index->visible;                    // this frame's flags from the caller's earlier call, if any
     }
+    const VoxelTest test = index ? make_voxel_test(pp) : VoxelTest{};
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(L.pre_blocks), dim3(kPreBlock), 0, stream,
                            g.mean, g.scale, g.rot, g.opacity, g.sh, g.cov3d, g.n, pp, kc,
                            out.depth, out.tiles_touched, reinterpret_cast<ushort4 *>(out.rect),
                            reinterpret_cast<float4 *>(out.feat),
                            reinterpret_cast<u32 *>(scratch + L.tile_masks),
-                           vflags, boxes, ranges, num_voxels, index ? block_visible : nullptr, header,
+                           vflags, boxes, ranges, num_voxels, test, index ? block_visible : nullptr, header,
                            tile_count, num_tiles, block_sums);
     };
     switch (g.sh_degree) {
@@ -628,7 +686,7 @@ hipError_t launch_box_flags(const float *box, u32 count, const ProjParams &pp, u
 {
     if (count == 0) return hipSuccess;
     hipLaunchKernelGGL(voxel_flags_kernel, dim3((count + 255) / 256), dim3(256), 0, stream,
-                       reinterpret_cast<const float4 *>(box), count, pp, visible);
+                       reinterpret_cast<const float4 *>(box), count, pp, make_voxel_test(pp), visible);
     return hipGetLastError();
 }
 

@@ -80,3 +80,14 @@ def test_rejects_a_camera_that_is_not_rigid():
     with pytest.raises(B.LmkGsError) as e:
         B.preprocess(dev, B.make_camera(cam), fr, index=vi)
     assert e.value.code == B.ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("voxel", [0.02, 1.0, 2.0, 6.0])
+def test_groups_of_few_and_of_many_voxels(voxel):
+    """The test of a group's voxels inside the projection: eight lanes a voxel up to 64 of them, one beyond."""
+    n = 40_000
+    spans = np.diff(B.VoxelIndex(scenes.make_scene(2, n=n, seed=302), voxel).block_range.astype(np.int64), axis=1) + 1
+    few = float((spans <= 64).mean())
+    assert few < 0.02 if voxel < 1.0 else 0.1 < few < 0.98 if voxel < 6.0 else few > 0.98, few
+    for view, binning in ((4, 1), (5, 0), (0, 1)):
+        test_filtered_frame_is_the_unfiltered_frame(2, n, voxel, 1.0, view, (640, 360), binning)
