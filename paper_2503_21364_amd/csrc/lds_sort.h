@@ -106,9 +106,7 @@ __device__ __forceinline__ void team_sync()
     if (THREADS > kWave) {
         __syncthreads();
     } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_fence();
     }
 }
 // Does any thread say so?  With team_sync; `flag` is a word of LDS, zero since before an earlier team_sync and the team's

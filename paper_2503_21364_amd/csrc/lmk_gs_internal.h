@@ -23,6 +23,14 @@ static_assert(kScanGroup % (kBinBlock / kPreBlock) == 0, "the blocks of one coun
 constexpr u32 kLdsTilesSmall = 8192, kLdsTilesLarge = 32768;
 constexpr u32 kChunk = 4096;            // pairs sorted in LDS by one workgroup of the per-tile sort
 
+// LDS accesses of one wavefront complete in program order: only the compiler has to keep to it
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Header at the start of the scratch buffer.
 struct ScratchHeader {
     u64 dup_count;      // D = pairs of the frame = sum of tiles_touched (known when lmk_gs_preprocess is done)

@@ -29,14 +29,6 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// LDS accesses of one wavefront complete in program order: only the compiler has to keep to it
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 struct ShK { float k1, k2, k20, k33, k32, k31, k30, k32b, k0; };
 
 ShK make_shk()

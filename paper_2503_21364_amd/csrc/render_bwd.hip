@@ -61,13 +61,6 @@ struct BwdParams {
     float bg0, bg1, bg2;
 };
 
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // one list entry on its way from the feature records to LDS: fetched a batch ahead, so that the two
 // dependent reads (index, then record) are in flight while the previous batch is walked
 struct Fetched { float4 a, b; float blue; u32 id; };

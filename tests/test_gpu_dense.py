@@ -1,7 +1,8 @@
 """Stage 2 of frames with very many pairs per primitive (the primitives are put into depth order once
 and every tile's list is written front to back): keys, values and ranges against the oracle, bit for
-bit.  Taken when the buffers hold 2^22 pairs and 32 per primitive, and the frame has 32 per primitive;
-the cases sit on both sides of that line and at the edges of the bins of 8 x 8 tiles."""
+bit.  Taken when the buffers hold 2^18 pairs and, in images of up to 300 bins, 32 per primitive, and the
+frame has 32 per primitive (the line itself, larger images and the merge rounds: test_gpu_routes.py); the cases
+are images whose bins of 4 x 4 tiles are cut at the edges, few and many primitives, and a frame below the line."""
 import numpy as np
 import pytest
 import torch
@@ -42,7 +43,7 @@ def test_lists_equal_the_oracle(n, w, h, mul, flat, dense, binning):
     fr = P.gpu_frame(dev, cam, cap)
     P.compare_binned(fr, ofr.binned)
     P.compare_image(fr, ofr.img, cam)
-    # again on the same buffers, and with culled primitives in between
+    # again on the same buffers
     B.bin_sort(B.make_camera(cam), fr)
     torch.cuda.synchronize()
     P.compare_binned(fr, ofr.binned)

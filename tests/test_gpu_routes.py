@@ -85,3 +85,89 @@ def test_the_order_of_chunks_and_merge_rounds(n, binning):
     fr = P.gpu_frame(B.Scene(sc), cam, binned.D + 5)
     P.compare_binned(fr, binned)
     assert went_dense(fr)
+
+
+# ---- counting and sorting pairs, for frames that the other way would take as well: keys_alt at an odd multiple of
+# 8 bytes rules that out
+def _counting_frame(n, w, h, capacity):
+    fr = B.Frame(n, w, h, capacity, want_offsets=True)
+    fr.keys_alt = torch.empty(capacity + 1, dtype=torch.int64, device="cuda")[1:]
+    assert fr.keys_alt.data_ptr() % 16 == 8
+    fr.binned.keys_alt = fr.keys_alt.data_ptr()
+    return fr
+
+
+def _sizes_scene(n, seed, largest=60.0):
+    rng = np.random.default_rng(seed)
+    sc = scenes.make_scene(0, n=n, seed=seed)
+    sc["scale"] = sc["scale"] * np.exp(rng.uniform(np.log(0.5), np.log(largest), n)).astype(np.float32)[None, :]
+    return sc
+
+
+def _areas(pre):
+    rc = pre.rect.astype(int)
+    return ((rc[:, 2] - rc[:, 0]) * (rc[:, 3] - rc[:, 1]))[pre.tiles_touched > 0]
+
+
+@pytest.mark.parametrize("binning", [0, 1])
+@pytest.mark.parametrize("n,w,h", [
+    (4000, 1920, 1080),         # 8160 tiles: counters in 32 KB
+    (1500, 3000, 2000),         # 23500: in 128 KB
+    (1000, 4096, 2304),         # 36864: every primitive is listed
+])
+def test_rectangles_of_every_size_class_by_counting(n, w, h, binning):
+    """Rectangles walked by a lane, a wavefront and a workgroup (the switches are at 32 and 2048 tiles)."""
+    sc = _sizes_scene(n, 55)
+    cam = dict(scenes.make_cameras(0, w, h)[0], binning=binning)
+    pre = ref.preprocess(sc, cam)
+    binned = ref.bin_sort(pre, cam)
+    area = _areas(pre)
+    for lo, hi in ((0, 16), (16, 32), (32, 64), (1000, 2048), (2048, 1 << 22)):
+        assert ((area > lo) & (area <= hi)).sum() > 10, (lo, hi)
+    fr = _counting_frame(n, w, h, binned.D + 100)
+    B.render_frame(B.Scene(sc), B.make_camera(cam), fr)
+    torch.cuda.synchronize()
+    P.compare_binned(fr, binned)
+    assert not went_dense(fr)
+    B.bin_sort(B.make_camera(cam), fr)                      # the counters are left clean
+    torch.cuda.synchronize()
+    P.compare_binned(fr, binned)
+
+
+@pytest.mark.parametrize("binning", [0, 1])
+def test_fewer_pairs_than_the_line_in_an_image_of_many_tiles(binning):
+    """8193 to 32768 tiles, buffers with room for the other way, pairs below the line."""
+    n, w, h = 3000, 2560, 1440
+    sc = _sizes_scene(n, 12, largest=2.0)
+    cam = dict(scenes.make_cameras(0, w, h)[0], binning=binning)
+    pre = ref.preprocess(sc, cam)
+    binned = ref.bin_sort(pre, cam)
+    assert 8192 < (w // 16) * (h // 16) <= 32768 and (_areas(pre) > 32).sum() > 100
+    assert binned.D < per_primitive(w, h) * n < 1 << 18
+    fr = P.gpu_frame(B.Scene(sc), cam, 1 << 18)
+    P.compare_binned(fr, binned)
+    assert not went_dense(fr)
+
+
+@pytest.mark.parametrize("binning", [0, 1])
+@pytest.mark.parametrize("dense", [False, True])
+def test_overflow_with_large_rectangles_and_a_retry(binning, dense):
+    """More pairs than the buffers hold, with rectangles of every size: empty ranges, nothing written, and the same
+    frame in larger buffers afterwards."""
+    n, w, h = 4000, 1920, 1080
+    sc = _sizes_scene(n, 55)
+    cam = dict(scenes.make_cameras(0, w, h)[0], binning=binning)
+    binned = ref.bin_sort(ref.preprocess(sc, cam), cam)
+    dev, c = B.Scene(sc), B.make_camera(cam)
+    make = B.Frame if dense else _counting_frame
+    small = make(n, w, h, binned.D // 2)
+    small.keys.fill_(-1)
+    B.render_frame(dev, c, small)
+    torch.cuda.synchronize()
+    assert B.read_status(small) == (binned.D, B.ERR_CAPACITY) and went_dense(small) == dense
+    assert not small.tile_offsets.any().item() and (small.keys == -1).all().item() and (small.out_T == 1.0).all().item()
+    fr = make(n, w, h, binned.D + 7, want_offsets=True) if dense else make(n, w, h, binned.D + 7)
+    B.render_frame(dev, c, fr)
+    torch.cuda.synchronize()
+    P.compare_binned(fr, binned)
+    assert went_dense(fr) == dense
