@@ -1082,7 +1082,7 @@ constexpr u32 kMergeBlocks1 = 1024, kMergeBlocks2 = 2048;
 constexpr u32 kShortPerBlock = kLowThreads / kSmallThreads;
 static_assert(kLowThreads == kDenseThreads, "the launch carries both ways");
 // (five wavefronts per SIMD as without the other way, whose registers would leave room for four: 23.6 us
-// instead of 26.3 on lists of 1.5 M primitives, and the other way itself no slower)
+// instead of 26.3 on lists of 1.5 M primitives; its emit tests two rows of tiles at a time for that, without spills)
 template <bool TIGHT, class Dense>
 __global__ __launch_bounds__(kLowThreads, Dense::kDense ? 5 : 1) void tile_sort_low_kernel(
     u64 *__restrict__ keys, u32 *__restrict__ vals, u64 *__restrict__ keys_alt, u32 *__restrict__ vals_alt,

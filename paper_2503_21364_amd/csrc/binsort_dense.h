@@ -402,12 +402,12 @@ __device__ __forceinline__ Ops load_ops(u32 pos, const ushort4 *__restrict__ rec
     return p;
 }
 
-// the tiles of the bin that a primitive keeps, tile by tile
-template <bool TIGHT>
+// the tiles of the bin that a primitive keeps, tile by tile, ROWS rows of tests in flight
+template <bool TIGHT, u32 ROWS>
 __device__ __forceinline__ u32 bin_mask(const Ops &p, u32 bx, u32 by)
 {
     u32 mask = 0;
-#pragma unroll
+#pragma unroll ROWS
     for (u32 j = 0; j < kBinEdge; ++j) {
         const u32 ty = by + j;
 #pragma unroll
@@ -424,7 +424,7 @@ __device__ __forceinline__ u32 bin_mask(const Ops &p, u32 bx, u32 by)
 // Masks of the queued primitives 0 .. count (count <= BATCH) to masks[0 .. BATCH): those that a look at the
 // whole bin decides first, then the others, put together so that the tile tests run on full wavefronts.
 // `undecided` is room for BATCH numbers.
-template <bool TIGHT, u32 BATCH>
+template <bool TIGHT, u32 BATCH, u32 ROWS>
 __device__ __forceinline__ void bin_masks(const u32 *queued, u32 count, const ushort4 *__restrict__ rects,
                                           const float4 *__restrict__ ops, u32 bx, u32 by, u32 lane,
                                           unsigned short *masks, unsigned short *undecided)
@@ -438,7 +438,7 @@ __device__ __forceinline__ void bin_masks(const u32 *queued, u32 count, const us
         if (k < count) {
             const Ops p = load_ops<TIGHT>(queued[k], rects, ops);
             if (TIGHT) ask = !bin_decided(p, bx, by, mask);
-            else mask = bin_mask<false>(p, bx, by);
+            else mask = bin_mask<false, ROWS>(p, bx, by);
         }
         masks[k] = (unsigned short)mask;
         if (TIGHT) {
@@ -453,7 +453,7 @@ __device__ __forceinline__ void bin_masks(const u32 *queued, u32 count, const us
         for (u32 j0 = 0; j0 < open; j0 += kWave) {
             if (j0 + lane < open) {
                 const u32 k = undecided[j0 + lane];
-                masks[k] = (unsigned short)bin_mask<true>(load_ops<true>(queued[k], rects, ops), bx, by);
+                masks[k] = (unsigned short)bin_mask<true, ROWS>(load_ops<true>(queued[k], rects, ops), bx, by);
             }
         }
         wave_fence();
@@ -479,7 +479,7 @@ __device__ __forceinline__ void dense_count(const DenseArgs &d, const ScratchHea
     WaveSpace &my = space[wv];
     u32 mine = 0;                                           // kept by tile `lane` of the bin
     bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
-        bin_masks<TIGHT, kBatch>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
+        bin_masks<TIGHT, kBatch, kBinEdge>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
         u32 m[kSets];
 #pragma unroll
         for (u32 set = 0; set < kSets; ++set) m[set] = my.mask[set * kWave + lane];
@@ -530,7 +530,7 @@ __device__ __forceinline__ void dense_emit(const DenseArgs &d, const ScratchHead
     }
     u32 next_lo = (u32)first, next_hi = (u32)(first >> 32);
     bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
-        bin_masks<TIGHT, kBatch>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
+        bin_masks<TIGHT, kBatch, 2u>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
         u32 m[kSets];
         u64 pair[kSets];
 #pragma unroll
