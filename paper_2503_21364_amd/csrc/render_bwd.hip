@@ -12,10 +12,10 @@
 // on neither o nor q.
 //
 // One workgroup per 16x16 tile, one thread per pixel, each wavefront an 8x8 block, each group of 16
-// lanes (row) a 4x4 sub-block of it.  Entries are staged in LDS in batches of 255 (slot 255 is a null
-// record that never contributes).  Per batch every wavefront first tests, one entry per lane, which
-// entries can reach alpha >= 1/255 in its block and then in each sub-block (the tests of blend_kernel) and
-// keeps their slots in one list per row; the pixels of a row walk that list, four entries at a time.
+// lanes (row) a 4x4 cell of it.  Entries are staged in LDS in batches of 255 (slot 255 is a null
+// record that never contributes), with the cells that they can reach (entry_cells, as in blend_kernel).  Per batch
+// every wavefront puts the entries of its cells on one list per row; the pixels of a row walk that list, four
+// entries at a time.  Tiles that the image would wait for go another way, see backward_block.
 // Pass 1 repeats the forward walk with the arithmetic of blend_kernel (same expression for log2(alpha),
 // same comparisons), which gives every pixel its final transmittance and the position of its last
 // composited entry.  Pass 2 takes the batches, and each list, back to front: T_i is recovered as
@@ -61,69 +61,23 @@ struct BwdParams {
     float bg0, bg1, bg2;
 };
 
-// one list entry on its way from the feature records to LDS: fetched a batch ahead, so that the two
-// dependent reads (index, then record) are in flight while the previous batch is walked
+// B' = -log2(e) B and C' = -0.5 log2(e) C of a fetched entry, for the flush
+__device__ __forceinline__ float2 entry_bc(const float4 a, const float4 b)
+{
+    const float kL2E = 1.4426950408889634f;
+    return make_float2(-kL2E * a.w, -0.5f * kL2E * b.x);
+}
+
+// one list entry on its way from the feature records to LDS: the index is read two batches ahead and the record one,
+// both unconditionally (see fetch_record of the forward pass)
 struct Fetched { float4 a, b; float blue; u32 id; };
-__device__ __forceinline__ Fetched fetch_entry(const u32 *__restrict__ vals, const float4 *__restrict__ feat,
-                                               u64 pos, bool valid)
+__device__ __forceinline__ Fetched fetch_entry(const float4 *__restrict__ feat, u32 index)
 {
+    const float4 *f = feat + (size_t)index * (LMK_GS_FEAT_STRIDE / 4);
     Fetched r;
-    r.a = r.b = make_float4(0.f, 0.f, 0.f, 0.f); r.blue = 0.0f; r.id = 0u;
-    if (valid) {
-        r.id = vals[pos];
-        const float4 *f = feat + (size_t)r.id * (LMK_GS_FEAT_STRIDE / 4);
-        r.a = f[0]; r.b = f[1]; r.blue = f[2].x;
-    }
+    r.id = index;
+    r.a = f[0]; r.b = f[1]; r.blue = reinterpret_cast<const float *>(f)[8];
     return r;
-}
-
-// the survivors of one batch for one wavefront: slots of the entries that pass the block test
-__device__ __forceinline__ u32 block_survivors(const float4 *s_geo, const float4 *s_cop, const float4 *s_tst,
-                                               u32 cnt, float bx, float by, u32 lane, slot_t *list)
-{
-    u32 n8 = 0;
-    for (u32 c0 = 0; c0 < cnt; c0 += kWave) {
-        const u32 e = c0 + lane;
-        const float4 g = s_geo[e < cnt ? e : 0u];
-        const float4 t = s_tst[e < cnt ? e : 0u];
-        const float4 co = s_cop[e < cnt ? e : 0u];
-        const float best = square_reach(g.x - bx, g.y - by, g.z, t.x, t.y, g.w, t.w, 3.5f);
-        const bool pass = e < cnt && best + co.y >= kBlockPass;
-        const u64 mask = __builtin_amdgcn_ballot_w64(pass);
-        const u32 rank = __builtin_amdgcn_mbcnt_hi((u32)(mask >> 32), __builtin_amdgcn_mbcnt_lo((u32)mask, 0u));
-        if (pass) list[n8 + rank] = (slot_t)e;
-        n8 += (u32)__builtin_popcountll(mask);
-    }
-    return n8;
-}
-
-// ... and of those, per 4x4 sub-block (the 16 lanes of a row), the ones that can reach it: one
-// survivor per lane, tested against the four sub-blocks; list order is kept
-__device__ __forceinline__ void subblock_survivors(const float4 *s_geo, const float4 *s_cop, const float4 *s_tst,
-                                                   const slot_t *list8, u32 n8, float bx, float by, u32 lane,
-                                                   slot_t (*list4)[kBwdList], u32 (&n4)[4], const u32 (&limit)[4])
-{
-    n4[0] = n4[1] = n4[2] = n4[3] = 0u;
-    for (u32 k0 = 0; k0 < n8; k0 += kWave) {
-        const u32 k = k0 + lane;
-        const bool valid = k < n8;
-        const u32 e = valid ? (u32)list8[k] : 0u;
-        const float4 g = s_geo[e];
-        const float4 t = s_tst[e];
-        const float4 co = s_cop[e];
-        const float xs = g.x - bx, ys = g.y - by;
-#pragma unroll
-        for (u32 q = 0; q < 4; ++q) {
-            const float qx = (q & 1u) ? 2.0f : -2.0f, qy = (q >> 1) ? 2.0f : -2.0f;
-            const float best = square_reach(xs - qx, ys - qy, g.z, t.x, t.y, g.w, t.w, 1.5f);
-            // limit[q]: slots from there on lie behind the last composited entry of every pixel of the sub-block
-            const bool pass = valid && e < limit[q] && best + co.y >= kBlockPass;
-            const u64 mask = __builtin_amdgcn_ballot_w64(pass);
-            const u32 rank = __builtin_amdgcn_mbcnt_hi((u32)(mask >> 32), __builtin_amdgcn_mbcnt_lo((u32)mask, 0u));
-            if (pass) list4[q][n4[q] + rank] = (slot_t)e;
-            n4[q] += (u32)__builtin_popcountll(mask);
-        }
-    }
 }
 
 // the four slots at position k of a row's list; beyond the row's own end null slots
@@ -132,29 +86,61 @@ __device__ __forceinline__ u32 list_word(const slot_t *list, u32 k, u32 n_pad)
     return *reinterpret_cast<const u32 *>(list + (k < n_pad ? k : n_pad));
 }
 
-__global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
-    const u64 *__restrict__ tile_offsets, const u32 *__restrict__ tile_order, const u32 *__restrict__ vals,
-    const float4 *__restrict__ feat, BwdParams bp, const float *__restrict__ grad_rgb,
+// the staged form of blend_kernel (stage_entry), so that log2(alpha) is evaluated exactly as there
+struct BwdSpace {
+    float4 geo[kBwdBatch + 1];              // du, dv, A', -B/A
+    float4 cop[kBwdBatch + 1];              // -0.5 log2(e) (C - B^2/A), lo, r, g
+    float2 bc[kBwdBatch + 1];               // B' = -log2(e) B, C' = -0.5 log2(e) C
+    float blue[kBwdBatch + 1];              // b
+    u32 id[kBwdBatch + 1];                  // primitive index
+    unsigned short cells[kBwdBatch + 1];    // the cells that the entry reaches
+    double acc[kBwdBatch + 1][kGradComps];
+    // per wavefront: m (and w) of a step on their way from lane = pixel to lane = (entry, pixels)
+    __attribute__((aligned(16))) float turn[kBwdWaves][kBwdStep * kTurnStride];
+    __attribute__((aligned(16))) slot_t list[kBwdWaves][4][kBwdList];
+    u32 last[kBwdWaves];
+    u32 odd;                                // a colour of the list is not finite
+};
+
+// From the moments of an entry to its gradient.  About the splat's centre (u, v), seen from the
+// reference point: sum m dx = u M - M_x with dx = u - x, and so on; q = A dx^2 + 2 B dx dy + C dy^2,
+// da/dq = -a / 2, da/do = a / o; the staged A' = -0.5 log2(e) A, B' = -log2(e) B, C' = -0.5 log2(e) C
+// give d/du = ln 2 (2 A' sum m dx + B' sum m dy), d/dv = ln 2 (B' sum m dx + 2 C' sum m dy).
+// Consecutive lanes take the consecutive components of an entry, so that the atomics of one
+// instruction fall into few cache lines (nine lanes per 36-byte record).
+__device__ __forceinline__ void flush_entries(u32 cnt, const BwdSpace &s, float *__restrict__ grad_feat)
+{
+    for (u32 idx = threadIdx.x; idx < cnt * kGradComps; idx += kBwdThreads) {
+        const u32 e = idx / kGradComps, c = idx - e * kGradComps;
+        const float kLn2 = 0.6931471805599453f;
+        const double *rec = s.acc[e];
+        double own = rec[c];
+        if (c < 5u) {
+            const float4 g = s.geo[e];
+            const double u = (double)g.x, v = (double)g.y, M = rec[5], mx = u * M - rec[0], my = v * M - rec[1];
+            if (c < 2u) {
+                const double Aq = (double)g.z, Bq = (double)s.bc[e].x, Cq = (double)s.bc[e].y;
+                own = (double)kLn2 * (c == 0u ? 2.0 * Aq * mx + Bq * my : Bq * mx + 2.0 * Cq * my);
+            } else {
+                // sum m p q' with p, q' in {dx, dy}: p (sum m q') - q'_centre M_p + M_pq
+                const double p = c == 4u ? v : u, q = c == 2u ? u : v, mq = c == 2u ? mx : my;
+                const double Mp = c == 4u ? rec[1] : rec[0];
+                own = p * mq - q * Mp + own;
+                own *= c == 3u ? -1.0 : -0.5;
+            }
+        } else if (c == 5u) {
+            own *= (double)__builtin_amdgcn_exp2f(-s.cop[e].y);       // 1 / opacity
+        }
+        const float v = (float)own;
+        if (v != 0.0f) atomicAdd(grad_feat + (size_t)s.id[e] * LMK_GS_FEAT_STRIDE + c, v);
+    }
+}
+
+__device__ __forceinline__ void backward_tile(
+    BwdSpace &s, u32 tile, const u64 *__restrict__ tile_offsets, const u32 *__restrict__ vals,
+    const float4 *__restrict__ feat, const BwdParams &bp, const float *__restrict__ grad_rgb,
     const float *__restrict__ grad_T, float *__restrict__ grad_feat)
 {
-    // the staged form of blend_kernel (stage_entry), so that log2(alpha) is evaluated exactly as there
-    __shared__ float4 s_geo[kBwdBatch + 1];      // du, dv, A', -B/A
-    __shared__ float4 s_cop[kBwdBatch + 1];      // -0.5 log2(e) (C - B^2/A), lo, r, g
-    __shared__ float4 s_tst[kBwdBatch + 1];      // B', C', b, -B/C
-    __shared__ u32 s_id[kBwdBatch + 1];          // primitive index
-    __shared__ double s_acc[kBwdBatch + 1][kGradComps];
-    // per wavefront: the block's survivors while the lists are built, then m (and w) of a step on their
-    // way from lane = pixel to lane = (entry, pixels)
-    __shared__ __attribute__((aligned(16))) float s_turn[kBwdWaves][kBwdStep * kTurnStride];
-    __shared__ __attribute__((aligned(16))) slot_t s_list4[kBwdWaves][4][kBwdList];
-    __shared__ u32 s_last[kBwdWaves];
-    __shared__ u32 s_odd;                        // a colour of the list is not finite
-    static_assert(sizeof(s_turn[0]) >= kBwdBatch, "the survivors' slots fit");
-
-    if (blockIdx.x >= bp.num_tiles) return;
-    // the tiles with the longest lists first, when the caller has the hint
-    const u32 tile = tile_order ? tile_order[blockIdx.x] : blockIdx.x;
-    if (tile >= bp.num_tiles) return;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const u32 tx = tile % bp.tiles_x, ty = tile / bp.tiles_x;
     const u32 grp = lane >> 4, gl = lane & 15u;                    // 4x4 sub-block of the lane, pixel inside it
@@ -170,20 +156,20 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     const u64 len64 = end - start;
     const u32 len = len64 < 0xffffff00ull ? (u32)len64 : 0xffffff00u;     // a tile's list is far shorter
     if (len == 0u) return;                                          // the same for the whole workgroup
-    slot_t *my_list = reinterpret_cast<slot_t *>(s_turn[wv]);
-    slot_t *my_list4 = s_list4[wv][grp];
+    const u32 cells_shift = wave_cells_shift(wv);
+    slot_t *my_list4 = s.list[wv][grp];
 
     if (tid == kNullSlot) {
-        s_geo[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-        s_cop[tid] = make_float4(0.f, -1000.0f, 0.f, 0.f);
-        s_tst[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-        s_id[tid] = 0u;
+        s.geo[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+        s.cop[tid] = make_float4(0.f, -1000.0f, 0.f, 0.f);
+        s.blue[tid] = 0.0f;
+        s.id[tid] = 0u;
     }
-    // lists of the staged batch; returns the longest of the four, n_mine = the length of this row's
-    auto build_lists = [&](u32 cnt, const u32 (&limit)[4], u32 (&n4)[4], u32 &n_mine) -> u32 {
-        const u32 n8 = block_survivors(s_geo, s_cop, s_tst, cnt, bx, by, lane, my_list);
-        wave_fence();
-        subblock_survivors(s_geo, s_cop, s_tst, my_list, n8, bx, by, lane, s_list4[wv], n4, limit);
+    // lists of the staged batch's first `cnt` entries; returns the longest of the four, n_mine = the length of this row's.
+    // limit[q]: slots from there on lie behind the last composited entry of every pixel of cell q
+    auto build_lists = [&](auto limited, u32 cnt, u32 wanted, const u32 (&limit)[4], u32 (&n4)[4], u32 &n_mine) -> u32 {
+        list_cells<decltype(limited)::value>(s.cells, cnt, cells_shift, wanted, limit, lane, n4,
+                                             [&](u32 q, u32 rank, u32 entry) { s.list[wv][q][rank] = (slot_t)entry; });
         n_mine = grp == 0u ? n4[0] : (grp == 1u ? n4[1] : (grp == 2u ? n4[2] : n4[3]));
         if (gl < 2u * kBwdStep) my_list4[n_mine + gl] = (slot_t)kNullSlot;
         wave_fence();
@@ -195,20 +181,29 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     float T = 1.0f;
     u32 last = 0;                       // entries of the list up to and including the last composited one
     bool done = !inside;
-    Fetched next = fetch_entry(vals, feat, start + tid, tid < kBwdBatch && tid < len);
+    const u32 *list = vals + start;
+    auto entry = [&](u32 k) { return list[k < len ? k : len - 1u]; };
+    u32 index = entry(tid);
+    Fetched next = fetch_entry(feat, index);
+    index = entry(kBwdBatch + tid);
     for (u32 base = 0; base < len; base += kBwdBatch) {
         if (__syncthreads_and(done)) break;        // also: everyone is past the previous batch
         const u32 cnt = len - base < kBwdBatch ? len - base : kBwdBatch;
         if (tid < cnt) {
             const StagedEntry se = stage_entry(next.a, next.b, 0.0f, X0, Y0);
-            s_geo[tid] = se.geo; s_cop[tid] = se.cop; s_tst[tid] = se.tst;
+            s.geo[tid] = se.geo; s.cop[tid] = se.cop;
+            s.cells[tid] = (unsigned short)entry_cells(se);
+        } else {
+            s.cells[tid] = 0;
         }
         __syncthreads();
-        next = fetch_entry(vals, feat, start + base + kBwdBatch + tid, tid < kBwdBatch && base + kBwdBatch + tid < len);
-        if (__builtin_amdgcn_ballot_w64(!done) == 0ull) continue;     // this wavefront is finished
+        next = fetch_entry(feat, index);
+        index = entry(base + 2u * kBwdBatch + tid);
+        const u64 alive = __builtin_amdgcn_ballot_w64(!done);
+        if (alive == 0ull) continue;                                  // this wavefront is finished
         u32 n4[4], n_mine;
-        const u32 no_limit[4] = { kBwdBatch, kBwdBatch, kBwdBatch, kBwdBatch };
-        const u32 longest = build_lists(cnt, no_limit, n4, n_mine);
+        const u32 no_limit[4] = {};
+        const u32 longest = build_lists(std::false_type(), cnt, cells_alive(alive), no_limit, n4, n_mine);
         const u32 n_pad = (n_mine + kBwdStep - 1u) & ~(kBwdStep - 1u);
         for (u32 k = 0; k < longest; k += kBwdStep) {
             const u32 word = list_word(my_list4, k, n_pad);
@@ -216,8 +211,8 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
 #pragma unroll
             for (u32 q = 0; q < kBwdStep; ++q) {
                 const u32 j = (word >> (8u * q)) & 255u;
-                const float4 g = s_geo[j];
-                const float2 co = *reinterpret_cast<const float2 *>(&s_cop[j]);
+                const float4 g = s.geo[j];
+                const float2 co = *reinterpret_cast<const float2 *>(&s.cop[j]);
                 alpha[q] = fminf(0.99f, __builtin_amdgcn_exp2f(log2_alpha(g, make_float4(co.x, co.y, 0.f, 0.f), g.x - ox, g.y - oy)));
             }
 #pragma unroll
@@ -250,12 +245,12 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
         wl = t > wl ? t : wl;
     }
     __syncthreads();                    // pass 1 is over in every wavefront: LDS is free
-    if (lane == 0) s_last[wv] = wl;
-    if (tid == 0) s_odd = 0u;
+    if (lane == 0) s.last[wv] = wl;
+    if (tid == 0) s.odd = 0u;
     __syncthreads();
     u32 max_last = 0;
 #pragma unroll
-    for (u32 k = 0; k < kBwdWaves; ++k) max_last = s_last[k] > max_last ? s_last[k] : max_last;
+    for (u32 k = 0; k < kBwdWaves; ++k) max_last = s.last[k] > max_last ? s.last[k] : max_last;
     if (max_last == 0) return;
 
     // ---- pass 2: back to front
@@ -274,7 +269,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     // j + 4 b + 16 k, the result (entry i, moment j) in lane j + 4 b + 16 i.  In instruction s of four the
     // pixel slot k stands for pixel (x, y) = (s, k) of the sub-block.
     const u32 ml = lane & 3u, mb = (lane >> 2) & 3u, mk = lane >> 4;
-    float *turn = s_turn[wv];
+    float *turn = s.turn[wv];
     double B1[kBwdStep], B2[kBwdStep], B3[kBwdStep];
     {
         turn[lane] = gr; turn[kWave + lane] = gg; turn[2 * kWave + lane] = gb;
@@ -289,23 +284,28 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
         }
         wave_fence();
     }
-    const slot_t *out_list = s_list4[wv][mb];
+    const slot_t *out_list = s.list[wv][mb];
     const u32 batches = (max_last + kBwdBatch - 1) / kBwdBatch;
-    next = fetch_entry(vals, feat, start + (batches - 1u) * kBwdBatch + tid,
-                       tid < kBwdBatch && (batches - 1u) * kBwdBatch + tid < max_last);
+    next = fetch_entry(feat, entry((batches - 1u) * kBwdBatch + tid));
+    index = entry(batches > 1u ? (batches - 2u) * kBwdBatch + tid : tid);
     for (u32 b = batches; b-- > 0;) {
         const u32 base = b * kBwdBatch;
         const u32 cnt = max_last - base < kBwdBatch ? max_last - base : kBwdBatch;
         __syncthreads();                // the previous batch has been flushed
         if (tid < cnt) {
             const StagedEntry se = stage_entry(next.a, next.b, next.blue, X0, Y0);
-            s_geo[tid] = se.geo; s_cop[tid] = se.cop; s_tst[tid] = se.tst;
-            s_id[tid] = next.id;
-            if (!(fabsf(se.cop.z) + fabsf(se.cop.w) + fabsf(se.tst.z) < 3.0e38f)) s_odd = 1u;
+            s.geo[tid] = se.geo; s.cop[tid] = se.cop; s.blue[tid] = se.blue;
+            s.bc[tid] = entry_bc(next.a, next.b);
+            s.id[tid] = next.id;
+            s.cells[tid] = (unsigned short)entry_cells(se);
+            if (!(fabsf(se.cop.z) + fabsf(se.cop.w) + fabsf(se.blue) < 3.0e38f)) s.odd = 1u;
+        } else {
+            s.cells[tid] = 0;
         }
         // the batch in front of this one (all of its slots lie below max_last)
-        next = fetch_entry(vals, feat, start + base - kBwdBatch + tid, b > 0u && tid < kBwdBatch);
-        for (u32 k = tid; k < cnt * kGradComps; k += kBwdThreads) (&s_acc[0][0])[k] = 0.0;
+        next = fetch_entry(feat, index);
+        index = entry(b > 1u ? base - 2u * kBwdBatch + tid : tid);
+        for (u32 k = tid; k < cnt * kGradComps; k += kBwdThreads) (&s.acc[0][0])[k] = 0.0;
         __syncthreads();
         // a wavefront none of whose pixels walked this far has nothing to add (it still takes part
         // in the barriers and the flush below)
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
             u32 limit[4];
 #pragma unroll
             for (u32 q = 0; q < 4; ++q) limit[q] = sub_last[q] > base ? sub_last[q] - base : 0u;
-            longest = build_lists(cnt, limit, n4, n_mine);
+            longest = build_lists(std::true_type(), cnt, 0xffffu, limit, n4, n_mine);
         }
         const u32 n_pad = (n_mine + kBwdStep - 1u) & ~(kBwdStep - 1u);
         const u32 n_out = mb == 0u ? n4[0] : (mb == 1u ? n4[1] : (mb == 2u ? n4[2] : n4[3]));
@@ -334,8 +334,8 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
 #pragma unroll
                 for (u32 q = 0; q < kBwdStep; ++q) {
                     const u32 j = (word >> (8u * q)) & 255u;
-                    const float4 g = s_geo[j];
-                    co[q] = s_cop[j];
+                    const float4 g = s.geo[j];
+                    co[q] = s.cop[j];
                     raw[q] = __builtin_amdgcn_exp2f(log2_alpha(g, co[q], g.x - ox, g.y - oy));
                     hit[q] = j < my_last && !(raw[q] < 1.0f / 255.0f);          // of fminf(0.99, raw): the same
                     any = any || hit[q];
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
 #pragma unroll
                 for (u32 q = kBwdStep; q-- > 0;) {
                     const float a = hit[q] ? fminf(0.99f, raw[q]) : 0.0f;
-                    const float blue = ODD && !hit[q] ? 0.0f : s_tst[(word >> (8u * q)) & 255u].z;
+                    const float blue = ODD && !hit[q] ? 0.0f : s.blue[(word >> (8u * q)) & 255u];
                     const float inv = __builtin_amdgcn_rcpf(1.0f - a);     // 1 - a >= 0.01; one ulp is enough here
                     // dL/da = (dL/dC . (T c - S) - dL/dT_end T_end) / (1 - a), T = transmittance behind the entry
                     const float num = fmaf(gr, fmaf(T, co[q].z, -Sr), fmaf(gg, fmaf(T, co[q].w, -Sg), fmaf(gb, fmaf(T, blue, -Sb), -gT_end)));
@@ -391,47 +391,240 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
                     if (((h >> (16u * mb)) & 0xffffull) == 0ull) slot = kNullSlot;
                 }
                 if (slot != kNullSlot) {
-                    double *rec = s_acc[slot];
+                    double *rec = s.acc[slot];
                     atomicAdd(rec + (ml == 0u ? 5u : ml - 1u), d1);
                     if (ml < 2u) atomicAdd(rec + 3u + ml, d2);
                     if (ml < 3u) atomicAdd(rec + 6u + ml, d3);
                 }
             }
         };
-        if (odd_grad || s_odd != 0u) walk(std::true_type());                // wave-uniform
+        if (odd_grad || s.odd != 0u) walk(std::true_type());                // wave-uniform
         else walk(std::false_type());
         __syncthreads();
-        // from the moments of an entry to its gradient.  About the splat's centre (u, v), seen from the
-        // reference point: sum m dx = u M - M_x with dx = u - x, and so on; q = A dx^2 + 2 B dx dy + C dy^2,
-        // da/dq = -a / 2, da/do = a / o; the staged A' = -0.5 log2(e) A, B' = -log2(e) B, C' = -0.5 log2(e) C
-        // give d/du = ln 2 (2 A' sum m dx + B' sum m dy), d/dv = ln 2 (B' sum m dx + 2 C' sum m dy).
-        // Consecutive lanes take the consecutive components of an entry, so that the atomics of one
-        // instruction fall into few cache lines (nine lanes per 36-byte record)
-        for (u32 idx = tid; idx < cnt * kGradComps; idx += kBwdThreads) {
-            const u32 e = idx / kGradComps, c = idx - e * kGradComps;
-            const float kLn2 = 0.6931471805599453f;
-            const double *rec = s_acc[e];
-            double own = rec[c];
-            if (c < 5u) {
-                const float4 g = s_geo[e];
-                const double u = (double)g.x, v = (double)g.y, M = rec[5], mx = u * M - rec[0], my = v * M - rec[1];
-                if (c < 2u) {
-                    const double Aq = (double)g.z, Bq = (double)s_tst[e].x, Cq = (double)s_tst[e].y;
-                    own = (double)kLn2 * (c == 0u ? 2.0 * Aq * mx + Bq * my : Bq * mx + 2.0 * Cq * my);
-                } else {
-                    // sum m p q' with p, q' in {dx, dy}: p (sum m q') - q'_centre M_p + M_pq
-                    const double p = c == 4u ? v : u, q = c == 2u ? u : v, mq = c == 2u ? mx : my;
-                    const double Mp = c == 4u ? rec[1] : rec[0];
-                    own = p * mq - q * Mp + own;
-                    own *= c == 3u ? -1.0 : -0.5;
-                }
-            } else if (c == 5u) {
-                own *= (double)__builtin_amdgcn_exp2f(-s_cop[e].y);       // 1 / opacity
-            }
-            const float v = (float)own;
-            if (v != 0.0f) atomicAdd(grad_feat + (size_t)s_id[e] * LMK_GS_FEAT_STRIDE + c, v);
-        }
+        flush_entries(cnt, s, grad_feat);
     }
+}
+
+// The same for block `block` of a fine tile (see kFineTiles): a wavefront per 4x4 cell, four lanes a pixel, a lane
+// for each of four consecutive entries.  Pass 1 is the walk of blend_tile<true>.  In pass 2 a lane has its own
+// entry's alpha, 1 / (1 - alpha) and dL/dC . c; T goes through the four entries back to front, and so does the sum P =
+// dL/dC . S + dL/dT_end T_end, which is all that dL/da needs of the colour behind.  m and w are then where
+// the matrix instruction wants them: in v_mfma_f64_4x4x4 operand A (entry i, pixel slot k of block b) sits in lane i + 4 b +
+// 16 k, that is pixel b + 4 k of the cell; the four blocks' results are added up over the lanes.
+// the sum over the lanes of a row of sixteen that agree in lane mod 4, in all of them
+__device__ __forceinline__ double row_sum4(double v)
+{
+    auto turned = [](double x, auto ctrl) {
+        const u64 b = (u64)__double_as_longlong(x);
+        const u32 lo = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)b, decltype(ctrl)::value, 0xf, 0xf, true);
+        const u32 hi = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)(b >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+    };
+    v += turned(v, std::integral_constant<int, 0x124>());       // row_ror 4
+    return v + turned(v, std::integral_constant<int, 0x128>()); // row_ror 8
+}
+
+__device__ __forceinline__ void backward_block(
+    BwdSpace &s, u32 tile, u32 block, const u64 *__restrict__ tile_offsets, const u32 *__restrict__ vals,
+    const float4 *__restrict__ feat, const BwdParams &bp, const float *__restrict__ grad_rgb,
+    const float *__restrict__ grad_T, float *__restrict__ grad_feat)
+{
+    const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const u32 pix = lane >> 2, own = lane & 3u;         // pixel of the cell; entry of the four, and moment
+    const u32 tx = tile % bp.tiles_x, ty = tile / bp.tiles_x;
+    const u32 bi = (block & 1u) * 8u + (wv & 1u) * 4u + (pix & 3u), bj = (block >> 1) * 8u + (wv >> 1) * 4u + (pix >> 2);
+    const u32 pxi = tx * LMK_GS_TILE + bi, pyi = ty * LMK_GS_TILE + bj;
+    const bool inside = pxi < bp.width && pyi < bp.height;
+    const float ox = (float)bi - 3.5f, oy = (float)bj - 3.5f;
+    const float X0 = (float)(tx * LMK_GS_TILE) + 4.0f, Y0 = (float)(ty * LMK_GS_TILE) + 4.0f;
+    const u32 cell = wave_cells_shift(block) + (wv >> 1) * 4u + (wv & 1u);
+    const u64 start = tile_offsets[tile], end = tile_offsets[tile + 1];
+    const u64 len64 = end - start;
+    const u32 len = len64 < 0xffffff00ull ? (u32)len64 : 0xffffff00u;
+    if (len == 0u) return;                              // the same for the whole workgroup
+    slot_t *my_list = s.list[wv][0];
+
+    if (tid == kNullSlot) {
+        s.geo[kNullSlot] = make_float4(0.f, 0.f, 0.f, 0.f);
+        s.cop[kNullSlot] = make_float4(0.f, -1000.0f, 0.f, 0.f);
+        s.blue[kNullSlot] = 0.0f;
+    }
+    // the list of this cell: entries of the staged batch in front of `limit`, null entries behind them
+    auto build_list = [&](u32 cnt, u32 limit) -> u32 {
+        const u32 n = list_cell(s.cells, cnt, cell, limit, lane, [&](u32 rank, u32 entry) { my_list[rank] = (slot_t)entry; });
+        if (lane < 8u) my_list[n + lane] = (slot_t)kNullSlot;
+        wave_fence();
+        return n;
+    };
+    auto my_alpha = [&](float4 g, float4 co) { return __builtin_amdgcn_exp2f(log2_alpha(g, co, g.x - ox, g.y - oy)); };
+
+    // ---- pass 1: the forward walk
+    float T = 1.0f;
+    u32 last = 0;                       // entries of the list up to and including the last composited one
+    bool done = !inside;
+    const u32 *list = vals + start;
+    auto entry = [&](u32 k) { return list[k < len ? k : len - 1u]; };
+    u32 index = entry(tid);
+    Fetched next = fetch_entry(feat, index);
+    index = entry(kBwdBatch + tid);
+    for (u32 base = 0; base < len; base += kBwdBatch) {
+        if (__syncthreads_and(done)) break;             // also: everyone is past the previous batch
+        const u32 cnt = len - base < kBwdBatch ? len - base : kBwdBatch;
+        if (tid < cnt) {
+            const StagedEntry se = stage_entry(next.a, next.b, 0.0f, X0, Y0);
+            s.geo[tid] = se.geo; s.cop[tid] = se.cop;
+            s.cells[tid] = (unsigned short)entry_cells(se);
+        } else {
+            s.cells[tid] = 0;
+        }
+        __syncthreads();
+        next = fetch_entry(feat, index);
+        index = entry(base + 2u * kBwdBatch + tid);
+        if (__builtin_amdgcn_ballot_w64(!done) == 0ull) continue;       // this wavefront is finished
+        const u32 n = build_list(cnt, kBwdBatch);
+        u32 last_k = ~0u;                               // step of the last entry of this lane that the pixel composited
+        float4 g, co;
+        auto read_step = [&](u32 k) { const u32 e = my_list[k + own]; g = s.geo[e]; co = s.cop[e]; };
+        if (n) read_step(0);
+        for (u32 k = 0; k < n; k += 4) {
+            const float4 g0 = g, co0 = co;
+            read_step(k + 4u);                          // while this step is taken; null entries behind the list
+            __builtin_amdgcn_sched_barrier(0);
+            const float raw = my_alpha(g0, co0);
+            const float a = !(raw < 1.0f / 255.0f) && !done ? fminf(0.99f, raw) : 0.0f;
+            float alpha[4] = { quad_lane<0>(a), quad_lane<1>(a), quad_lane<2>(a), quad_lane<3>(a) }, Tq[5];
+            quad_walk(T, alpha, Tq, done);
+            const float mine = own == 0u ? alpha[0] : (own == 1u ? alpha[1] : (own == 2u ? alpha[2] : alpha[3]));
+            last_k = mine != 0.0f ? k : last_k;
+            T = Tq[4];
+            if (__builtin_amdgcn_ballot_w64(!done) == 0ull) break;
+        }
+        if (last_k != ~0u) last = base + 1u + my_list[last_k + own];
+        wave_fence();
+    }
+    {   // of the pixel, the last of the four
+        const u32 t = (u32)__builtin_amdgcn_update_dpp(0, (int)last, 0xB1, 0xf, 0xf, true);
+        last = t > last ? t : last;
+        const u32 t2 = (u32)__builtin_amdgcn_update_dpp(0, (int)last, 0x4E, 0xf, 0xf, true);
+        last = t2 > last ? t2 : last;
+    }
+    const float T_end = T;
+
+    // the longest walk of this cell and of the tile bound pass 2
+    u32 wl = last;
+#pragma unroll
+    for (int o = 32; o >= 4; o >>= 1) {
+        const u32 t = (u32)__shfl_xor((int)wl, o, 64);
+        wl = t > wl ? t : wl;
+    }
+    wl = (u32)__builtin_amdgcn_readfirstlane((int)wl);
+    __syncthreads();                    // pass 1 is over in every wavefront: LDS is free
+    if (lane == 0) s.last[wv] = wl;
+    if (tid == 0) s.odd = 0u;
+    __syncthreads();
+    u32 max_last = 0;
+#pragma unroll
+    for (u32 k = 0; k < kBwdWaves; ++k) max_last = s.last[k] > max_last ? s.last[k] : max_last;
+    if (max_last == 0) return;
+
+    // ---- pass 2: back to front
+    const size_t plane = (size_t)bp.width * bp.height;
+    const size_t at = (size_t)pyi * bp.width + pxi;
+    const float gr = inside ? grad_rgb[at] : 0.0f;
+    const float gg = inside ? grad_rgb[plane + at] : 0.0f;
+    const float gb = inside ? grad_rgb[2 * plane + at] : 0.0f;
+    const float gT = (inside && grad_T) ? grad_T[at] : 0.0f;
+    const float gT_end = gT * T_end;
+    const bool odd_grad = __builtin_amdgcn_ballot_w64(!(fabsf(gr) + fabsf(gg) + fabsf(gb) + fabsf(gT_end) < 3.0e38f)) != 0ull;
+    float P = fmaf(gr, bp.bg0 * T_end, fmaf(gg, bp.bg1 * T_end, fmaf(gb, bp.bg2 * T_end, gT_end)));
+    T = T_end;
+    // operand B (pixel slot k, moment j of block b) sits in lane j + 4 b + 16 k: moment `own` of this lane's pixel
+    const double B1 = own == 0u ? 1.0 : (double)(own == 1u ? ox : (own == 2u ? oy : ox * ox));
+    const double B2 = own == 0u ? (double)(ox * oy) : (own == 1u ? (double)(oy * oy) : 0.0);
+    const double B3 = own == 0u ? (double)gr : (own == 1u ? (double)gg : (own == 2u ? (double)gb : 0.0));
+    // a result lane j + 4 b + 16 i adds moment j of instruction b of entry i: components 5, 0, 1, 2 | 3, 4 | 6, 7, 8
+    const u32 blk = (lane >> 2) & 3u, ent = lane >> 4;
+    const u32 comp = blk == 0u ? (own == 0u ? 5u : own - 1u) : (blk == 1u ? 3u + own : 6u + own);
+    const bool adds = blk == 0u || (blk == 1u && own < 2u) || (blk == 2u && own < 3u);
+    const u32 batches = (max_last + kBwdBatch - 1) / kBwdBatch;
+    next = fetch_entry(feat, entry((batches - 1u) * kBwdBatch + tid));
+    index = entry(batches > 1u ? (batches - 2u) * kBwdBatch + tid : tid);
+    for (u32 b = batches; b-- > 0;) {
+        const u32 base = b * kBwdBatch;
+        const u32 cnt = max_last - base < kBwdBatch ? max_last - base : kBwdBatch;
+        __syncthreads();                // the previous batch has been flushed
+        if (tid < cnt) {
+            const StagedEntry se = stage_entry(next.a, next.b, next.blue, X0, Y0);
+            s.geo[tid] = se.geo; s.cop[tid] = se.cop; s.blue[tid] = se.blue;
+            s.bc[tid] = entry_bc(next.a, next.b);
+            s.id[tid] = next.id;
+            s.cells[tid] = (unsigned short)entry_cells(se);
+            if (!(fabsf(se.cop.z) + fabsf(se.cop.w) + fabsf(se.blue) < 3.0e38f)) s.odd = 1u;
+        } else {
+            s.cells[tid] = 0;
+        }
+        next = fetch_entry(feat, index);
+        index = entry(b > 1u ? base - 2u * kBwdBatch + tid : tid);
+        for (u32 k = tid; k < cnt * kGradComps; k += kBwdThreads) (&s.acc[0][0])[k] = 0.0;
+        __syncthreads();
+        const u32 n = base < wl ? build_list(cnt, wl - base) : 0u;
+        const u32 my_last = last > base ? last - base : 0u;             // slots below it lie in front of this pixel's end
+        const bool odd = odd_grad || s.odd != 0u;                       // wave-uniform
+        u32 e1, slot1;
+        float4 g1, co1;
+        float blue1;
+        auto read_step = [&](u32 k) { slot1 = my_list[k + ent]; e1 = my_list[k + own]; g1 = s.geo[e1]; co1 = s.cop[e1]; blue1 = s.blue[e1]; };
+        const u32 n_pad = (n + 3u) & ~3u;
+        if (n) read_step(n_pad - 4u);
+        for (u32 k = n_pad; k > 0;) {
+            k -= 4u;
+            const u32 e = e1, slot = slot1;
+            const float4 g = g1, co = co1;
+            const float blue = blue1;
+            read_step(k >= 4u ? k - 4u : 0u);           // while this step is taken
+            __builtin_amdgcn_sched_barrier(0);
+            const float raw = my_alpha(g, co);
+            const bool hit = e < my_last && !(raw < 1.0f / 255.0f);     // of fminf(0.99, raw): the same
+            const u64 hits = __builtin_amdgcn_ballot_w64(hit);
+            if (hits == 0ull) continue;
+            // without a contribution everything below is as for a = 0: T and P stay as they are, m and w are zero
+            const float a = hit ? fminf(0.99f, raw) : 0.0f;
+            const float gc = hit ? fmaf(gr, co.z, fmaf(gg, co.w, gb * blue)) : 0.0f;
+            const float inv = __builtin_amdgcn_rcpf(1.0f - a);
+            const float T2 = T * quad_lane<3>(inv), T1 = T2 * quad_lane<2>(inv), T0 = T1 * quad_lane<1>(inv), Tf = T0 * quad_lane<0>(inv);
+            const float behind = own == 3u ? T : (own == 2u ? T2 : (own == 1u ? T1 : T0));      // transmittance behind this lane's entry
+            const float w = a * (own == 3u ? T2 : (own == 2u ? T1 : (own == 1u ? T0 : Tf)));   // ... and in front
+            const float part = w * gc;
+            const float P2 = P + quad_lane<3>(part), P1 = P2 + quad_lane<2>(part), P0 = P1 + quad_lane<1>(part);
+            const float Pb = own == 3u ? P : (own == 2u ? P2 : (own == 1u ? P1 : P0));
+            P = P0 + quad_lane<0>(part);
+            T = Tf;
+            // dL/da = (dL/dC . (T c - S) - dL/dT_end T_end) / (1 - a); a clamped alpha depends on nothing
+            const float m = (raw > 0.99f ? 0.0f : a) * (fmaf(behind, gc, -Pb) * inv);
+            const double d1 = row_sum4(__builtin_amdgcn_mfma_f64_4x4x4f64((double)m, B1, 0.0, 0, 0, 0));
+            const double d2 = row_sum4(__builtin_amdgcn_mfma_f64_4x4x4f64((double)m, B2, 0.0, 0, 0, 0));
+            const double d3 = row_sum4(__builtin_amdgcn_mfma_f64_4x4x4f64((double)w, B3, 0.0, 0, 0, 0));
+            // zero times a value that is not finite is NaN: an entry that no pixel of the cell composites adds nothing
+            bool add = adds && slot != kNullSlot;
+            if (odd) add = add && ((hits >> ent) & 0x1111111111111111ull) != 0ull;
+            if (add) atomicAdd(&s.acc[slot][comp], blk == 0u ? d1 : (blk == 1u ? d2 : d3));
+        }
+        __syncthreads();
+        flush_entries(cnt, s, grad_feat);
+    }
+}
+
+// Workgroups of fine_grid(): the tiles with the longest lists first, when the caller has the hint.
+__global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
+    const u64 *__restrict__ tile_offsets, const u32 *__restrict__ tile_order, const u32 *__restrict__ vals,
+    const float4 *__restrict__ feat, BwdParams bp, const float *__restrict__ grad_rgb,
+    const float *__restrict__ grad_T, float *__restrict__ grad_feat)
+{
+    __shared__ BwdSpace space;
+    const TileWork w = tile_work(bp.num_tiles, tile_order, tile_offsets, reinterpret_cast<unsigned short *>(space.turn));
+    if (w.tile >= bp.num_tiles) return;
+    if (w.fine) backward_block(space, w.tile, w.block, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
+    else backward_tile(space, w.tile, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
 }
 
 __global__ __launch_bounds__(256) void zero_kernel(float4 *__restrict__ p, size_t count4)
@@ -461,7 +654,7 @@ hipError_t launch_render_backward(const lmk_gs_projected &proj, u32 n, const lmk
     bp.tiles_x = pp.tiles_x; bp.num_tiles = pp.tiles_x * pp.tiles_y;
     bp.bg0 = pp.cam.bg[0]; bp.bg1 = pp.cam.bg[1]; bp.bg2 = pp.cam.bg[2];
     if (n == 0 || binned.capacity == 0) return hipSuccess;
-    hipLaunchKernelGGL(blend_backward_kernel, dim3(bp.num_tiles), dim3(kBwdThreads), 0, stream,
+    hipLaunchKernelGGL(blend_backward_kernel, dim3(fine_grid(bp.num_tiles, binned.tile_order != nullptr)), dim3(kBwdThreads), 0, stream,
                        binned.tile_offsets, binned.tile_order, binned.vals,
                        reinterpret_cast<const float4 *>(proj.feat), bp, grad_rgb, grad_T, grad_feat);
     return hipGetLastError();
