@@ -231,8 +231,10 @@ __device__ __forceinline__ void block_total(u32 cnt, u32 *s_part, u32 *__restric
     }
 }
 
+// (the wavefronts per SIMD asked for are those that the registers allowed before row_kept was part of it; at degree 1 asking
+// for six spills, and five take as long)
 template <u32 DEG>
-__global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
+__global__ __launch_bounds__(kPreBlock, DEG == 0 ? 7 : 4) void preprocess_kernel(
     const float *__restrict__ mean, const float *__restrict__ scale, const float *__restrict__ rot,
     const float *__restrict__ opacity, const float *__restrict__ sh, const float *__restrict__ cov3d, u32 n,
     ProjParams pp, ShConsts kc,
@@ -415,14 +417,13 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
                     c += k ? 1u : 0u;
                 }
             } else {
-                // 8 x 8 tiles a step, down the columns: no division, and what depends on the column only
-                // is computed once (400 000 splats of 1500 tiles: 2.1 ms of projection before, 1.6 ms so;
-                // with the line at 512 tiles a close-up view loses 1 us to steps that are cut at the edges,
-                // with it at 4096 the 1.6 ms are 1.8)
+                // a row of tiles a lane, of which only those near the ends are asked (400 000 splats of 1500 tiles at
+                // 3840 x 2160: a frame 7240 us with 8 x 8 tiles a step, all asked, 6080 so)
                 const u32 bx1 = bx0 + bw, by1 = __shfl(y1, src, 64);
-                for (u32 tx = bx0 + (lane & 7u); tx - (lane & 7u) < bx1; tx += 8u)
-                    for (u32 ty = by0 + (lane >> 3); ty - (lane >> 3) < by1; ty += 8u)
-                        c += (tile_kept(bt, tx, ty) && tx < bx1 && ty < by1) ? 1u : 0u;
+                const float fx = fmaxf(fabsf((float)(bx0 * LMK_GS_TILE) - bt.u), fabsf((float)(bx1 * LMK_GS_TILE) - bt.u));
+                const float fy = fmaxf(fabsf((float)(by0 * LMK_GS_TILE) - bt.v), fabsf((float)(by1 * LMK_GS_TILE) - bt.v));
+                const float slack = 2e-5f * (bt.A * fx * fx + bt.C * fy * fy);
+                for (u32 ty = by0 + lane; ty < by1; ty += kWave) c += row_kept(bt, ty, bx0, bx1, slack);
             }
 #pragma unroll
             for (int o2 = 32; o2 > 0; o2 >>= 1) c += __shfl_xor(c, o2, 64);

@@ -40,7 +40,8 @@ __device__ __forceinline__ float quad_adj(const TileTest &t, float ex, float ey)
     return q - 4e-6f * m;
 }
 
-__device__ __forceinline__ bool tile_kept(const TileTest &t, u32 tx, u32 ty)
+// the least q (less a margin for rounding) on the square of a tile's pixel centres
+__device__ __forceinline__ float tile_reach(const TileTest &t, u32 tx, u32 ty)
 {
     const float h = 0.5f * (float)LMK_GS_TILE - 0.5f;
     const float xs = t.u - ((float)(tx * LMK_GS_TILE) + 0.5f * (float)LMK_GS_TILE);
@@ -51,8 +52,54 @@ __device__ __forceinline__ bool tile_kept(const TileTest &t, u32 tx, u32 ty)
     const float ex2 = clampf3(xs + t.rx * ey2, -h, h) - xs;
     const float q1 = quad_adj(t, ex1, ey1);
     const float q2 = quad_adj(t, ex2, ey2);
-    const float qmin = q1 < q2 ? q1 : q2;
-    return qmin <= t.tau;
+    return q1 < q2 ? q1 : q2;
+}
+__device__ __forceinline__ bool tile_kept(const TileTest &t, u32 tx, u32 ty) { return tile_reach(t, tx, ty) <= t.tau; }
+
+// How many of the tiles x0 <= tx < x1 of row ty are kept, as tile_kept decides them, but asked only where that is not
+// certain.  Exactly taken, the least q of a tile is a convex function of tx; tile_reach is within 5e-6 M of it, M =
+// A fx^2 + C fy^2 over the rectangle, and `slack` is 2e-5 M.  So all tiles between two that are within tau - slack are
+// kept, and behind one beyond tau + slack, seen from the tile with the row's least q, none is.  The ends are
+// guessed from where the ellipse q = tau crosses the row, a bad guess only costs time.
+__device__ __forceinline__ u32 row_kept(const TileTest &t, u32 ty, u32 x0, u32 x1, float slack)
+{
+    const float TS = (float)LMK_GS_TILE, h = 0.5f * TS - 0.5f;
+    const float yc = ((float)(ty * LMK_GS_TILE) + 0.5f * TS) - t.v, y0 = yc - h, y1 = yc + h;
+    const float cn = t.C + t.B * t.rx, inv = __builtin_amdgcn_rcpf(t.A);
+    const float yr = t.rx * __builtin_amdgcn_sqrtf(fmaxf(t.tau * t.A * __builtin_amdgcn_rcpf(t.C * cn), 0.0f));       // row of the rightmost point; the leftmost's is -yr
+    const float last = (float)(x1 - 1u), first = (float)x0;
+    auto tile_at = [&](float x) { return clampf3(floorf((x + t.u) / TS), first, last); };    // NaN passes: made x0 below
+    const float yR = clampf3(yr, y0, y1), yL = clampf3(-yr, y0, y1);
+    const float hi = tile_at(t.rx * yR + __builtin_amdgcn_sqrtf(fmaxf((t.tau - cn * yR * yR) * inv, 0.0f)));
+    const float lo = tile_at(t.rx * yL - __builtin_amdgcn_sqrtf(fmaxf((t.tau - cn * yL * yL) * inv, 0.0f)));
+    const u32 mid = (u32)fmaxf(tile_at(t.rx * clampf3(0.0f, y0, y1)), first);
+    u32 a = (u32)fmaxf(lo, first), b = (u32)fmaxf(hi, first), kept = 0;
+    a = a < mid ? a : mid;
+    b = b > mid ? b : mid;
+    const float in = t.tau - slack, out = t.tau + slack;
+    for (u32 tx = b + 1u; tx < x1; ++tx) {                                      // to the right of the guess
+        const float q = tile_reach(t, tx, ty);
+        kept += q <= t.tau ? 1u : 0u;
+        if (q > out && tx >= mid + 2u) break;
+    }
+    for (u32 tx = a; tx-- > x0;) {                                              // to the left of it
+        const float q = tile_reach(t, tx, ty);
+        kept += q <= t.tau ? 1u : 0u;
+        if (q > out && tx + 2u <= mid) break;
+    }
+    bool sure = false;
+    for (; a <= b; ++a) {                                                       // from its left end to a tile that is certain
+        const float q = tile_reach(t, a, ty);
+        if (q <= in) { sure = true; break; }
+        kept += q <= t.tau ? 1u : 0u;
+    }
+    if (!sure) return kept;
+    for (; b > a; --b) {                                                        // and from its right end
+        const float q = tile_reach(t, b, ty);
+        if (q <= in) break;
+        kept += q <= t.tau ? 1u : 0u;
+    }
+    return kept + (b - a + 1u);
 }
 
 // t / w and t % w for t < 2^22 (a tile grid has at most 2^22 tiles), 1 <= w <= 4096; inv_w = 1 / w
