@@ -407,8 +407,8 @@ __device__ __forceinline__ void backward_tile(
 
 // The same for block `block` of a fine tile (see kFineTiles): a wavefront per 4x4 cell, four lanes a pixel, a lane
 // for each of four consecutive entries.  Pass 1 is the walk of blend_tile<true>.  In pass 2 a lane has its own
-// entry's alpha, 1 / (1 - alpha) and dL/dC . c; T goes through the four entries back to front, and so does the sum P =
-// dL/dC . S + dL/dT_end T_end, which is all that dL/da needs of the colour behind.  m and w are then where
+// entry's alpha, 1 / (1 - alpha) and colour; T and the colour S behind go through the four entries back to front, with the
+// operations of backward_tile.  m and w are then where
 // the matrix instruction wants them: in v_mfma_f64_4x4x4 operand A (entry i, pixel slot k of block b) sits in lane i + 4 b +
 // 16 k, that is pixel b + 4 k of the cell; the four blocks' results are added up over the lanes.
 // the sum over the lanes of a row of sixteen that agree in lane mod 4, in all of them
@@ -536,7 +536,7 @@ __device__ __forceinline__ void backward_block(
     const float gT = (inside && grad_T) ? grad_T[at] : 0.0f;
     const float gT_end = gT * T_end;
     const bool odd_grad = __builtin_amdgcn_ballot_w64(!(fabsf(gr) + fabsf(gg) + fabsf(gb) + fabsf(gT_end) < 3.0e38f)) != 0ull;
-    float P = fmaf(gr, bp.bg0 * T_end, fmaf(gg, bp.bg1 * T_end, fmaf(gb, bp.bg2 * T_end, gT_end)));
+    float Sr = bp.bg0 * T_end, Sg = bp.bg1 * T_end, Sb = bp.bg2 * T_end;
     T = T_end;
     // operand B (pixel slot k, moment j of block b) sits in lane j + 4 b + 16 k: moment `own` of this lane's pixel
     const double B1 = own == 0u ? 1.0 : (double)(own == 1u ? ox : (own == 2u ? oy : ox * ox));
@@ -587,20 +587,26 @@ __device__ __forceinline__ void backward_block(
             const bool hit = e < my_last && !(raw < 1.0f / 255.0f);     // of fminf(0.99, raw): the same
             const u64 hits = __builtin_amdgcn_ballot_w64(hit);
             if (hits == 0ull) continue;
-            // without a contribution everything below is as for a = 0: T and P stay as they are, m and w are zero
+            // without a contribution everything below is as for a = 0: T and S stay as they are, m and w are zero
             const float a = hit ? fminf(0.99f, raw) : 0.0f;
-            const float gc = hit ? fmaf(gr, co.z, fmaf(gg, co.w, gb * blue)) : 0.0f;
+            const float red = hit ? co.z : 0.0f, green = hit ? co.w : 0.0f, blu = hit ? blue : 0.0f;
             const float inv = __builtin_amdgcn_rcpf(1.0f - a);
             const float T2 = T * quad_lane<3>(inv), T1 = T2 * quad_lane<2>(inv), T0 = T1 * quad_lane<1>(inv), Tf = T0 * quad_lane<0>(inv);
             const float behind = own == 3u ? T : (own == 2u ? T2 : (own == 1u ? T1 : T0));      // transmittance behind this lane's entry
             const float w = a * (own == 3u ? T2 : (own == 2u ? T1 : (own == 1u ? T0 : Tf)));   // ... and in front
-            const float part = w * gc;
-            const float P2 = P + quad_lane<3>(part), P1 = P2 + quad_lane<2>(part), P0 = P1 + quad_lane<1>(part);
-            const float Pb = own == 3u ? P : (own == 2u ? P2 : (own == 1u ? P1 : P0));
-            P = P0 + quad_lane<0>(part);
+            const float w4[4] = { quad_lane<0>(w), quad_lane<1>(w), quad_lane<2>(w), quad_lane<3>(w) };
             T = Tf;
+            // the colour behind this lane's entry, and S moved on to in front of the four
+            auto behind_own = [&](float c, float &S) {
+                const float S2 = fmaf(quad_lane<3>(c), w4[3], S), S1 = fmaf(quad_lane<2>(c), w4[2], S2), S0 = fmaf(quad_lane<1>(c), w4[1], S1);
+                const float mine = own == 3u ? S : (own == 2u ? S2 : (own == 1u ? S1 : S0));
+                S = fmaf(quad_lane<0>(c), w4[0], S0);
+                return mine;
+            };
             // dL/da = (dL/dC . (T c - S) - dL/dT_end T_end) / (1 - a); a clamped alpha depends on nothing
-            const float m = (raw > 0.99f ? 0.0f : a) * (fmaf(behind, gc, -Pb) * inv);
+            const float num = fmaf(gr, fmaf(behind, red, -behind_own(red, Sr)), fmaf(gg, fmaf(behind, green, -behind_own(green, Sg)),
+                              fmaf(gb, fmaf(behind, blu, -behind_own(blu, Sb)), -gT_end)));
+            const float m = (raw > 0.99f ? 0.0f : a) * (num * inv);
             const double d1 = row_sum4(__builtin_amdgcn_mfma_f64_4x4x4f64((double)m, B1, 0.0, 0, 0, 0));
             const double d2 = row_sum4(__builtin_amdgcn_mfma_f64_4x4x4f64((double)m, B2, 0.0, 0, 0, 0));
             const double d3 = row_sum4(__builtin_amdgcn_mfma_f64_4x4x4f64((double)w, B3, 0.0, 0, 0, 0));
