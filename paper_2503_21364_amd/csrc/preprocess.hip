@@ -409,7 +409,7 @@ __global__ __launch_bounds__(kPreBlock, DEG == 0 ? 7 : 4) void preprocess_kernel
             const u32 bw = __shfl(w, src, 64), barea = __shfl(area, src, 64);
             u32 c = 0;
             bool k0 = false;                                  // this lane's slot of the first 64
-            if (barea <= 16u * kWave) {
+            if (barea <= 8u * kWave) {
                 for (u32 t = lane; t < barea; t += kWave) {
                     const u32 row = t / bw;
                     const bool k = tile_kept(bt, bx0 + (t - row * bw), by0 + row);
@@ -418,7 +418,8 @@ __global__ __launch_bounds__(kPreBlock, DEG == 0 ? 7 : 4) void preprocess_kernel
                 }
             } else {
                 // a row of tiles a lane, of which only those near the ends are asked (400 000 splats of 1500 tiles at
-                // 3840 x 2160: a frame 7240 us with 8 x 8 tiles a step, all asked, 6080 so)
+                // 3840 x 2160: a frame 7240 us with 8 x 8 tiles a step, all asked, 6080 so; the line at 256, 512, 1024 tiles: 60 000
+                // at 1500 x 900 541, 534, 542 us, 5000 at 1200 x 1000 267, 259, 272)
                 const u32 bx1 = bx0 + bw, by1 = __shfl(y1, src, 64);
                 const float fx = fmaxf(fabsf((float)(bx0 * LMK_GS_TILE) - bt.u), fabsf((float)(bx1 * LMK_GS_TILE) - bt.u));
                 const float fy = fmaxf(fabsf((float)(by0 * LMK_GS_TILE) - bt.v), fabsf((float)(by1 * LMK_GS_TILE) - bt.v));
