@@ -450,20 +450,21 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     __shared__ u32 s_wave[kWaves];
     // slots are scattered and one compute unit does all the address work: the order is put
     // together in LDS and written out in whole lines (images of up to kOrderStage tiles)
-    __shared__ u32 s_order[SMALL ? kLdsTilesSmall : kOrderStage];
-    __shared__ u32 s_len[SMALL ? kLdsTilesSmall : 1];      // SMALL: the list lengths, for the chunk list
+    __shared__ __attribute__((aligned(16))) u32 s_space[SMALL ? 2 * kLdsTilesSmall : kOrderStage];
+    u32 *const s_order = s_space;
+    u32 *const s_len = s_space + (SMALL ? kLdsTilesSmall : 0u);     // SMALL: the list lengths, for the chunk list
     const bool staged = SMALL || num_tiles <= kOrderStage;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
 
     // ---- (1) D
     // a tile's list = the runs of the counting workgroups (tile_count) followed by the pairs of
     // the listed primitives (large_count)
-    u32 mine8[kScanItems], runs8[kScanItems];  // SMALL: list length and length of the runs of tiles tid * kScanItems + j
+    u32 mine8[kScanItems], runs8[kScanItems];  // SMALL: list length and length of the runs of tiles j * kScanThreads + tid
     u64 part = 0;
     if (SMALL) {
 #pragma unroll
         for (u32 j = 0; j < kScanItems; ++j) {
-            const u32 t = tid * kScanItems + j;
+            const u32 t = j * kScanThreads + tid;
             runs8[j] = t < num_tiles ? tile_count[t] : 0u;
             mine8[j] = runs8[j] + (t < num_tiles ? large_count[t] : 0u);
             part += mine8[j];
@@ -493,27 +494,66 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
 #pragma unroll
         for (u32 j = 0; j < kScanItems; ++j) {
             if (overflow) { mine8[j] = 0u; runs8[j] = 0u; }
-            s_len[tid * kScanItems + j] = mine8[j];
+            s_len[j * kScanThreads + tid] = mine8[j];
         }
     }
     __syncthreads();                           // s_sum is reused below
 
-    // ---- (2) per-tile ranges: kScanItems consecutive tiles per thread, entry num_tiles = the end
+    // ---- (2) of up to kLdsTilesSmall tiles: consecutive lanes read and write consecutive tiles, and LDS changes between that
+    // and kScanItems consecutive tiles per thread (addressed in memory like that, one compute unit takes some 3.5 us for
+    // the lines of the offsets alone; frame of 500 000 at 1080p, 8160 tiles: 249.0 us so, 239.5 through LDS)
+    if (SMALL && ranges_part) {
+        const uint4 c0 = *reinterpret_cast<const uint4 *>(s_len + tid * kScanItems), c1 = *reinterpret_cast<const uint4 *>(s_len + tid * kScanItems + 4);
+        const u32 c[kScanItems] = { c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w };
+        u64 mine = 0;
+#pragma unroll
+        for (u32 j = 0; j < kScanItems; ++j) mine += c[j];
+        u64 incl = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const u64 v = __shfl_up(incl, o, 64);
+            if ((int)lane >= o) incl += v;
+        }
+        if (lane == kWave - 1) s_sum[wv] = incl;
+        __syncthreads();                       // also: every length has been read
+        u64 run = incl - mine, total = 0;
+#pragma unroll
+        for (u32 k = 0; k < kWaves; ++k) {
+            const u64 v = s_sum[k];
+            if (k < wv) run += v;
+            total += v;
+        }
+        u64 *s_run = reinterpret_cast<u64 *>(s_space);
+#pragma unroll
+        for (u32 j = 0; j < kScanItems; ++j) { s_run[tid * kScanItems + j] = run; run += c[j]; }
+        __syncthreads();
+#pragma unroll
+        for (u32 j = 0; j < kScanItems; ++j) {
+            const u32 t = j * kScanThreads + tid;
+            if (t <= num_tiles) {
+                const u64 at = s_run[t];
+                tile_offsets[t] = at;
+                tile_cursor[t] = (wide ? 0u : (u32)at) + runs8[j];     // the listed primitives' pairs follow the runs
+            }
+        }
+        if (num_tiles == kLdsTilesSmall && tid == 0) {
+            tile_offsets[num_tiles] = total;
+            tile_cursor[num_tiles] = wide ? 0u : (u32)total;
+        }
+        return;
+    }
+
+    // ---- (2) per-tile ranges of more tiles: kScanItems consecutive ones per thread, entry num_tiles = the end
     u64 carry = 0;
-    for (u32 base = 0; ranges_part && base <= num_tiles; base += kScanThreads * kScanItems) {
+    for (u32 base = 0; !SMALL && ranges_part && base <= num_tiles; base += kScanThreads * kScanItems) {
         const u32 t0 = base + tid * kScanItems;
         u32 c[kScanItems], runs[kScanItems];
         u64 mine = 0;
 #pragma unroll
         for (u32 j = 0; j < kScanItems; ++j) {
-            if (SMALL) {
-                c[j] = base == 0u ? mine8[j] : 0u;
-                runs[j] = base == 0u ? runs8[j] : 0u;
-            } else {
-                const bool in = !overflow && t0 + j < num_tiles;
-                runs[j] = in ? tile_count[t0 + j] : 0u;
-                c[j] = runs[j] + (in ? large_count[t0 + j] : 0u);
-            }
+            const bool in = !overflow && t0 + j < num_tiles;
+            runs[j] = in ? tile_count[t0 + j] : 0u;
+            c[j] = runs[j] + (in ? large_count[t0 + j] : 0u);
             mine += c[j];
         }
         u64 incl = mine;
@@ -546,8 +586,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
 
     if (ranges_part) return;
 
-    // ---- (3) order and size classes.  Tile of (thread, round j): SMALL tid * kScanItems + j, else
-    // base + j * kScanThreads + tid.
+    // ---- (3) order and size classes.  Tile of (thread, round j): base + j * kScanThreads + tid.
     const u32 copy = tid & (kOrderCopies - 1);
     for (u32 k = tid; k < kOrderCounters; k += kScanThreads) s_cnt[k] = 0;
     __syncthreads();
@@ -555,7 +594,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     for (u32 base = 0; base < (SMALL ? 1u : num_tiles); base += sweep) {
 #pragma unroll
         for (u32 j = 0; j < kScanItems; ++j) {
-            const u32 t = SMALL ? tid * kScanItems + j : base + j * kScanThreads + tid;
+            const u32 t = base + j * kScanThreads + tid;
             if (t < num_tiles) {
                 const u32 b = length_bucket(SMALL ? mine8[j] : (overflow ? 0u : tile_count[t] + large_count[t]));
                 atomicAdd(&s_cnt[(32 - b) * kOrderCopies + copy], 1u);      // long lists first
@@ -593,7 +632,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     for (u32 base = 0; base < (SMALL ? 1u : num_tiles); base += sweep) {
 #pragma unroll
         for (u32 j = 0; j < kScanItems; ++j) {
-            const u32 t = SMALL ? tid * kScanItems + j : base + j * kScanThreads + tid;
+            const u32 t = base + j * kScanThreads + tid;
             if (t >= num_tiles) continue;
             const u32 b = length_bucket(SMALL ? mine8[j] : (overflow ? 0u : tile_count[t] + large_count[t]));
             const u32 slot = atomicAdd(&s_cnt[(32 - b) * kOrderCopies + copy], 1u);
