@@ -134,10 +134,10 @@ __device__ __forceinline__ void list_cells(const unsigned short *s_cells, u32 cn
 // to entry is passed inside the four lanes (quad_perm).  This needs about twice the vector instructions a pixel, so
 // that it is the better way only where the compute units are not full: for all tiles of an image of up to kFineTiles, in
 // one of up to kFineMaxTiles for as many in front of the caller's order by list length as have 1 / kFineShare
-// of the frame's pairs, else for none (a 3 M overview at 1080p has one such tile in 8160).
-// A training step, us, without / with: 30 000 primitives at 333 x 217 241 / 184; 1 M in clusters, 400 x 300, 1750 / 970,
-// 800 x 600 1012 / 681.  The line, 200 000 evenly in a cube, frame and training step, no tile fine / these rules / all:
-// 256 tiles 119, 342 / 110, 297 / 110, 296; 475 tiles 106, 293 / 104, 274 / 112, 310; 1900 tiles 107, 272 / 107, 264 / 140,
+// of the frame's pairs, else for none (a 3 M overview at 1080p has no such tile among 8160).
+// A training step, us, without / with: 30 000 primitives at 333 x 217 241 / 184; 1 M in clusters, 400 x 300, 1750 / 991,
+// 800 x 600 1012 / 678.  The line, 200 000 evenly in a cube, frame and training step, no tile fine / these rules / all:
+// 256 tiles 119, 342 / 110, 313 / the same; 475 tiles 106, 293 / 103, 271 / 112, 310; 1900 tiles 107, 272 / 104, 262 / 140,
 // 434.  A 128th instead of a 256th of the pairs: the clusters at 400 x 300 1170 instead of 980.
 constexpr u32 kFineTiles = 256, kFineMaxTiles = 2048, kFineShare = 256;
 constexpr u32 kFineThreads = 256;           // of the workgroups, and the most tiles that can be fine beyond kFineTiles
