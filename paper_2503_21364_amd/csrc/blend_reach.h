@@ -46,6 +46,42 @@ __device__ __forceinline__ float log2_alpha(const float4 geo, const float4 cop, 
 // log2(alpha_max) >= log2(1/255) - margin is a reach, i.e. alpha down to 0.99990/255
 constexpr float kBlockPass = -7.994353436858858f - 1.5e-4f;
 
+// Upper bound, with the rounding margin folded in, of A' dx^2 + B' dx dy + C' dy^2 over the square [-half, half]^2 about a
+// centre from which the splat centre lies at (xs, ys).  tx = -B / A, ty = -B / C.
+__device__ __forceinline__ float square_reach(float xs, float ys, float Aq, float Bq, float Cq, float tx, float ty, float half)
+{
+    auto clamped = [&](float v) { return __builtin_amdgcn_fmed3f(v, -half, half); };
+    const float kRelMargin = -2e-6f;    // times (A' ex^2 + C' ey^2) <= 0: covers fp32 rounding of the test
+    // candidate 1: x clamped into the square, best y on that vertical line
+    const float ex1 = clamped(xs) - xs;
+    const float ey1 = clamped(fmaf(ty, ex1, ys)) - ys;
+    const float m1 = fmaf(Aq * ex1, ex1, Cq * ey1 * ey1);
+    const float p1 = fmaf(Bq * ex1, ey1, m1);
+    // candidate 2: y clamped, best x on that horizontal line
+    const float ey2 = clamped(ys) - ys;
+    const float ex2 = clamped(fmaf(tx, ey2, xs)) - xs;
+    const float m2 = fmaf(Aq * ex2, ex2, Cq * ey2 * ey2);
+    const float p2 = fmaf(Bq * ex2, ey2, m2);
+    return fmaxf(fmaf(m1, kRelMargin, p1), fmaf(m2, kRelMargin, p2));
+}
+
+// The cells of an entry whose level is no ellipse in fp32 (a singular conic, a value that is not finite): those where the
+// exponent's largest value over the 8x8 block and over the cell passes.  A comparison with NaN does not pass.
+__device__ __forceinline__ u32 entry_cells_any(const StagedEntry &s, float B, float C)
+{
+    const float kL2E = 1.4426950408889634f;
+    const float Bq = -kL2E * B, Cq = -0.5f * kL2E * C, ty = -B / C;
+    auto passes = [&](float xs, float ys, float half) { return square_reach(xs, ys, s.geo.z, Bq, Cq, s.geo.w, ty, half) + s.cop.y >= kBlockPass; };
+    u32 cells = 0;
+#pragma unroll 1
+    for (u32 k = 0; k < 16; ++k) {
+        const float xs = s.geo.x - (float)((k & 2u) * 4u), ys = s.geo.y - (float)((k & 8u));    // from the centre of the block
+        const bool pass = passes(xs, ys, 3.5f) && passes(xs - ((k & 1u) ? 2.0f : -2.0f), ys - ((k & 4u) ? 2.0f : -2.0f), 1.5f);
+        cells |= pass ? 1u << k : 0u;
+    }
+    return cells;
+}
+
 // ---- the cells a staged entry reaches: bit 4 r + c = the square of the pixel centres of cell (column c, row r)
 // holds a point with log2(alpha) >= kBlockPass.  About the splat's centre the points of that level are
 //   X = nr Y +- sqrt((L + c2' Y^2) / -A'),   L = lo - kBlockPass, nr = -B / A,
@@ -57,7 +93,9 @@ constexpr float kBlockPass = -7.994353436858858f - 1.5e-4f;
 // One lane does this for an entry as it stages it: 150 vector instructions per 64 entries and tile, 250 with the lists,
 // where testing them against four 8x8 blocks (the exponent's largest value over a square), then the survivors
 // against four 4x4 cells each, took 450: 94.0 M -> 86.6 M per launch forward, 278 M -> 264 M backward (3 M overview).
-__device__ __forceinline__ u32 entry_cells(const StagedEntry &s)
+// record(): the index of the entry's feature record, read again where the level is no ellipse.
+template <class Record>
+__device__ __forceinline__ u32 entry_cells(const StagedEntry &s, const float4 *__restrict__ feat, Record &&record)
 {
     const float du = s.geo.x, dv = s.geo.y, nr = s.geo.w, An = -s.geo.z, cn = -s.cop.x;
     const float L = s.cop.y - kBlockPass;
@@ -81,9 +119,12 @@ __device__ __forceinline__ u32 entry_cells(const StagedEntry &s)
         const u32 row = (1u << c1) - (1u << c0);
         cells |= (dR >= 0.0f ? row : 0u) << (4u * r);       // a strip beyond the ellipse: no point of it there
     }
-    // where the level is no ellipse in fp32 (a singular conic, an infinite value) nothing is left out
-    const bool sound = level < 3.0e38f && bend < 3.0e38f && bend > 0.0f && fabsf(yr) < 3.0e38f;
-    return L >= 0.0f && fabsf(du) + fabsf(dv) < 3.0e38f ? (sound ? cells : 0xffffu) : 0u;
+    const bool sound = level < 3.0e38f && bend < 3.0e38f && bend > 0.0f && fabsf(yr) < 3.0e38f && fabsf(du) + fabsf(dv) < 3.0e38f;
+    if (!sound) {                                           // L < 0 among them: yr is NaN
+        const float4 *f = feat + (size_t)record() * (LMK_GS_FEAT_STRIDE / 4);
+        cells = entry_cells_any(s, f[0].w, f[1].x);
+    }
+    return cells;
 }
 
 // The entries of a staged batch that reach each of the wavefront's four cells, in list order: put(cell, rank, entry)

@@ -118,10 +118,11 @@ __device__ __forceinline__ void blend_tile(
                 // every thread stages one slot; slots past the end of the list reach nothing
                 const bool valid = tid < cnt;
                 const StagedEntry se = stage_entry(next.a, next.b, next.blue, X0, Y0);
+                const u32 cells = entry_cells(se, feat, [&] { return entry(base + tid); });
                 s.geo[tid] = valid ? se.geo : make_float4(0.f, 0.f, 0.f, 0.f);
                 s.cop[tid] = valid ? se.cop : make_float4(0.f, -1000.0f, 0.f, 0.f);
                 s.blue[tid].x = valid ? se.blue : 0.0f;
-                s.cells[tid] = (unsigned short)(valid ? entry_cells(se) : 0u);
+                s.cells[tid] = (unsigned short)(valid ? cells : 0u);
             }
             __syncthreads();
             next = fetch_record(feat, index);                          // in flight during the loops below

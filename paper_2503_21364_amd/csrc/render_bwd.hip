@@ -192,7 +192,7 @@ __device__ __forceinline__ void backward_tile(
         if (tid < cnt) {
             const StagedEntry se = stage_entry(next.a, next.b, 0.0f, X0, Y0);
             s.geo[tid] = se.geo; s.cop[tid] = se.cop;
-            s.cells[tid] = (unsigned short)entry_cells(se);
+            s.cells[tid] = (unsigned short)entry_cells(se, feat, [&] { return next.id; });
         } else {
             s.cells[tid] = 0;
         }
@@ -297,7 +297,7 @@ __device__ __forceinline__ void backward_tile(
             s.geo[tid] = se.geo; s.cop[tid] = se.cop; s.blue[tid] = se.blue;
             s.bc[tid] = entry_bc(next.a, next.b);
             s.id[tid] = next.id;
-            s.cells[tid] = (unsigned short)entry_cells(se);
+            s.cells[tid] = (unsigned short)entry_cells(se, feat, [&] { return next.id; });
             if (!(fabsf(se.cop.z) + fabsf(se.cop.w) + fabsf(se.blue) < 3.0e38f)) s.odd = 1u;
         } else {
             s.cells[tid] = 0;
@@ -473,7 +473,7 @@ __device__ __forceinline__ void backward_block(
         if (tid < cnt) {
             const StagedEntry se = stage_entry(next.a, next.b, 0.0f, X0, Y0);
             s.geo[tid] = se.geo; s.cop[tid] = se.cop;
-            s.cells[tid] = (unsigned short)entry_cells(se);
+            s.cells[tid] = (unsigned short)entry_cells(se, feat, [&] { return next.id; });
         } else {
             s.cells[tid] = 0;
         }
@@ -558,7 +558,7 @@ __device__ __forceinline__ void backward_block(
             s.geo[tid] = se.geo; s.cop[tid] = se.cop; s.blue[tid] = se.blue;
             s.bc[tid] = entry_bc(next.a, next.b);
             s.id[tid] = next.id;
-            s.cells[tid] = (unsigned short)entry_cells(se);
+            s.cells[tid] = (unsigned short)entry_cells(se, feat, [&] { return next.id; });
             if (!(fabsf(se.cop.z) + fabsf(se.cop.w) + fabsf(se.blue) < 3.0e38f)) s.odd = 1u;
         } else {
             s.cells[tid] = 0;
