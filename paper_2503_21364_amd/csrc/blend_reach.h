@@ -223,6 +223,7 @@ __device__ __forceinline__ TileWork tile_work(u32 num_tiles, const u32 *__restri
     u32 slot = w.fine ? b - w.block * apart : b - 4u * apart + first;
     if (w.fine && slot >= first) slot = num_tiles;
     if (some && slot < kFineThreads) slot = map[slot];
+    slot = (u32)__builtin_amdgcn_readfirstlane((int)slot);
     w.tile = slot < num_tiles ? (tile_order ? tile_order[slot] : slot) : num_tiles;
     return w;                                                           // a corrupt hint is for the caller to check
 }
