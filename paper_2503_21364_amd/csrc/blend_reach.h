@@ -66,10 +66,12 @@ __device__ __forceinline__ float square_reach(float xs, float ys, float Aq, floa
 }
 
 // The cells of an entry whose level is no ellipse in fp32 (a singular conic, a value that is not finite): those where the
-// exponent's largest value over the 8x8 block and over the cell passes.  A comparison with NaN does not pass.
-__device__ __forceinline__ u32 entry_cells_any(const StagedEntry &s, float B, float C)
+// exponent's largest value over the 8x8 block and over the cell passes.  A comparison with NaN does not pass.  B and C are read
+// again from the feature record, so that the path that all other entries take keeps its registers.
+__device__ __forceinline__ u32 entry_cells_any(const StagedEntry &s, const float4 *__restrict__ feat, u32 index)
 {
     const float kL2E = 1.4426950408889634f;
+    const float B = feat[(size_t)index * (LMK_GS_FEAT_STRIDE / 4)].w, C = feat[(size_t)index * (LMK_GS_FEAT_STRIDE / 4) + 1].x;
     const float Bq = -kL2E * B, Cq = -0.5f * kL2E * C, ty = -B / C;
     auto passes = [&](float xs, float ys, float half) { return square_reach(xs, ys, s.geo.z, Bq, Cq, s.geo.w, ty, half) + s.cop.y >= kBlockPass; };
     u32 cells = 0;
@@ -93,9 +95,9 @@ __device__ __forceinline__ u32 entry_cells_any(const StagedEntry &s, float B, fl
 // One lane does this for an entry as it stages it: 150 vector instructions per 64 entries and tile, 250 with the lists,
 // where testing them against four 8x8 blocks (the exponent's largest value over a square), then the survivors
 // against four 4x4 cells each, took 450: 94.0 M -> 86.6 M per launch forward, 278 M -> 264 M backward (3 M overview).
-// record(): the index of the entry's feature record, read again where the level is no ellipse.
-template <class Record>
-__device__ __forceinline__ u32 entry_cells(const StagedEntry &s, const float4 *__restrict__ feat, Record &&record)
+// Where the level is no ellipse in fp32 the answer is kNoEllipse, and entry_cells_any() has to be asked.
+constexpr u32 kNoEllipse = 0x10000u;
+__device__ __forceinline__ u32 entry_cells(const StagedEntry &s)
 {
     const float du = s.geo.x, dv = s.geo.y, nr = s.geo.w, An = -s.geo.z, cn = -s.cop.x;
     const float L = s.cop.y - kBlockPass;
@@ -119,12 +121,9 @@ __device__ __forceinline__ u32 entry_cells(const StagedEntry &s, const float4 *_
         const u32 row = (1u << c1) - (1u << c0);
         cells |= (dR >= 0.0f ? row : 0u) << (4u * r);       // a strip beyond the ellipse: no point of it there
     }
-    const bool sound = level < 3.0e38f && bend < 3.0e38f && bend > 0.0f && fabsf(yr) < 3.0e38f && fabsf(du) + fabsf(dv) < 3.0e38f;
-    if (!sound) {                                           // L < 0 among them: yr is NaN
-        const float4 *f = feat + (size_t)record() * (LMK_GS_FEAT_STRIDE / 4);
-        cells = entry_cells_any(s, f[0].w, f[1].x);
-    }
-    return cells;
+    // a value that is not finite, and a root of a negative one (L < 0, C' < 0), come through the sum
+    const bool sound = bend > 0.0f && level + bend + fabsf(yr) + fabsf(du) + fabsf(dv) < 3.0e38f;
+    return sound ? cells : kNoEllipse;
 }
 
 // The entries of a staged batch that reach each of the wavefront's four cells, in list order: put(cell, rank, entry)
@@ -167,67 +166,8 @@ __device__ __forceinline__ void list_cells(const unsigned short *s_cells, u32 cn
     }
 }
 
-// ---- tiles that the image would wait for: a wavefront per cell instead of per four
-// A tile's workgroup takes its list from front to back, 64 pixels a wavefront.  An image of a few hundred tiles then
-// leaves most of the chip idle, and one with a few very long lists waits for these.  Such tiles ("fine") have
-// a workgroup per 8x8 block, so that every cell has a wavefront, with four lanes a pixel, a lane for each of four
-// consecutive entries of the list: the exponentials of a step are evaluated side by side, and what goes from entry
-// to entry is passed inside the four lanes (quad_perm).  This needs about twice the vector instructions a pixel, so
-// that it is the better way only where the compute units are not full: for all tiles of an image of up to kFineTiles, in
-// one of up to kFineMaxTiles for as many in front of the caller's order by list length as have 1 / kFineShare
-// of the frame's pairs, else for none (a 3 M overview at 1080p has no such tile among 8160).
-// A training step, us, without / with: 30 000 primitives at 333 x 217 241 / 184; 1 M in clusters, 400 x 300, 1750 / 991,
-// 800 x 600 1012 / 678.  The line, 200 000 evenly in a cube, frame and training step, no tile fine / these rules / all:
-// 256 tiles 119, 342 / 110, 313 / the same; 475 tiles 106, 293 / 103, 271 / 112, 310; 1900 tiles 107, 272 / 104, 262 / 140,
-// 434.  A 128th instead of a 256th of the pairs: the clusters at 400 x 300 1170 instead of 980.
-constexpr u32 kFineTiles = 256, kFineMaxTiles = 2048, kFineShare = 256;
-constexpr u32 kFineThreads = 256;           // of the workgroups, and the most tiles that can be fine beyond kFineTiles
-static_assert(kFineShare <= kFineThreads && kFineThreads <= kFineTiles, "no more tiles have such a share; the order has an entry for every thread");
-
-// which tile, and how, workgroup blockIdx.x of fine_grid() takes: block = the 8x8 block of a fine tile; num_tiles: none
-struct TileWork { u32 tile, block; bool fine; };
-inline u32 fine_grid(u32 num_tiles, bool ordered)
-{
-    return num_tiles <= kFineTiles ? 4u * num_tiles : num_tiles + (ordered && num_tiles <= kFineMaxTiles ? 3u * kFineThreads + 32u : 0u);
-}
-// By the whole workgroup of kFineThreads threads (no more tiles than that have such a share; the order within a power of two of
-// the length is any, so that they need not be the first); `map`: LDS for kFineThreads + 4 numbers, free again after
-// the next barrier.
-__device__ __forceinline__ TileWork tile_work(u32 num_tiles, const u32 *__restrict__ tile_order, const u64 *__restrict__ tile_offsets,
-                                              unsigned short *map)
-{
-    const u32 b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const bool some = tile_order && num_tiles > kFineTiles && num_tiles <= kFineMaxTiles;
-    u32 first = num_tiles <= kFineTiles ? num_tiles : 0u;               // how many are fine
-    if (some) {
-        const u32 t = tile_order[tid];
-        const bool fine = t < num_tiles && (tile_offsets[t + 1] - tile_offsets[t]) * kFineShare >= tile_offsets[num_tiles];
-        const u64 mask = __builtin_amdgcn_ballot_w64(fine);
-        if (lane == 0) map[kFineThreads + wv] = (unsigned short)__builtin_popcountll(mask);
-        __syncthreads();
-        u32 before = 0;                                                 // fine ones in front of this wavefront's
-        for (u32 k = 0; k < kFineThreads / kWave; ++k) {
-            const u32 c = map[kFineThreads + k];
-            before += k < wv ? c : 0u;
-            first += c;
-        }
-        const u32 rank = __builtin_amdgcn_mbcnt_hi((u32)(mask >> 32), __builtin_amdgcn_mbcnt_lo((u32)mask, before));
-        map[fine ? rank : first + tid - rank] = (unsigned short)tid;    // the fine ones, then the others
-        __syncthreads();
-    }
-    // the blocks of a tile are a multiple of the eight dies apart: they read the same records through one L2
-    const u32 apart = some ? (first + 7u) & ~7u : first;
-    TileWork w;
-    w.fine = b < 4u * apart;
-    w.block = w.fine ? b / apart : 0u;
-    u32 slot = w.fine ? b - w.block * apart : b - 4u * apart + first;
-    if (w.fine && slot >= first) slot = num_tiles;
-    if (some && slot < kFineThreads) slot = map[slot];
-    slot = (u32)__builtin_amdgcn_readfirstlane((int)slot);
-    w.tile = slot < num_tiles ? (tile_order ? tile_order[slot] : slot) : num_tiles;
-    return w;                                                           // a corrupt hint is for the caller to check
-}
-
+// ---- a tile shared by workgroups (tile_work.h): a wavefront per cell, four lanes a pixel, a lane for each of four
+// consecutive entries of the list
 // lane q's value in all four lanes of a pixel
 template <u32 Q>
 __device__ __forceinline__ float quad_lane(float v)

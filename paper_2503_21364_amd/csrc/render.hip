@@ -28,6 +28,7 @@
 // VALU issue; HBM traffic is the 52 bytes per list entry of the gather.
 #include "lmk_gs_internal.h"
 #include "blend_reach.h"
+#include "tile_work.h"
 
 namespace lmk {
 
@@ -70,31 +71,33 @@ struct BlendSpace {
     __attribute__((aligned(16))) unsigned short list[kBlendThreads / kWave][4][kListLen];
 };
 
-// FINE: workgroup `block` of four of the tile, a wavefront per cell (see kFineTiles).  A lane evaluates one of four
+// SHARED: workgroup `block` of four of the tile, a wavefront per cell (see tile_work.h).  A lane evaluates one of four
 // entries; all four lanes then take the pixel through the four in order, with the operations of the other form,
 // and add up a colour channel each.
-template <bool FINE>
+template <bool SHARED>
 __device__ __forceinline__ void blend_tile(
     BlendSpace &s, u32 tile, u32 block, const u64 *__restrict__ tile_offsets, const u32 *__restrict__ vals,
     const float4 *__restrict__ feat, const BlendParams &bp, float *__restrict__ out_rgb, float *__restrict__ out_T)
 {
-    const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    u32 tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));          // what follows from it is not kept in registers from one work to the next
+    const u32 lane = tid & (kWave - 1), wv = tid / kWave;
     const u32 tx = tile % bp.tiles_x, ty = tile / bp.tiles_x;
     // cell and pixel inside it of this lane: its group of 16 and place there, or its wavefront and group of 4
-    const u32 grp = FINE ? wv : lane >> 4, gl = FINE ? lane >> 2 : lane & 15u, own = lane & 3u;
-    const u32 quarter = FINE ? block : wv;                      // the 8x8 block
+    const u32 grp = SHARED ? wv : lane >> 4, gl = SHARED ? lane >> 2 : lane & 15u, own = lane & 3u;
+    const u32 quarter = SHARED ? block : wv;                      // the 8x8 block
     const u32 bi = (quarter & 1u) * 8u + (grp & 1u) * 4u + (gl & 3u), bj = (quarter >> 1) * 8u + (grp >> 1) * 4u + (gl >> 2);
     const u32 pxi = tx * LMK_GS_TILE + bi, pyi = ty * LMK_GS_TILE + bj;     // (bi, bj) = pixel inside the tile
     const bool inside = pxi < bp.width && pyi < bp.height;
     const float ox = (float)bi - 3.5f, oy = (float)bj - 3.5f;
     const float X0 = (float)(tx * LMK_GS_TILE) + 4.0f, Y0 = (float)(ty * LMK_GS_TILE) + 4.0f;
-    const u32 cells_shift = FINE ? wave_cells_shift(block) + (wv >> 1) * 4u + (wv & 1u) : wave_cells_shift(wv);
+    const u32 cells_shift = SHARED ? wave_cells_shift(block) + (wv >> 1) * 4u + (wv & 1u) : wave_cells_shift(wv);
     const char *geo = reinterpret_cast<const char *>(s.geo), *cop = reinterpret_cast<const char *>(s.cop);
     const char *blu = reinterpret_cast<const char *>(s.blue);
-    const char *channel = own < 2u ? cop + 8u + 4u * own : blu;             // FINE: of this lane (none for the last of the four)
+    const char *channel = own < 2u ? cop + 8u + 4u * own : blu;             // SHARED: of this lane (none for the last of the four)
 
     const u64 start = tile_offsets[tile], end = tile_offsets[tile + 1];
-    float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;           // FINE: channel `own` in cr
+    float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;           // SHARED: channel `own` in cr
     bool done = !inside;
     constexpr u32 kNullOfs = kBatch * 16u;
 
@@ -118,11 +121,12 @@ __device__ __forceinline__ void blend_tile(
                 // every thread stages one slot; slots past the end of the list reach nothing
                 const bool valid = tid < cnt;
                 const StagedEntry se = stage_entry(next.a, next.b, next.blue, X0, Y0);
-                const u32 cells = entry_cells(se, feat, [&] { return entry(base + tid); });
+                const u32 cells = valid ? entry_cells(se) : 0u;
                 s.geo[tid] = valid ? se.geo : make_float4(0.f, 0.f, 0.f, 0.f);
                 s.cop[tid] = valid ? se.cop : make_float4(0.f, -1000.0f, 0.f, 0.f);
                 s.blue[tid].x = valid ? se.blue : 0.0f;
-                s.cells[tid] = (unsigned short)(valid ? cells : 0u);
+                s.cells[tid] = (unsigned short)cells;
+                if (__builtin_expect(cells == kNoEllipse, 0)) s.cells[tid] = (unsigned short)entry_cells_any(se, feat, entry(base + tid));
             }
             __syncthreads();
             next = fetch_record(feat, index);                          // in flight during the loops below
@@ -130,7 +134,7 @@ __device__ __forceinline__ void blend_tile(
             const u64 alive = __builtin_amdgcn_ballot_w64(!done);
             if (alive == 0ull) continue;                               // this wavefront is finished
 
-            if (FINE) {
+            if (SHARED) {
                 unsigned short *my_list = s.list[wv][0];
                 const u32 n = list_cell(s.cells, cnt, cells_shift, kBatch, lane, [&](u32 rank, u32 entry) { my_list[rank] = (unsigned short)(entry * 16u); });
                 if (lane < 8u) my_list[n + lane] = (unsigned short)kNullOfs;
@@ -214,7 +218,7 @@ __device__ __forceinline__ void blend_tile(
     if (inside) {
         const size_t plane = (size_t)bp.width * bp.height;
         const size_t p = (size_t)pyi * bp.width + pxi;
-        if (FINE) {
+        if (SHARED) {
             float *dst = own == 3u ? out_T : out_rgb + own * plane;
             dst[p] = own == 3u ? T : cr + T * (own == 0u ? bp.bg0 : (own == 1u ? bp.bg1 : bp.bg2));
         } else {
@@ -226,7 +230,7 @@ __device__ __forceinline__ void blend_tile(
     }
 }
 
-// Workgroups of fine_grid(): with the caller's order the tiles with the longest lists start first, and consecutive
+// Workgroups of tile_work_grid(): with the caller's order the tiles with the longest lists start first, and consecutive
 // workgroup ids, dealt round-robin to the dies, spread them; without it each die gets one contiguous band of
 // tiles, so that neighbouring tiles share its L2.
 __global__ __launch_bounds__(kBlendThreads, 6) void blend_kernel(
@@ -236,17 +240,16 @@ __global__ __launch_bounds__(kBlendThreads, 6) void blend_kernel(
 {
     __shared__ BlendSpace space;
     TileWork w;
-    if (tile_order || bp.num_tiles <= kFineTiles) {
-        w = tile_work(bp.num_tiles, tile_order, tile_offsets, space.list[0][0]);
+    if (!tile_order && bp.num_tiles > kSharedTiles) {
+        const u32 tile = (blockIdx.x % kXcds) * bp.tiles_per_xcd + blockIdx.x / kXcds;
+        w = { blockIdx.x / kXcds < bp.tiles_per_xcd && tile < bp.num_tiles ? tile : bp.num_tiles, bp.num_tiles, 0u };
     } else {
-        w.tile = (blockIdx.x % kXcds) * bp.tiles_per_xcd + blockIdx.x / kXcds;
-        w.block = 0u;
-        w.fine = false;
-        if (blockIdx.x / kXcds >= bp.tiles_per_xcd) return;
+        w = tile_work(blockIdx.x, bp.num_tiles, tile_order, tile_offsets);
     }
-    if (w.tile >= bp.num_tiles) return;
-    if (w.fine) blend_tile<true>(space, w.tile, w.block, tile_offsets, vals, feat, bp, out_rgb, out_T);
-    else blend_tile<false>(space, w.tile, 0u, tile_offsets, vals, feat, bp, out_rgb, out_T);
+    if (w.whole < bp.num_tiles) blend_tile<false>(space, w.whole, 0u, tile_offsets, vals, feat, bp, out_rgb, out_T);
+    if (w.shared >= bp.num_tiles) return;
+    if (w.whole < bp.num_tiles) __syncthreads();                // every wavefront is past the first
+    blend_tile<true>(space, w.shared, w.share, tile_offsets, vals, feat, bp, out_rgb, out_T);
 }
 
 hipError_t launch_render(const lmk_gs_projected &proj, const lmk_gs_binned &binned, const ProjParams &pp,
@@ -257,8 +260,8 @@ hipError_t launch_render(const lmk_gs_projected &proj, const lmk_gs_binned &binn
     bp.tiles_x = pp.tiles_x; bp.num_tiles = pp.tiles_x * pp.tiles_y;
     bp.tiles_per_xcd = (bp.num_tiles + kXcds - 1) / kXcds;
     bp.bg0 = pp.cam.bg[0]; bp.bg1 = pp.cam.bg[1]; bp.bg2 = pp.cam.bg[2];
-    const bool listed = binned.tile_order || bp.num_tiles <= kFineTiles;
-    const u32 grid = listed ? fine_grid(bp.num_tiles, binned.tile_order != nullptr) : bp.tiles_per_xcd * kXcds;
+    const bool listed = binned.tile_order || bp.num_tiles <= kSharedTiles;
+    const u32 grid = listed ? tile_work_grid(bp.num_tiles, binned.tile_order != nullptr) : bp.tiles_per_xcd * kXcds;
     hipLaunchKernelGGL(blend_kernel, dim3(grid), dim3(kBlendThreads), 0, stream,
                        binned.tile_offsets, binned.tile_order, binned.vals,
                        reinterpret_cast<const float4 *>(proj.feat), bp, out_rgb, out_T);

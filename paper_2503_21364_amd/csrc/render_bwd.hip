@@ -15,7 +15,7 @@
 // lanes (row) a 4x4 cell of it.  Entries are staged in LDS in batches of 255 (slot 255 is a null
 // record that never contributes), with the cells that they can reach (entry_cells, as in blend_kernel).  Per batch
 // every wavefront puts the entries of its cells on one list per row; the pixels of a row walk that list, four
-// entries at a time.  Tiles that the image would wait for (kFineTiles) are shared by four workgroups, which take a part of
+// entries at a time.  Tiles that the image would wait for (kSharedTiles) are shared by four workgroups, which take a part of
 // the list each, see backward_tile.
 // Pass 1 repeats the forward walk with the arithmetic of blend_kernel (same expression for log2(alpha),
 // same comparisons), which gives every pixel its final transmittance and the position of its last
@@ -43,6 +43,7 @@
 
 #include "lmk_gs_internal.h"
 #include "blend_reach.h"
+#include "tile_work.h"
 
 namespace lmk {
 
@@ -156,7 +157,9 @@ __device__ __forceinline__ void backward_tile(
     const float4 *__restrict__ feat, const BwdParams &bp, const float *__restrict__ grad_rgb,
     const float *__restrict__ grad_T, float *__restrict__ grad_feat)
 {
-    const u32 tid = threadIdx.x, lane = tid & (kWave - 1);
+    u32 tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));          // what follows from it is not kept in registers from one work to the next
+    const u32 lane = tid & (kWave - 1);
     const u32 wv = (u32)__builtin_amdgcn_readfirstlane((int)(tid / kWave));     // the same for the wavefront: kept in scalar registers
     const u32 tx = tile % bp.tiles_x, ty = tile / bp.tiles_x;
     const u32 grp = lane >> 4, gl = lane & 15u;                    // 4x4 sub-block of the lane, pixel inside it
@@ -232,7 +235,9 @@ __device__ __forceinline__ void backward_tile(
             const StagedEntry se = stage_entry(next.a, next.b, PARTS ? next.blue : 0.0f, X0, Y0);
             s.geo[tid] = se.geo; s.cop[tid] = se.cop;
             if (PARTS) s.blue[tid] = se.blue;
-            s.cells[tid] = (unsigned short)entry_cells(se, feat, [&] { return next.id; });
+            const u32 cells = entry_cells(se);
+            s.cells[tid] = (unsigned short)cells;
+            if (__builtin_expect(cells == kNoEllipse, 0)) s.cells[tid] = (unsigned short)entry_cells_any(se, feat, next.id);
         } else {
             s.cells[tid] = 0;
         }
@@ -357,8 +362,10 @@ __device__ __forceinline__ void backward_tile(
             s.geo[tid] = se.geo; s.cop[tid] = se.cop; s.blue[tid] = se.blue;
             s.bc[tid] = entry_bc(next.a, next.b);
             s.id[tid] = next.id;
-            s.cells[tid] = (unsigned short)entry_cells(se, feat, [&] { return next.id; });
+            const u32 cells = entry_cells(se);
+            s.cells[tid] = (unsigned short)cells;
             if (!(fabsf(se.cop.z) + fabsf(se.cop.w) + fabsf(se.blue) < 3.0e38f)) s.odd = 1u;
+            if (__builtin_expect(cells == kNoEllipse, 0)) s.cells[tid] = (unsigned short)entry_cells_any(se, feat, next.id);
         } else {
             s.cells[tid] = 0;
         }
@@ -465,19 +472,21 @@ __device__ __forceinline__ void backward_tile(
     }
 }
 
-// Workgroups of fine_grid(): the tiles with the longest lists first, when the caller has the hint.
+// Workgroups of tile_work_grid(): the tiles with the longest lists first, when the caller has the hint.
 __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
     const u64 *__restrict__ tile_offsets, const u32 *__restrict__ tile_order, const u32 *__restrict__ vals,
     const float4 *__restrict__ feat, BwdParams bp, const float *__restrict__ grad_rgb,
     const float *__restrict__ grad_T, float *__restrict__ grad_feat)
 {
     __shared__ BwdSpace space;
-    const TileWork w = tile_work(bp.num_tiles, tile_order, tile_offsets, reinterpret_cast<unsigned short *>(space.turn));
-    if (w.tile >= bp.num_tiles) return;
+    const TileWork w = tile_work(blockIdx.x, bp.num_tiles, tile_order, tile_offsets);
     // a list of one batch has no parts
-    const bool parts = w.fine && tile_offsets[w.tile + 1] - tile_offsets[w.tile] > kBwdBatch;
-    if (parts) backward_tile<true>(space, w.tile, w.block, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
-    else if (w.block == 0u) backward_tile<false>(space, w.tile, 0u, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
+    const bool parts = w.shared < bp.num_tiles && tile_offsets[w.shared + 1] - tile_offsets[w.shared] > kBwdBatch;
+    const u32 whole = w.whole < bp.num_tiles ? w.whole : (w.shared < bp.num_tiles && !parts && w.share == 0u ? w.shared : bp.num_tiles);
+    if (whole < bp.num_tiles) backward_tile<false>(space, whole, 0u, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
+    if (!parts) return;
+    if (whole < bp.num_tiles) __syncthreads();                 // every wavefront is past the first
+    backward_tile<true>(space, w.shared, w.share, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
 }
 
 __global__ __launch_bounds__(256) void zero_kernel(float4 *__restrict__ p, size_t count4)
@@ -507,7 +516,7 @@ hipError_t launch_render_backward(const lmk_gs_projected &proj, u32 n, const lmk
     bp.tiles_x = pp.tiles_x; bp.num_tiles = pp.tiles_x * pp.tiles_y;
     bp.bg0 = pp.cam.bg[0]; bp.bg1 = pp.cam.bg[1]; bp.bg2 = pp.cam.bg[2];
     if (n == 0 || binned.capacity == 0) return hipSuccess;
-    hipLaunchKernelGGL(blend_backward_kernel, dim3(fine_grid(bp.num_tiles, binned.tile_order != nullptr)), dim3(kBwdThreads), 0, stream,
+    hipLaunchKernelGGL(blend_backward_kernel, dim3(tile_work_grid(bp.num_tiles, binned.tile_order != nullptr)), dim3(kBwdThreads), 0, stream,
                        binned.tile_offsets, binned.tile_order, binned.vals,
                        reinterpret_cast<const float4 *>(proj.feat), bp, grad_rgb, grad_T, grad_feat);
     return hipGetLastError();
