@@ -231,10 +231,8 @@ __device__ __forceinline__ void block_total(u32 cnt, u32 *s_part, u32 *__restric
     }
 }
 
-// (the wavefronts per SIMD asked for are those that the registers allowed before row_kept was part of it; at degree 1 asking
-// for six spills, and five take as long)
 template <u32 DEG>
-__global__ __launch_bounds__(kPreBlock, DEG == 0 ? 7 : 4) void preprocess_kernel(
+__global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
     const float *__restrict__ mean, const float *__restrict__ scale, const float *__restrict__ rot,
     const float *__restrict__ opacity, const float *__restrict__ sh, const float *__restrict__ cov3d, u32 n,
     ProjParams pp, ShConsts kc,
@@ -401,12 +399,15 @@ __global__ __launch_bounds__(kPreBlock, DEG == 0 ? 7 : 4) void preprocess_kernel
         while (big != 0ull) {
             const int src = (int)__builtin_ctzll(big);
             big &= big - 1ull;
-            TileTest bt;
-            bt.u = __shfl(tt.u, src, 64); bt.v = __shfl(tt.v, src, 64);
-            bt.A = __shfl(tt.A, src, 64); bt.B = __shfl(tt.B, src, 64); bt.C = __shfl(tt.C, src, 64);
-            bt.rx = __shfl(tt.rx, src, 64); bt.ry = __shfl(tt.ry, src, 64); bt.tau = __shfl(tt.tau, src, 64);
-            const u32 bx0 = __shfl(x0, src, 64), by0 = __shfl(y0, src, 64);
-            const u32 bw = __shfl(w, src, 64), barea = __shfl(area, src, 64);
+            // Degrees 0 and 1: in scalar registers.  Through __shfl they are a dozen vector registers, and with row_kept degree 1
+            // then has 88 instead of 77, five wavefronts per SIMD instead of six (3 M overview 102.3 us, so 98.5).  Beyond,
+            // the SH block in flight sets the wavefronts, and row_kept is faster on vector registers, of which an
+            // instruction takes more than one (degree 3, 400 000 splats of 1500 tiles 387 us, on scalar ones 408; degree 1
+            // 358 and 382 of a frame of 6 ms).
+            auto of_u = [&](u32 x) { return DEG < 2 ? (u32)__builtin_amdgcn_readlane((int)x, src) : __shfl(x, src, 64); };
+            auto of_f = [&](float x) { return __uint_as_float(of_u(__float_as_uint(x))); };
+            const TileTest bt = { of_f(tt.u), of_f(tt.v), of_f(tt.A), of_f(tt.B), of_f(tt.C), of_f(tt.rx), of_f(tt.ry), of_f(tt.tau) };
+            const u32 bx0 = of_u(x0), by0 = of_u(y0), bw = of_u(w), barea = of_u(area);
             u32 c = 0;
             bool k0 = false;                                  // this lane's slot of the first 64
             if (barea <= 8u * kWave) {
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(kPreBlock, DEG == 0 ? 7 : 4) void preprocess_kernel
                 // a row of tiles a lane, of which only those near the ends are asked (400 000 splats of 1500 tiles at
                 // 3840 x 2160: a frame 7240 us with 8 x 8 tiles a step, all asked, 6080 so; the line at 256, 512, 1024 tiles: 60 000
                 // at 1500 x 900 541, 534, 542 us, 5000 at 1200 x 1000 267, 259, 272)
-                const u32 bx1 = bx0 + bw, by1 = __shfl(y1, src, 64);
+                const u32 bx1 = bx0 + bw, by1 = of_u(y1);
                 const float fx = fmaxf(fabsf((float)(bx0 * LMK_GS_TILE) - bt.u), fabsf((float)(bx1 * LMK_GS_TILE) - bt.u));
                 const float fy = fmaxf(fabsf((float)(by0 * LMK_GS_TILE) - bt.v), fabsf((float)(by1 * LMK_GS_TILE) - bt.v));
                 const float slack = 2e-5f * (bt.A * fx * fx + bt.C * fy * fy);
