@@ -58,6 +58,7 @@
 #include "lds_sort.h"
 #include "lmk_gs_internal.h"
 #include "tile_test.h"
+#include "tile_work.h"
 
 namespace lmk {
 
@@ -426,9 +427,10 @@ constexpr u32 kSmallBucket = 9, kLowBucket = 11, kMidBucket = 12, kHugeBucket = 
 // Most tiles fall into a handful of buckets, and LDS atomics on one word are served one after
 // the other: every bucket has kOrderCopies counters, picked by the low lane bits, so that the 64
 // atomics of a wavefront spread over that many words.  An exclusive scan over
-// [bucket][copy] turns the counts into the first slot of every (bucket, copy).
+// [bucket][copy] turns the counts into the first slot of every (bucket, copy).  A bucket's lists that the compositing kernels
+// may share between workgroups (long_list_from) come in front of its others, so that they are the first of the order.
 constexpr u32 kScanThreads = 1024, kScanItems = 8;
-constexpr u32 kOrderCopies = 16, kOrderBuckets = 33, kOrderCounters = kOrderBuckets * kOrderCopies;
+constexpr u32 kOrderCopies = 16, kOrderBuckets = 2 * 33, kOrderCounters = kOrderBuckets * kOrderCopies;
 constexpr u32 kOrderStage = 32768;
 static_assert(kOrderCounters <= 2 * kScanThreads, "the counters are scanned two per thread");
 static_assert(kLdsTilesSmall == kScanThreads * kScanItems, "SMALL: one round of kScanItems tiles per thread");
@@ -588,6 +590,11 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
 
     // ---- (3) order and size classes.  Tile of (thread, round j): base + j * kScanThreads + tid.
     const u32 copy = tid & (kOrderCopies - 1);
+    const u64 min64 = overflow || num_tiles > kSharedMaxTiles ? 0ull : long_list_from(D);
+    const u32 min_long = min64 < 0xffffffffull ? (u32)min64 : 0xffffffffu;
+    auto order_counter = [&](u32 len) {                                 // long lists first
+        return ((32u - length_bucket(len)) * 2u + (len >= min_long ? 0u : 1u)) * kOrderCopies + copy;
+    };
     for (u32 k = tid; k < kOrderCounters; k += kScanThreads) s_cnt[k] = 0;
     __syncthreads();
     const u32 sweep = SMALL ? 1u : kScanThreads * kScanItems;
@@ -595,10 +602,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
 #pragma unroll
         for (u32 j = 0; j < kScanItems; ++j) {
             const u32 t = base + j * kScanThreads + tid;
-            if (t < num_tiles) {
-                const u32 b = length_bucket(SMALL ? mine8[j] : (overflow ? 0u : tile_count[t] + large_count[t]));
-                atomicAdd(&s_cnt[(32 - b) * kOrderCopies + copy], 1u);      // long lists first
-            }
+            if (t < num_tiles) atomicAdd(&s_cnt[order_counter(SMALL ? mine8[j] : (overflow ? 0u : tile_count[t] + large_count[t]))], 1u);
         }
     }
     __syncthreads();
@@ -621,10 +625,10 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     __syncthreads();
     if (tid == 0) {
         // tiles in buckets above a class limit = first slot of the first bucket at or below it
-        const u32 huge = s_cnt[(32 - kHugeBucket) * kOrderCopies];
-        const u32 lng = s_cnt[(32 - kMidBucket) * kOrderCopies];
-        const u32 mid = s_cnt[(32 - kLowBucket) * kOrderCopies];
-        const u32 low = s_cnt[(32 - kSmallBucket) * kOrderCopies];
+        const u32 huge = s_cnt[(32 - kHugeBucket) * 2 * kOrderCopies];
+        const u32 lng = s_cnt[(32 - kMidBucket) * 2 * kOrderCopies];
+        const u32 mid = s_cnt[(32 - kLowBucket) * 2 * kOrderCopies];
+        const u32 low = s_cnt[(32 - kSmallBucket) * 2 * kOrderCopies];
         classes[0] = huge; classes[3] = lng - huge; classes[1] = mid - lng; classes[2] = low - mid;
         s_long[0] = huge; s_long[1] = lng - huge;
     }
@@ -634,8 +638,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
         for (u32 j = 0; j < kScanItems; ++j) {
             const u32 t = base + j * kScanThreads + tid;
             if (t >= num_tiles) continue;
-            const u32 b = length_bucket(SMALL ? mine8[j] : (overflow ? 0u : tile_count[t] + large_count[t]));
-            const u32 slot = atomicAdd(&s_cnt[(32 - b) * kOrderCopies + copy], 1u);
+            const u32 slot = atomicAdd(&s_cnt[order_counter(SMALL ? mine8[j] : (overflow ? 0u : tile_count[t] + large_count[t]))], 1u);
             if (staged) {
                 s_order[slot] = t;
             } else {

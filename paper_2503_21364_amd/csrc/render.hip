@@ -247,9 +247,7 @@ __global__ __launch_bounds__(kBlendThreads, 6) void blend_kernel(
         w = tile_work(blockIdx.x, bp.num_tiles, tile_order, tile_offsets);
     }
     if (w.whole < bp.num_tiles) blend_tile<false>(space, w.whole, 0u, tile_offsets, vals, feat, bp, out_rgb, out_T);
-    if (w.shared >= bp.num_tiles) return;
-    if (w.whole < bp.num_tiles) __syncthreads();                // every wavefront is past the first
-    blend_tile<true>(space, w.shared, w.share, tile_offsets, vals, feat, bp, out_rgb, out_T);
+    else if (w.shared < bp.num_tiles) blend_tile<true>(space, w.shared, w.share, tile_offsets, vals, feat, bp, out_rgb, out_T);
 }
 
 hipError_t launch_render(const lmk_gs_projected &proj, const lmk_gs_binned &binned, const ProjParams &pp,

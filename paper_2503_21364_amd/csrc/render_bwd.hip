@@ -480,13 +480,13 @@ __global__ __launch_bounds__(kBwdThreads, 4) void blend_backward_kernel(
 {
     __shared__ BwdSpace space;
     const TileWork w = tile_work(blockIdx.x, bp.num_tiles, tile_order, tile_offsets);
+    if (w.shared < bp.num_tiles && tile_offsets[w.shared + 1] - tile_offsets[w.shared] > kBwdBatch) {
+        backward_tile<true>(space, w.shared, w.share, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
+        return;
+    }
     // a list of one batch has no parts
-    const bool parts = w.shared < bp.num_tiles && tile_offsets[w.shared + 1] - tile_offsets[w.shared] > kBwdBatch;
-    const u32 whole = w.whole < bp.num_tiles ? w.whole : (w.shared < bp.num_tiles && !parts && w.share == 0u ? w.shared : bp.num_tiles);
+    const u32 whole = w.shared < bp.num_tiles && w.share == 0u ? w.shared : w.whole;
     if (whole < bp.num_tiles) backward_tile<false>(space, whole, 0u, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
-    if (!parts) return;
-    if (whole < bp.num_tiles) __syncthreads();                 // every wavefront is past the first
-    backward_tile<true>(space, w.shared, w.share, tile_offsets, vals, feat, bp, grad_rgb, grad_T, grad_feat);
 }
 
 __global__ __launch_bounds__(256) void zero_kernel(float4 *__restrict__ p, size_t count4)

@@ -5,50 +5,47 @@
 // 8x8 block, a wavefront per 4x4 cell, four lanes a pixel with an entry each; of the gradient a part of the list.  Either way
 // takes about twice the vector instructions, so that it is the better one only where the image would wait:
 //  * images of up to kSharedTiles tiles: all tiles;
-//  * of up to kSharedMaxTiles, with the caller's order by list length: those of the first kSharedPlaces places whose list
-//    has a 1 / kSharedPairs of the frame's pairs, if there is room for three helpers each (below);
+//  * of up to kSharedMaxTiles, with the caller's order by list length: those whose list has a 1 / kSharedPairs of the
+//    frame's pairs (no more than kSharedPairs tiles have, and they are the first of the order);
 //  * else none (a 3 M overview at 1080p has no such list among 8160).
-// The helpers are the workgroups of the shortest lists, which take their share when their own tile is done, and idle ones that
-// make up the number in images of fewer tiles; a place has helpers always in images of up to kSharedHelpers tiles.  Workgroups for
-// every share that there might be cost 2 to 5 us where these are not; working out beforehand, in every workgroup, how many
-// tiles are shared cost 3 (30 000 primitives at 640 x 480: 27.8 us unshared, 31.6 so, 28.1 with the helpers).  Helpers have to be
-// short of work: if the longest helper's list has a 1 / (4 kSharedPairs) of the pairs or less all places are served; else only those
-// with idle helpers are, and only where the list is twice as long as the first that goes without, as the image would wait
-// for that one all the same (200 000 evenly in a cube, 414 tiles, training step: 297 us without this line, 279 with it or unshared).
-// A tile's workgroups decide from a few places of the order, all alike; which they are is the same for all.  The shares of a tile are a
-// multiple of the eight dies apart, so that they read the same records through one L2.
+// Every workgroup looks at a few places of the order to see how many first places hold all the long lists, rounded up; four
+// workgroups of each of these come first, then the other places, then idle ones for the shares that this image does not have.
+// The shares of a tile are on one die, so that they read the same records through one L2, and on different compute units of it.
+// What the looks cost, and the idle workgroups, is 1 us where no list is long.
 //
-// Measured, us, compositing and its gradient, every tile whole / so: 30 000 primitives at 333 x 217 43, 140 / 27, 96; 1 M in
-// clusters, 400 x 300, 291, 1184 / 148, 685, 800 x 600 176, 663 / 122, 463; 200 000 evenly in a cube, 256 x 256, 57, 199 / 49, 144, 400 x 300
-// 49, 165 / 46, 149, 800 x 600 38, 142 / 36, 133 (of these last the lists are not shared: other steps).
+// Measured, us, compositing, every tile whole / so: 30 011 primitives at 640 x 480 27.8 / 28; 333 x 217 43 / 27; clusters at 400 x 300,
+// 1 M, 291 / 150; 10 000 at 256 x 256, a frame, all shares of a tile on one compute unit 73.0, so 65.7.
 #ifndef LMK_GS_TILE_WORK_H
 #define LMK_GS_TILE_WORK_H
 #include "lmk_gs_internal.h"
 
 namespace lmk {
 
-constexpr u32 kSharedTiles = 256, kSharedMaxTiles = 2048, kSharedPairs = 256, kSharedPlaces = 128;
-constexpr u32 kSharedHelpers = 3u * kSharedPlaces;
-static_assert(kSharedPlaces % 8u == 0u && 2u * kSharedPlaces <= kSharedTiles, "the places lie in the longer half of the order");
+constexpr u32 kSharedTiles = 256, kSharedMaxTiles = 2048, kSharedPairs = 256;
+static_assert(kSharedPairs <= kSharedTiles, "every image with an order has as many places");
 
-__host__ __device__ __forceinline__ u32 order_half(u32 num_tiles) { return ((num_tiles + 15u) >> 4) * 8u; }
-__host__ __device__ __forceinline__ u32 idle_helpers(u32 num_tiles)
+// the shortest list that has a 1 / kSharedPairs of them
+__host__ __device__ __forceinline__ u64 long_list_from(u64 pairs) { return (pairs + (kSharedPairs - 1u)) / kSharedPairs; }
+
+// Which of `apart` places, a multiple of eight, workgroup `b` of share `share` of them takes.  Workgroups go to the dies in turn, and on
+// a die to its 32 compute units: a quarter of the places further with each share, so that the shares of a tile are on four
+// of these.
+__host__ __device__ __forceinline__ u32 shared_place(u32 b, u32 share, u32 apart)
 {
-    const u32 half = order_half(num_tiles);
-    if (num_tiles <= kSharedHelpers) return kSharedHelpers;
-    return half < kSharedHelpers ? kSharedHelpers - half : 0u;
+    const u32 groups = apart >> 3, turned = (b >> 3) + groups - share * ((groups + 3u) >> 2) % groups;
+    return (turned < groups ? turned : turned - groups) * 8u + (b & 7u);
 }
 
 // number of workgroups
 __host__ __device__ __forceinline__ u32 tile_work_grid(u32 num_tiles, bool ordered)
 {
     if (num_tiles <= kSharedTiles) return 4u * ((num_tiles + 7u) & ~7u);
-    return ordered && num_tiles <= kSharedMaxTiles ? 2u * order_half(num_tiles) + idle_helpers(num_tiles) : num_tiles;
+    return ordered && num_tiles <= kSharedMaxTiles ? num_tiles + 3u * kSharedPairs : num_tiles;
 }
 
-// what workgroup `b` of them takes: a whole tile, then one of the four shares of another; num_tiles: none
+// what workgroup `b` of them takes: a whole tile, or a share of one; num_tiles: none
 struct TileWork { u32 whole, shared, share; };
-__host__ __device__ __forceinline__ TileWork tile_work(u32 b, u32 num_tiles, const u32 *__restrict__ tile_order,
+__device__ __forceinline__ TileWork tile_work(u32 b, u32 num_tiles, const u32 *__restrict__ tile_order,
                                                        const u64 *__restrict__ tile_offsets)
 {
     auto at = [&](u32 place) {                                          // num_tiles for a corrupt hint too
@@ -57,28 +54,29 @@ __host__ __device__ __forceinline__ TileWork tile_work(u32 b, u32 num_tiles, con
     };
     if (num_tiles <= kSharedTiles) {
         const u32 apart = (num_tiles + 7u) & ~7u, share = b / apart;
-        return { num_tiles, at(b - share * apart), share };
+        return { num_tiles, at(shared_place(b - share * apart, share, apart)), share };
     }
     if (!tile_order || num_tiles > kSharedMaxTiles) return { at(b), num_tiles, 0u };
-    // workgroups: the longer half of the places, the idle helpers, the shorter half.  Helpers: the idle ones, then from the
-    // last place on (by eights, in their order)
-    const u32 half = order_half(num_tiles), idle = idle_helpers(num_tiles);
-    auto from_end = [&](u32 i) { return half - 8u - (i & ~7u) + (i & 7u); };
-    auto length = [&](u32 t) { return t < num_tiles ? tile_offsets[t + 1] - tile_offsets[t] : 0ull; };
-    const bool longer = b < half, own = longer || b >= half + idle;
-    const u32 place = longer ? b : b - idle;
-    const u32 helper = longer ? kSharedHelpers : (own ? idle + from_end(b - half - idle) : b - half);
-    const u32 of = longer ? place : (helper < kSharedHelpers ? helper / 24u * 8u + (helper & 7u) : kSharedPlaces);
-    u32 shared = num_tiles;
-    if (of < kSharedPlaces) {
-        const u32 served = idle / 24u * 8u;                             // places with idle helpers
-        const u32 t = at(of), next = at(served);
-        const u32 longest = idle < kSharedHelpers ? at(half + from_end(kSharedHelpers - 1u - idle)) : num_tiles;
-        const u64 len = length(t), pairs = tile_offsets[num_tiles];
-        const bool room = length(longest) * (4u * kSharedPairs) <= pairs || (of < served && len >= 2u * length(next));
-        if (len * kSharedPairs >= pairs && room) shared = t;
+    const u64 min_long = long_list_from(tile_offsets[num_tiles]);
+    auto is_long = [&](u32 t) { return tile_offsets[t + 1] - tile_offsets[t] >= min_long; };
+    // two trips to memory for all of them: without the barrier the compiler waits for each length by itself
+    constexpr u32 kLooks = 6, look[kLooks + 1] = { 0u, 16u, 32u, 64u, 128u, 192u, 256u };
+    static_assert(look[kLooks] == kSharedPairs, "room for all long lists, and the grid has a workgroup for each of their shares");
+    u64 from[kLooks], to[kLooks];
+#pragma unroll
+    for (u32 k = 0; k < kLooks; ++k) {
+        u32 t = tile_order[look[k]];
+        t = t < num_tiles ? t : num_tiles - 1u;
+        from[k] = tile_offsets[t]; to[k] = tile_offsets[t + 1];
     }
-    return { own && !(longer && shared < num_tiles) ? at(place) : num_tiles, shared, longer ? 0u : 1u + (helper >> 3) % 3u };
+    __builtin_amdgcn_sched_barrier(0);
+    u32 places = 0;
+#pragma unroll
+    for (u32 k = 0; k < kLooks; ++k) places = to[k] - from[k] >= min_long ? look[k + 1] : places;
+    if (b >= 4u * places) return { at(b - 3u * places), num_tiles, 0u };
+    const u32 share = b / places, t = at(shared_place(b - share * places, share, places));
+    if (t < num_tiles && is_long(t)) return { num_tiles, t, share };
+    return { share == 0u ? t : num_tiles, num_tiles, 0u };
 }
 
 }  // namespace lmk

@@ -39,3 +39,4 @@ static inline uint32_t __builtin_amdgcn_mbcnt_hi(uint32_t, uint32_t) { return 0;
 static inline int __builtin_amdgcn_update_dpp(int, int, int, int, int, bool) { return 0; }
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
 #define __builtin_amdgcn_wave_barrier() ((void)0)
+#define __builtin_amdgcn_sched_barrier(mask) ((void)0)
