@@ -43,10 +43,11 @@ __host__ __device__ __forceinline__ u32 tile_work_grid(u32 num_tiles, bool order
     return ordered && num_tiles <= kSharedMaxTiles ? num_tiles + 3u * kSharedPairs : num_tiles;
 }
 
-// what workgroup `b` of them takes: a whole tile, or a share of one; num_tiles: none
+// what workgroup `b` of them takes: a whole tile, or a share of one; num_tiles: none.  In images of more than kSharedTiles tiles none is
+// shared if more than `most` lists are long.
 struct TileWork { u32 whole, shared, share; };
 __device__ __forceinline__ TileWork tile_work(u32 b, u32 num_tiles, const u32 *__restrict__ tile_order,
-                                                       const u64 *__restrict__ tile_offsets)
+                                              const u64 *__restrict__ tile_offsets, u32 most = kSharedPairs)
 {
     auto at = [&](u32 place) {                                          // num_tiles for a corrupt hint too
         const u32 t = place < num_tiles ? (tile_order ? tile_order[place] : place) : num_tiles;
@@ -73,6 +74,7 @@ __device__ __forceinline__ TileWork tile_work(u32 b, u32 num_tiles, const u32 *_
     u32 places = 0;
 #pragma unroll
     for (u32 k = 0; k < kLooks; ++k) places = to[k] - from[k] >= min_long ? look[k + 1] : places;
+    if (places > most) places = 0u;
     if (b >= 4u * places) return { at(b - 3u * places), num_tiles, 0u };
     const u32 share = b / places, t = at(shared_place(b - share * places, share, places));
     if (t < num_tiles && is_long(t)) return { num_tiles, t, share };

@@ -117,7 +117,7 @@ static int rows(uint64_t count)
 }
 
 // every tile whole by one workgroup, or its four shares by one each, these on one die; shared are exactly the long lists
-static int work(u32 tiles, int kind, bool ordered, bool all_bad)
+static int work(u32 tiles, int kind, bool ordered, bool all_bad, u32 most)
 {
     std::vector<u64> len(tiles), offsets(tiles + 1, 0);
     for (u32 t = 0; t < tiles; ++t) {
@@ -135,7 +135,7 @@ static int work(u32 tiles, int kind, bool ordered, bool all_bad)
     std::vector<u32> whole(tiles, 0), shares(tiles, 0), die(tiles, 8);
     int bad = 0, shared = 0;
     for (u32 b = 0; b < tile_work_grid(tiles, ordered); ++b) {
-        const TileWork w = tile_work(b, tiles, ordered ? order.data() : nullptr, offsets.data());
+        const TileWork w = tile_work(b, tiles, ordered ? order.data() : nullptr, offsets.data(), most);
         if (w.whole > tiles || w.shared > tiles || w.share > 3u) { ++bad; continue; }
         if (w.whole < tiles) ++whole[w.whole];
         if (w.shared < tiles) {
@@ -145,11 +145,13 @@ static int work(u32 tiles, int kind, bool ordered, bool all_bad)
             bad += die[w.shared] != b % 8;
         }
     }
+    u32 longs = 0;
+    for (u32 t = 0; t < tiles; ++t) longs += len[t] >= long_list_from(offsets[tiles]) ? 1u : 0u;
     const bool by_length = ordered && !all_bad && tiles > kSharedTiles && tiles <= kSharedMaxTiles && offsets[tiles] != 0u;
     for (u32 t = 0; t < tiles; ++t) {
         const bool one = (whole[t] == 1 && shares[t] == 0) || (whole[t] == 0 && shares[t] == 15);
         bad += all_bad && ordered ? (whole[t] || shares[t]) : !one;
-        if (by_length) bad += (shares[t] == 15) != (len[t] >= long_list_from(offsets[tiles]));
+        if (by_length) bad += (shares[t] == 15) != (longs <= most && len[t] >= long_list_from(offsets[tiles]));
         shared += shares[t] == 15;
     }
     if (bad) printf("work: %u tiles, lists %d, ordered %d: %d wrong, %d shared\n", tiles, kind, (int)ordered, bad, shared);
@@ -164,7 +166,8 @@ int main()
                        769u, 770u, 783u, 1200u, 1900u, 2047u, 2048u, 2049u, 8160u })
         for (int kind = 0; kind < 5; ++kind)
             for (int ordered = 0; ordered < 2; ++ordered)
-                for (int all_bad = 0; all_bad < 2; ++all_bad, ++runs) bad += work(tiles, kind, ordered != 0, all_bad != 0);
+                for (int all_bad = 0; all_bad < 2; ++all_bad)
+                    for (u32 most : { 128u, 256u }) { ++runs; bad += work(tiles, kind, ordered != 0, all_bad != 0, most); }
     printf("work: %d grids\nheaders driver %s\n", runs, bad ? "FAILED" : "done");
     return bad ? 1 : 0;
 }
