@@ -13,8 +13,9 @@
 // The shares of a tile are on one die, so that they read the same records through one L2, and on different compute units of it.
 // What the looks cost, and the idle workgroups, is 1 us where no list is long.
 //
-// Measured, us, compositing, every tile whole / so: 30 011 primitives at 640 x 480 27.8 / 28; 333 x 217 43 / 27; clusters at 400 x 300,
-// 1 M, 291 / 150; 10 000 at 256 x 256, a frame, all shares of a tile on one compute unit 73.0, so 65.7.
+// Measured, us, compositing, every tile whole / so: 30 011 primitives at 640 x 480 28.6 / 29.7, at 333 x 217 43 / 25; 1 M in clusters at
+// 400 x 300 236 / 160; 3 M of a city at 400 x 300 130 / 67; 10 000 at 256 x 256, a frame, all shares of a tile on one compute
+// unit 73.0, so 65.7.
 #ifndef LMK_GS_TILE_WORK_H
 #define LMK_GS_TILE_WORK_H
 #include "lmk_gs_internal.h"
