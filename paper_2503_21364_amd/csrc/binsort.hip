@@ -24,26 +24,21 @@
 //            frame sit in a few workgroups; the list spreads them over the whole chip.
 //   scan     one workgroup: the capacity check, exclusive prefix sum of the per-tile counts = the
 //            per-tile ranges, a running position per tile for the listed primitives, the tiles by
-//            descending list length with the size classes and the chunk list of the per-tile
-//            sort; it leaves the counters zero.
+//            descending list length with the size classes of the per-tile sort.
 //   emit     the same walks again.  A workgroup sets its LDS counters to range start + run start
 //            for the tiles of its list and hands out positions from them.  A listed primitive
 //            advances the tile's running position pair by pair, again with lane-consecutive
 //            atomics, eight steps in flight.  What is written is the composite the list is
 //            ordered by, depth bits << 32 | index.
 //   tile sort  every tile's slice is sorted by that composite and rewritten in its final form (key = tile <<
-//            32 | depth bits, value = index): 512 threads for lists of up to 4096 pairs, 256 up to 2048, one
-//            wavefront up to 512 (the two smaller classes in one launch).  The pairs go to buckets of
+//            32 | depth bits, value = index), in two launches: lists beyond 4096 pairs by 1024 threads with all the LDS
+//            of a compute unit; the others by 512 threads, or by one wavefront up to 512 pairs.  The pairs go to buckets of
 //            equal depth steps in LDS, one or two in each, and are ranked inside them; where the buckets get
-//            too full (equal depths, dense clusters) the list goes through a merge sort instead.  A
-//            list of up to 16384 pairs is cut into 4096-pair chunks, sorted by workgroups of the 512-thread
-//            launch and merged in two rounds between the two pair buffers, by workgroups of the 256-thread
-//            launch and by a launch of wavefronts.  Lists beyond that get a workgroup of 1024 threads each:
-//            16384-pair chunks merge-sorted in LDS, then pairwise merges through LDS-staged windows.
+//            too full (equal depths, dense clusters) the list goes through a merge sort instead.  Lists beyond 16384
+//            pairs are merge-sorted in chunks of that many, then merged pairwise between the two pair buffers.
 //
-// Frames of many pairs per primitive are put together in another way (binsort_dense.h), in the same launches:
-// where the buffers could hold such a frame, count, the count of large rectangles and the last sort launch
-// carry both ways and pick by D.
+// Frames of many pairs per primitive are put together in another way (binsort_dense.h): where the buffers could hold such a
+// frame, count and the count of large rectangles carry both ways and pick by D, and a last launch writes its lists.
 //
 // Integer work, bound by HBM traffic, global atomic throughput and, in the per-tile sorts, by
 // LDS bandwidth and vector issue.  Atomics on one address are served one after the other (about
@@ -398,25 +393,22 @@ __global__ __launch_bounds__(kLargeThreads) void count_large_kernel(
 // status, and every list is treated as empty from here on.  Workgroup 0: (2) tile_offsets =
 // exclusive prefix sum of the counts.  Workgroup 1: (3) tile ids by descending list length, bucketed by the bit length of (length - 1), so that
 // the size classes of the per-tile sort are whole buckets.  From the front of `order`:
-//   classes[0]  lists longer than kHuge pairs          one workgroup each, merges between the pair buffers
-//   classes[3]  kMid + 1 .. kHuge ("long")             cut into chunks of kMid pairs, see below
-//   classes[1]  kLow + 1 .. kMid                       one workgroup of 512
-//   classes[2]  kSmallCap + 1 .. kLow                  one workgroup of 256
+//   classes[0]  lists longer than kHuge pairs          one workgroup of 1024 each, merges between the pair buffers
+//   classes[3]  kMid + 1 .. kHuge ("long")             one workgroup of 1024
+//   classes[1]  kLow + 1 .. kMid                       one workgroup of 512, eight pairs a thread
+//   classes[2]  kSmallCap + 1 .. kLow                  one workgroup of 512, four pairs a thread
 //   the rest                                           one wavefront each
 // Within a bucket the order is whatever the atomics give -- it only decides which workgroup
-// starts first, never a result.  A long list is sorted as 2 .. 4 chunks by workgroups of the
-// 512-thread kernel and merged in two rounds by workgroups of the next two kernels, so that it
-// costs no kernel of its own: chunk_list = (tile, chunk) of every such chunk, classes[4] = how many.
-// The counters stay as they are until both workgroups are done with them; the first kernel of the
+// starts first, never a result.  The counters stay as they are until both workgroups are done with them; the last kernel of the
 // per-tile sort leaves them zero for the next call.
 // With SMALL (up to 8192 tiles) every thread reads its eight counters once and everything else works
 // from registers and LDS.
 //   classes[5]  (kDenseClass) 1 = the frame's lists come from dense_emit, sorted: nothing is emitted or sorted here
 constexpr u32 kSmallThreads = 64, kSmallItems = 8, kSmallCap = kSmallThreads * kSmallItems;   // 512
-constexpr u32 kLowThreads = 256, kLowItems = 8;                                               // 2048
+constexpr u32 kLow = 2048;                                                                    // kMidThreads * kMidItems / 2
 constexpr u32 kMidThreads = 512, kMidItems = 8, kMid = kMidThreads * kMidItems;               // 4096
 constexpr u32 kHugeThreads = 1024, kHugeItems = 16, kHuge = kHugeThreads * kHugeItems;        // 16384
-static_assert(kMid == kChunk, "the launch bounds on the host use kChunk");
+constexpr u32 kLongBlocks = 256;                            // compute units
 
 __device__ __forceinline__ u32 length_bucket(u32 len)
 {
@@ -439,8 +431,7 @@ template <bool SMALL>
 __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     const u32 *__restrict__ tile_count, const u32 *__restrict__ large_count, u32 num_tiles, u64 capacity, ScratchHeader *__restrict__ header,
     u64 *__restrict__ tile_offsets, u32 *__restrict__ tile_cursor, u64 *__restrict__ prim_offsets_if_empty,
-    u32 *__restrict__ order, u32 *__restrict__ order_copy, u32 *__restrict__ classes,
-    uint2 *__restrict__ chunk_list, u64 chunk_capacity, u64 dense_min)
+    u32 *__restrict__ order, u32 *__restrict__ order_copy, u32 *__restrict__ classes, u64 dense_min)
 {
     constexpr u32 kWaves = kScanThreads / kWave;
     // the running positions of the emit kernel are 32 bits wide: absolute where every position
@@ -448,13 +439,12 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     const bool wide = capacity > 0xffffffffull;
     __shared__ u64 s_sum[kWaves];
     __shared__ u32 s_cnt[kOrderCounters];
-    __shared__ u32 s_long[2];                  // first long tile in `order`, number of long tiles
     __shared__ u32 s_wave[kWaves];
     // slots are scattered and one compute unit does all the address work: the order is put
     // together in LDS and written out in whole lines (images of up to kOrderStage tiles)
     __shared__ __attribute__((aligned(16))) u32 s_space[SMALL ? 2 * kLdsTilesSmall : kOrderStage];
     u32 *const s_order = s_space;
-    u32 *const s_len = s_space + (SMALL ? kLdsTilesSmall : 0u);     // SMALL: the list lengths, for the chunk list
+    u32 *const s_len = s_space + (SMALL ? kLdsTilesSmall : 0u);     // SMALL: the list lengths
     const bool staged = SMALL || num_tiles <= kOrderStage;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
 
@@ -482,8 +472,8 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
 #pragma unroll
     for (u32 k = 0; k < kWaves; ++k) D += s_sum[k];
     const bool overflow = D > capacity;
-    // two workgroups share the work: 0 writes D, the status and the ranges, 1 the order, the size
-    // classes and the chunk list; both need the list lengths and D
+    // two workgroups share the work: 0 writes D, the status and the ranges, 1 the order and the size
+    // classes; both need the list lengths and D
     const bool ranges_part = blockIdx.x == 0;
     if (tid == 0 && ranges_part) {
         classes[kDenseClass] = dense_min != ~0ull && header->dup_count >= dense_min ? 1u : 0u;   // as the counting kernels decided
@@ -630,9 +620,8 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
         const u32 mid = s_cnt[(32 - kLowBucket) * 2 * kOrderCopies];
         const u32 low = s_cnt[(32 - kSmallBucket) * 2 * kOrderCopies];
         classes[0] = huge; classes[3] = lng - huge; classes[1] = mid - lng; classes[2] = low - mid;
-        s_long[0] = huge; s_long[1] = lng - huge;
     }
-    __syncthreads();
+    __syncthreads();                           // the counters are advanced below
     for (u32 base = 0; base < (SMALL ? 1u : num_tiles); base += sweep) {
 #pragma unroll
         for (u32 j = 0; j < kScanItems; ++j) {
@@ -654,42 +643,8 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
             order[k] = t;
             if (order_copy) order_copy[k] = t;
         }
-    } else {
-        __threadfence_block();                 // this workgroup reads its own writes of `order` below
-        __syncthreads();
     }
-    // the chunks of the long lists: an exclusive scan of their chunk counts places the entries
-    const u32 long_first = s_long[0], long_count = s_long[1];
-    u32 chunk_carry = 0;
-    for (u32 base = 0; base < long_count; base += kScanThreads) {
-        const u32 k = base + tid;
-        u32 tile = 0, nch = 0;
-        if (k < long_count) {
-            tile = staged ? s_order[long_first + k] : order[long_first + k];
-            if (tile < num_tiles) nch = ((SMALL ? s_len[tile] : tile_count[tile] + large_count[tile]) + kMid - 1) / kMid;
-        }
-        u32 inc = nch;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const u32 v = __shfl_up(inc, o, 64);
-            if ((int)lane >= o) inc += v;
-        }
-        __syncthreads();                       // s_wave free again
-        if (lane == kWave - 1) s_wave[wv] = inc;
-        __syncthreads();
-        u32 bef = chunk_carry, total = chunk_carry;
-        for (u32 w = 0; w < kWaves; ++w) {
-            const u32 c = s_wave[w];
-            if (w < wv) bef += c;
-            total += c;
-        }
-        const u32 at = bef + inc - nch;
-        for (u32 c = 0; c < nch; ++c)
-            if ((u64)at + c < chunk_capacity) chunk_list[at + c] = make_uint2(tile, c);
-        chunk_carry = total;
-    }
-    if (tid == 0) classes[4] = (u64)chunk_carry < chunk_capacity ? chunk_carry : (u32)chunk_capacity;
-    // the counters are left as they are: the other workgroup may still be reading them; the first
+    // the counters are left as they are: the other workgroup may still be reading them; the last
     // kernel of the per-tile sort zeroes them
 }
 
@@ -834,22 +789,24 @@ __device__ __forceinline__ void sort_pairs_in_lds(u64 *keys, u32 *vals, u64 beg,
 // The same result for up to THREADS * ITEMS pairs with one counting step instead of the merge rounds: the
 // composites go to buckets by depth, equal steps between the list's smallest and largest, as many buckets
 // as pairs fit; a bucket holds one or two of them, and the place of a pair in its
-// bucket is the number of smaller ones there.  Some 60 vector instructions and a dozen LDS accesses a pair
-// where the merge sort takes 300 and 25.  1080p, 3 M primitives, 4.9 M pairs: lists of 2049 to 4096 pairs and
-// chunks 42 -> 24 us, of 513 to 2048 35 -> 22 us.  Equal steps of the depth's bits instead of the depth
+// bucket is the number of smaller ones there.  Equal steps of the depth's bits instead of the depth
 // (steps of equal ratio) crowd what is far into few buckets: inside a scene half of the long lists then
 // fell back.
 //
 // What the buckets cost beyond that is the ranking, by the size of a pair's bucket on average over the pairs:
-// lists of clusters of one size are even with the merge sort, less the try, at 7 (64 threads), 18 (256) and 22
+// lists of clusters of one size are even with the merge sort, less the try, at 7 (64 threads) and 22
 // (512), and one large bucket holds up its wavefront.  Beyond these limits (a surface in front of a far background,
 // equal depths) the list is left to the merge sort: returns false, nothing written.  Lists that are far beyond
 // show it in a quarter of their pairs, or in their depths being one, and leave before the rest is counted.
-// Stage 2 of 1024 lists of 3500 pairs: evenly spread 133 us (merge sort alone 154), a thin surface before a far
-// background 158 (170 without the early leave); of 1500 pairs 76 (86), 88 (96); of 450 pairs 47 (49), 50 (54).
 // Called by the whole team (a workgroup, or one wavefront); cnt holds THREADS * ITEMS / 2 words, two 16-bit counters each.
+//
+// Bound by vector issue (half of the time of all lists together) and the latency of a list's steps; one list of 16 000 pairs
+// evenly spread takes 15 us on its compute unit, in crowded buckets (15 a pair) 31, by merging 53.  So lanes talk by DPP, an atomic
+// that counts also gives the pair its place in the bucket, and offsets are 32 bits wide behind a scalar base: 11.2 M -> 8.4 M
+// vector instructions for the lists of up to 4096 of a 3 M overview, 35.8 -> 31.2 us; 500 000 in a cube 26.2 -> 22.6 us.
+// Four pairs of a thread ranked side by side with their buckets' first three read at once: no faster.
 template <u32 THREADS> struct BucketLimits {
-    static constexpr u32 kMean = THREADS == 64u ? 7u : (THREADS == 256u ? 18u : 22u);
+    static constexpr u32 kMean = THREADS == 64u ? 7u : 22u;
     static constexpr u32 kMax = THREADS == 64u ? 24u : 64u;
     static constexpr u32 kProbeMax = THREADS == 64u ? 12u : 24u;     // in a quarter of the list
 };
@@ -859,36 +816,34 @@ __device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg,
 {
     constexpr u32 CAP = THREADS * ITEMS, kWords = ITEMS / 2, kWaves = THREADS / kWave;
     constexpr u32 kProbe = ITEMS < 4u ? 1u : ITEMS / 4u;
-    // a thread's share of the sum of squares is clamped, so that it and the count fit one word
-    constexpr u32 kCountBits = 13, kShareMax = 1000;
     using Limits = BucketLimits<THREADS>;
-    static_assert(CAP < (1u << kCountBits) && THREADS * kShareMax < (1u << (32 - kCountBits)), "one word");
     static_assert(CAP < 65536u && ITEMS % 2u == 0u, "positions are 16 bits wide, two to a word");
+    static_assert(CAP * Limits::kMax < (1u << 31), "the sum of the places fits a word");
     const u32 tid = team_thread<THREADS>(), lane = tid & (kWave - 1), wv = tid / kWave;
+    char *const list = reinterpret_cast<char *>(keys + beg), *const indices = reinterpret_cast<char *>(vals + beg);
     u64 e[ITEMS];
-    u32 lo = ~0u, hi = 0u;
 #pragma unroll
-    for (u32 k = 0; k < ITEMS; ++k) {
+    for (u32 k = 0; k < ITEMS; ++k) {                           // beyond the end its last pair again
         const u32 p = k * THREADS + tid;
-        e[k] = p < n ? keys[beg + p] : 0ull;
-    }
-#pragma unroll
-    for (u32 k = 0; k < ITEMS; ++k) {
-        const u32 d = (u32)(e[k] >> 32);
-        if (k * THREADS + tid < n) { lo = d < lo ? d : lo; hi = d > hi ? d : hi; }
+        e[k] = *reinterpret_cast<const u64 *>(list + (p < n ? p : n - 1u) * 8u);
     }
 #pragma unroll
     for (u32 k = 0; k < kWords; ++k) cnt[k * THREADS + tid] = 0;
+    u32 lo = ~0u, hi = 0u;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const u32 a = __shfl_xor(lo, o, 64), b = __shfl_xor(hi, o, 64);
-        lo = a < lo ? a : lo; hi = b > hi ? b : hi;
+    for (u32 k = 0; k < ITEMS; ++k) {
+        const u32 d = (u32)(e[k] >> 32);
+        lo = d < lo ? d : lo; hi = d > hi ? d : hi;
     }
-    u32 *part = reinterpret_cast<u32 *>(s), *flag = part + 2u * kWaves;     // free until the scatter
+    lo = wave_min(lo); hi = wave_max(hi);
+    // of the wavefronts: depths, sums of the places, sums of the counts; free until the scatter
+    u32 *const part = reinterpret_cast<u32 *>(s), *const places = part + 2u * kWaves, *const counts = places + kWaves, *const flag = counts + kWaves;
     if (kWaves > 1u) {
         if (tid < 2u) flag[tid] = 0u;
         if (lane == 0) { part[2 * wv] = lo; part[2 * wv + 1] = hi; }
-        team_sync<THREADS>();
+    }
+    team_sync<THREADS>();                                        // also: the counters are clear
+    if (kWaves > 1u) {
 #pragma unroll
         for (u32 k = 0; k < kWaves; ++k) {
             const u32 a = part[2 * k], b = part[2 * k + 1];
@@ -897,95 +852,83 @@ __device__ __forceinline__ bool bucket_sort_pairs(u64 *keys, u32 *vals, u64 beg,
     }
     // equal steps of the depth itself (positive, so its bits order alike): a pixel column holds more of what
     // is far.  A difference, a product with a positive constant and a conversion are all monotone, which is
-    // all that is needed; an infinite depth is left to the merge sort.
+    // all that is needed; an infinite depth is left to the merge sort.  The last counter stays free: it ends the bucket before.
     const float z0 = __uint_as_float(lo), z1 = __uint_as_float(hi);
     const float scale = z1 > z0 ? (float)CAP / (z1 - z0) : 0.0f;
     if (!(z1 < 3.0e38f) || scale == 0.0f || !(scale < 3.0e38f)) return false;         // the same for the whole team
     auto bucket = [&](u64 c) -> u32 {
-        return (u32)fminf((__uint_as_float((u32)(c >> 32)) - z0) * scale, (float)(CAP - 1u));     // NaN: the last one
+        return (u32)fminf((__uint_as_float((u32)(c >> 32)) - z0) * scale, (float)(CAP - 2u));     // NaN: the last one
     };
-    team_sync<THREADS>();                                        // counters clear, `part` read
-    bool over = false;
-#pragma unroll
-    for (u32 k = 0; k < kProbe; ++k) {
+    u32 at[ITEMS], most = 0, sum = 0;                           // at: bucket, and above it the place in the bucket, in order of arrival
+    auto count = [&](u32 k) {
+        at[k] = 0;
         if (k * THREADS + tid < n) {
             const u32 b = bucket(e[k]), sh = (b & 1u) * 16u;
-            over = over || ((atomicAdd(&cnt[b >> 1], 1u << sh) >> sh) & 0xffffu) >= Limits::kProbeMax;
+            const u32 place = (atomicAdd(&cnt[b >> 1], 1u << sh) >> sh) & 0xffffu;
+            at[k] = b | (place << 16);
+            most = place > most ? place : most;
+            sum += place;
         }
-    }
-    if (team_any<THREADS>(over, flag)) return false;            // the same for the whole team
+    };
 #pragma unroll
-    for (u32 k = kProbe; k < ITEMS; ++k) {
-        if (k * THREADS + tid < n) {
-            const u32 b = bucket(e[k]);
-            atomicAdd(&cnt[b >> 1], 1u << ((b & 1u) * 16u));
-        }
+    for (u32 k = 0; k < kProbe; ++k) count(k);
+    if (team_any<THREADS>(most >= Limits::kProbeMax, flag)) return false;      // the same for the whole team
+#pragma unroll
+    for (u32 k = kProbe; k < ITEMS; ++k) count(k);
+    bool over = most >= Limits::kMax;
+    u32 total = wave_sum(sum);
+    if (kWaves > 1u && lane == 0) places[wv] = total;
+    if (team_any<THREADS>(over, flag + 1)) return false;        // also: every pair has been counted
+    if (kWaves > 1u) {
+        total = 0;
+#pragma unroll
+        for (u32 k = 0; k < kWaves; ++k) total += places[k];
     }
-    team_sync<THREADS>();
-    // exclusive scan: ITEMS consecutive buckets per thread; above the count the sum of the squares
-    u32 w[kWords], sum = 0, squares = 0;
+    // the sum of the squares of the counts
+    if (2u * total + n > Limits::kMean * n) return false;       // the same for the whole team
+    if (kWaves == 1u) team_sync<THREADS>();
+    // exclusive scan: ITEMS consecutive buckets per thread
+    u32 w[kWords], mine = 0;
 #pragma unroll
     for (u32 k = 0; k < kWords; ++k) {
         w[k] = cnt[tid * kWords + k];
-        const u32 c0 = w[k] & 0xffffu, c1 = w[k] >> 16;
-        over = over || c0 > Limits::kMax || c1 > Limits::kMax;
-        sum += c0 + c1;
-        squares += c0 * c0 + c1 * c1;
+        mine += (w[k] & 0xffffu) + (w[k] >> 16);
     }
-    sum |= (squares < kShareMax ? squares : kShareMax) << kCountBits;
-    u32 incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const u32 t = __shfl_up(incl, o, 64);
-        if ((int)lane >= o) incl += t;
-    }
-    if (kWaves > 1u && lane == kWave - 1) part[wv] = incl;
-    if (team_any<THREADS>(over, flag + 1)) return false;
-    u32 run = incl - sum, total = kWaves > 1u ? 0u : (u32)__builtin_amdgcn_readlane((int)incl, (int)kWave - 1);
+    const u32 incl = wave_scan(mine);
+    u32 run = incl - mine;
     if (kWaves > 1u) {
+        if (lane == kWave - 1) counts[wv] = incl;
+        team_sync<THREADS>();
 #pragma unroll
-        for (u32 k = 0; k < kWaves; ++k) {
-            run += k < wv ? part[k] : 0u;
-            total += part[k];
-        }
+        for (u32 k = 0; k < kWaves; ++k) run += k < wv ? counts[k] : 0u;
     }
-    if ((total >> kCountBits) > Limits::kMean * n) return false;        // the same for the whole team
-    run &= (1u << kCountBits) - 1u;
 #pragma unroll
     for (u32 k = 0; k < kWords; ++k) {
-        const u32 c0 = w[k] & 0xffffu, c1 = w[k] >> 16;
-        cnt[tid * kWords + k] = run | ((run + c0) << 16);
-        run += c0 + c1;
+        cnt[tid * kWords + k] = run * 0x10001u + (w[k] << 16);
+        run += (w[k] & 0xffffu) + (w[k] >> 16);
     }
     team_sync<THREADS>();
+    const unsigned short *const start = reinterpret_cast<const unsigned short *>(cnt);
 #pragma unroll
-    for (u32 k = 0; k < ITEMS; ++k) {
-        if (k * THREADS + tid < n) {
-            const u32 b = bucket(e[k]), sh = (b & 1u) * 16u;
-            s[(atomicAdd(&cnt[b >> 1], 1u << sh) >> sh) & 0xffffu] = e[k];
-        }
-    }
+    for (u32 k = 0; k < ITEMS; ++k)
+        if (k * THREADS + tid < n) s[start[at[k] & 0xffffu] + (at[k] >> 16)] = e[k];
     team_sync<THREADS>();
-    // a bucket's counter now stands at its end, the one before at its start
     const u64 hi_bits = (u64)tile << 32;
 #pragma unroll 2
     for (u32 p = tid; p < n; p += THREADS) {
         const u64 c = s[p];
-        const u32 b = bucket(c);
-        const u32 end = (cnt[b >> 1] >> ((b & 1u) * 16u)) & 0xffffu;
-        const u32 start = b ? (cnt[(b - 1u) >> 1] >> (((b - 1u) & 1u) * 16u)) & 0xffffu : 0u;
-        u32 at = start;
-        for (u32 j = start; j < end; ++j) at += s[j] < c ? 1u : 0u;
-        keys[beg + at] = hi_bits | (c >> 32);
-        vals[beg + at] = (u32)c;
+        const u32 b = bucket(c), end = start[b + 1u];
+        u32 to = start[b];
+        for (u32 j = to; j < end; ++j) to += s[j] < c ? 1u : 0u;
+        *reinterpret_cast<u64 *>(list + to * 8u) = hi_bits | (c >> 32);
+        *reinterpret_cast<u32 *>(indices + to * 4u) = (u32)c;
     }
     return true;
 }
 
-// a list (or chunk) of 1 .. THREADS * ITEMS pairs, in place; s: list_words(THREADS * ITEMS) words.  The counters lie behind
+// a list of 1 .. THREADS * ITEMS pairs, in place; s: list_words(THREADS * ITEMS) words.  The counters lie behind
 // the composites, where the merge sort has the end of its padded ones: 40 KB for 4096 pairs, so that four
-// workgroups fit a compute unit (43 KB, three: 1.5 M primitives in roomy buffers, 30 000 such workgroups of which most leave at
-// once, 350 us a frame instead of 344); 20 KB for 2048, eight (21 KB, seven: a launch of 1024 such lists 30 us instead of 23).
+// workgroups fit a compute unit; 160 KB, all that there is, for 16384.
 constexpr u32 list_words(u32 pairs) { return pairs + pairs / 4u; }
 template <u32 THREADS, u32 ITEMS>
 __device__ __forceinline__ void sort_list(u64 *keys, u32 *vals, u64 beg, u32 n, u32 tile, u64 *s)
@@ -997,7 +940,7 @@ __device__ __forceinline__ void sort_list(u64 *keys, u32 *vals, u64 beg, u32 n, 
     sort_pairs_in_lds<THREADS, ITEMS>(keys, vals, beg, n, tile, s);
 }
 
-// ---------------------------------------------------------------- merges between the pair buffers
+// ---------------------------------------------------------------- lists beyond kHuge pairs
 __device__ __forceinline__ bool pair_less(u64 ka, u32 va, u64 kb, u32 vb)
 {
     return ka < kb || (ka == kb && va < vb);
@@ -1028,222 +971,16 @@ __device__ __forceinline__ u64 wave_merge_split(const u64 *__restrict__ sk, cons
     return lo;
 }
 
-// One output segment of THREADS * ITEMS pairs of a merge round over the sorted runs of length
-// `run` of one tile's list (L pairs at sk/sv, result to dk/dv): two wavefronts find where the
-// segment starts and ends in its pair of runs, the two input windows are staged in LDS as
-// composites, merged there and written out coalesced.  A run without a partner is copied.
-// Called by the whole workgroup; `s` holds THREADS * ITEMS composites (padded), s_split two words.
-template <u32 THREADS, u32 ITEMS>
-__device__ __forceinline__ void merge_segment(const u64 *__restrict__ sk, const u32 *__restrict__ sv,
-                                              u64 *__restrict__ dk, u32 *__restrict__ dv,
-                                              u64 L, u64 run, u64 seg, u32 tile, u64 *s, u64 *s_split)
-{
-    constexpr u32 CAP = THREADS * ITEMS;
-    const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const u64 o = seg * CAP;
-    if (o >= L) return;                                     // the same for the whole workgroup
-    const u64 a0 = (o / (2 * run)) * (2 * run);
-    const u64 a1 = a0 + run < L ? a0 + run : L;
-    const u64 b1 = a0 + 2 * run < L ? a0 + 2 * run : L;
-    const u64 oe = o + CAP < b1 ? o + CAP : b1;
-    if (wv == 0) {
-        const u64 i0 = wave_merge_split(sk, sv, a0, a1, b1, o - a0, lane);
-        if (lane == 0) s_split[0] = i0;
-    }
-    if (wv == (THREADS > kWave ? 1u : 0u)) {
-        const u64 i1 = wave_merge_split(sk, sv, a0, a1, b1, oe - a0, lane);
-        if (lane == 0) s_split[1] = i1;
-    }
-    __syncthreads();
-    const u64 i0 = s_split[0], i1 = s_split[1];
-    const u64 j0 = (o - a0) - i0;                           // elements of B before the segment
-    const u32 la = (u32)(i1 - i0), total = (u32)(oe - o);
-    for (u32 p = tid; p < total; p += THREADS) {
-        const u64 src = p < la ? a0 + i0 + p : a1 + j0 + (p - la);
-        s[ts_slot(p)] = (sk[src] << 32) | (u64)sv[src];
-    }
-    __syncthreads();
-    const u32 o0 = tid * ITEMS;
-    u64 e[ITEMS];
-    if (o0 < total) merge_from_lds<ITEMS>(s, 0u, la, total, o0, e);
-    __syncthreads();
-    if (o0 < total) {
-#pragma unroll
-        for (u32 k = 0; k < ITEMS; ++k)
-            if (o0 + k < total) s[ts_slot(o0 + k)] = e[k];
-    }
-    __syncthreads();
-    const u64 hi_bits = (u64)tile << 32;
-    for (u32 p = tid; p < total; p += THREADS) {
-        const u64 c = s[ts_slot(p)];
-        dk[o + p] = hi_bits | (c >> 32);
-        dv[o + p] = (u32)c;
-    }
-    __syncthreads();                                        // s and s_split may be reused by the caller
-}
-
-// Lists of kLow + 1 .. kMid pairs, one workgroup each, and before them the chunks of the long
-// lists (kMid + 1 .. kHuge pairs), which are sorted in place like a list of their own.
-// Both count for more than kLow pairs each, which bounds the grid.
-__global__ __launch_bounds__(kMidThreads) void tile_sort_mid_kernel(
-    u64 *__restrict__ keys, u32 *__restrict__ vals, const u64 *__restrict__ tile_offsets,
-    const u32 *__restrict__ order, const u32 *__restrict__ classes, const uint2 *__restrict__ chunk_list,
-    u32 num_tiles)
-{
-    __shared__ u64 s[list_words(kMid)];
-    const u32 chunks = classes[4], elsewhere = classes[kDenseClass];
-    if (elsewhere) return;
-    if (blockIdx.x < chunks) {
-        const uint2 c = chunk_list[blockIdx.x];
-        if (c.x >= num_tiles) return;
-        const u64 beg = tile_offsets[c.x];
-        const u64 len = tile_offsets[c.x + 1] - beg;
-        const u64 c0 = (u64)c.y * kMid;
-        if (c0 >= len) return;                              // cannot happen with a consistent table
-        const u32 n = (u32)(len - c0 < (u64)kMid ? len - c0 : (u64)kMid);
-        sort_list<kMidThreads, kMidItems>(keys, vals, beg + c0, n, c.x, s);     // n >= 1
-        return;
-    }
-    const u32 k = blockIdx.x - chunks;
-    const u32 first = classes[0] + classes[3];
-    if (k >= classes[1] || first + k >= num_tiles) return;
-    const u32 tile = order[first + k];
-    if (tile >= num_tiles) return;
-    const u64 beg = tile_offsets[tile];
-    const u64 len = tile_offsets[tile + 1] - beg;
-    if (len < 2 || len > (u64)kMid) return;                 // cannot happen with a consistent table
-    sort_list<kMidThreads, kMidItems>(keys, vals, beg, (u32)len, tile, s);
-}
-
-// Lists of up to kLow pairs: one workgroup each above kSmallCap pairs, one wavefront each below.  Before
-// them the first merge round of the long lists (runs of kMid pairs, pair buffers -> alternate buffers), kLow
-// outputs per workgroup: a fixed number of workgroups walks the segments.  All of this is latency rather
-// than work, so it shares a launch (the short lists in one of their own: 10 000 primitives at 256 x 256
-// 6.4 + 7.0 us, together 7.7 us).
-constexpr u32 kMergeBlocks1 = 1024, kMergeBlocks2 = 2048;
-constexpr u32 kShortPerBlock = kLowThreads / kSmallThreads;
-static_assert(kLowThreads == kDenseThreads, "the launch carries both ways");
-// (five wavefronts per SIMD as without the other way, whose registers would leave room for four: 23.6 us
-// instead of 26.3 on lists of 1.5 M primitives; its emit tests two rows of tiles at a time for that, without spills)
-template <bool TIGHT, class Dense>
-__global__ __launch_bounds__(kLowThreads, Dense::kDense ? 5 : 1) void tile_sort_low_kernel(
-    u64 *__restrict__ keys, u32 *__restrict__ vals, u64 *__restrict__ keys_alt, u32 *__restrict__ vals_alt,
-    const u64 *__restrict__ tile_offsets, const u32 *__restrict__ order, const u32 *__restrict__ classes,
-    const uint2 *__restrict__ chunk_list, u32 num_tiles, u32 merge_blocks, u32 low_blocks,
-    u32 blocks, u64 capacity, const ScratchHeader *__restrict__ header, Dense dense)
-{
-    constexpr u32 CAP = kLowThreads * kLowItems;
-    constexpr u32 kPerChunk = kMid / CAP;                   // output segments per chunk
-    constexpr u32 kShortWords = list_words(kSmallCap);      // LDS of a wavefront's own list
-    constexpr u32 kListWords = list_words(CAP);
-    constexpr u32 kEmitWords = Dense::kDense ? kDenseWaves * (u32)(sizeof(EmitSpace) / sizeof(u64)) : 0u;
-    __shared__ __attribute__((aligned(16))) u64 s[kListWords > kEmitWords ? kListWords : kEmitWords];
-    u64 *s_split = s + CAP + CAP / 16;                      // two words behind what the merge stages
-    static_assert(CAP + CAP / 16 + 2 <= kListWords, "they fit");
-    // (the flag is read together with what is needed anyway: one round trip to memory)
-    const u32 first = classes[0] + classes[3] + classes[1], low = classes[2], chunks = classes[4], elsewhere = classes[kDenseClass];
-    if constexpr (Dense::kDense) {
-        if (elsewhere) {
-            dense_emit<TIGHT>(dense, header, tile_offsets, capacity, keys, vals, reinterpret_cast<EmitSpace *>(s));
-            return;
-        }
-        if (blockIdx.x >= blocks) return;
-    }
-    static_assert(kShortPerBlock * kShortWords <= kListWords, "a share each");
-    if (blockIdx.x < merge_blocks) {
-        const u64 segments = (u64)chunks * kPerChunk;
-        for (u64 g = blockIdx.x; g < segments; g += merge_blocks) {
-            const uint2 c = chunk_list[g / kPerChunk];
-            if (c.x >= num_tiles) continue;
-            const u64 beg = tile_offsets[c.x];
-            const u64 len = tile_offsets[c.x + 1] - beg;
-            merge_segment<kLowThreads, kLowItems>(keys + beg, vals + beg, keys_alt + beg, vals_alt + beg, len,
-                                                  (u64)kMid, (u64)c.y * kPerChunk + g % kPerChunk, c.x, s, s_split);
-        }
-        return;
-    }
-    const u32 block = blockIdx.x - merge_blocks;
-    if (block < low_blocks) {
-        if (block >= low || first + block >= num_tiles) return;
-        const u32 tile = order[first + block];
-        if (tile >= num_tiles) return;
-        const u64 beg = tile_offsets[tile];
-        const u64 len = tile_offsets[tile + 1] - beg;
-        if (len < 2 || len > (u64)CAP) return;              // cannot happen with a consistent table
-        sort_list<kLowThreads, kLowItems>(keys, vals, beg, (u32)len, tile, s);
-        return;
-    }
-    // the short lists, 1 .. kSmallCap pairs; from here on every wavefront goes its own way
-    const u32 wv = threadIdx.x / kWave;
-    const u32 k = first + low + (block - low_blocks) * kShortPerBlock + wv;
-    if (k >= num_tiles) return;
-    const u32 tile = order[k];
-    if (tile >= num_tiles) return;
-    const u64 beg = tile_offsets[tile];
-    const u64 len = tile_offsets[tile + 1] - beg;
-    if (len < 1 || len > (u64)kSmallCap) return;
-    if (len == 1) {                                         // nothing to sort: only the pair's form changes
-        if ((threadIdx.x & (kWave - 1u)) == 0u) {
-            const u64 c = keys[beg];
-            keys[beg] = ((u64)tile << 32) | (c >> 32); vals[beg] = (u32)c;
-        }
-        return;
-    }
-    u64 *my_s = s + wv * kShortWords;
-    // fewer elements per lane for shorter lists
-    if (len <= 2u * kSmallThreads) sort_list<kSmallThreads, 2u>(keys, vals, beg, (u32)len, tile, my_s);
-    else if (len <= 4u * kSmallThreads) sort_list<kSmallThreads, 4u>(keys, vals, beg, (u32)len, tile, my_s);
-    else sort_list<kSmallThreads, kSmallItems>(keys, vals, beg, (u32)len, tile, my_s);
-}
-
-// The second and last merge round of the long lists (runs of 2 * kMid pairs, alternate buffers -> pair
-// buffers; a list of one such run is copied), kSmallCap outputs per segment.
-__global__ __launch_bounds__(kSmallThreads) void tile_merge_kernel(
-    u64 *__restrict__ keys, u32 *__restrict__ vals, const u64 *__restrict__ keys_alt, const u32 *__restrict__ vals_alt,
-    const u64 *__restrict__ tile_offsets, const u32 *__restrict__ classes,
-    const uint2 *__restrict__ chunk_list, u32 num_tiles)
-{
-    constexpr u32 kPerChunk = kMid / kSmallCap;
-    __shared__ u64 s[kSmallCap + kSmallCap / 16];
-    __shared__ u64 s_split[2];
-    const u64 segments = classes[kDenseClass] ? 0ull : (u64)classes[4] * kPerChunk;
-    for (u64 g = blockIdx.x; g < segments; g += gridDim.x) {
-        const uint2 c = chunk_list[g / kPerChunk];
-        if (c.x >= num_tiles) continue;
-        const u64 beg = tile_offsets[c.x];
-        const u64 len = tile_offsets[c.x + 1] - beg;
-        merge_segment<kSmallThreads, kSmallItems>(keys_alt + beg, vals_alt + beg, keys + beg, vals + beg, len,
-                                                  2 * (u64)kMid, (u64)c.y * kPerChunk + g % kPerChunk, c.x, s, s_split);
-    }
-}
-
-// ---------------------------------------------------------------- lists beyond kHuge pairs
-// One workgroup of 1024 threads per tile whose list is longer than kHuge pairs (the front of
-// `order`): chunks of kHuge pairs are sorted in LDS, then merged pairwise (run length
-// doubling) between the two pair buffers, kHuge outputs at a time: sixteen wavefronts find the
+// A list of L > kHuge pairs by a workgroup of 1024 threads: chunks of kHuge pairs are sorted in LDS, then merged
+// pairwise (run length doubling) between the two pair buffers, kHuge outputs at a time: sixteen wavefronts find the
 // splits of sixteen output segments, then each segment's two input windows are staged in
-// LDS, merged there and written out coalesced.  The result ends in keys/vals.
-__global__ __launch_bounds__(kHugeThreads) void tile_sort_huge_kernel(
-    u64 *__restrict__ keys, u32 *__restrict__ vals, u64 *__restrict__ keys_alt, u32 *__restrict__ vals_alt,
-    const u64 *__restrict__ tile_offsets, const u32 *__restrict__ order, const u32 *__restrict__ classes,
-    u32 num_tiles, ScratchHeader *__restrict__ header, u32 *__restrict__ tile_count)
+// LDS, merged there and written out coalesced.  The result ends in keys/vals.  s: kHuge + kHuge / 16 composites and
+// behind them two words per wavefront.
+__device__ __forceinline__ void sort_huge_list(u64 *__restrict__ keys, u32 *__restrict__ vals, u64 *__restrict__ keys_alt,
+                                               u32 *__restrict__ vals_alt, u64 beg, u64 L, u32 tile, u64 *s)
 {
-    __shared__ u64 s[kHuge + kHuge / 16];
-    __shared__ u64 s_split[kHugeThreads / kWave][2];
-    // the scan has read the per-tile counters (both halves) and the emit kernel has consumed the
-    // deferred list: leave them empty for the next call
-    if (blockIdx.x == 0) {
-        if (threadIdx.x == 0) { header->big_count = 0; header->giant_count = 0; }
-        for (u32 t = threadIdx.x; t < 2u * (num_tiles + 1u); t += kHugeThreads) tile_count[t] = 0;
-    }
-    const u32 huge = classes[kDenseClass] ? 0u : classes[0];
-    if (blockIdx.x >= huge || blockIdx.x >= num_tiles) return;
-    const u32 tile = order[blockIdx.x];
-    if (tile >= num_tiles) return;
-    const u64 beg = tile_offsets[tile];
-    const u64 L = tile_offsets[tile + 1] - beg;
-    if (L <= (u64)kHuge) return;                            // cannot happen with a consistent table
-    const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    u64 *s_split = s + kHuge + kHuge / 16;
+    const u32 tid = team_thread<kHugeThreads>(), lane = tid & (kWave - 1), wv = tid / kWave;
     constexpr u32 kWaves = kHugeThreads / kWave;
 
     // an odd number of merge rounds: the chunk sorts write to the alternate buffers, so that the
@@ -1281,7 +1018,7 @@ __global__ __launch_bounds__(kHugeThreads) void tile_sort_huge_kernel(
                     const u64 oe = o + kHuge < b1 ? o + kHuge : b1;
                     const u64 i0 = wave_merge_split(sk, sv, a0, a1, b1, o - a0, lane);
                     const u64 i1 = wave_merge_split(sk, sv, a0, a1, b1, oe - a0, lane);
-                    if (lane == 0) { s_split[wv][0] = i0; s_split[wv][1] = i1; }
+                    if (lane == 0) { s_split[2 * wv] = i0; s_split[2 * wv + 1] = i1; }
                 }
             }
             __syncthreads();
@@ -1291,7 +1028,7 @@ __global__ __launch_bounds__(kHugeThreads) void tile_sort_huge_kernel(
                 const u64 a1 = a0 + run < L ? a0 + run : L;
                 const u64 b1 = a0 + 2 * run < L ? a0 + 2 * run : L;
                 const u64 oe = o + kHuge < b1 ? o + kHuge : b1;
-                const u64 i0 = s_split[w][0], i1 = s_split[w][1];
+                const u64 i0 = s_split[2 * w], i1 = s_split[2 * w + 1];
                 const u64 j0 = (o - a0) - i0;                // elements of B before the segment
                 const u32 la = (u32)(i1 - i0), total = (u32)(oe - o);
                 // stage A[i0, i1) then B[j0, j0 + total - la) as composites
@@ -1326,6 +1063,94 @@ __global__ __launch_bounds__(kHugeThreads) void tile_sort_huge_kernel(
     }
 }
 
+// ---------------------------------------------------------------- the launches of the per-tile sort
+// The lists beyond kMid pairs, the first of `order`: one workgroup each, up to kHuge pairs whole in the LDS of a compute unit.
+// Such a list was cut into chunks of 4096 before, sorted with the lists of up to 4096 and merged in two rounds, which took
+// two launches more (four in all; 3 M overview, 85 long lists 75 -> 62 us, 20 M of a city 88 -> 60, and where no list is long
+// the launches themselves: 1.2 M inside 20 -> 12, 30 011 at 333 x 217 22 -> 10).  No more workgroups than compute units: an idle
+// one would wait for all of one's LDS.
+__global__ __launch_bounds__(kHugeThreads) void tile_sort_long_kernel(
+    u64 *__restrict__ keys, u32 *__restrict__ vals, u64 *__restrict__ keys_alt, u32 *__restrict__ vals_alt,
+    const u64 *__restrict__ tile_offsets, const u32 *__restrict__ order, const u32 *__restrict__ classes, u32 num_tiles)
+{
+    __shared__ __attribute__((aligned(16))) u64 s[list_words(kHuge)];
+    static_assert(kHuge + kHuge / 16 + 2 * (kHugeThreads / kWave) <= list_words(kHuge), "the merges fit as well");
+    u32 lists = classes[0] + classes[3];
+    const u32 elsewhere = classes[kDenseClass];
+    if (elsewhere) return;
+    if (lists > num_tiles) lists = num_tiles;               // cannot happen with a consistent table
+    for (u32 k = blockIdx.x; k < lists; k += gridDim.x) {
+        const u32 tile = order[k];
+        if (tile >= num_tiles) continue;
+        const u64 beg = tile_offsets[tile];
+        const u64 len = tile_offsets[tile + 1] - beg;
+        if (len > (u64)kHuge) sort_huge_list(keys, vals, keys_alt, vals_alt, beg, len, tile, s);
+        else if (len > (u64)kHuge / 2) sort_list<kHugeThreads, kHugeItems>(keys, vals, beg, (u32)len, tile, s);
+        else if (len > 1) sort_list<kHugeThreads, kHugeItems / 2>(keys, vals, beg, (u32)len, tile, s);
+        __syncthreads();                                    // `s` is free again
+    }
+}
+
+// Lists of up to kMid pairs: one workgroup each above kSmallCap pairs, one wavefront each below.  (Two pairs a thread for up to 1024
+// takes as long as four.)
+constexpr u32 kShortPerBlock = kMidThreads / kSmallThreads;
+__global__ __launch_bounds__(kMidThreads, 8) void tile_sort_kernel(
+    u64 *__restrict__ keys, u32 *__restrict__ vals, const u64 *__restrict__ tile_offsets,
+    const u32 *__restrict__ order, const u32 *__restrict__ classes, u32 num_tiles,
+    ScratchHeader *__restrict__ header, u32 *__restrict__ tile_count)
+{
+    constexpr u32 kShortWords = list_words(kSmallCap);      // LDS of a wavefront's own list
+    static_assert(kShortPerBlock * kShortWords <= list_words(kMid), "a share each");
+    __shared__ __attribute__((aligned(16))) u64 s[list_words(kMid)];
+    const u32 first = classes[0] + classes[3], mid = classes[1], low = classes[2], elsewhere = classes[kDenseClass];
+    // the scan has read the per-tile counters (both halves) and the emit kernel has consumed the
+    // deferred list: leave them empty for the next call
+    const u32 tid = threadIdx.x;
+    for (u32 t = blockIdx.x * kMidThreads + tid; t < 2u * (num_tiles + 1u); t += gridDim.x * kMidThreads) tile_count[t] = 0;
+    if (blockIdx.x == 0 && tid == 0) { header->big_count = 0; header->giant_count = 0; }
+    const u32 whole = mid + low;
+    if (elsewhere || (u64)first + whole > num_tiles) return;    // the second cannot happen with a consistent table
+    const u32 wv = (u32)__builtin_amdgcn_readfirstlane((int)(tid / kWave)), b = blockIdx.x;     // the same for the wavefront
+    const u32 k = b < whole ? first + b : first + whole + (b - whole) * kShortPerBlock + wv;
+    if (k >= num_tiles) return;
+    const u32 tile = order[k];
+    if (tile >= num_tiles) return;
+    const u64 beg = tile_offsets[tile];
+    const u64 len = tile_offsets[tile + 1] - beg;
+    if (b < whole) {                                        // the same for the workgroup
+        if (len < 2 || len > (u64)kMid) return;             // cannot happen with a consistent table
+        if (len > (u64)kLow) sort_list<kMidThreads, 8u>(keys, vals, beg, (u32)len, tile, s);
+        else sort_list<kMidThreads, 4u>(keys, vals, beg, (u32)len, tile, s);
+        return;
+    }
+    // from here on every wavefront goes its own way
+    if (len < 1 || len > (u64)kSmallCap) return;
+    if (len == 1) {                                         // nothing to sort: only the pair's form changes
+        if ((tid & (kWave - 1u)) == 0u) {
+            const u64 c = keys[beg];
+            keys[beg] = ((u64)tile << 32) | (c >> 32); vals[beg] = (u32)c;
+        }
+        return;
+    }
+    u64 *my_s = s + wv * kShortWords;
+    // fewer elements per lane for shorter lists
+    if (len <= 2u * kSmallThreads) sort_list<kSmallThreads, 2u>(keys, vals, beg, (u32)len, tile, my_s);
+    else if (len <= 4u * kSmallThreads) sort_list<kSmallThreads, 4u>(keys, vals, beg, (u32)len, tile, my_s);
+    else sort_list<kSmallThreads, kSmallItems>(keys, vals, beg, (u32)len, tile, my_s);
+}
+
+// The other way's lists.  As part of the sort launch it would take registers from the lists of all frames whose buffers could hold such a
+// frame; a launch that leaves at once costs these frames 2 us.
+template <bool TIGHT>
+__global__ __launch_bounds__(kDenseThreads, 5) void dense_emit_kernel(
+    u64 *__restrict__ keys, u32 *__restrict__ vals, const u64 *__restrict__ tile_offsets, u64 capacity,
+    const ScratchHeader *__restrict__ header, const u32 *__restrict__ classes, DenseArgs dense)
+{
+    __shared__ __attribute__((aligned(16))) EmitSpace s_space[kDenseWaves];
+    if (!classes[kDenseClass]) return;
+    dense_emit<TIGHT>(dense, header, tile_offsets, capacity, keys, vals, s_space);
+}
+
 // ---------------------------------------------------------------- launcher
 hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams &pp, const lmk_gs_binned &out,
                            char *scratch, const ScratchLayout &L, hipStream_t stream)
@@ -1342,7 +1167,6 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
     u32 *big_idx = reinterpret_cast<u32 *>(scratch + L.big_idx);
     u32 *order = reinterpret_cast<u32 *>(scratch + L.order);
     u32 *classes = reinterpret_cast<u32 *>(scratch + L.classes);
-    uint2 *chunk_list = reinterpret_cast<uint2 *>(scratch + L.chunk_list);
     const ushort4 *rect = reinterpret_cast<const ushort4 *>(proj.rect);
     const float4 *feat = reinterpret_cast<const float4 *>(proj.feat);
     // the (tile, start) lists of the counting workgroups live in the alternate key buffer, which
@@ -1395,13 +1219,11 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
     if (num_tiles <= kLdsTilesSmall)
         hipLaunchKernelGGL(tile_scan_kernel<true>, dim3(2), dim3(kScanThreads), 0, stream,
                            tile_count, large_count, num_tiles, out.capacity, header, out.tile_offsets, tile_cursor,
-                           n == 0 ? proj.offsets : nullptr, order, out.tile_order, classes, chunk_list,
-                           out.capacity / 2048 + 2, dense_min);
+                           n == 0 ? proj.offsets : nullptr, order, out.tile_order, classes, dense_min);
     else
         hipLaunchKernelGGL(tile_scan_kernel<false>, dim3(2), dim3(kScanThreads), 0, stream,
                            tile_count, large_count, num_tiles, out.capacity, header, out.tile_offsets, tile_cursor,
-                           n == 0 ? proj.offsets : nullptr, order, out.tile_order, classes, chunk_list,
-                           out.capacity / 2048 + 2, dense_min);
+                           n == 0 ? proj.offsets : nullptr, order, out.tile_order, classes, dense_min);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (L.bin_blocks > 0) {
@@ -1428,37 +1250,23 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
             if (e != hipSuccess) return e;
         }
     }
-    // The lists beyond kHuge pairs first (few workgroups that run long), then by falling length.
-    // The grids are upper bounds from the capacity, surplus workgroups leave at once: a list of
-    // the class above kHuge / kLow / kSmallCap pairs, and likewise every chunk of a long list,
-    // counts for more than that many pairs.
+    // The long lists first, a workgroup a compute unit at most (each takes all of its LDS); none if the buffers do not hold that
+    // many pairs.  The others' grid is an upper bound from the capacity, surplus workgroups leave at once.
     auto at_most = [](u64 a, u64 b) { return (u32)(a < b ? a : b); };
-    const u32 max_huge = at_most(out.capacity / (kHuge + 1) + 1, num_tiles);
-    const u32 max_mid = at_most(out.capacity / (kLowThreads * kLowItems + 1) + 1, 4ull * num_tiles);
-    const u32 max_low = at_most(out.capacity / (kSmallCap + 1) + 1, num_tiles);
-    const u32 merge1 = at_most(2ull * max_mid, kMergeBlocks1), merge2 = at_most(8ull * max_mid, kMergeBlocks2);
-    hipLaunchKernelGGL(tile_sort_huge_kernel, dim3(max_huge), dim3(kHugeThreads), 0, stream,
-                       out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, order, classes, num_tiles, header,
-                       tile_count);
-    hipLaunchKernelGGL(tile_sort_mid_kernel, dim3(max_mid), dim3(kMidThreads), 0, stream,
-                       out.keys, out.vals, out.tile_offsets, order, classes, chunk_list, num_tiles);
-    const u32 short_blocks = (num_tiles + kShortPerBlock - 1) / kShortPerBlock;
-    const u32 low_grid = merge1 + max_low + short_blocks;
-    both([&](auto d) {
-        using Dense = decltype(d);
-        auto low = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(most(low_grid, dense_grid)), dim3(kLowThreads), 0, stream,
-                               out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, order, classes,
-                               chunk_list, num_tiles, merge1, max_low, low_grid, out.capacity, header, d);
-        };
-        if constexpr (Dense::kDense) { if (tight) low(tile_sort_low_kernel<true, Dense>); else low(tile_sort_low_kernel<false, Dense>); }
-        else low(tile_sort_low_kernel<false, Dense>);
-    });
-    // no list of the frame can be long if the buffers do not hold that many pairs
     if (out.capacity > kMid)
-        hipLaunchKernelGGL(tile_merge_kernel, dim3(merge2), dim3(kSmallThreads), 0, stream,
-                           out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, classes,
-                           chunk_list, num_tiles);
+        hipLaunchKernelGGL(tile_sort_long_kernel, dim3(at_most(at_most(out.capacity / (kMid + 1u), num_tiles), kLongBlocks)), dim3(kHugeThreads), 0, stream,
+                           out.keys, out.vals, out.keys_alt, out.vals_alt, out.tile_offsets, order, classes, num_tiles);
+    const u32 whole = at_most(out.capacity / (kSmallCap + 1u), num_tiles), shorts = (num_tiles + kShortPerBlock - 1) / kShortPerBlock;
+    hipLaunchKernelGGL(tile_sort_kernel, dim3(whole + shorts), dim3(kMidThreads), 0, stream,
+                       out.keys, out.vals, out.tile_offsets, order, classes, num_tiles, header, tile_count);
+    if (dense) {
+        const DenseArgs d = dense_args(proj, n, pp, out, DL, dense_min);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(dense_grid), dim3(kDenseThreads), 0, stream,
+                               out.keys, out.vals, out.tile_offsets, out.capacity, header, classes, d);
+        };
+        if (tight) go(dense_emit_kernel<true>); else go(dense_emit_kernel<false>);
+    }
     return hipGetLastError();
 }
 

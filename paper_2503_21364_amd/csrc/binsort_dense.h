@@ -19,11 +19,8 @@
 //            the per-tile sorts to do.
 //
 // Whether a frame goes this way is known on the device only, so buffers with room for such a frame pay for
-// both ways.  The steps are therefore bodies that share the launches of the other way -- the chunk sort that of
-// count_kernel, the count that of count_large_kernel, emit that of tile_sort_low_kernel -- and only the merge rounds
-// are launches of their own.  A frame in roomy buffers that does not go this way, us: 1000 primitives at 256 x 256
-// 46 (buffers too small for this way 46; with every step a launch of its own 57), 10 000 78 (76; 85), 100 000 at
-// 1080p 144 (138; 158), 1.5 M 351 (329; 366).
+// both ways.  The chunk sort and the count are therefore bodies that share the launches of the other way, count_kernel and
+// count_large_kernel; only the merge rounds and the emit are launches of their own, 2 us each where they leave at once.
 //
 // Bound by the vector instructions of the tile tests (twice per candidate) and by writing 12 bytes a
 // pair.  400 000 primitives at 3840 x 2160, 615 M pairs: order 0.1 ms, count 1.2 ms, emit 3.3 ms (2.2 TB/s),

@@ -21,7 +21,6 @@ static_assert(kScanGroup % (kBinBlock / kPreBlock) == 0, "the blocks of one coun
 // 8160) in 32 KB, up to 32768 (2160p has 32400) in 128 KB.  Larger images take the route of the
 // large rectangles for every primitive: one global atomic per pair.
 constexpr u32 kLdsTilesSmall = 8192, kLdsTilesLarge = 32768;
-constexpr u32 kChunk = 4096;            // pairs sorted in LDS by one workgroup of the per-tile sort
 
 // LDS accesses of one wavefront complete in program order: only the compiler has to keep to it
 __device__ __forceinline__ void wave_fence()
@@ -56,7 +55,7 @@ struct ScratchLayout {
     size_t big_idx;       // u32 [n]         deferred list: primitives whose rectangles are walked by wavefronts of their own
     size_t order;         // u32 [tiles]     tile ids by descending list length
     size_t classes;       // u32 [8]         tiles per size class of the per-tile sort (see tile_scan_kernel)
-    size_t chunk_list;    // uint2 [capacity / 2048 + 2]  (tile, chunk) of every chunk of the lists sorted in chunks
+    size_t spare;         // 8 bytes [capacity / 2048 + 2]  no kernel's; the workspace keeps the size that callers have planned with
     size_t total;
     u32 pre_blocks;       // ceil(n / kPreBlock)
     u32 bin_blocks;       // ceil(n / kBinBlock)
@@ -81,7 +80,7 @@ inline ScratchLayout scratch_layout(u32 n, u64 capacity, u32 tiles)
     L.big_idx = o;       o += align256(sizeof(u32) * ((size_t)n + 1));
     L.order = o;         o += align256(sizeof(u32) * (size_t)(tiles + 1));
     L.classes = o;       o += align256(sizeof(u32) * 8);
-    L.chunk_list = o;    o += align256(sizeof(u32) * 2 * (size_t)(capacity / 2048 + 2));
+    L.spare = o;         o += align256(sizeof(u32) * 2 * (size_t)(capacity / 2048 + 2));
     L.total = o;
     return L;
 }
