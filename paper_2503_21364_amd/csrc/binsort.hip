@@ -365,13 +365,13 @@ __device__ __forceinline__ void for_each_listed(const ScratchHeader *__restrict_
 
 static_assert(kLargeThreads == kDenseThreads, "the launch carries the count of both ways");
 template <bool TIGHT, class Dense>
-__global__ __launch_bounds__(kLargeThreads) void count_large_kernel(
+__global__ __launch_bounds__(kLargeThreads, Dense::kDense ? 5 : 1) void count_large_kernel(     // (the other way's tests: 96 registers)
     const ushort4 *__restrict__ rect, const float4 *__restrict__ feat, ProjParams pp, u32 n, u32 num_tiles,
     u32 *__restrict__ large_count, const ScratchHeader *__restrict__ header, const u32 *__restrict__ big_idx,
     u32 giant_blocks, u32 blocks, u32 *__restrict__ tile_count, Dense dense)
 {
     if constexpr (Dense::kDense) {
-        __shared__ WaveSpace s_space[kDenseWaves];
+        __shared__ CountSpace s_space[kDenseWaves];
         if (header->dup_count >= dense.dense_min) {
             dense_count<TIGHT>(dense, header, tile_count, s_space);
             return;
@@ -1141,14 +1141,14 @@ __global__ __launch_bounds__(kMidThreads, 8) void tile_sort_kernel(
 
 // The other way's lists.  As part of the sort launch it would take registers from the lists of all frames whose buffers could hold such a
 // frame; a launch that leaves at once costs these frames 2 us.
-template <bool TIGHT>
+template <bool TIGHT, bool RECORDS>
 __global__ __launch_bounds__(kDenseThreads, 5) void dense_emit_kernel(
     u64 *__restrict__ keys, u32 *__restrict__ vals, const u64 *__restrict__ tile_offsets, u64 capacity,
     const ScratchHeader *__restrict__ header, const u32 *__restrict__ classes, DenseArgs dense)
 {
-    __shared__ __attribute__((aligned(16))) EmitSpace s_space[kDenseWaves];
+    __shared__ __attribute__((aligned(16))) u64 s[kDenseWaves * (u32)((RECORDS ? sizeof(EmitRuns) : sizeof(EmitSpace)) / sizeof(u64))];
     if (!classes[kDenseClass]) return;
-    dense_emit<TIGHT>(dense, header, tile_offsets, capacity, keys, vals, s_space);
+    dense_emit<TIGHT, RECORDS>(dense, header, tile_offsets, capacity, keys, vals, s);
 }
 
 // ---------------------------------------------------------------- launcher
@@ -1265,7 +1265,9 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
             hipLaunchKernelGGL(kernel, dim3(dense_grid), dim3(kDenseThreads), 0, stream,
                                out.keys, out.vals, out.tile_offsets, out.capacity, header, classes, d);
         };
-        if (tight) go(dense_emit_kernel<true>); else go(dense_emit_kernel<false>);
+        if (d.records) { if (tight) go(dense_emit_kernel<true, true>); else go(dense_emit_kernel<false, true>); }
+        else if (tight) go(dense_emit_kernel<true, false>);
+        else go(dense_emit_kernel<false, false>);
     }
     return hipGetLastError();
 }

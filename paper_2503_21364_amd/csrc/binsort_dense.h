@@ -11,24 +11,32 @@
 //            meet it queue up in order, and 256 of them at a time (lane = primitive) get a mask of the 16
 //            tiles they keep: all or none where a look at the whole bin decides (an inner or an outer
 //            part of a large splat), else from the tile test.  Per tile the number kept is the
-//            population count of a ballot; one atomic per wavefront and tile adds it up.
+//            population count of a ballot; one atomic per wavefront and tile adds it up.  Where the workspace has the room
+//            the primitives that keep a tile are left with their masks for the emit ("records").
 //   scan     tile_scan_kernel, as for every frame.
-//   emit     the count walk again.  The ballots give every kept primitive its place in the tile's list,
+//   emit     the records again, or the count's walk.  The ballots give every kept primitive its place in the tile's list,
 //            behind what the units before keep there: a tile's share of the 256 is put together in LDS and
 //            leaves as one run of consecutive keys and values, sorted, with no atomics and nothing left for
-//            the per-tile sorts to do.
+//            the per-tile sorts to do.  From records, runs leave in whole lines: what does not fill one waits in LDS for the next 256.
 //
 // Whether a frame goes this way is known on the device only, so buffers with room for such a frame pay for
 // both ways.  The chunk sort and the count are therefore bodies that share the launches of the other way, count_kernel and
 // count_large_kernel; only the merge rounds and the emit are launches of their own, 2 us each where they leave at once.
 //
-// Bound by the vector instructions of the tile tests (twice per candidate) and by writing 12 bytes a
-// pair.  400 000 primitives at 3840 x 2160, 615 M pairs: order 0.1 ms, count 1.2 ms, emit 3.3 ms (2.2 TB/s),
-// where counting, emitting and sorting pairs took 8.5 + 10.4 + 15.7 ms.  Tried there: bins of 8 x 8 tiles
+// Bound by the vector instructions of the tile tests (count) and by writing 12 bytes a
+// pair (emit).  What writing costs is the lines that are not written whole: runs of 150 pairs from anywhere reach 2.4 to 3 TB/s, from
+// multiples of 32 pairs on 5.4.  400 000 primitives at 3840 x 2160, 615 M pairs, 48 M records: order 0.1 ms, count 1.26, emit
+// 1.87 ms (4.0 TB/s); with records but runs as they come 2.9; with the walk instead of records (count 1.16 without them) 3.3;
+// counting, emitting and sorting pairs took 8.5 + 10.4 + 15.7 ms.  Tried there: bins of 8 x 8 tiles
 // (a third of the tested tiles kept instead of 44 %; count 1.9 ms), testing every tile of every candidate
-// (count 1.8 ms), storing each ballot's pairs as they come (emit 3.7 ms), one tile at a time through LDS
-// (3.5 ms), cached instead of streaming stores (+ 0.3 ms).  The workspace is the alternate key buffer, which
-// only the merges of the per-tile sort use.
+// (count 1.8 ms), storing each ballot's pairs as they come (emit 3.7 ms); from records one tile at a time through LDS (1.90 ms), multiples
+// of 64 pairs (1.86, and half of the wavefronts), a quarter of the units (2.04, count 1.72) or twice (1.93, 1.39), cached instead of
+// streaming stores (2.16; only for a unit's first and last lines, which two of them write, is cached the better one: 1.88 and 2.00).
+// Lines held back on the walk: slower (3 M pairs to 110 M, 20 %), its LDS leaves three wavefronts per SIMD.
+// The workspace is the alternate key buffer, which only the longest lists of the per-tile sort use.  Records take 4 bytes per
+// primitive and bin of it, so buffers with room for bins / 2 pairs per primitive have them (1080p 255, 2160p 1020); bin_sort in buffers that
+// have, and with the walk: 100 000 of 52 tiles at 1080p 210 us, 275; 300 000 of 62 441, 637; 400 000 of 104 at 1440p 660, 993; 200 000 of
+// 558 at 2160p 945, 1244.
 #ifndef LMK_GS_BINSORT_DENSE_H
 #define LMK_GS_BINSORT_DENSE_H
 #include "lds_sort.h"
@@ -78,13 +86,18 @@ inline u64 power(u32 base, u32 exponent)
     return p;
 }
 
+// room for the records of a bin: units, which start at whole wavefronts, start at whole lines
+__host__ __device__ inline size_t record_row(u32 n) { return ((size_t)n + kWave - 1) / kWave * kWave; }
+
 // Carving of the workspace (all offsets multiples of 256 bytes).
 struct DenseLayout {
     size_t ops;         // float4 [n][2]  operands of the tile test in depth order: u, v, A, B | C, rx, ry, tau
     size_t pairs0, pairs1;   // u64 [n]   depth bits << 32 | index: ping and pong of the merge rounds
     size_t rects;       // ushort4 [n]    rectangles in depth order
     size_t counts;      // u32 [bins][units][kBinTiles]
-    size_t total;
+    size_t kept;        // u32 [bins][units]    number of records of a unit
+    size_t records;     // u32 [bins][record_row(n)]        a unit's from its first primitive on; behind `total`, if the workspace has the room
+    size_t total, with_records;
     u32 bins_x, bins, units;
     u32 chunk, chunks;  // primitives sorted in LDS at a time (the last may be fewer), and how many of them
     u32 ways, rounds;   // runs merged at a time, merge rounds: the order ends in pairs0 if even, else in pairs1
@@ -118,7 +131,10 @@ DenseLayout dense_layout(u32 n, u64 capacity, u32 tiles_x, u32 tiles_y)
     L.pairs1 = o; o += align256((size_t)n * sizeof(u64));
     L.rects = o;  o += align256((size_t)n * sizeof(ushort4));
     L.counts = o; o += align256((size_t)L.bins * L.units * kBinTiles * sizeof(u32));
+    L.kept = o;   o += align256((size_t)L.bins * L.units * sizeof(u32));
     L.total = o;
+    L.records = o; o += (size_t)L.bins * record_row(n) * sizeof(u32);
+    L.with_records = o;
     return L;
 }
 
@@ -139,6 +155,7 @@ struct DenseArgs {
     u64 *pairs;                 // of the chunk sort
     const u64 *ordered;         // of the last round
     ushort4 *rects; float4 *ops; u32 *counts;
+    u32 *kept, *records;        // records: null if the workspace has no room for them
     const float *depth; const u32 *tiles_touched; const ushort4 *rect; const float4 *feat;
 };
 
@@ -268,11 +285,17 @@ __global__ __launch_bounds__(kRankThreads) void depth_rank_kernel(
 // ---------------------------------------------------------------- count / emit
 // What a wavefront works on: bin and unit from the grid position, the unit's share of the order.
 struct UnitWork { u32 bin, unit, bx, by, beg, end; };
-
-// of the `units` that the workspace and the grid have room for, those that this frame's pairs are worth
-__device__ __forceinline__ u32 units_in_use(const ScratchHeader *__restrict__ header, u32 bins, u32 units)
+// ordered primitives of a unit: whole wavefronts
+__host__ __device__ __forceinline__ u32 unit_share(u32 n, u32 units)
 {
-    const u64 worth = units_worth(header->dup_count, bins);
+    const u32 rounds = (n + kWave - 1) / kWave;
+    return (rounds + units - 1) / units * kWave;
+}
+
+// of the `units` that the workspace and the grid have room for, those that a frame of D pairs is worth
+__host__ __device__ __forceinline__ u32 units_in_use(u64 D, u32 bins, u32 units)
+{
+    const u64 worth = units_worth(D, bins);
     if (worth >= units) return units;
     return worth < kDenseWaves ? kDenseWaves : (u32)worth / kDenseWaves * kDenseWaves;
 }
@@ -294,7 +317,7 @@ __device__ __forceinline__ UnitWork unit_work(u32 n, u32 bins_x, u32 bins, u32 u
     w.unit = (by_share ? blockIdx.x / bins : blockIdx.x % per_bin) * kDenseWaves + wv;
     w.bx = (w.bin % bins_x) * kBinEdge;
     w.by = (w.bin / bins_x) * kBinEdge;
-    const u32 rounds = (n + kWave - 1) / kWave, per = (rounds + units - 1) / units * kWave;
+    const u32 per = unit_share(n, units);
     const u64 b = (u64)w.unit * per, e = b + per;
     w.beg = b < n ? (u32)b : n;
     w.end = e < n ? (u32)e : n;
@@ -462,24 +485,54 @@ struct WaveSpace {
     u32 queue[kBatch + kWave];
     unsigned short mask[kBatch], open[kBatch];
 };
+struct CountSpace : WaveSpace { u32 records[kBatch + 2 * kWave]; };
+// of the emit: a batch's pairs of two tiles; from records, also what does not fill a line of values (and two of keys) of every tile yet
+constexpr u32 kLine = 32;
 struct EmitSpace { WaveSpace w; u64 run[2 * kBatch]; };
+struct EmitRuns { u64 run[2 * kBatch], carry[kBinTiles * kLine]; };
+
+// A record of the count for the emit: a primitive that keeps a tile of the bin, its position in the unit's share and the mask of the
+// tiles.
+constexpr u32 kRecordBits = 16;
+static_assert(kBinTiles <= 32 - kRecordBits, "a record is a word");
 
 // workgroup blockIdx.x of the count: kDenseThreads threads
 template <bool TIGHT>
 __device__ __forceinline__ void dense_count(const DenseArgs &d, const ScratchHeader *__restrict__ header,
-                                            u32 *__restrict__ tile_count, WaveSpace *space)
+                                            u32 *__restrict__ tile_count, CountSpace *space)
 {
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const u32 used = units_in_use(header, d.bins, d.units);
+    const u32 used = units_in_use(header->dup_count, d.bins, d.units);
     const UnitWork w = unit_work(d.n, d.bins_x, d.bins, used, wv);
     if (w.bin >= d.bins) return;
-    WaveSpace &my = space[wv];
+    CountSpace &my = space[wv];
     u32 mine = 0;                                           // kept by tile `lane` of the bin
+    const bool saved = d.records != nullptr;
+    u32 *rec = saved ? d.records + (size_t)w.bin * record_row(d.n) + w.beg : nullptr;
+    u32 kept_prims = 0, waiting = 0;                        // records written, and in LDS
     bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
         bin_masks<TIGHT, kBatch, kBinEdge>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
         u32 m[kSets];
 #pragma unroll
         for (u32 set = 0; set < kSets; ++set) m[set] = my.mask[set * kWave + lane];
+        if (saved) {
+#pragma unroll
+            for (u32 set = 0; set < kSets; ++set) {         // (beyond `count` the masks are zero)
+                const u64 some = __builtin_amdgcn_ballot_w64(m[set] != 0u);
+                if (m[set]) my.records[waiting + lanes_below(some)] = (queued[set * kWave + lane] - w.beg) | (m[set] << 16);
+                waiting += (u32)__builtin_popcountll(some);
+            }
+            wave_fence();
+            u32 out = 0;                                    // whole wavefronts of them, so that whole lines are written
+            for (; out + kWave <= waiting; out += kWave) rec[kept_prims + out + lane] = my.records[out + lane];
+            if (out) {
+                const u32 rest = my.records[out + lane];
+                wave_fence();
+                my.records[lane] = rest;
+                kept_prims += out;
+                waiting -= out;
+            }
+        }
 #pragma unroll
         for (u32 tile = 0; tile < kBinTiles; ++tile) {
             u32 kept = 0;
@@ -490,6 +543,10 @@ __device__ __forceinline__ void dense_count(const DenseArgs &d, const ScratchHea
         }
         wave_fence();
     });
+    if (saved) {
+        if (lane < waiting) rec[kept_prims + lane] = my.records[lane];
+        if (lane == 0) d.kept[(size_t)w.bin * d.units + w.unit] = kept_prims + waiting;
+    }
     if (lane < kBinTiles) {
         d.counts[((size_t)w.bin * d.units + w.unit) * kBinTiles + lane] = mine;
         const u32 tx = w.bx + lane % kBinEdge, ty = w.by + lane / kBinEdge;
@@ -497,19 +554,21 @@ __device__ __forceinline__ void dense_count(const DenseArgs &d, const ScratchHea
     }
 }
 
-// workgroup blockIdx.x of the emit: kDenseThreads threads
-template <bool TIGHT>
+// workgroup blockIdx.x of the emit: kDenseThreads threads; RECORDS: from what the count has left
+template <bool TIGHT, bool RECORDS>
 __device__ __forceinline__ void dense_emit(const DenseArgs &d, const ScratchHeader *__restrict__ header,
                                            const u64 *__restrict__ tile_offsets, u64 capacity,
-                                           u64 *__restrict__ keys, u32 *__restrict__ vals, EmitSpace *space)
+                                           u64 *__restrict__ keys, u32 *__restrict__ vals, u64 *space)
 {
     if (header->status != LMK_GS_OK) return;                // more pairs than the buffers hold: nothing is emitted
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const u32 used = units_in_use(header, d.bins, d.units);
+    const u32 used = units_in_use(header->dup_count, d.bins, d.units);
     const UnitWork w = unit_work(d.n, d.bins_x, d.bins, used, wv);
     if (w.bin >= d.bins) return;
-    WaveSpace &my = space[wv].w;
-    u64 *run = space[wv].run;
+    EmitRuns &lines = reinterpret_cast<EmitRuns *>(space)[RECORDS ? wv : 0u];
+    EmitSpace &walk = reinterpret_cast<EmitSpace *>(space)[RECORDS ? 0u : wv];
+    WaveSpace &my = walk.w;
+    u64 *const run = RECORDS ? lines.run : walk.run, *const carry = lines.carry;
     const u64 *ordered = d.ordered;
     const u32 tiles_x = d.pp.tiles_x;
     // what the units before this one keep: lane = (a quarter of them, tile), then added up
@@ -525,17 +584,13 @@ __device__ __forceinline__ void dense_emit(const DenseArgs &d, const ScratchHead
         const u32 tx = w.bx + lane % kBinEdge, ty = w.by + lane / kBinEdge;
         if (lane < kBinTiles && tx < tiles_x && ty < d.pp.tiles_y) first = tile_offsets[ty * tiles_x + tx] + before;
     }
-    u32 next_lo = (u32)first, next_hi = (u32)(first >> 32);
-    bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
-        bin_masks<TIGHT, kBatch, 2u>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
-        u32 m[kSets];
-        u64 pair[kSets];
-#pragma unroll
-        for (u32 set = 0; set < kSets; ++set) {
-            const u32 k = set * kWave + lane;
-            m[set] = my.mask[k];
-            pair[set] = k < count ? ordered[queued[k]] : 0ull;
-        }
+    u32 next_lo = (u32)first, next_hi = (u32)(first >> 32), left = 0;
+    auto position = [&](u32 tile) -> u64 {
+        return ((u64)(u32)__builtin_amdgcn_readlane((int)next_hi, (int)tile) << 32) | (u64)(u32)__builtin_amdgcn_readlane((int)next_lo, (int)tile);
+    };
+    auto tile_id = [&](u32 tile) -> u64 { return (u64)((w.by + tile / kBinEdge) * tiles_x + w.bx + tile % kBinEdge) << 32; };
+    // kBatch primitives, kSets per lane: masks of their tiles, and composites
+    auto put = [&](const u32 (&m)[kSets], const u64 (&pair)[kSets]) {
 #pragma unroll 1
         for (u32 tile0 = 0; tile0 < kBinTiles; tile0 += 2) {
             u32 total[2];
@@ -554,27 +609,96 @@ __device__ __forceinline__ void dense_emit(const DenseArgs &d, const ScratchHead
 #pragma unroll
             for (u32 q = 0; q < 2; ++q) {
                 const u32 tile = tile0 + q;
-                const u64 at = ((u64)(u32)__builtin_amdgcn_readlane((int)next_hi, (int)tile) << 32) |
-                               (u64)(u32)__builtin_amdgcn_readlane((int)next_lo, (int)tile);
-                const u64 after = at + total[q];
-                next_lo = lane == tile ? (u32)after : next_lo;
-                next_hi = lane == tile ? (u32)(after >> 32) : next_hi;
-                const u64 id = (u64)((w.by + tile / kBinEdge) * tiles_x + w.bx + tile % kBinEdge) << 32;
-                u64 v[kSets];
+                const u64 at = position(tile);
+                const u32 old = RECORDS ? (u32)__builtin_amdgcn_readlane((int)left, (int)tile) : 0u, have = old + total[q];
+                const u64 line = (at + have) & ~(u64)(kLine - 1u);
+                const u32 out = !RECORDS ? have : (line > at ? (u32)(line - at) : 0u);   // then all that was left before is among them
+                const u64 *const found = run + q * kBatch;
+                const u64 id = tile_id(tile);
 #pragma unroll
-                for (u32 r = 0; r < kSets; ++r) v[r] = run[q * kBatch + r * kWave + lane];
-#pragma unroll
-                for (u32 r = 0; r < kSets; ++r) {
+                for (u32 r = 0; r < kSets + (RECORDS ? 1u : 0u); ++r) {
                     const u32 k = r * kWave + lane;
-                    if (k < total[q] && at + k < capacity) {
-                        __builtin_nontemporal_store(id | (v[r] >> 32), keys + at + k);
-                        __builtin_nontemporal_store((u32)v[r], vals + at + k);
+                    if (k < out && at + k < capacity) {
+                        const u64 v = RECORDS && k < old ? carry[tile * kLine + k] : found[k - old];
+                        if (RECORDS && ((u32)at & (kLine - 1u))) {      // the unit's first; the same for the wavefront
+                            keys[at + k] = id | (v >> 32);
+                            vals[at + k] = (u32)v;
+                        } else {
+                            __builtin_nontemporal_store(id | (v >> 32), keys + at + k);
+                            __builtin_nontemporal_store((u32)v, vals + at + k);
+                        }
                     }
                 }
+                if constexpr (RECORDS) {
+                    const u32 from = out ? out - old : 0u, to = out ? 0u : old;
+                    if (from + lane < total[q] && to + lane < kLine) carry[tile * kLine + to + lane] = found[from + lane];
+                }
+                const u64 after = at + out;
+                next_lo = lane == tile ? (u32)after : next_lo;
+                next_hi = lane == tile ? (u32)(after >> 32) : next_hi;
+                left = lane == tile ? have - out : left;
             }
             wave_fence();
         }
-    });
+    };
+    // what is left of every tile, less than a line
+    auto finish = [&] {
+#pragma unroll 1
+        for (u32 tile = 0; tile < kBinTiles; ++tile) {
+            const u64 at = position(tile) + lane;
+            if (lane < (u32)__builtin_amdgcn_readlane((int)left, (int)tile) && at < capacity) {
+                const u64 v = carry[tile * kLine + lane];
+                keys[at] = tile_id(tile) | (v >> 32);
+                vals[at] = (u32)v;
+            }
+        }
+    };
+    if constexpr (RECORDS) {
+        // (the records are read two batches ahead and the composites one; beyond the end a record of no tiles)
+        const u32 *rec = d.records + (size_t)w.bin * record_row(d.n) + w.beg;
+        u32 count = d.kept[(size_t)w.bin * d.units + w.unit];
+        count = count < w.end - w.beg ? count : w.end - w.beg;          // cannot happen: one per primitive at most
+        if (count == 0u) return;
+        u32 r0[kSets], r1[kSets];
+        u64 c0[kSets];
+        auto load = [&](u32 k0, u32 (&r)[kSets]) {
+#pragma unroll
+            for (u32 set = 0; set < kSets; ++set) {
+                const u32 k = k0 + set * kWave + lane;
+                r[set] = k < count ? rec[k] : 0u;
+            }
+        };
+        auto fetch = [&](const u32 (&r)[kSets], u64 (&c)[kSets]) {
+#pragma unroll
+            for (u32 set = 0; set < kSets; ++set) c[set] = ordered[w.beg + (r[set] & ((1u << kRecordBits) - 1u))];
+        };
+        load(0, r0);
+        load(kBatch, r1);
+        fetch(r0, c0);
+        for (u32 k0 = 0; k0 < count; k0 += kBatch) {
+            u32 m[kSets];
+            u64 pair[kSets];
+#pragma unroll
+            for (u32 set = 0; set < kSets; ++set) { m[set] = r0[set] >> kRecordBits; pair[set] = c0[set]; r0[set] = r1[set]; }
+            fetch(r0, c0);
+            load(k0 + 2u * kBatch, r1);
+            put(m, pair);
+        }
+        finish();
+    } else {
+        bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
+            bin_masks<TIGHT, kBatch, 2u>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
+            u32 m[kSets];
+            u64 pair[kSets];
+#pragma unroll
+            for (u32 set = 0; set < kSets; ++set) {
+                const u32 k = set * kWave + lane;
+                m[set] = my.mask[k];
+                pair[set] = k < count ? ordered[queued[k]] : 0ull;
+            }
+            put(m, pair);
+        });
+    }
 }
 
 // ---------------------------------------------------------------- host side
@@ -604,6 +728,10 @@ inline DenseArgs dense_args(const lmk_gs_projected &proj, u32 n, const ProjParam
     d.rects = reinterpret_cast<ushort4 *>(w + L.rects);
     d.ops = reinterpret_cast<float4 *>(w + L.ops);
     d.counts = reinterpret_cast<u32 *>(w + L.counts);
+    d.kept = reinterpret_cast<u32 *>(w + L.kept);
+    // a frame that goes this way has dense_min pairs at least, so no unit's share is larger than that many are worth
+    const bool fit = unit_share(n, units_in_use(dense_min, L.bins, L.units)) <= (1u << kRecordBits);
+    d.records = fit && L.with_records <= out.capacity * sizeof(u64) ? reinterpret_cast<u32 *>(w + L.records) : nullptr;
     d.depth = proj.depth; d.tiles_touched = proj.tiles_touched;
     d.rect = reinterpret_cast<const ushort4 *>(proj.rect);
     d.feat = reinterpret_cast<const float4 *>(proj.feat);
