@@ -364,7 +364,7 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
     constexpr u32 kSlot = kPart + 1;                        // padded record stride in LDS (bank spread)
     constexpr u32 kDirectMax = 40;                          // survivors per wavefront served by direct loads
     static_assert(kPart * kParts == kVec, "records are staged in equal parts");
-    __shared__ f32x4 s_sh[kPreBlock / kWave][kWave * kSlot];
+    __shared__ f32x4 s_sh[kPreBlock / kWave][kWave * (kSlot < 3 ? 3 : kSlot)];
     const u32 sh_lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const bool staged = (u32)__builtin_popcountll(__builtin_amdgcn_ballot_w64(cnt > 0)) > kDirectMax;   // wave-uniform
     const u32 first = blockIdx.x * kPreBlock + wv * kWave;  // first primitive of this wavefront
@@ -506,23 +506,39 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             }
         }
-        if (cnt) {
-            const float r = fmaxf(acc[0], 0.0f), g = fmaxf(acc[1], 0.0f), bl = fmaxf(acc[2], 0.0f);
-
-            depth[i] = pz;
-            rect[i] = make_ushort4((unsigned short)x0, (unsigned short)y0,
-                                   (unsigned short)x1, (unsigned short)y1);
-            float4 *f = feat + (size_t)i * (LMK_GS_FEAT_STRIDE / 4);
-            f[0] = make_float4(u, v, cA, cB);
-            f[1] = make_float4(cC, o, r, g);
-            f[2] = make_float4(bl, 0.0f, 0.0f, 0.0f);
+        // Outputs leave in whole lines: where a wavefront has any primitive left it writes depth, rectangle and mask of all, and of the
+        // feature records every line that holds a part of one that is left (the rest is unspecified).  A line that is
+        // written in part costs the memory side several times a whole one (20 M of a city, a quarter left, degree 0, rule 0: each its
+        // own 617 us, so 412, without the records' stores 307).
+        const u64 left = __builtin_amdgcn_ballot_w64(cnt != 0u);
+        if (left != 0ull) {
+            if (i < n) {
+                depth[i] = pz;
+                rect[i] = make_ushort4((unsigned short)x0, (unsigned short)y0,
+                                       (unsigned short)x1, (unsigned short)y1);
+                // rectangles of up to 32 tiles: the emit stage expands the kept tiles from this mask
+                if (pp.cam.binning == 1u) tile_masks[i] = kept_mask;
+            }
+            const f32x4 f0 = { u, v, cA, cB }, f1 = { cC, o, fmaxf(acc[0], 0.0f), fmaxf(acc[1], 0.0f) }, f2 = { fmaxf(acc[2], 0.0f), 0.0f, 0.0f, 0.0f };
+            f32x4 *block = reinterpret_cast<f32x4 *>(feat) + (size_t)first * 3u;
+            if ((u32)__builtin_popcountll(left) == recs) {
+                if (i < n) { block[3u * sh_lane] = f0; block[3u * sh_lane + 1u] = f1; block[3u * sh_lane + 2u] = f2; }
+            } else {
+                f32x4 *const st = s_sh[wv];
+                wave_fence();
+                st[3u * sh_lane] = f0; st[3u * sh_lane + 1u] = f1; st[3u * sh_lane + 2u] = f2;
+                wave_fence();
+#pragma unroll
+                for (u32 j = 0; j < 3; ++j) {
+                    const u32 idx = j * kWave + sh_lane, v0 = idx & ~7u;        // the line's first vector
+                    const u32 r0 = v0 / 3u, r1 = (v0 + 7u) / 3u;                // the records it holds parts of, three or four
+                    const u64 of_line = (left >> r0) & ((2ull << (r1 - r0)) - 1ull);
+                    if (of_line != 0ull && idx < 3u * recs) block[idx] = st[idx];
+                }
+            }
         }
     }
-    if (i < n) {
-        tiles_touched[i] = cnt;
-        // rectangles of up to 32 tiles: the emit stage expands the kept tiles from this mask
-        if (pp.cam.binning == 1u && cnt) tile_masks[i] = kept_mask;
-    }
+    if (i < n) tiles_touched[i] = cnt;
     block_total(cnt, s_part, block_sums);
 }
 
