@@ -13,6 +13,7 @@
 // culls.
 #include "lmk_gs_internal.h"
 #include "tile_test.h"
+#include "wave_ops.h"
 
 #include <cmath>
 
@@ -355,8 +356,11 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
         }
     }
 
-    // SH records (see below): a wavefront most of whose primitives are still alive requests its
-    // whole block of records now, so that the loads are in flight during the tile counting
+    // SH records (see below), requested now, so that the loads are in flight during the tile counting: the whole block of a
+    // wavefront most of whose primitives are still alive, else each one's own.  Those of one record share lines, so they
+    // go through the caches (20 M of a city, a quarter alive: after the counting and past the caches 739 us, before it and past
+    // them 890, so 711).  The records of those alive as one row of vectors, a lane a vector: a fifth of the load instructions,
+    // but 147 registers, three wavefronts per SIMD, 790.
     constexpr u32 kVec = LMK_GS_SH_STRIDE(DEG) / 4;         // 16-byte vectors per record
     constexpr u32 kCoef = (DEG + 1) * (DEG + 1);
     constexpr u32 kPart = kVec > 7 ? kVec / 2 : kVec;       // vectors of a record staged at a time
@@ -364,8 +368,9 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
     constexpr u32 kSlot = kPart + 1;                        // padded record stride in LDS (bank spread)
     constexpr u32 kDirectMax = 40;                          // survivors per wavefront served by direct loads
     static_assert(kPart * kParts == kVec, "records are staged in equal parts");
-    __shared__ f32x4 s_sh[kPreBlock / kWave][kWave * (kSlot < 3 ? 3 : kSlot)];
-    const u32 sh_lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    constexpr u32 kStage = kWave * kSlot, kTiles = kWave * 3u + kWave / 4u;       // SH; the tile tests, and outputs
+    __shared__ f32x4 s_sh[kPreBlock / kWave][kStage > kTiles ? kStage : kTiles];
+    const u32 sh_lane = threadIdx.x & (kWave - 1), wv = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const bool staged = (u32)__builtin_popcountll(__builtin_amdgcn_ballot_w64(cnt > 0)) > kDirectMax;   // wave-uniform
     const u32 first = blockIdx.x * kPreBlock + wv * kWave;  // first primitive of this wavefront
     const u32 recs = first < n ? (n - first < kWave ? n - first : kWave) : 0u;
@@ -378,21 +383,55 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
             const u32 idx = j * kWave + sh_lane;
             buf[j] = idx < recs * kVec ? src[idx] : f32x4{0.f, 0.f, 0.f, 0.f};
         }
+    } else if (cnt) {
+        const f32x4 *rec = reinterpret_cast<const f32x4 *>(sh) + (size_t)i * kVec;      // this primitive's record
+#pragma unroll
+        for (u32 j = 0; j < kVec; ++j) buf[j] = rec[j];
     }
 
     // binning rule 1: count only the tiles of the rectangle that the splat can reach.
-    // Small rectangles are walked by their own lane; large ones one at a time by the whole
+    // The tiles of small rectangles are put in a row, a lane each, 64 per step: a lane finds its primitive by a running maximum
+    // over marks at their first tiles, and the ballot of a step holds everyone's mask (rectangles walked by their own lane
+    // take as many steps as the largest has tiles: 402 M vector instructions for 20 M of a city, 333 M so, 798 -> 750 us).  Large
+    // rectangles are walked one at a time by the whole
     // wavefront (64 tiles per step), so that one huge splat does not stall 63 idle lanes.
     if (pp.cam.binning == 1u) {
         const TileTest tt = make_tile_test(u, v, cA, cB, cC, opacity_tau(pp, o));
         const u32 area = cnt, w = x1 - x0;
         constexpr u32 kOwn = 16;
         u32 kept = 0;
-        if (area > 0 && area <= kOwn) {
-            u32 slot = 0;
-            for (u32 ty = y0; ty < y1; ++ty)
-                for (u32 tx = x0; tx < x1; ++tx, ++slot)
-                    if (tile_kept(tt, tx, ty)) { ++kept; kept_mask |= 1u << slot; }
+        {
+            const u32 mine = area <= kOwn ? area : 0u, start = wave_scan(mine) - mine, tiles = wave_sum(mine);
+            if (tiles) {                                        // wave-uniform
+                f32x4 *const of = s_sh[wv];                     // what a tile's lane has to know of its primitive
+                u32 *const mark = reinterpret_cast<u32 *>(of + 3u * kWave);
+                of[3u * sh_lane] = f32x4{ tt.u, tt.v, tt.A, tt.B };
+                of[3u * sh_lane + 1u] = f32x4{ tt.C, tt.rx, tt.ry, tt.tau };
+                of[3u * sh_lane + 2u] = f32x4{ __uint_as_float(start), __uint_as_float(x0), __uint_as_float(y0), (float)w };
+                u32 owner = 0;
+                for (u32 base = 0; base < tiles; base += kWave) {
+                    mark[sh_lane] = 0;
+                    wave_fence();
+                    if (mine && start - base < kWave) mark[start - base] = sh_lane;       // the first lane's start is 0
+                    wave_fence();
+                    const u32 before = owner;
+                    owner = wave_scan_max(mark[sh_lane]);
+                    owner = owner > before ? owner : before;
+                    const f32x4 a = of[3u * owner], b = of[3u * owner + 1u], c = of[3u * owner + 2u];
+                    const TileTest ot = { a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3] };
+                    const u32 slot = base + sh_lane - __float_as_uint(c[0]);
+                    // slot / width for a slot of up to 16: half a step from the next integer, far more than the rounding
+                    const u32 row = (u32)(((float)slot + 0.5f) * __builtin_amdgcn_rcpf(c[3])), col = slot - row * (u32)c[3];
+                    const u64 m = __builtin_amdgcn_ballot_w64(base + sh_lane < tiles &&
+                                                              tile_kept(ot, __float_as_uint(c[1]) + col, __float_as_uint(c[2]) + row));
+                    const u32 ahead = start - base;             // of this step's tiles, or, wrapped, how many of mine it follows
+                    const u32 bits = ahead < kWave ? (u32)(m >> ahead) : (0u - ahead < kOwn ? (u32)m << (0u - ahead) : 0u);
+                    kept_mask |= bits & ((1u << mine) - 1u);
+                    owner = wave_last(owner);
+                    wave_fence();
+                }
+                kept = (u32)__builtin_popcount(kept_mask);
+            }
         }
         u64 big = __builtin_amdgcn_ballot_w64(area > kOwn);
         const u32 lane = threadIdx.x & (kWave - 1);
@@ -443,7 +482,6 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
     // lines per load instruction); where few are (close-up views cull most primitives), each survivor
     // fetches only its own record and the rest of the block is never read.
     {
-        const f32x4 *rec = reinterpret_cast<const f32x4 *>(sh) + (size_t)i * kVec;   // this primitive's record
         const f32x4 *lrec = &s_sh[wv][sh_lane * kSlot];
 
         float Y[16];
@@ -492,7 +530,7 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
 #pragma unroll
                 for (u32 j = 0; j < kPart; ++j) {
                     const u32 jj = part * kPart + j;
-                    const f32x4 q = staged ? lrec[j] : __builtin_nontemporal_load(rec + jj);
+                    const f32x4 q = staged ? lrec[j] : buf[jj];
 #pragma unroll
                     for (u32 m = 0; m < 4; ++m) {
                         const u32 e = 4 * jj + m;               // compile-time: coefficient e / 3, channel e % 3
