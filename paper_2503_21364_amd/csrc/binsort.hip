@@ -7,7 +7,7 @@
 // sort fixes it.  The pairs are therefore written straight into their tile's slice, never
 // partitioned by a sort over the tile bits: count per tile, scan, then write on a second walk.
 //
-//   count    one workgroup per kBinBlock (2048) consecutive primitives.  A rectangle of up to 32 tiles (nearly
+//   count    one workgroup per 512 to 8192 (bin_block) consecutive primitives.  A rectangle of up to 32 tiles (nearly
 //            all of them) is walked by its own lane -- binning rule 0: every tile; rule 1: the kept
 //            tiles, from the bit mask the projection kernel left -- and counted per tile in LDS.  A
 //            scene in spatial order puts a workgroup's pairs into few tiles, and the workgroup then
@@ -136,21 +136,22 @@ __device__ __forceinline__ void walk_large(ushort4 r, const float4 *__restrict__
 // LDS_TILES > 0: the image has at most LDS_TILES tiles, rectangles of up to kMaskArea tiles are
 // counted in LDS, larger ones listed.  LDS_TILES == 0 (images of more tiles): every primitive is
 // listed.
-// A workgroup takes kBinBlock consecutive primitives, kBinBlock / THREADS per thread (primitive
-// tid + j THREADS in round j).  What bounds these kernels is the chain of memory round trips of a
+// A workgroup takes bin_block() consecutive primitives, in rounds of 2048, kPer per thread (primitive
+// tid + j THREADS).  What bounds these kernels is the chain of memory round trips of a
 // workgroup, so the compute unit should be full of wavefronts: with 32 KB of counters four
 // workgroups fit, and four workgroups of 512 threads are all the wavefronts it can hold.
-constexpr u32 kRunBits = 11;             // a workgroup's pairs in one tile, minus one, fit these many bits
-static_assert(kBinBlock <= (1u << kRunBits), "(count - 1) of a run is packed into kRunBits bits");
+constexpr u32 kRunBits = 17;             // a workgroup's pairs in one tile, minus one, fit these many bits
+static_assert(kBinBlockMax <= (1u << kRunBits) && kLdsTilesLarge <= (1u << (32 - kRunBits)), "a tile and (count - 1) of a run are packed into a word");
 template <u32 LDS_TILES> struct BinShape {
-    static constexpr u32 kThreads = LDS_TILES == kLdsTilesSmall ? kBinBlock / 4u : 1024u;
-    static constexpr u32 kPer = kBinBlock / kThreads;
+    static constexpr u32 kThreads = LDS_TILES == kLdsTilesSmall ? 512u : 1024u;
+    static constexpr u32 kPer = 2048u / kThreads;           // primitives per thread and round
+    static_assert(kBinBlockMax / kThreads <= 32u, "a bit for each of a thread's primitives");
     static constexpr u32 kWaves = kThreads / kWave;
     static constexpr u32 kRounds = LDS_TILES / kThreads;    // counters per thread
 };
 constexpr u32 kGiantArea = 2048;    // listed rectangles beyond this many tiles get a workgroup, not a wavefront
 
-// Where the list of counting workgroup b starts: the pairs of all primitives before its own, from
+// Where the list of the counting workgroup whose first preprocess group is b starts: the pairs of all primitives before its own, from
 // the two-level prefix sum the projection stage left (block_offsets inside a group of kScanGroup
 // preprocess workgroups, plus the totals of the groups before).  Called by the whole workgroup
 // ahead of a barrier; one partial sum per wavefront goes to s_part, list_first_finish adds them.
@@ -158,7 +159,7 @@ template <u32 THREADS>
 __device__ __forceinline__ void list_first_start(const u64 *__restrict__ group_totals, u32 b, u64 *s_part,
                                                  u32 tid, u32 lane, u32 wv)
 {
-    const u32 groups_before = (b * (kBinBlock / kPreBlock)) / kScanGroup;
+    const u32 groups_before = b / kScanGroup;
     u64 part = 0;
     for (u32 g = tid; g < groups_before; g += THREADS) part += group_totals[g];
 #pragma unroll
@@ -168,7 +169,7 @@ __device__ __forceinline__ void list_first_start(const u64 *__restrict__ group_t
 template <u32 WAVES>
 __device__ __forceinline__ u64 list_first_finish(const u64 *__restrict__ block_offsets, u32 b, const u64 *s_part)
 {
-    u64 first = block_offsets[b * (kBinBlock / kPreBlock)];
+    u64 first = block_offsets[b];
 #pragma unroll
     for (u32 k = 0; k < WAVES; ++k) first += s_part[k];
     return first;
@@ -198,59 +199,59 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     bool other_way = false;
     if constexpr (Dense::kDense) other_way = header->dup_count >= dense.dense_min;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const u32 block = bin_block(n, num_tiles, header->ordered != 0u);
+    const u32 beg = blockIdx.x * block, end = n - beg < block ? n : beg + block;
+    if constexpr (Dense::kDense) {
+        if (other_way) {                                    // the same for the whole workgroup
+            sort_chunk<kThreads, TIGHT>(dense, reinterpret_cast<u64 *>(s_hist));
+            return;
+        }
+    }
+    if ((u64)blockIdx.x * block >= n) return;               // there for a chunk, or for smaller blocks
     {   // the projection stage counted the pairs of every 256 primitives: a workgroup none of whose
         // primitives was binned (culled, or a skipped voxel range) leaves without reading one
-        u32 pairs = 0;
-#pragma unroll
-        for (u32 q = 0; q < kBinBlock / kPreBlock; ++q) {
-            const u32 pb = blockIdx.x * (kBinBlock / kPreBlock) + q;
-            pairs |= pb < pre_blocks ? block_sums[pb] : 0u;
-        }
-        if constexpr (Dense::kDense) {
-            if (other_way) {                                // the same for the whole workgroup
-                sort_chunk<kThreads, TIGHT>(dense, reinterpret_cast<u64 *>(s_hist));
-                return;
-            }
-            if ((u64)blockIdx.x * kBinBlock >= n) return;   // there for a chunk only
-        }
-        if (pairs == 0u) {                                  // the same for the whole workgroup
+        const u32 pb = beg / kPreBlock + lane;
+        static_assert(kBinBlockMax / kPreBlock <= kWave, "a lane for each");
+        const bool some = lane < block / kPreBlock && pb < pre_blocks && block_sums[pb] != 0u;
+        if (__builtin_amdgcn_ballot_w64(some) == 0ull) {    // the same for the whole workgroup
             if (LDS && tid == 0) bin_count[blockIdx.x] = 0;
             return;
         }
     }
-    // everything this thread will need is requested at once: one round trip to memory
-    u32 cnt[kPer], mask[kPer];
-    ushort4 r[kPer];
-    bool any = false;
+    // everything that a thread needs of its primitives of a round is requested at once, a round ahead
+    struct Round { u32 cnt[kPer], mask[kPer]; ushort4 r[kPer]; } next;
+    auto request = [&](u32 first) {
 #pragma unroll
-    for (u32 j = 0; j < kPer; ++j) {
-        const u32 i = blockIdx.x * kBinBlock + j * kThreads + tid;
-        cnt[j] = i < n ? tiles_touched[i] : 0u;
-        r[j] = i < n ? rect[i] : make_ushort4(0, 0, 0, 0);
-        mask[j] = (TIGHT && LDS && i < n) ? tile_masks[i] : 0u;
-    }
+        for (u32 j = 0; j < kPer; ++j) {
+            const u32 i = first + j * kThreads + tid;
+            const bool in = i < end;
+            next.cnt[j] = in ? tiles_touched[i] : 0u;
+            next.r[j] = in ? rect[i] : make_ushort4(0, 0, 0, 0);
+            next.mask[j] = (TIGHT && LDS && in) ? tile_masks[i] : 0u;
+        }
+    };
+    request(beg);
     if (LDS) {
-        list_first_start<kThreads>(group_totals, blockIdx.x, s_part, tid, lane, wv);
+        list_first_start<kThreads>(group_totals, beg / kPreBlock, s_part, tid, lane, wv);
         for (u32 t = tid; t < num_tiles; t += kThreads) s_hist[t] = 0;
         if (tid == 0) s_next = 0;
     }
+    __syncthreads();
+    u32 large_bits = 0, giant_bits = 0;                     // bit k: this thread's primitive beg + k kThreads + tid goes to the list
+    for (u32 first = beg, k = 0; first < end; first += kPer * kThreads) {
+        const Round now = next;
+        request(first + kPer * kThreads);
 #pragma unroll
-    for (u32 j = 0; j < kPer; ++j) any = any || cnt[j] != 0u;
-    if (!__syncthreads_or(any)) {                           // nothing of this workgroup was binned
-        if (LDS && tid == 0) bin_count[blockIdx.x] = 0;
-        return;
-    }
-    u32 large_bits = 0, giant_bits = 0;                     // bit j: primitive j of this thread goes to the list
-#pragma unroll
-    for (u32 j = 0; j < kPer; ++j) {
-        const u32 area = cnt[j] ? ((u32)r[j].z - (u32)r[j].x) * ((u32)r[j].w - (u32)r[j].y) : 0u;
-        if (LDS && area > 0u && area <= kSmallMax) {
-            walk_small<TIGHT>(r[j], area, mask[j], tiles_x, [&](u32 tile) {
-                if (tile < num_tiles) atomicAdd(&s_hist[tile], 1u);     // a rectangle never leaves the grid; a corrupt one must not either
-            });
+        for (u32 j = 0; j < kPer; ++j, ++k) {
+            const u32 area = now.cnt[j] ? ((u32)now.r[j].z - (u32)now.r[j].x) * ((u32)now.r[j].w - (u32)now.r[j].y) : 0u;
+            if (LDS && area > 0u && area <= kSmallMax) {
+                walk_small<TIGHT>(now.r[j], area, now.mask[j], tiles_x, [&](u32 tile) {
+                    if (tile < num_tiles) atomicAdd(&s_hist[tile], 1u);     // a rectangle never leaves the grid; a corrupt one must not either
+                });
+            }
+            if (area > kGiantArea) giant_bits |= 1u << k;
+            else if (area > kSmallMax) large_bits |= 1u << k;
         }
-        if (area > kGiantArea) giant_bits |= 1u << j;
-        else if (area > kSmallMax) large_bits |= 1u << j;
     }
     // the lists of the other primitives (wavefront-sized rectangles from the front of big_idx,
     // workgroup-sized ones from the back): one global atomic each per workgroup that has any
@@ -278,17 +279,15 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
         __syncthreads();
         u32 slot = s_base[0] + before + incl - my_large;
         u32 slot2 = s_base[1] + before2 + incl2 - my_giant;
-#pragma unroll
-        for (u32 j = 0; j < kPer; ++j) {
-            const u32 i = blockIdx.x * kBinBlock + j * kThreads + tid;
-            // the two lists hold one entry per primitive at most, n in all, and never meet
-            if (large_bits & (1u << j)) { if (slot < n) big_idx[slot] = i; ++slot; }
-            if (giant_bits & (1u << j)) { if (slot2 < n) big_idx[n - 1u - slot2] = i; ++slot2; }
-        }
+        // the two lists hold one entry per primitive at most, n in all, and never meet
+        for (; large_bits; large_bits &= large_bits - 1u, ++slot)
+            if (slot < n) big_idx[slot] = beg + (u32)__builtin_ctz(large_bits) * kThreads + tid;
+        for (; giant_bits; giant_bits &= giant_bits - 1u, ++slot2)
+            if (slot2 < n) big_idx[n - 1u - slot2] = beg + (u32)__builtin_ctz(giant_bits) * kThreads + tid;
     }
     if (!LDS) return;
     // The tiles this workgroup touched, compacted to the front of s_hist as tile << kRunBits | (count - 1)
-    // (a workgroup holds kBinBlock primitives and a primitive has one pair per tile at most): every
+    // (a workgroup holds at most kBinBlockMax primitives and a primitive has one pair per tile at most): every
     // thread first reads its counters, then, all reads done, the entries are written.
     u32 c[kRounds];
 #pragma unroll
@@ -311,7 +310,7 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     }
     __syncthreads();
     const u32 touched = s_next;
-    const u64 first = list_first_finish<kWaves>(block_offsets, blockIdx.x, s_part);
+    const u64 first = list_first_finish<kWaves>(block_offsets, beg / kPreBlock, s_part);
     if (tid == 0) bin_count[blockIdx.x] = touched;
     // one reservation per touched tile: the run of this workgroup starts where the tile's counter
     // stood; up to kFlush entries per thread with their atomics in flight together
@@ -649,7 +648,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
 }
 
 // ---------------------------------------------------------------- emit
-// Workgroups [0, bin_blocks) repeat the walk of the small rectangles of their kBinBlock primitives; the
+// Workgroups [0, bin_blocks) repeat the walk of the small rectangles of their primitives; the
 // LDS counters now start at the tile's range start + the workgroup's run start and hand out
 // positions.  The workgroups behind them walk the listed primitives and advance the tiles'
 // running positions pair by pair.
@@ -689,39 +688,49 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void emit_kernel(
         return;
     }
     if (!LDS) return;                                       // every primitive is on a list
+    const u32 block = bin_block(n, num_tiles, header->ordered != 0u);
+    if ((u64)blockIdx.x * block >= n) return;
     const u32 entries = bin_count[blockIdx.x];
     if (entries == 0u) return;                              // the same for the whole workgroup
-    list_first_start<kThreads>(group_totals, blockIdx.x, s_part, tid, lane, wv);
-    // this thread's primitives: requested now, used after the counters are set up
-    u32 cnt[kPer], mask[kPer], dbits[kPer];
-    ushort4 r[kPer];
+    const u32 beg = blockIdx.x * block, end_prim = n - beg < block ? n : beg + block;
+    list_first_start<kThreads>(group_totals, beg / kPreBlock, s_part, tid, lane, wv);
+    // this thread's primitives of a round: requested a round ahead, the first before the counters are set up
+    struct Round { u32 cnt[kPer], mask[kPer], dbits[kPer]; ushort4 r[kPer]; } next;
+    auto request = [&](u32 from) {
 #pragma unroll
-    for (u32 j = 0; j < kPer; ++j) {
-        const u32 i = blockIdx.x * kBinBlock + j * kThreads + tid;
-        cnt[j] = i < n ? tiles_touched[i] : 0u;
-        r[j] = i < n ? rect[i] : make_ushort4(0, 0, 0, 0);
-        mask[j] = (TIGHT && i < n) ? tile_masks[i] : 0u;
-        dbits[j] = i < n ? __float_as_uint(depth[i]) : 0u;
-    }
+        for (u32 j = 0; j < kPer; ++j) {
+            const u32 i = from + j * kThreads + tid;
+            const bool in = i < end_prim;
+            next.cnt[j] = in ? tiles_touched[i] : 0u;
+            next.r[j] = in ? rect[i] : make_ushort4(0, 0, 0, 0);
+            next.mask[j] = (TIGHT && in) ? tile_masks[i] : 0u;
+            next.dbits[j] = in ? __float_as_uint(depth[i]) : 0u;
+        }
+    };
+    request(beg);
     __syncthreads();
-    const u64 first = list_first_finish<kWaves>(block_offsets, blockIdx.x, s_part);
+    const u64 first = list_first_finish<kWaves>(block_offsets, beg / kPreBlock, s_part);
     for (u32 k = tid; k < entries; k += kThreads) {
         if (first + k >= list_capacity) break;
         const uint2 e = list[first + k];
         if (e.x < num_tiles) s_cur[e.x] = WIDE ? e.y : (u32)tile_offsets[e.x] + e.y;
     }
     __syncthreads();
+    for (u32 from = beg; from < end_prim; from += kPer * kThreads) {
+        const Round now = next;
+        request(from + kPer * kThreads);
 #pragma unroll
-    for (u32 j = 0; j < kPer; ++j) {
-        const u32 area = cnt[j] ? ((u32)r[j].z - (u32)r[j].x) * ((u32)r[j].w - (u32)r[j].y) : 0u;
-        if (area == 0u || area > kMaskArea) continue;
-        const u64 comp = ((u64)dbits[j] << 32) | (u64)(blockIdx.x * kBinBlock + j * kThreads + tid);
-        walk_small<TIGHT>(r[j], area, mask[j], pp.tiles_x, [&](u32 tile) {
-            if (tile >= num_tiles) return;
-            const u32 at = atomicAdd(&s_cur[tile], 1u);
-            const u64 pos = WIDE ? tile_offsets[tile] + at : (u64)at;
-            if (pos < capacity) keys[pos] = comp;
-        });
+        for (u32 j = 0; j < kPer; ++j) {
+            const u32 area = now.cnt[j] ? ((u32)now.r[j].z - (u32)now.r[j].x) * ((u32)now.r[j].w - (u32)now.r[j].y) : 0u;
+            if (area == 0u || area > kMaskArea) continue;
+            const u64 comp = ((u64)now.dbits[j] << 32) | (u64)(from + j * kThreads + tid);
+            walk_small<TIGHT>(now.r[j], area, now.mask[j], pp.tiles_x, [&](u32 tile) {
+                if (tile >= num_tiles) return;
+                const u32 at = atomicAdd(&s_cur[tile], 1u);
+                const u64 pos = WIDE ? tile_offsets[tile] + at : (u64)at;
+                if (pos < capacity) keys[pos] = comp;
+            });
+        }
     }
 }
 

@@ -14,9 +14,7 @@ typedef uint32_t u32;
 
 constexpr u32 kWave = 64;               // CDNA wavefront width
 constexpr u32 kPreBlock = LMK_GS_PRE_BLOCK;   // primitives per preprocess workgroup
-constexpr u32 kBinBlock = 2048;         // primitives per workgroup of the counting and emit kernels of stage 2
 constexpr u32 kScanGroup = 256;         // preprocess workgroups per group of the two-level prefix sum
-static_assert(kScanGroup % (kBinBlock / kPreBlock) == 0, "the blocks of one counting workgroup lie in one group");
 // The counting and emit kernels keep one counter per tile in LDS: up to 8192 tiles (1080p has
 // 8160) in 32 KB, up to 32768 (2160p has 32400) in 128 KB.  Larger images take the route of the
 // large rectangles for every primitive: one global atomic per pair.
@@ -34,7 +32,7 @@ __device__ __forceinline__ void wave_fence()
 struct ScratchHeader {
     u64 dup_count;      // D = pairs of the frame = sum of tiles_touched (known when lmk_gs_preprocess is done)
     int32_t status;     // LMK_GS_* code of the frame's latest stage 2 (LMK_GS_OK after stage 1)
-    int32_t pad;
+    u32 ordered;        // the primitives are in voxel order: the projection had an index
     u32 big_count;      // stage 2: primitives on the deferred list, from the front (one wavefront each)
     u32 giant_count;    // ... and from the back (one workgroup each)
     u32 pad2[2];
@@ -58,8 +56,27 @@ struct ScratchLayout {
     size_t spare;         // 8 bytes [capacity / 2048 + 2]  no kernel's; the workspace keeps the size that callers have planned with
     size_t total;
     u32 pre_blocks;       // ceil(n / kPreBlock)
-    u32 bin_blocks;       // ceil(n / kBinBlock)
+    u32 bin_blocks;       // counting workgroups: of scenes in order, the others have fewer
 };
+
+// Primitives per workgroup of the counting and emit kernels of stage 2: a power of two of whole preprocess groups, so that those of
+// one workgroup lie in one group of kScanGroup.  Small scenes are short of workgroups, and a workgroup's time is the latency of its steps;
+// large ones in no spatial order have so few pairs per workgroup and tile that every pair costs an atomic, fewer the more
+// primitives share a workgroup.  Whether there is an order the device knows, by whether the projection had an index
+// (ScratchHeader::ordered); grids are sized for the smaller.  Both kernels, us, 512, 1024, 2048, 4096, 8192 primitives:
+//   10 000 at 256 x 256      13.6  15.9  19.9  29.4  48.8      1.2 M inside, ordered   29.2  30.1  32.3  45.8  68.2
+//   30 011 at 333 x 217      11.4  12.2  15.0  22.4  35.6      3 M overview, ordered   82.6  59.0  52.1  55.4  63.7
+//   500 000 in a cube        90.3  76.5  71.1  75.1  96.1      20 M of a city           823   601   451   373   340
+// and all of stage 2: 60 000 in a cube 37.6 37.4 43.2 55.9 73.0, 250 000 61.0 60.8 59.0 72.2 93.7, in order 49.2 47.3 55.8 73.6 94.5; 3 M of
+// a city 163 128 111 98 100; 6 M 278 217 173 155 140, in order 99 85 81 89 105.
+constexpr u32 kBinBlockMax = 8192;
+static_assert(kScanGroup % (kBinBlockMax / kPreBlock) == 0, "the blocks of one counting workgroup lie in one group");
+__host__ __device__ __forceinline__ u32 bin_block(u32 n, u32 tiles, bool ordered)
+{
+    if (tiles <= kLdsTilesSmall && n <= (ordered ? 1u << 17 : 1u << 16)) return 512u;
+    if (tiles <= kLdsTilesSmall && n <= (ordered ? 1u << 18 : 1u << 17)) return 1024u;
+    return ordered || n < 2000000u ? 2048u : (n < 5000000u ? 4096u : kBinBlockMax);
+}
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -67,7 +84,8 @@ inline ScratchLayout scratch_layout(u32 n, u64 capacity, u32 tiles)
 {
     ScratchLayout L;
     L.pre_blocks = (n + kPreBlock - 1) / kPreBlock;
-    L.bin_blocks = (n + kBinBlock - 1) / kBinBlock;
+    const u32 block = bin_block(n, tiles, true);
+    L.bin_blocks = (u32)(((u64)n + block - 1) / block);
     size_t o = 0;
     L.header = o;        o += align256(sizeof(ScratchHeader));
     L.tile_count = o;    o += align256(sizeof(u32) * 2 * ((size_t)tiles + 1));

@@ -196,12 +196,12 @@ hipError_t launch_build_cov3d(const lmk_gs_gaussians &g, float *cov3d, hipStream
 // into them with atomics, and leaves them zero again).  Called by every thread of a grid of
 // `threads` threads, `g` = global thread id.
 __device__ __forceinline__ void reset_frame_state(ScratchHeader *header, u32 *__restrict__ tile_count,
-                                                  u32 num_tiles, u32 g, u32 threads)
+                                                  u32 num_tiles, u32 g, u32 threads, bool ordered = false)
 {
     if (g == 0) {
         header->dup_count = 0;
         header->status = LMK_GS_OK;
-        header->pad = 0;
+        header->ordered = ordered ? 1u : 0u;
         header->big_count = 0;
         header->giant_count = 0;
         header->pad2[0] = header->pad2[1] = 0;
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
 {
     __shared__ u32 s_part[kPreBlock / kWave];
     const u32 i = blockIdx.x * kPreBlock + threadIdx.x;
-    reset_frame_state(header, tile_count, num_tiles, i, gridDim.x * kPreBlock);
+    reset_frame_state(header, tile_count, num_tiles, i, gridDim.x * kPreBlock, block_range != nullptr);
     if (block_range) {
         // voxel filter: does any voxel holding one of this workgroup's primitives pass?  The caller's flags
         // of this frame, or the test itself: by eight lanes a voxel where the group has primitives of a voxel or
