@@ -364,7 +364,7 @@ __device__ __forceinline__ void for_each_listed(const ScratchHeader *__restrict_
 
 static_assert(kLargeThreads == kDenseThreads, "the launch carries the count of both ways");
 template <bool TIGHT, class Dense>
-__global__ __launch_bounds__(kLargeThreads, Dense::kDense ? 5 : 1) void count_large_kernel(     // (the other way's tests: 96 registers)
+__global__ __launch_bounds__(kLargeThreads, Dense::kDense ? 6 : 1) void count_large_kernel(     // (the other way's count: 79 registers)
     const ushort4 *__restrict__ rect, const float4 *__restrict__ feat, ProjParams pp, u32 n, u32 num_tiles,
     u32 *__restrict__ large_count, const ScratchHeader *__restrict__ header, const u32 *__restrict__ big_idx,
     u32 giant_blocks, u32 blocks, u32 *__restrict__ tile_count, Dense dense)

@@ -10,7 +10,7 @@
 //            ordered primitives.  64 rectangles at a time are tested against the bin; those that
 //            meet it queue up in order, and 256 of them at a time (lane = primitive) get a mask of the 16
 //            tiles they keep: all or none where a look at the whole bin decides (an inner or an outer
-//            part of a large splat), else from the tile test.  Per tile the number kept is the
+//            part of a large splat), else from where its ellipse crosses the rows of tiles, and the tile test at its ends.  Per tile the number kept is the
 //            population count of a ballot; one atomic per wavefront and tile adds it up.  Where the workspace has the room
 //            the primitives that keep a tile are left with their masks for the emit ("records").
 //   scan     tile_scan_kernel, as for every frame.
@@ -25,8 +25,8 @@
 //
 // Bound by the vector instructions of the tile tests (count) and by writing 12 bytes a
 // pair (emit).  What writing costs is the lines that are not written whole: runs of 150 pairs from anywhere reach 2.4 to 3 TB/s, from
-// multiples of 32 pairs on 5.4.  400 000 primitives at 3840 x 2160, 615 M pairs, 48 M records: order 0.1 ms, count 1.26, emit
-// 1.87 ms (4.0 TB/s); with records but runs as they come 2.9; with the walk instead of records (count 1.16 without them) 3.3;
+// multiples of 32 pairs on 5.4.  400 000 primitives at 3840 x 2160, 615 M pairs, 48 M records: order 0.1 ms, count 1.05, emit
+// 1.87 ms (4.0 TB/s); with all 16 tiles of an undecided primitive tested count 1.26, rectangles compared a word at a time 1.09; with records but runs as they come 2.9; with the walk instead of records 3.3 (count then 0.1 less);
 // counting, emitting and sorting pairs took 8.5 + 10.4 + 15.7 ms.  Tried there: bins of 8 x 8 tiles
 // (a third of the tested tiles kept instead of 44 %; count 1.9 ms), testing every tile of every candidate
 // (count 1.8 ms), storing each ballot's pairs as they come (emit 3.7 ms); from records one tile at a time through LDS (1.90 ms), multiples
@@ -60,7 +60,6 @@ constexpr u32 kDenseClass = 5;                      // entry of ScratchLayout::c
 
 constexpr u32 kSortChunk = 4096;                            // primitives sorted in LDS by one workgroup
 constexpr u32 kRankThreads = 256;
-constexpr u32 kBinEdge = 4, kBinTiles = kBinEdge * kBinEdge;
 constexpr u32 kDenseThreads = 256, kDenseWaves = kDenseThreads / kWave;
 constexpr u32 kSets = 4, kBatch = kSets * kWave;            // primitives of an emit batch
 static_assert(kBinTiles <= 16, "masks are 16 bits wide");
@@ -334,6 +333,8 @@ __device__ __forceinline__ void bin_candidates(const ushort4 *__restrict__ rects
     // kAhead rounds of 64 rectangles in flight: most rounds find little, and the walk is then bound by the
     // latency of these loads (one round ahead: 0.27 ms for 300 000 primitives and the 510 bins of 1080p)
     constexpr u32 kAhead = 4;
+    typedef short tiles_t __attribute__((ext_vector_type(2)));
+    const tiles_t bin_beg = __builtin_bit_cast(tiles_t, w.bx | (w.by << 16)), bin_end = __builtin_bit_cast(tiles_t, (w.bx + kBinEdge) | ((w.by + kBinEdge) << 16));
     const u64 *r64 = reinterpret_cast<const u64 *>(rects);
     u32 queued = 0;
     u64 next[kAhead];                                       // x0 | y0 | x1 | y1, 16 bits each
@@ -352,10 +353,11 @@ __device__ __forceinline__ void bin_candidates(const ushort4 *__restrict__ rects
         }
 #pragma unroll
         for (u32 q = 0; q < kAhead; ++q) {
-            const u32 lo = (u32)r[q], hi = (u32)(r[q] >> 32);
-            // an empty rectangle (all zero) meets nothing
-            const bool meets = (lo & 0xffffu) < w.bx + kBinEdge && (hi & 0xffffu) > w.bx &&
-                               (lo >> 16) < w.by + kBinEdge && (hi >> 16) > w.by;
+            // x0 < bx + kBinEdge, y0 < by + kBinEdge, bx < x1, by < y1, two 16-bit differences at a time (a grid has at most 4096
+            // tiles along an axis); an empty rectangle (all zero) meets nothing
+            const u32 ahead = __builtin_bit_cast(u32, __builtin_bit_cast(tiles_t, (u32)r[q]) - bin_end);
+            const u32 behind = __builtin_bit_cast(u32, bin_beg - __builtin_bit_cast(tiles_t, (u32)(r[q] >> 32)));
+            const bool meets = (ahead & behind & 0x80008000u) == 0x80008000u;
             const u64 m = __builtin_amdgcn_ballot_w64(meets);
             if (meets) queue[queued + lanes_below(m)] = i0 + q * kWave + lane;
             queued += (u32)__builtin_popcountll(m);         // at most BATCH - 1 + 64
@@ -422,29 +424,35 @@ __device__ __forceinline__ Ops load_ops(u32 pos, const ushort4 *__restrict__ rec
     return p;
 }
 
-// the tiles of the bin that a primitive keeps, tile by tile, ROWS rows of tests in flight
-template <bool TIGHT, u32 ROWS>
+// the tiles of the bin that a primitive keeps: those of its rectangle, of which only those near its ellipse are asked
+template <bool TIGHT>
 __device__ __forceinline__ u32 bin_mask(const Ops &p, u32 bx, u32 by)
 {
-    u32 mask = 0;
-#pragma unroll ROWS
-    for (u32 j = 0; j < kBinEdge; ++j) {
-        const u32 ty = by + j;
-#pragma unroll
-        for (u32 i = 0; i < kBinEdge; ++i) {
-            const u32 tx = bx + i;
-            bool keep = ty >= p.y0 && ty < p.y1 && tx >= p.x0 && tx < p.x1;
-            if (TIGHT) keep = keep & tile_kept(p.t, tx, ty);
-            mask |= keep ? 1u << (j * kBinEdge + i) : 0u;
-        }
+    auto within = [](u32 first, u32 end, u32 from) -> uint2 {                  // of kBinEdge tiles from `from` on
+        const u32 a = first > from ? first - from : 0u, b = end > from ? end - from : 0u;
+        return make_uint2(a < kBinEdge ? a : kBinEdge, b < kBinEdge ? b : kBinEdge);
+    };
+    const uint2 cols = within(p.x0, p.x1, bx), rows = within(p.y0, p.y1, by);
+    if (cols.x >= cols.y || rows.x >= rows.y) return 0u;
+    const u32 rect = ((1u << cols.y) - (1u << cols.x)) * 0x1111u & ((1u << (kBinEdge * rows.y)) - (1u << (kBinEdge * rows.x)));
+    if (!TIGHT) return rect;
+    u32 mask, open;
+    bin_tiles(p.t, bx, by, mask, open);
+    mask &= rect;
+    open &= rect;
+    while (open) {
+        const u32 tile = (u32)__builtin_ctz(open);
+        open &= open - 1u;
+        if (tile_kept(p.t, bx + tile % kBinEdge, by + tile / kBinEdge)) mask |= 1u << tile;
     }
     return mask;
 }
+static_assert(kBinEdge == 4, "rows of four bits");
 
 // Masks of the queued primitives 0 .. count (count <= BATCH) to masks[0 .. BATCH): those that a look at the
 // whole bin decides first, then the others, put together so that the tile tests run on full wavefronts.
 // `undecided` is room for BATCH numbers.
-template <bool TIGHT, u32 BATCH, u32 ROWS>
+template <bool TIGHT, u32 BATCH>
 __device__ __forceinline__ void bin_masks(const u32 *queued, u32 count, const ushort4 *__restrict__ rects,
                                           const float4 *__restrict__ ops, u32 bx, u32 by, u32 lane,
                                           unsigned short *masks, unsigned short *undecided)
@@ -458,7 +466,7 @@ __device__ __forceinline__ void bin_masks(const u32 *queued, u32 count, const us
         if (k < count) {
             const Ops p = load_ops<TIGHT>(queued[k], rects, ops);
             if (TIGHT) ask = !bin_decided(p, bx, by, mask);
-            else mask = bin_mask<false, ROWS>(p, bx, by);
+            else mask = bin_mask<false>(p, bx, by);
         }
         masks[k] = (unsigned short)mask;
         if (TIGHT) {
@@ -473,7 +481,7 @@ __device__ __forceinline__ void bin_masks(const u32 *queued, u32 count, const us
         for (u32 j0 = 0; j0 < open; j0 += kWave) {
             if (j0 + lane < open) {
                 const u32 k = undecided[j0 + lane];
-                masks[k] = (unsigned short)bin_mask<true, ROWS>(load_ops<true>(queued[k], rects, ops), bx, by);
+                masks[k] = (unsigned short)bin_mask<true>(load_ops<true>(queued[k], rects, ops), bx, by);
             }
         }
         wave_fence();
@@ -511,7 +519,7 @@ __device__ __forceinline__ void dense_count(const DenseArgs &d, const ScratchHea
     u32 *rec = saved ? d.records + (size_t)w.bin * record_row(d.n) + w.beg : nullptr;
     u32 kept_prims = 0, waiting = 0;                        // records written, and in LDS
     bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
-        bin_masks<TIGHT, kBatch, kBinEdge>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
+        bin_masks<TIGHT, kBatch>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
         u32 m[kSets];
 #pragma unroll
         for (u32 set = 0; set < kSets; ++set) m[set] = my.mask[set * kWave + lane];
@@ -687,7 +695,7 @@ __device__ __forceinline__ void dense_emit(const DenseArgs &d, const ScratchHead
         finish();
     } else {
         bin_candidates<kBatch>(d.rects, w, lane, my.queue, [&](const u32 *queued, u32 count) {
-            bin_masks<TIGHT, kBatch, 2u>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
+            bin_masks<TIGHT, kBatch>(queued, count, d.rects, d.ops, w.bx, w.by, lane, my.mask, my.open);
             u32 m[kSets];
             u64 pair[kSets];
 #pragma unroll

@@ -102,6 +102,45 @@ __device__ __forceinline__ u32 row_kept(const TileTest &t, u32 ty, u32 x0, u32 x
     return kept + (b - a + 1u);
 }
 
+// The tiles of a bin of kBinEdge x kBinEdge, bit kBinEdge j + i = tile (bx + i, by + j): those that tile_kept surely keeps, and those that have
+// to be asked.  A tile is kept where its square meets the ellipse q = tau, and in a row of tiles, a strip of y, the ellipse
+// lies between its leftmost and rightmost points there (as in row_kept), so two square roots a row give the columns.  M
+// bounds A x^2 + C y^2 over the bin.  tile_reach is within 5e-6 M of the least q of a tile, and the ends in here are those of an
+// ellipse that differs by as little (cn and the products by some 1e-6 M in q, an end by 2e-6 of the bin's distance, which is 6e-6 M), so
+// that the ellipse of tau - slack, slack = 4e-5 M, holds no tile that is not kept, and beyond that of tau + slack none
+// is (over the random ellipses of tests/host/bin_tiles_driver.cpp none is wrong down to 5e-6 M).  Where the numbers are no
+// ellipse all are to be asked.
+constexpr u32 kBinEdge = 4, kBinTiles = kBinEdge * kBinEdge;
+__device__ __forceinline__ void bin_tiles(const TileTest &t, u32 bx, u32 by, u32 &sure, u32 &open)
+{
+    const float TS = (float)LMK_GS_TILE, h = 0.5f * TS - 0.5f, span = (float)((kBinEdge - 1u) * LMK_GS_TILE);
+    const float xc = ((float)(bx * LMK_GS_TILE) + 0.5f * TS) - t.u, yc = ((float)(by * LMK_GS_TILE) + 0.5f * TS) - t.v;   // centre of the first tile
+    const float fx = fmaxf(fabsf(xc - h), fabsf(xc + (span + h))), fy = fmaxf(fabsf(yc - h), fabsf(yc + (span + h)));
+    const float slack = 4e-5f * (t.A * fx * fx + t.C * fy * fy);
+    const float cn = t.C + t.B * t.rx, inv = __builtin_amdgcn_rcpf(t.A), bend = t.A * __builtin_amdgcn_rcpf(t.C * cn);
+    const float lo0 = (-h - xc) / TS, hi0 = (h - xc) / TS + 1.0f;
+    auto inside = [&](float level) -> u32 {
+        const float yr = t.rx * __builtin_amdgcn_sqrtf(fmaxf(level * bend, 0.0f));
+        u32 mask = 0;
+#pragma unroll
+        for (u32 j = 0; j < kBinEdge; ++j) {
+            const float y0 = yc + ((float)(j * LMK_GS_TILE) - h), y1 = yc + ((float)(j * LMK_GS_TILE) + h);
+            const float yR = __builtin_amdgcn_fmed3f(yr, y0, y1), yL = __builtin_amdgcn_fmed3f(-yr, y0, y1);
+            const float dR = (level - cn * yR * yR) * inv, dL = (level - cn * yL * yL) * inv;
+            const float right = t.rx * yR + __builtin_amdgcn_sqrtf(fmaxf(dR, 0.0f)), left = t.rx * yL - __builtin_amdgcn_sqrtf(fmaxf(dL, 0.0f));
+            const float hi = floorf(right / TS + hi0), lo = ceilf(left / TS + lo0);
+            const u32 c1 = (u32)__builtin_amdgcn_fmed3f(hi, 0.0f, (float)kBinEdge), c0 = (u32)__builtin_amdgcn_fmed3f(lo, 0.0f, (float)kBinEdge);
+            const bool some = dR >= 0.0f && c1 > c0;
+            mask |= (some ? (1u << c1) - (1u << c0) : 0u) << (kBinEdge * j);
+        }
+        return mask;
+    };
+    const bool sound = t.A > 0.0f && cn > 0.0f && slack + inv + fabsf(bend) + fabsf(t.rx) + fabsf(t.tau) < 3.0e38f;
+    const u32 outer = inside(t.tau + slack), inner = inside(t.tau - slack);
+    sure = sound ? inner & outer : 0u;
+    open = sound ? outer & ~inner : (1u << kBinTiles) - 1u;
+}
+
 // t / w and t % w for t < 2^22 (a tile grid has at most 2^22 tiles), 1 <= w <= 4096; inv_w = 1 / w
 __device__ __forceinline__ void div_tiles(u32 t, u32 w, float inv_w, u32 &row, u32 &col)
 {
