@@ -400,8 +400,9 @@ __global__ __launch_bounds__(kLargeThreads, Dense::kDense ? 6 : 1) void count_la
 // Within a bucket the order is whatever the atomics give -- it only decides which workgroup
 // starts first, never a result.  The counters stay as they are until both workgroups are done with them; the last kernel of the
 // per-tile sort leaves them zero for the next call.
-// With SMALL (up to 8192 tiles) every thread reads its eight counters once and everything else works
-// from registers and LDS.
+// With CHUNKS (1 up to 8192 tiles, 4 up to 32768) every thread reads its eight counters of each chunk of 8192 once, all together, and
+// everything else works from registers and LDS; more tiles (0) are read again for every step (32 400 tiles: 66 us so, 21 with
+// four chunks).
 //   classes[5]  (kDenseClass) 1 = the frame's lists come from dense_emit, sorted: nothing is emitted or sorted here
 constexpr u32 kSmallThreads = 64, kSmallItems = 8, kSmallCap = kSmallThreads * kSmallItems;   // 512
 constexpr u32 kLow = 2048;                                                                    // kMidThreads * kMidItems / 2
@@ -424,9 +425,10 @@ constexpr u32 kScanThreads = 1024, kScanItems = 8;
 constexpr u32 kOrderCopies = 16, kOrderBuckets = 2 * 33, kOrderCounters = kOrderBuckets * kOrderCopies;
 constexpr u32 kOrderStage = 32768;
 static_assert(kOrderCounters <= 2 * kScanThreads, "the counters are scanned two per thread");
-static_assert(kLdsTilesSmall == kScanThreads * kScanItems, "SMALL: one round of kScanItems tiles per thread");
+constexpr u32 kScanChunk = kScanThreads * kScanItems;
+static_assert(kLdsTilesSmall == kScanChunk && kLdsTilesLarge == 4u * kScanChunk && kOrderStage >= 4u * kScanChunk, "chunks of kScanItems tiles per thread");
 
-template <bool SMALL>
+template <u32 CHUNKS>
 __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     const u32 *__restrict__ tile_count, const u32 *__restrict__ large_count, u32 num_tiles, u64 capacity, ScratchHeader *__restrict__ header,
     u64 *__restrict__ tile_offsets, u32 *__restrict__ tile_cursor, u64 *__restrict__ prim_offsets_if_empty,
@@ -441,24 +443,30 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     __shared__ u32 s_wave[kWaves];
     // slots are scattered and one compute unit does all the address work: the order is put
     // together in LDS and written out in whole lines (images of up to kOrderStage tiles)
-    __shared__ __attribute__((aligned(16))) u32 s_space[SMALL ? 2 * kLdsTilesSmall : kOrderStage];
+    constexpr u32 kHeld = CHUNKS * kScanItems;
+    constexpr bool HELD = CHUNKS > 0;
+    __shared__ __attribute__((aligned(16))) u32 s_space[CHUNKS == 1u ? 2 * kScanChunk : kOrderStage];
     u32 *const s_order = s_space;
-    u32 *const s_len = s_space + (SMALL ? kLdsTilesSmall : 0u);     // SMALL: the list lengths
-    const bool staged = SMALL || num_tiles <= kOrderStage;
+    u32 *const s_len = s_space + kScanChunk;                        // HELD: the list lengths of a chunk
+    const bool staged = HELD || num_tiles <= kOrderStage;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
 
     // ---- (1) D
     // a tile's list = the runs of the counting workgroups (tile_count) followed by the pairs of
     // the listed primitives (large_count)
-    u32 mine8[kScanItems], runs8[kScanItems];  // SMALL: list length and length of the runs of tiles j * kScanThreads + tid
+    u32 held[HELD ? kHeld : 1], runs[HELD ? kHeld : 1];    // HELD: list length and length of the runs of tiles j * kScanThreads + tid
     u64 part = 0;
-    if (SMALL) {
+    if constexpr (HELD) {
 #pragma unroll
-        for (u32 j = 0; j < kScanItems; ++j) {
+        for (u32 j = 0; j < kHeld; ++j) {
             const u32 t = j * kScanThreads + tid;
-            runs8[j] = t < num_tiles ? tile_count[t] : 0u;
-            mine8[j] = runs8[j] + (t < num_tiles ? large_count[t] : 0u);
-            part += mine8[j];
+            runs[j] = t < num_tiles ? tile_count[t] : 0u;
+            held[j] = t < num_tiles ? large_count[t] : 0u;
+        }
+#pragma unroll
+        for (u32 j = 0; j < kHeld; ++j) {
+            held[j] += runs[j];
+            part += held[j];
         }
     } else {
         for (u32 t = tid; t < num_tiles; t += kScanThreads) part += (u64)tile_count[t] + large_count[t];
@@ -481,62 +489,70 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
         // with no primitives nothing else writes the one-entry prefix sum over the primitives
         if (prim_offsets_if_empty) prim_offsets_if_empty[0] = 0;
     }
-    if (SMALL) {
+    if constexpr (HELD) {
 #pragma unroll
-        for (u32 j = 0; j < kScanItems; ++j) {
-            if (overflow) { mine8[j] = 0u; runs8[j] = 0u; }
-            s_len[j * kScanThreads + tid] = mine8[j];
-        }
+        for (u32 j = 0; j < kHeld; ++j)
+            if (overflow) { held[j] = 0u; runs[j] = 0u; }
     }
     __syncthreads();                           // s_sum is reused below
 
-    // ---- (2) of up to kLdsTilesSmall tiles: consecutive lanes read and write consecutive tiles, and LDS changes between that
+    // ---- (2) HELD: consecutive lanes read and write consecutive tiles, and LDS changes between that
     // and kScanItems consecutive tiles per thread (addressed in memory like that, one compute unit takes some 3.5 us for
     // the lines of the offsets alone; frame of 500 000 at 1080p, 8160 tiles: 249.0 us so, 239.5 through LDS)
-    if (SMALL && ranges_part) {
-        const uint4 c0 = *reinterpret_cast<const uint4 *>(s_len + tid * kScanItems), c1 = *reinterpret_cast<const uint4 *>(s_len + tid * kScanItems + 4);
-        const u32 c[kScanItems] = { c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w };
-        u64 mine = 0;
+    if (HELD && ranges_part) {
+        u64 carry = 0;
 #pragma unroll
-        for (u32 j = 0; j < kScanItems; ++j) mine += c[j];
-        u64 incl = mine;
+        for (u32 chunk = 0; chunk < CHUNKS; ++chunk) {
+            if (chunk * kScanChunk > num_tiles) break;
+            if (chunk) __syncthreads();        // the chunk before has been written
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const u64 v = __shfl_up(incl, o, 64);
-            if ((int)lane >= o) incl += v;
-        }
-        if (lane == kWave - 1) s_sum[wv] = incl;
-        __syncthreads();                       // also: every length has been read
-        u64 run = incl - mine, total = 0;
+            for (u32 j = 0; j < kScanItems; ++j) s_len[j * kScanThreads + tid] = held[HELD ? chunk * kScanItems + j : 0u];
+            __syncthreads();
+            const uint4 c0 = *reinterpret_cast<const uint4 *>(s_len + tid * kScanItems), c1 = *reinterpret_cast<const uint4 *>(s_len + tid * kScanItems + 4);
+            const u32 c[kScanItems] = { c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w };
+            u64 mine = 0;
 #pragma unroll
-        for (u32 k = 0; k < kWaves; ++k) {
-            const u64 v = s_sum[k];
-            if (k < wv) run += v;
-            total += v;
-        }
-        u64 *s_run = reinterpret_cast<u64 *>(s_space);
+            for (u32 j = 0; j < kScanItems; ++j) mine += c[j];
+            u64 incl = mine;
 #pragma unroll
-        for (u32 j = 0; j < kScanItems; ++j) { s_run[tid * kScanItems + j] = run; run += c[j]; }
-        __syncthreads();
+            for (int o = 1; o < 64; o <<= 1) {
+                const u64 v = __shfl_up(incl, o, 64);
+                if ((int)lane >= o) incl += v;
+            }
+            if (lane == kWave - 1) s_sum[wv] = incl;
+            __syncthreads();                   // also: every length has been read
+            u64 run = carry + incl - mine, total = 0;
 #pragma unroll
-        for (u32 j = 0; j < kScanItems; ++j) {
-            const u32 t = j * kScanThreads + tid;
-            if (t <= num_tiles) {
-                const u64 at = s_run[t];
-                tile_offsets[t] = at;
-                tile_cursor[t] = (wide ? 0u : (u32)at) + runs8[j];     // the listed primitives' pairs follow the runs
+            for (u32 k = 0; k < kWaves; ++k) {
+                const u64 v = s_sum[k];
+                if (k < wv) run += v;
+                total += v;
+            }
+            carry += total;
+            u64 *s_run = reinterpret_cast<u64 *>(s_space);
+#pragma unroll
+            for (u32 j = 0; j < kScanItems; ++j) { s_run[tid * kScanItems + j] = run; run += c[j]; }
+            __syncthreads();
+#pragma unroll
+            for (u32 j = 0; j < kScanItems; ++j) {
+                const u32 in = j * kScanThreads + tid, t = chunk * kScanChunk + in;
+                if (t <= num_tiles) {
+                    const u64 at = s_run[in];
+                    tile_offsets[t] = at;
+                    tile_cursor[t] = (wide ? 0u : (u32)at) + runs[HELD ? chunk * kScanItems + j : 0u];     // the listed primitives' pairs follow the runs
+                }
             }
         }
-        if (num_tiles == kLdsTilesSmall && tid == 0) {
-            tile_offsets[num_tiles] = total;
-            tile_cursor[num_tiles] = wide ? 0u : (u32)total;
+        if (num_tiles == CHUNKS * kScanChunk && tid == 0) {
+            tile_offsets[num_tiles] = carry;
+            tile_cursor[num_tiles] = wide ? 0u : (u32)carry;
         }
         return;
     }
 
     // ---- (2) per-tile ranges of more tiles: kScanItems consecutive ones per thread, entry num_tiles = the end
     u64 carry = 0;
-    for (u32 base = 0; !SMALL && ranges_part && base <= num_tiles; base += kScanThreads * kScanItems) {
+    for (u32 base = 0; !HELD && ranges_part && base <= num_tiles; base += kScanChunk) {
         const u32 t0 = base + tid * kScanItems;
         u32 c[kScanItems], runs[kScanItems];
         u64 mine = 0;
@@ -586,14 +602,25 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     };
     for (u32 k = tid; k < kOrderCounters; k += kScanThreads) s_cnt[k] = 0;
     __syncthreads();
-    const u32 sweep = SMALL ? 1u : kScanThreads * kScanItems;
-    for (u32 base = 0; base < (SMALL ? 1u : num_tiles); base += sweep) {
+    // f(tile, list length) for this thread's tiles
+    auto each_tile = [&](auto &&f) {
+        if constexpr (HELD) {
 #pragma unroll
-        for (u32 j = 0; j < kScanItems; ++j) {
-            const u32 t = base + j * kScanThreads + tid;
-            if (t < num_tiles) atomicAdd(&s_cnt[order_counter(SMALL ? mine8[j] : (overflow ? 0u : tile_count[t] + large_count[t]))], 1u);
+            for (u32 j = 0; j < kHeld; ++j) {
+                const u32 t = j * kScanThreads + tid;
+                if (t < num_tiles) f(t, held[j]);
+            }
+        } else {
+            for (u32 base = 0; base < num_tiles; base += kScanChunk) {
+#pragma unroll
+                for (u32 j = 0; j < kScanItems; ++j) {
+                    const u32 t = base + j * kScanThreads + tid;
+                    if (t < num_tiles) f(t, overflow ? 0u : tile_count[t] + large_count[t]);
+                }
+            }
         }
-    }
+    };
+    each_tile([&](u32, u32 len) { atomicAdd(&s_cnt[order_counter(len)], 1u); });
     __syncthreads();
     // exclusive scan of the counters, two per thread
     const u32 k0 = 2 * tid, k1 = 2 * tid + 1;
@@ -621,20 +648,15 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
         classes[0] = huge; classes[3] = lng - huge; classes[1] = mid - lng; classes[2] = low - mid;
     }
     __syncthreads();                           // the counters are advanced below
-    for (u32 base = 0; base < (SMALL ? 1u : num_tiles); base += sweep) {
-#pragma unroll
-        for (u32 j = 0; j < kScanItems; ++j) {
-            const u32 t = base + j * kScanThreads + tid;
-            if (t >= num_tiles) continue;
-            const u32 slot = atomicAdd(&s_cnt[order_counter(SMALL ? mine8[j] : (overflow ? 0u : tile_count[t] + large_count[t]))], 1u);
-            if (staged) {
-                s_order[slot] = t;
-            } else {
-                order[slot] = t;
-                if (order_copy) order_copy[slot] = t;
-            }
+    each_tile([&](u32 t, u32 len) {
+        const u32 slot = atomicAdd(&s_cnt[order_counter(len)], 1u);
+        if (staged) {
+            s_order[slot] = t;
+        } else {
+            order[slot] = t;
+            if (order_copy) order_copy[slot] = t;
         }
-    }
+    });
     if (staged) {
         __syncthreads();
         for (u32 k = tid; k < num_tiles; k += kScanThreads) {
@@ -1225,14 +1247,14 @@ hipError_t launch_bin_sort(const lmk_gs_projected &proj, u32 n, const ProjParams
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (num_tiles <= kLdsTilesSmall)
-        hipLaunchKernelGGL(tile_scan_kernel<true>, dim3(2), dim3(kScanThreads), 0, stream,
+    auto scan = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(2), dim3(kScanThreads), 0, stream,
                            tile_count, large_count, num_tiles, out.capacity, header, out.tile_offsets, tile_cursor,
                            n == 0 ? proj.offsets : nullptr, order, out.tile_order, classes, dense_min);
-    else
-        hipLaunchKernelGGL(tile_scan_kernel<false>, dim3(2), dim3(kScanThreads), 0, stream,
-                           tile_count, large_count, num_tiles, out.capacity, header, out.tile_offsets, tile_cursor,
-                           n == 0 ? proj.offsets : nullptr, order, out.tile_order, classes, dense_min);
+    };
+    if (num_tiles <= kLdsTilesSmall) scan(tile_scan_kernel<1u>);
+    else if (num_tiles <= kLdsTilesLarge) scan(tile_scan_kernel<4u>);
+    else scan(tile_scan_kernel<0u>);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (L.bin_blocks > 0) {
