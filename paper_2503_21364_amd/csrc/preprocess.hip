@@ -233,7 +233,7 @@ __device__ __forceinline__ void block_total(u32 cnt, u32 *s_part, u32 *__restric
 }
 
 template <u32 DEG>
-__global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
+__global__ __launch_bounds__(kPreBlock, DEG == 0 ? 8 : 1) void preprocess_kernel(
     const float *__restrict__ mean, const float *__restrict__ scale, const float *__restrict__ rot,
     const float *__restrict__ opacity, const float *__restrict__ sh, const float *__restrict__ cov3d, u32 n,
     ProjParams pp, ShConsts kc,
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
             const u32 bx0 = of_u(x0), by0 = of_u(y0), bw = of_u(w), barea = of_u(area);
             u32 c = 0;
             bool k0 = false;                                  // this lane's slot of the first 64
-            if (barea <= 8u * kWave) {
+            if (barea <= 2u * kWave) {
                 for (u32 t = lane; t < barea; t += kWave) {
                     const u32 row = t / bw;
                     const bool k = tile_kept(bt, bx0 + (t - row * bw), by0 + row);
@@ -457,9 +457,9 @@ __global__ __launch_bounds__(kPreBlock) void preprocess_kernel(
                     c += k ? 1u : 0u;
                 }
             } else {
-                // a row of tiles a lane, of which only those near the ends are asked (400 000 splats of 1500 tiles at
-                // 3840 x 2160: a frame 7240 us with 8 x 8 tiles a step, all asked, 6080 so; the line at 256, 512, 1024 tiles: 60 000
-                // at 1500 x 900 541, 534, 542 us, 5000 at 1200 x 1000 267, 259, 272)
+                // a row of tiles a lane, counted from its ends (400 000 splats of 1500 tiles at 3840 x 2160, projection alone: rows from 512
+                // tiles on, their ends found by asking tiles, 386 us, from two ellipses 190; from 256 180, 128 175, 64 178 us; 8000 of
+                // 100 at 1000 x 600 80.7, 73.2, 59.5, 53.2, 55.3)
                 const u32 bx1 = bx0 + bw, by1 = of_u(y1);
                 const float fx = fmaxf(fabsf((float)(bx0 * LMK_GS_TILE) - bt.u), fabsf((float)(bx1 * LMK_GS_TILE) - bt.u));
                 const float fy = fmaxf(fabsf((float)(by0 * LMK_GS_TILE) - bt.v), fabsf((float)(by1 * LMK_GS_TILE) - bt.v));

@@ -57,49 +57,37 @@ __device__ __forceinline__ float tile_reach(const TileTest &t, u32 tx, u32 ty)
 __device__ __forceinline__ bool tile_kept(const TileTest &t, u32 tx, u32 ty) { return tile_reach(t, tx, ty) <= t.tau; }
 
 // How many of the tiles x0 <= tx < x1 of row ty are kept, as tile_kept decides them, but asked only where that is not
-// certain.  Exactly taken, the least q of a tile is a convex function of tx; tile_reach is within 5e-6 M of it, M =
-// A fx^2 + C fy^2 over the rectangle, and `slack` is 2e-5 M.  So all tiles between two that are within tau - slack are
-// kept, and behind one beyond tau + slack, seen from the tile with the row's least q, none is.  The ends are
-// guessed from where the ellipse q = tau crosses the row, a bad guess only costs time.
+// certain.  A tile is kept where its square meets the ellipse q = tau, and in a row of tiles, a strip of y, the ellipse lies
+// between its leftmost and rightmost points there: two square roots give the columns.  M bounds A x^2 + C y^2 over the rectangle,
+// `slack` is 2e-5 M.  tile_reach is within 5e-6 M of the least q of a tile, and the ends in here are those of an ellipse that differs by as
+// little (cn and the products by some 1e-6 M in q, an end by 2e-6 of the rectangle's distance, which is 6e-6 M), so that the ellipse of
+// tau - 2 slack holds no tile that is not kept, and beyond that of tau + 2 slack none is.  Where the numbers are no ellipse all
+// are asked.
 __device__ __forceinline__ u32 row_kept(const TileTest &t, u32 ty, u32 x0, u32 x1, float slack)
 {
     const float TS = (float)LMK_GS_TILE, h = 0.5f * TS - 0.5f;
-    const float yc = ((float)(ty * LMK_GS_TILE) + 0.5f * TS) - t.v, y0 = yc - h, y1 = yc + h;
-    const float cn = t.C + t.B * t.rx, inv = __builtin_amdgcn_rcpf(t.A);
-    const float yr = t.rx * __builtin_amdgcn_sqrtf(fmaxf(t.tau * t.A * __builtin_amdgcn_rcpf(t.C * cn), 0.0f));       // row of the rightmost point; the leftmost's is -yr
-    const float last = (float)(x1 - 1u), first = (float)x0;
-    auto tile_at = [&](float x) { return clampf3(floorf((x + t.u) / TS), first, last); };    // NaN passes: made x0 below
-    const float yR = clampf3(yr, y0, y1), yL = clampf3(-yr, y0, y1);
-    const float hi = tile_at(t.rx * yR + __builtin_amdgcn_sqrtf(fmaxf((t.tau - cn * yR * yR) * inv, 0.0f)));
-    const float lo = tile_at(t.rx * yL - __builtin_amdgcn_sqrtf(fmaxf((t.tau - cn * yL * yL) * inv, 0.0f)));
-    const u32 mid = (u32)fmaxf(tile_at(t.rx * clampf3(0.0f, y0, y1)), first);
-    u32 a = (u32)fmaxf(lo, first), b = (u32)fmaxf(hi, first), kept = 0;
-    a = a < mid ? a : mid;
-    b = b > mid ? b : mid;
-    const float in = t.tau - slack, out = t.tau + slack;
-    for (u32 tx = b + 1u; tx < x1; ++tx) {                                      // to the right of the guess
-        const float q = tile_reach(t, tx, ty);
-        kept += q <= t.tau ? 1u : 0u;
-        if (q > out && tx >= mid + 2u) break;
-    }
-    for (u32 tx = a; tx-- > x0;) {                                              // to the left of it
-        const float q = tile_reach(t, tx, ty);
-        kept += q <= t.tau ? 1u : 0u;
-        if (q > out && tx + 2u <= mid) break;
-    }
-    bool sure = false;
-    for (; a <= b; ++a) {                                                       // from its left end to a tile that is certain
-        const float q = tile_reach(t, a, ty);
-        if (q <= in) { sure = true; break; }
-        kept += q <= t.tau ? 1u : 0u;
-    }
-    if (!sure) return kept;
-    for (; b > a; --b) {                                                        // and from its right end
-        const float q = tile_reach(t, b, ty);
-        if (q <= in) break;
-        kept += q <= t.tau ? 1u : 0u;
-    }
-    return kept + (b - a + 1u);
+    const float xc = ((float)(x0 * LMK_GS_TILE) + 0.5f * TS) - t.u, yc = ((float)(ty * LMK_GS_TILE) + 0.5f * TS) - t.v;   // centre of the first tile
+    const float y0 = yc - h, y1 = yc + h, lo0 = (-h - xc) / TS, hi0 = (h - xc) / TS + 1.0f, wide = (float)(x1 - x0);
+    const float cn = t.C + t.B * t.rx, inv = __builtin_amdgcn_rcpf(t.A), bend = t.A * __builtin_amdgcn_rcpf(t.C * cn);
+    auto inside = [&](float level, u32 &first, u32 &end) {
+        const float yr = t.rx * __builtin_amdgcn_sqrtf(fmaxf(level * bend, 0.0f));      // row of the rightmost point; the leftmost's is -yr
+        const float yR = __builtin_amdgcn_fmed3f(yr, y0, y1), yL = __builtin_amdgcn_fmed3f(-yr, y0, y1);
+        const float dR = (level - cn * yR * yR) * inv, dL = (level - cn * yL * yL) * inv;
+        const float right = t.rx * yR + __builtin_amdgcn_sqrtf(fmaxf(dR, 0.0f)), left = t.rx * yL - __builtin_amdgcn_sqrtf(fmaxf(dL, 0.0f));
+        first = (u32)__builtin_amdgcn_fmed3f(ceilf(left / TS + lo0), 0.0f, wide);
+        end = dR >= 0.0f ? (u32)__builtin_amdgcn_fmed3f(floorf(right / TS + hi0), 0.0f, wide) : 0u;
+    };
+    u32 a, b, sure_a, sure_b, kept = 0;
+    inside(t.tau + 2.0f * slack, a, b);
+    inside(t.tau - 2.0f * slack, sure_a, sure_b);
+    if (!(t.A > 0.0f && cn > 0.0f && slack + inv + fabsf(bend) + fabsf(t.rx) + fabsf(t.tau) < 3.0e38f)) { a = 0u; b = x1 - x0; sure_b = 0u; }
+    if (sure_a < a) sure_a = a;
+    if (sure_b > b) sure_b = b;
+    if (sure_b <= sure_a) sure_a = sure_b = b;                  // none is sure
+    kept = sure_b - sure_a;
+    for (; a < sure_a; ++a) kept += tile_kept(t, x0 + a, ty) ? 1u : 0u;
+    for (; sure_b < b; ++sure_b) kept += tile_kept(t, x0 + sure_b, ty) ? 1u : 0u;
+    return kept;
 }
 
 // The tiles of a bin of kBinEdge x kBinEdge, bit kBinEdge j + i = tile (bx + i, by + j): those that tile_kept surely keeps, and those that have
