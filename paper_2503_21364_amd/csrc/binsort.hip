@@ -484,6 +484,7 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     const bool ranges_part = blockIdx.x == 0;
     if (tid == 0 && ranges_part) {
         classes[kDenseClass] = dense_min != ~0ull && header->dup_count >= dense_min ? 1u : 0u;   // as the counting kernels decided
+        header->counted = header->dup_count;
         header->dup_count = D;
         header->status = overflow ? LMK_GS_ERR_CAPACITY : LMK_GS_OK;      // of this call; the frame's earlier calls do not count
         // with no primitives nothing else writes the one-entry prefix sum over the primitives

@@ -570,7 +570,7 @@ __device__ __forceinline__ void dense_emit(const DenseArgs &d, const ScratchHead
 {
     if (header->status != LMK_GS_OK) return;                // more pairs than the buffers hold: nothing is emitted
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const u32 used = units_in_use(header->dup_count, d.bins, d.units);
+    const u32 used = units_in_use(header->counted, d.bins, d.units);           // those that the count had, whatever the lists add up to
     const UnitWork w = unit_work(d.n, d.bins_x, d.bins, used, wv);
     if (w.bin >= d.bins) return;
     EmitRuns &lines = reinterpret_cast<EmitRuns *>(space)[RECORDS ? wv : 0u];

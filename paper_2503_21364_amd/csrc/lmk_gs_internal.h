@@ -35,7 +35,7 @@ struct ScratchHeader {
     u32 ordered;        // the primitives are in voxel order: the projection had an index
     u32 big_count;      // stage 2: primitives on the deferred list, from the front (one wavefront each)
     u32 giant_count;    // ... and from the back (one workgroup each)
-    u32 pad2[2];
+    u64 counted;        // dup_count as the counting kernels saw it: the scan puts the sum of the lists in its place
 };
 
 // Carving of the caller's scratch buffer (all offsets multiples of 256 bytes).  The part up to

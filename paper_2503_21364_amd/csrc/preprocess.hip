@@ -204,7 +204,7 @@ __device__ __forceinline__ void reset_frame_state(ScratchHeader *header, u32 *__
         header->ordered = ordered ? 1u : 0u;
         header->big_count = 0;
         header->giant_count = 0;
-        header->pad2[0] = header->pad2[1] = 0;
+        header->counted = 0;
     }
     for (u32 t = g; t < 2u * (num_tiles + 1u); t += threads) tile_count[t] = 0;    // both halves: runs, listed primitives
 }

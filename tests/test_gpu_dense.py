@@ -78,3 +78,31 @@ def test_overflow_leaves_empty_ranges():
     assert D > CAP and status == B.ERR_CAPACITY
     assert not fr.tile_offsets.any().item() and (fr.keys == -1).all().item()
     assert (fr.out_T == 1.0).all().item()
+
+
+def test_lists_of_fewer_pairs_than_the_projection_counted():
+    """Primitives taken out (tiles_touched = 0) between the projection and stage 2: the frame's pair count that decides how the
+    depth order is shared out is then larger than what the lists add up to, and the emit has to go by the same one as the count.
+    The lists are those of the scene without them."""
+    n, w, h = 100_000, 1920, 1080
+    bins = 30 * 17
+    sc = scenes.make_scene(4, n=n, seed=3)
+    sc["scale"] = np.full_like(sc["scale"], 0.16)
+    out = np.random.default_rng(5).random(n) < 0.5
+    rest = dict(sc, opacity=np.where(out, np.float32(0.0), sc["opacity"]))
+    cam = B.make_camera(dict(scenes.make_cameras(4, w, h)[0], binning=0))
+    probe = B.Frame(n, w, h, 1)
+    B.preprocess(B.Scene(sc), cam, probe)
+    D = int(probe.tiles_touched.sum().item())
+    a, b = B.Frame(n, w, h, D), B.Frame(n, w, h, D)
+    B.preprocess(B.Scene(sc), cam, a)
+    a.tiles_touched[torch.from_numpy(out).cuda()] = 0
+    B.bin_sort(cam, a)
+    B.preprocess(B.Scene(rest), cam, b)
+    B.bin_sort(cam, b)
+    torch.cuda.synchronize()
+    kept, status = B.read_status(a)
+    assert (kept, status) == B.read_status(b) and status == B.OK
+    assert D // (bins * 2048) >= kept // (bins * 2048) + 8 and D >= 40 * n          # not shared out alike
+    assert torch.equal(a.tile_offsets, b.tile_offsets)
+    assert torch.equal(a.keys[:kept], b.keys[:kept]) and torch.equal(a.vals[:kept], b.vals[:kept])
