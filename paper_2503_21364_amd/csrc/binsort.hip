@@ -200,14 +200,15 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     if constexpr (Dense::kDense) other_way = header->dup_count >= dense.dense_min;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const u32 block = bin_block(n, num_tiles, header->ordered != 0u);
-    const u32 beg = blockIdx.x * block, end = n - beg < block ? n : beg + block;
+    const BinShare share = bin_share(blockIdx.x, block, n);
+    const u32 beg = share.beg;
     if constexpr (Dense::kDense) {
         if (other_way) {                                    // the same for the whole workgroup
             sort_chunk<kThreads, TIGHT>(dense, reinterpret_cast<u64 *>(s_hist));
             return;
         }
     }
-    if ((u64)blockIdx.x * block >= n) return;               // there for a chunk, or for smaller blocks
+    if (share.count == 0u) return;                          // there for a chunk, or for smaller blocks
     {   // the projection stage counted the pairs of every 256 primitives: a workgroup none of whose
         // primitives was binned (culled, or a skipped voxel range) leaves without reading one
         const u32 pb = beg / kPreBlock + lane;
@@ -220,17 +221,17 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     }
     // everything that a thread needs of its primitives of a round is requested at once, a round ahead
     struct Round { u32 cnt[kPer], mask[kPer]; ushort4 r[kPer]; } next;
-    auto request = [&](u32 first) {
+    auto request = [&](u32 first) {                         // of the share
 #pragma unroll
         for (u32 j = 0; j < kPer; ++j) {
-            const u32 i = first + j * kThreads + tid;
-            const bool in = i < end;
+            const u32 m = first + j * kThreads + tid, i = beg + m;
+            const bool in = m < share.count;
             next.cnt[j] = in ? tiles_touched[i] : 0u;
             next.r[j] = in ? rect[i] : make_ushort4(0, 0, 0, 0);
             next.mask[j] = (TIGHT && LDS && in) ? tile_masks[i] : 0u;
         }
     };
-    request(beg);
+    request(0u);
     if (LDS) {
         list_first_start<kThreads>(group_totals, beg / kPreBlock, s_part, tid, lane, wv);
         for (u32 t = tid; t < num_tiles; t += kThreads) s_hist[t] = 0;
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     }
     __syncthreads();
     u32 large_bits = 0, giant_bits = 0;                     // bit k: this thread's primitive beg + k kThreads + tid goes to the list
-    for (u32 first = beg, k = 0; first < end; first += kPer * kThreads) {
+    for (u32 first = 0, k = 0; first < share.count; first += kPer * kThreads) {
         const Round now = next;
         request(first + kPer * kThreads);
 #pragma unroll
@@ -712,25 +713,26 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void emit_kernel(
     }
     if (!LDS) return;                                       // every primitive is on a list
     const u32 block = bin_block(n, num_tiles, header->ordered != 0u);
-    if ((u64)blockIdx.x * block >= n) return;
+    const BinShare share = bin_share(blockIdx.x, block, n);
+    if (share.count == 0u) return;
     const u32 entries = bin_count[blockIdx.x];
     if (entries == 0u) return;                              // the same for the whole workgroup
-    const u32 beg = blockIdx.x * block, end_prim = n - beg < block ? n : beg + block;
+    const u32 beg = share.beg;
     list_first_start<kThreads>(group_totals, beg / kPreBlock, s_part, tid, lane, wv);
     // this thread's primitives of a round: requested a round ahead, the first before the counters are set up
     struct Round { u32 cnt[kPer], mask[kPer], dbits[kPer]; ushort4 r[kPer]; } next;
-    auto request = [&](u32 from) {
+    auto request = [&](u32 from) {                          // of the share
 #pragma unroll
         for (u32 j = 0; j < kPer; ++j) {
-            const u32 i = from + j * kThreads + tid;
-            const bool in = i < end_prim;
+            const u32 m = from + j * kThreads + tid, i = beg + m;
+            const bool in = m < share.count;
             next.cnt[j] = in ? tiles_touched[i] : 0u;
             next.r[j] = in ? rect[i] : make_ushort4(0, 0, 0, 0);
             next.mask[j] = (TIGHT && in) ? tile_masks[i] : 0u;
             next.dbits[j] = in ? __float_as_uint(depth[i]) : 0u;
         }
     };
-    request(beg);
+    request(0u);
     __syncthreads();
     const u64 first = list_first_finish<kWaves>(block_offsets, beg / kPreBlock, s_part);
     for (u32 k = tid; k < entries; k += kThreads) {
@@ -739,14 +741,14 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void emit_kernel(
         if (e.x < num_tiles) s_cur[e.x] = WIDE ? e.y : (u32)tile_offsets[e.x] + e.y;
     }
     __syncthreads();
-    for (u32 from = beg; from < end_prim; from += kPer * kThreads) {
+    for (u32 from = 0; from < share.count; from += kPer * kThreads) {
         const Round now = next;
         request(from + kPer * kThreads);
 #pragma unroll
         for (u32 j = 0; j < kPer; ++j) {
             const u32 area = now.cnt[j] ? ((u32)now.r[j].z - (u32)now.r[j].x) * ((u32)now.r[j].w - (u32)now.r[j].y) : 0u;
             if (area == 0u || area > kMaskArea) continue;
-            const u64 comp = ((u64)now.dbits[j] << 32) | (u64)(from + j * kThreads + tid);
+            const u64 comp = ((u64)now.dbits[j] << 32) | (u64)(beg + from + j * kThreads + tid);
             walk_small<TIGHT>(now.r[j], area, now.mask[j], pp.tiles_x, [&](u32 tile) {
                 if (tile >= num_tiles) return;
                 const u32 at = atomicAdd(&s_cur[tile], 1u);

@@ -78,6 +78,15 @@ __host__ __device__ __forceinline__ u32 bin_block(u32 n, u32 tiles, bool ordered
     return ordered || n < 2000000u ? 2048u : (n < 5000000u ? 4096u : kBinBlockMax);
 }
 
+// The primitives of counting workgroup b: `count` of them from `beg` on, none behind the last.  The kernels walk their numbers inside the share,
+// which never wrap, whatever n.
+struct BinShare { u32 beg, count; };
+__host__ __device__ __forceinline__ BinShare bin_share(u32 b, u32 block, u32 n)
+{
+    const u64 beg = (u64)b * block;
+    return { (u32)beg, beg >= n ? 0u : (n - beg < block ? (u32)(n - beg) : block) };
+}
+
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 inline ScratchLayout scratch_layout(u32 n, u64 capacity, u32 tiles)
