@@ -221,17 +221,17 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     }
     // everything that a thread needs of its primitives of a round is requested at once, a round ahead
     struct Round { u32 cnt[kPer], mask[kPer]; ushort4 r[kPer]; } next;
-    auto request = [&](u32 first) {                         // of the share
+    auto request = [&](u32 first) {
 #pragma unroll
         for (u32 j = 0; j < kPer; ++j) {
-            const u32 m = first + j * kThreads + tid, i = beg + m;
-            const bool in = m < share.count;
+            const u32 i = first + j * kThreads + tid;
+            const bool in = i - beg < share.count;
             next.cnt[j] = in ? tiles_touched[i] : 0u;
             next.r[j] = in ? rect[i] : make_ushort4(0, 0, 0, 0);
             next.mask[j] = (TIGHT && LDS && in) ? tile_masks[i] : 0u;
         }
     };
-    request(0u);
+    request(beg);
     if (LDS) {
         list_first_start<kThreads>(group_totals, beg / kPreBlock, s_part, tid, lane, wv);
         for (u32 t = tid; t < num_tiles; t += kThreads) s_hist[t] = 0;
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     }
     __syncthreads();
     u32 large_bits = 0, giant_bits = 0;                     // bit k: this thread's primitive beg + k kThreads + tid goes to the list
-    for (u32 first = 0, k = 0; first < share.count; first += kPer * kThreads) {
+    for (u32 first = beg, k = 0; first - beg < share.count; first += kPer * kThreads) {
         const Round now = next;
         request(first + kPer * kThreads);
 #pragma unroll
@@ -484,8 +484,13 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(
     // classes; both need the list lengths and D
     const bool ranges_part = blockIdx.x == 0;
     if (tid == 0 && ranges_part) {
-        classes[kDenseClass] = dense_min != ~0ull && header->dup_count >= dense_min ? 1u : 0u;   // as the counting kernels decided
-        header->counted = header->dup_count;
+        u32 elsewhere = 0u;
+        if (dense_min != ~0ull) {                           // (else nobody asks, and the read would be a trip to memory)
+            const u64 counted = header->dup_count;
+            elsewhere = counted >= dense_min ? 1u : 0u;     // as the counting kernels decided
+            header->counted = counted;
+        }
+        classes[kDenseClass] = elsewhere;
         header->dup_count = D;
         header->status = overflow ? LMK_GS_ERR_CAPACITY : LMK_GS_OK;      // of this call; the frame's earlier calls do not count
         // with no primitives nothing else writes the one-entry prefix sum over the primitives
@@ -721,18 +726,18 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void emit_kernel(
     list_first_start<kThreads>(group_totals, beg / kPreBlock, s_part, tid, lane, wv);
     // this thread's primitives of a round: requested a round ahead, the first before the counters are set up
     struct Round { u32 cnt[kPer], mask[kPer], dbits[kPer]; ushort4 r[kPer]; } next;
-    auto request = [&](u32 from) {                          // of the share
+    auto request = [&](u32 from) {
 #pragma unroll
         for (u32 j = 0; j < kPer; ++j) {
-            const u32 m = from + j * kThreads + tid, i = beg + m;
-            const bool in = m < share.count;
+            const u32 i = from + j * kThreads + tid;
+            const bool in = i - beg < share.count;
             next.cnt[j] = in ? tiles_touched[i] : 0u;
             next.r[j] = in ? rect[i] : make_ushort4(0, 0, 0, 0);
             next.mask[j] = (TIGHT && in) ? tile_masks[i] : 0u;
             next.dbits[j] = in ? __float_as_uint(depth[i]) : 0u;
         }
     };
-    request(0u);
+    request(beg);
     __syncthreads();
     const u64 first = list_first_finish<kWaves>(block_offsets, beg / kPreBlock, s_part);
     for (u32 k = tid; k < entries; k += kThreads) {
@@ -741,14 +746,14 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void emit_kernel(
         if (e.x < num_tiles) s_cur[e.x] = WIDE ? e.y : (u32)tile_offsets[e.x] + e.y;
     }
     __syncthreads();
-    for (u32 from = 0; from < share.count; from += kPer * kThreads) {
+    for (u32 from = beg; from - beg < share.count; from += kPer * kThreads) {
         const Round now = next;
         request(from + kPer * kThreads);
 #pragma unroll
         for (u32 j = 0; j < kPer; ++j) {
             const u32 area = now.cnt[j] ? ((u32)now.r[j].z - (u32)now.r[j].x) * ((u32)now.r[j].w - (u32)now.r[j].y) : 0u;
             if (area == 0u || area > kMaskArea) continue;
-            const u64 comp = ((u64)now.dbits[j] << 32) | (u64)(beg + from + j * kThreads + tid);
+            const u64 comp = ((u64)now.dbits[j] << 32) | (u64)(from + j * kThreads + tid);
             walk_small<TIGHT>(now.r[j], area, now.mask[j], pp.tiles_x, [&](u32 tile) {
                 if (tile >= num_tiles) return;
                 const u32 at = atomicAdd(&s_cur[tile], 1u);

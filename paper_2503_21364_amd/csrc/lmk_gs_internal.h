@@ -78,8 +78,8 @@ __host__ __device__ __forceinline__ u32 bin_block(u32 n, u32 tiles, bool ordered
     return ordered || n < 2000000u ? 2048u : (n < 5000000u ? 4096u : kBinBlockMax);
 }
 
-// The primitives of counting workgroup b: `count` of them from `beg` on, none behind the last.  The kernels walk their numbers inside the share,
-// which never wrap, whatever n.
+// The primitives of counting workgroup b: `count` of them from `beg` on, none behind the last.  The kernels compare distances from `beg` with
+// `count`, since positions behind the share may wrap.
 struct BinShare { u32 beg, count; };
 __host__ __device__ __forceinline__ BinShare bin_share(u32 b, u32 block, u32 n)
 {
