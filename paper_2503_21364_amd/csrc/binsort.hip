@@ -199,7 +199,7 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void count_kernel(
     bool other_way = false;
     if constexpr (Dense::kDense) other_way = header->dup_count >= dense.dense_min;
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const u32 block = bin_block(n, num_tiles, header->ordered != 0u);
+    const u32 block = bin_block(n, num_tiles, in_order(header, n));
     const BinShare share = bin_share(blockIdx.x, block, n);
     const u32 beg = share.beg;
     if constexpr (Dense::kDense) {
@@ -717,7 +717,7 @@ __global__ __launch_bounds__(BinShape<LDS_TILES>::kThreads) void emit_kernel(
         return;
     }
     if (!LDS) return;                                       // every primitive is on a list
-    const u32 block = bin_block(n, num_tiles, header->ordered != 0u);
+    const u32 block = bin_block(n, num_tiles, in_order(header, n));
     const BinShare share = bin_share(blockIdx.x, block, n);
     if (share.count == 0u) return;
     const u32 entries = bin_count[blockIdx.x];

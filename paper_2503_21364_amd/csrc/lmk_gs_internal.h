@@ -32,10 +32,11 @@ __device__ __forceinline__ void wave_fence()
 struct ScratchHeader {
     u64 dup_count;      // D = pairs of the frame = sum of tiles_touched (known when lmk_gs_preprocess is done)
     int32_t status;     // LMK_GS_* code of the frame's latest stage 2 (LMK_GS_OK after stage 1)
-    u32 ordered;        // the primitives are in voxel order: the projection had an index
+    u32 ordered;        // the projection had an index: the primitives are in its order
     u32 big_count;      // stage 2: primitives on the deferred list, from the front (one wavefront each)
     u32 giant_count;    // ... and from the back (one workgroup each)
     u64 counted;        // dup_count as the counting kernels saw it: the scan puts the sum of the lists in its place
+    u64 looks;          // without an index: pairs of primitives looked at, and above them how many of them lie near one another
 };
 
 // Carving of the caller's scratch buffer (all offsets multiples of 256 bytes).  The part up to
@@ -62,20 +63,34 @@ struct ScratchLayout {
 // Primitives per workgroup of the counting and emit kernels of stage 2: a power of two of whole preprocess groups, so that those of
 // one workgroup lie in one group of kScanGroup.  Small scenes are short of workgroups, and a workgroup's time is the latency of its steps;
 // large ones in no spatial order have so few pairs per workgroup and tile that every pair costs an atomic, fewer the more
-// primitives share a workgroup.  Whether there is an order the device knows, by whether the projection had an index
-// (ScratchHeader::ordered); grids are sized for the smaller.  Both kernels, us, 512, 1024, 2048, 4096, 8192 primitives:
+// primitives share a workgroup.  Whether there is an order the device knows (in_order); grids are sized for the smaller.  Both kernels, us, 512, 1024, 2048, 4096, 8192 primitives:
 //   10 000 at 256 x 256      13.6  15.9  19.9  29.4  48.8      1.2 M inside, ordered   29.2  30.1  32.3  45.8  68.2
 //   30 011 at 333 x 217      11.4  12.2  15.0  22.4  35.6      3 M overview, ordered   82.6  59.0  52.1  55.4  63.7
 //   500 000 in a cube        90.3  76.5  71.1  75.1  96.1      20 M of a city           823   601   451   373   340
 // and all of stage 2: 60 000 in a cube 37.6 37.4 43.2 55.9 73.0, 250 000 61.0 60.8 59.0 72.2 93.7, in order 49.2 47.3 55.8 73.6 94.5; 3 M of
 // a city 163 128 111 98 100; 6 M 278 217 173 155 140, in order 99 85 81 89 105.
-constexpr u32 kBinBlockMax = 8192;
+constexpr u32 kBinBlockMax = 8192, kLookForOrder = 2000000, kLookGroups = 32;
 static_assert(kScanGroup % (kBinBlockMax / kPreBlock) == 0, "the blocks of one counting workgroup lie in one group");
 __host__ __device__ __forceinline__ u32 bin_block(u32 n, u32 tiles, bool ordered)
 {
     if (tiles <= kLdsTilesSmall && n <= (ordered ? 1u << 17 : 1u << 16)) return 512u;
     if (tiles <= kLdsTilesSmall && n <= (ordered ? 1u << 18 : 1u << 17)) return 1024u;
-    return ordered || n < 2000000u ? 2048u : (n < 5000000u ? 4096u : kBinBlockMax);
+    return ordered || n < kLookForOrder ? 2048u : (n < 5000000u ? 4096u : kBinBlockMax);
+}
+
+// Are the primitives in spatial order?  With an index they are.  Without, where the workgroups for no order are the wrong ones for an order that
+// nobody told of, stage 1 looks: from kLookForOrder primitives on (bin_sort alone, us, with these workgroups and with those for order: 3 M
+// inside 98 and 80, 6 M inside 137 and 82, 3 M of a city 67 and 60, 6 M 102 and 78, 6 M overview 269 and 256, 4 M at 640 x 480 281 and
+// 285) in images of up to kLdsTilesSmall tiles (beyond: 3 M overview at 3840 x 2160 173 and 194, 6 M of a city at 2560 x 1440 114 and 135).
+// They are if most of the pairs of primitives 128 apart that are both binned lie within an eighth of the image of one another.  In
+// voxel order at least 0.92 of them do, and of runs of 512 or more that belong together 0.8; in no order or as runs of 10 or 64
+// 0.1 to 0.3, sorted along one axis up to 0.43.  Too few pairs, nearly all primitives being culled: no.
+__host__ __device__ __forceinline__ bool in_order(const ScratchHeader *h, u32 n)
+{
+    const bool indexed = h->ordered != 0u;
+    if (n < kLookForOrder) return indexed;
+    const u32 both = (u32)h->looks, near = (u32)(h->looks >> 32);
+    return indexed || (both >= 8u && 2u * near > both);
 }
 
 // The primitives of counting workgroup b: `count` of them from `beg` on, none behind the last.  The kernels compare distances from `beg` with

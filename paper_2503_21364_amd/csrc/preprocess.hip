@@ -205,6 +205,7 @@ __device__ __forceinline__ void reset_frame_state(ScratchHeader *header, u32 *__
         header->big_count = 0;
         header->giant_count = 0;
         header->counted = 0;
+        header->looks = 0;
     }
     for (u32 t = g; t < 2u * (num_tiles + 1u); t += threads) tile_count[t] = 0;    // both halves: runs, listed primitives
 }
@@ -586,12 +587,27 @@ __global__ __launch_bounds__(kPreBlock, DEG == 0 ? 8 : 1) void preprocess_kernel
 // the sum of the group totals, added to the header the preprocess kernel has just cleared.
 // (One workgroup scanning everything takes longer than the whole rest of this: its time is
 // the latency of one compute unit, not the data.)
+//
+// LOOK: are the primitives in spatial order (in_order)?  Of the 256 preprocess workgroups of every `every`-th group a pair of primitives
+// each, 128 apart: both binned, and within `reach` tiles of one another?  (About 1 us, 2 to 6 M primitives; one workgroup that looks at 1024 pairs
+// all over the scene took 4.)
+template <bool LOOK>
 __global__ __launch_bounds__(kScanGroup) void scan_block_sums_kernel(
     const u32 *__restrict__ block_sums, u32 nb, u64 *__restrict__ block_offsets,
-    u64 *__restrict__ group_totals, ScratchHeader *__restrict__ header)
+    u64 *__restrict__ group_totals, ScratchHeader *__restrict__ header,
+    const u32 *__restrict__ tiles_touched, const ushort4 *__restrict__ rect, u32 n, u32 reach, u32 every)
 {
+    const bool look = LOOK && blockIdx.x % every == 0u;
+    u32 cnt[2] = { 0u, 0u };
+    ushort4 r[2] = {};
+    if (look) {
+        const u64 p = ((u64)blockIdx.x * kScanGroup + threadIdx.x) * kPreBlock + kPreBlock / 4u;
+#pragma unroll
+        for (u32 j = 0; j < 2; ++j)
+            if (p + j * (kPreBlock / 2u) < n) { cnt[j] = tiles_touched[p + j * (kPreBlock / 2u)]; r[j] = rect[p + j * (kPreBlock / 2u)]; }
+    }
     constexpr u32 kWaves = kScanGroup / kWave;
-    __shared__ u64 s_wave[kWaves];
+    __shared__ u64 s_wave[kWaves], s_look[kWaves];
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const u32 b = blockIdx.x * kScanGroup + tid;
     const u32 x = b < nb ? block_sums[b] : 0u;
@@ -602,6 +618,13 @@ __global__ __launch_bounds__(kScanGroup) void scan_block_sums_kernel(
         if ((int)lane >= o) incl += t;
     }
     if (lane == kWave - 1) s_wave[wv] = incl;
+    if (look) {                                             // the same for the workgroup
+        const int dx = (int)r[0].x + (int)r[0].z - (int)r[1].x - (int)r[1].z, dy = (int)r[0].y + (int)r[0].w - (int)r[1].y - (int)r[1].w;   // twice the distance
+        const bool seen = cnt[0] != 0u && cnt[1] != 0u;
+        const u64 both = __builtin_amdgcn_ballot_w64(seen);
+        const u64 near = __builtin_amdgcn_ballot_w64(seen && (u32)abs(dx) <= 2u * reach && (u32)abs(dy) <= 2u * reach);
+        if (lane == 0) s_look[wv] = (u64)__builtin_popcountll(both) | ((u64)__builtin_popcountll(near) << 32);
+    }
     __syncthreads();
     u64 before = 0, total = 0;
 #pragma unroll
@@ -614,16 +637,29 @@ __global__ __launch_bounds__(kScanGroup) void scan_block_sums_kernel(
     if (tid == 0) {
         group_totals[blockIdx.x] = total;
         if (total) atomicAdd(reinterpret_cast<unsigned long long *>(&header->dup_count), (unsigned long long)total);
+        if (look) {
+            u64 looks = 0;
+#pragma unroll
+            for (u32 k = 0; k < kWaves; ++k) looks += s_look[k];
+            if (looks) atomicAdd(reinterpret_cast<unsigned long long *>(&header->looks), (unsigned long long)looks);
+        }
     }
 }
 
-static hipError_t launch_scan_block_sums(char *scratch, const ScratchLayout &L, hipStream_t stream)
+static hipError_t launch_scan_block_sums(const lmk_gs_projected &proj, u32 n, const ProjParams &pp, bool look,
+                                         char *scratch, const ScratchLayout &L, hipStream_t stream)
 {
-    hipLaunchKernelGGL(scan_block_sums_kernel, dim3((L.pre_blocks + kScanGroup - 1) / kScanGroup), dim3(kScanGroup), 0, stream,
-                       reinterpret_cast<const u32 *>(scratch + L.block_sums), L.pre_blocks,
-                       reinterpret_cast<u64 *>(scratch + L.block_offsets),
-                       reinterpret_cast<u64 *>(scratch + L.group_totals),
-                       reinterpret_cast<ScratchHeader *>(scratch + L.header));
+    const u32 groups = (L.pre_blocks + kScanGroup - 1) / kScanGroup, most = pp.tiles_x > pp.tiles_y ? pp.tiles_x : pp.tiles_y;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(groups), dim3(kScanGroup), 0, stream,
+                           reinterpret_cast<const u32 *>(scratch + L.block_sums), L.pre_blocks,
+                           reinterpret_cast<u64 *>(scratch + L.block_offsets),
+                           reinterpret_cast<u64 *>(scratch + L.group_totals),
+                           reinterpret_cast<ScratchHeader *>(scratch + L.header),
+                           proj.tiles_touched, reinterpret_cast<const ushort4 *>(proj.rect), n, most / 8u, (groups + kLookGroups - 1u) / kLookGroups);
+    };
+    if (look && n >= kLookForOrder && pp.tiles_x * pp.tiles_y <= kLdsTilesSmall) launch(scan_block_sums_kernel<true>);
+    else launch(scan_block_sums_kernel<false>);
     return hipGetLastError();
 }
 
@@ -668,7 +704,7 @@ hipError_t launch_preprocess(const lmk_gs_gaussians &g, const lmk_gs_voxel_index
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_scan_block_sums(scratch, L, stream);
+    return launch_scan_block_sums(out, g.n, pp, index == nullptr, scratch, L, stream);
 }
 
 // ---------------------------------------------------------------- hand-over rebuilt from the outputs
@@ -720,7 +756,7 @@ hipError_t launch_rebuild_handover(const lmk_gs_projected &proj, u32 n, const Pr
                        reinterpret_cast<u32 *>(scratch + L.block_sums));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_scan_block_sums(scratch, L, stream);
+    return launch_scan_block_sums(proj, n, pp, true, scratch, L, stream);
 }
 
 // {D, status} of the frame from the scratch header to a caller's device array of two 64-bit words
