@@ -68,7 +68,9 @@ struct ScratchLayout {
 //   30 011 at 333 x 217      11.4  12.2  15.0  22.4  35.6      3 M overview, ordered   82.6  59.0  52.1  55.4  63.7
 //   500 000 in a cube        90.3  76.5  71.1  75.1  96.1      20 M of a city           823   601   451   373   340
 // and all of stage 2: 60 000 in a cube 37.6 37.4 43.2 55.9 73.0, 250 000 61.0 60.8 59.0 72.2 93.7, in order 49.2 47.3 55.8 73.6 94.5; 3 M of
-// a city 163 128 111 98 100; 6 M 278 217 173 155 140, in order 99 85 81 89 105.
+// a city 163 128 111 98 100; 6 M 278 217 173 155 140, in order 99 85 81 89 105.  Images of more than kLdsTilesLarge tiles, whose primitives are
+// listed and not counted, have little of either: with 2048 and 8192, 6 M at 4096 x 2304, all of stage 2, city 1381 1364, in order 1339 1357; inside 621
+// 607, in order 583 594.
 constexpr u32 kBinBlockMax = 8192, kLookForOrder = 2000000, kLookGroups = 32;
 static_assert(kScanGroup % (kBinBlockMax / kPreBlock) == 0, "the blocks of one counting workgroup lie in one group");
 __host__ __device__ __forceinline__ u32 bin_block(u32 n, u32 tiles, bool ordered)

@@ -18,6 +18,7 @@ int main()
         for (u32 tiles : { 16u, 8160u, 8161u, 32768u, 32769u })
             for (int ordered = 0; ordered < 2; ++ordered) {
                 const u32 block = bin_block(n, tiles, ordered != 0);
+                bad += block > 2048u && ordered;
                 const u32 groups = scratch_layout(n, 0, tiles).bin_blocks;
                 u64 next = 0;
                 for (u32 b = 0; b < groups; ++b) {

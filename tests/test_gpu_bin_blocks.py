@@ -38,7 +38,8 @@ def test_by_number_and_order(n, ordered):
         P.compare_binned(fr, binned)
 
 
-@pytest.mark.parametrize("n,w,h", [(2_000_003, 700, 420), (5_000_001, 700, 420), (5_000_001, 2600, 1500)])
+@pytest.mark.parametrize("n,w,h", [(2_000_003, 700, 420), (5_000_001, 700, 420), (5_000_001, 2600, 1500),
+                                   (2_000_003, 4096, 2304)])             # 36864 tiles: every primitive is listed
 def test_large_and_in_no_order(n, w, h):
     sc = _scene(n, 7)
     cam = dict(scenes.make_cameras(1, w, h)[0], binning=1)
