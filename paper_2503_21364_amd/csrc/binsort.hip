@@ -22,8 +22,8 @@
 //            atomics of one instruction fall into one or two cache lines and the memory side takes
 //            them together (ten times the rate of scattered ones).  The close-up primitives of a
 //            frame sit in a few workgroups; the list spreads them over the whole chip.
-//   scan     one workgroup: the capacity check, exclusive prefix sum of the per-tile counts = the
-//            per-tile ranges, a running position per tile for the listed primitives, the tiles by
+//   scan     two workgroups: the capacity check, exclusive prefix sum of the per-tile counts = the
+//            per-tile ranges, a running position per tile for the listed primitives; and the tiles by
 //            descending list length with the size classes of the per-tile sort.
 //   emit     the same walks again.  A workgroup sets its LDS counters to range start + run start
 //            for the tiles of its list and hands out positions from them.  A listed primitive
@@ -834,7 +834,9 @@ __device__ __forceinline__ void sort_pairs_in_lds(u64 *keys, u32 *vals, u64 beg,
 //
 // What the buckets cost beyond that is the ranking, by the size of a pair's bucket on average over the pairs:
 // lists of clusters of one size are even with the merge sort, less the try, at 7 (64 threads) and 22
-// (512), and one large bucket holds up its wavefront.  Beyond these limits (a surface in front of a far background,
+// (512), and one large bucket holds up its wavefront.  With 1024 threads, alone on their compute unit, they are even at 56 only (200 lists of 16 384
+// in clusters of 16, 22, 32, 56: all of stage 2 93, 97, 105, 122 us, by merging 123; of 8192 66, 67, 71, 81, by merging 82); the limits are
+// those of 512 all the same.  Beyond these limits (a surface in front of a far background,
 // equal depths) the list is left to the merge sort: returns false, nothing written.  Lists that are far beyond
 // show it in a quarter of their pairs, or in their depths being one, and leave before the rest is counted.
 // Called by the whole team (a workgroup, or one wavefront); cnt holds THREADS * ITEMS / 2 words, two 16-bit counters each.

@@ -15,7 +15,7 @@ namespace lmk {
 // search) and merges them sequentially.  Runs are stored with one padding slot per 16 elements
 // so that the strided accesses of neighbouring threads spread over the LDS banks.  Instances:
 // 64 threads x 2 / 4 / 8 (one wavefront per short list, which is most tiles), 512 x 4 and 8,
-// 1024 x 8 and 16 (a compute unit's LDS) for long lists and the chunks of the longest.
+// 1024 x 8 and 16 (a compute unit's LDS) for long lists and the chunks of the longest; the depth order's chunks take 512 x 8 or 1024 x 4.
 __device__ __forceinline__ u32 ts_slot(u32 p) { return p + (p >> 4); }
 
 __device__ __forceinline__ void ts_cswap(u64 &a, u64 &b)

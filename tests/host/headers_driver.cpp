@@ -89,17 +89,30 @@ static int odd_cells()
     return bad;
 }
 
-static int rows(uint64_t count)
+// rows of random ellipses at thresholds of all opacities; with `odd`, at thresholds around and below zero, and of values that are no
+// ellipse (NaN, infinities, the largest numbers in each field, conics of no or negative determinant)
+static int rows(uint64_t count, bool odd)
 {
     uint64_t tested = 0, differ = 0, kept = 0;
     while (tested < count) {
         Conic k;
         const double most = tested % 7 ? 600.0 : 1e5;
         if (!draw_conic(most, k)) continue;
-        const float tau = (float)uniform(0.01, 11.1);
+        const float tau = (float)(odd ? uniform(-0.01, 0.02) : uniform(0.01, 11.1));
         const u32 x0 = (u32)below(40), x1 = x0 + 1u + (u32)below(250), y0 = (u32)below(40), y1 = y0 + 1u + (u32)below(60);
         const double hx = sqrt(11.09 * k.a), hy = sqrt(11.09 * k.c);
-        const TileTest t = make_tile_test((float)uniform(16.0 * x0 - hx, 16.0 * x1 + hx), (float)uniform(16.0 * y0 - hy, 16.0 * y1 + hy), k.A, k.B, k.C, tau);
+        TileTest t = make_tile_test((float)uniform(16.0 * x0 - hx, 16.0 * x1 + hx), (float)uniform(16.0 * y0 - hy, 16.0 * y1 + hy), k.A, k.B, k.C, tau);
+        if (odd && below(3)) {
+            const float values[6] = { NAN, kInf, -kInf, 3e38f, -3e38f, 0.0f };
+            if (below(2)) {
+                float *const field[6] = { &t.u, &t.v, &t.A, &t.B, &t.C, &t.tau };
+                for (u32 m = (u32)below(2); m < 2; ++m) *field[below(6)] = values[below(6)];
+                t = make_tile_test(t.u, t.v, t.A, t.B, t.C, t.tau);
+            } else {
+                const float B = (float)(sqrt((double)k.A * k.C) * uniform(0.999999, 1.5)) * (below(2) ? 1.0f : -1.0f);
+                t = make_tile_test(t.u, t.v, k.A, B, k.C, (float)uniform(0.01, 11.1));
+            }
+        }
         const float fx = fmaxf(fabsf((float)(x0 * LMK_GS_TILE) - t.u), fabsf((float)(x1 * LMK_GS_TILE) - t.u));
         const float fy = fmaxf(fabsf((float)(y0 * LMK_GS_TILE) - t.v), fabsf((float)(y1 * LMK_GS_TILE) - t.v));
         const float slack = 2e-5f * (t.A * fx * fx + t.C * fy * fy);
@@ -112,7 +125,7 @@ static int rows(uint64_t count)
             ++tested;
         }
     }
-    printf("rows: %llu, %llu tiles kept, %llu rows differ\n", (unsigned long long)tested, (unsigned long long)kept, (unsigned long long)differ);
+    printf("%srows: %llu, %llu tiles kept, %llu rows differ\n", odd ? "odd " : "", (unsigned long long)tested, (unsigned long long)kept, (unsigned long long)differ);
     return differ != 0;
 }
 
@@ -160,7 +173,7 @@ static int work(u32 tiles, int kind, bool ordered, bool all_bad, u32 most)
 
 int main()
 {
-    int bad = cells(1000000) + odd_cells() + rows(500000);
+    int bad = cells(1000000) + odd_cells() + rows(500000, false) + rows(500000, true);
     int runs = 0;
     for (u32 tiles : { 1u, 6u, 7u, 8u, 9u, 255u, 256u, 257u, 258u, 271u, 272u, 273u, 294u, 306u, 383u, 384u, 385u, 475u, 608u, 760u, 767u, 768u,
                        769u, 770u, 783u, 1200u, 1900u, 2047u, 2048u, 2049u, 8160u })

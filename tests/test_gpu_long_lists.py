@@ -26,8 +26,22 @@ def test_one_long_list(n, kind):
     P.compare_binned(P.gpu_frame(B.Scene(sc), cam, n + 5), ofr.binned)
 
 
+@pytest.mark.parametrize("n", [4097, 5000, 8192, 8193, 12000, 16384])
+@pytest.mark.parametrize("size", [17, 20, 22, 24, 40, 70])
+def test_clusters_around_the_limits(n, size):
+    """Clusters of one size, whose buckets are around the fullest that are still ranked (22 on average, 24 in a quarter of the list, 64)."""
+    rng = np.random.default_rng(n + size)
+    mean = np.zeros((n, 3))
+    mean[:, 2] = rng.permutation(2.0 + 0.01 * (np.arange(n) // size) + 1e-6 * rng.integers(0, 2, n))
+    sc = scenes.hand_placed_scene(mean, (0.01, 0.01, 0.01), opacity=list(rng.uniform(0.05, 0.9, n)))
+    cam = scenes.make_camera(np.eye(3, 4), (0, 0, 0), 16, 16, 60.0)
+    binned = ref.bin_sort(ref.preprocess(sc, cam), cam)
+    assert binned.D == n
+    P.compare_binned(P.gpu_frame(B.Scene(sc), cam, n + 5), binned)
+
+
 def test_more_long_lists_than_workgroups():
-    """300 tiles of 4097 to 5000 pairs each, counted and sorted (an odd multiple of 8 bytes rules the other way out)."""
+    """300 tiles of 4097 to 5000 pairs each, counted and sorted (with one pair per primitive the other way is far off)."""
     rng = np.random.default_rng(3)
     tx, ty = 20, 15
     per = rng.integers(4097, 5001, tx * ty)

@@ -3,7 +3,7 @@
 Frames of many pairs per primitive are put together from the depth-ordered primitives, all others from
 counted and sorted pairs; the line is 22 pairs per primitive and one more for every 30 bins of 4 x 4 tiles, at
 least 32, in buffers of at least 2^18 pairs.  The word that the device leaves in the scratch buffer (the sixth of the
-eight in front of the chunk list, which is the last part) tells which way a frame went."""
+eight in front of the last part, which no kernel uses) tells which way a frame went."""
 import numpy as np
 import pytest
 import torch

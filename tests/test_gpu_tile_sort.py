@@ -1,4 +1,4 @@
-"""The per-tile sort at the edges of its size classes (64 / 256 / 512 threads, chunks of 4096, merges) for
+"""The per-tile sort at the edges of its size classes (64 / 512 / 1024 threads, merges beyond 16384) for
 depths that spread over the buckets, that fall into a few of them and that are all alike (then the index
 decides and the merge sort takes over): one tile whose list has n pairs, against the oracle, bit for bit."""
 import numpy as np

@@ -1,5 +1,5 @@
-"""Rectangles of more than 512 tiles under the tile test: the projection counts a row of tiles by asking only near its
-ends.  Round splats, ellipses and needles of every direction, axis-parallel and nearly so, that cover, cross, touch or
+"""Rectangles of more than 128 tiles under the tile test: the projection counts a row of tiles from where two ellipses cross
+it and asks those in between.  Round splats, ellipses and needles of every direction, axis-parallel and nearly so, that cover, cross, touch or
 miss the edges of a large image: tiles kept per primitive and the sorted lists against the oracle, exactly."""
 import numpy as np
 import pytest
